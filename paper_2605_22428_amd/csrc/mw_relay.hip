@@ -130,11 +130,8 @@ __device__ __forceinline__ uint32_t relay_index_hop(
         // kept groups that fit are a prefix of the kept groups: the largest (index + 1, end
         // row) pair describes the child.  Reduced over the wave first: same-address LDS
         // atomics of a whole workgroup would serialise.
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) {
-            fit_g = max(fit_g, (uint32_t)__shfl_xor((int)fit_g, d, 64));
-            fit_r = max(fit_r, (uint32_t)__shfl_xor((int)fit_r, d, 64));
-        }
+        fit_g = mw_wave_max(fit_g);
+        fit_r = mw_wave_max(fit_r);
         if ((tid & 63) == 0 && fit_g) { atomicMax(&fit[0], fit_g); atomicMax(&fit[1], fit_r); }
         carry_g += tot_g; carry_r += tot_r;
     }
@@ -477,8 +474,8 @@ __device__ __forceinline__ void relay_packets_index_body(
                 ++taken;
             }
         }
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) { taken += __shfl_xor(taken, d, 64); dests += __shfl_xor(dests, d, 64); }
+        taken = mw_wave_sum(taken);
+        dests = mw_wave_sum(dests);
         if ((tid & 63) == 0) { atomicAdd(&acc[0], (unsigned long long)taken); atomicAdd(&acc[1], (unsigned long long)dests); }
         mw_lds_barrier();
         if (tid == 0) {

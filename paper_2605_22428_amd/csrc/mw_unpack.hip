@@ -190,8 +190,7 @@ __device__ __forceinline__ void recv_index_body(
     if (tid < 3) scratch[18 + tid] = 0;
     mw_lds_barrier();
     // at most 256 peers of at most 65536 rows, so 32 bits are enough; a sum, so order-free
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) part += __shfl_xor(part, d, 64);
+    part = mw_wave_sum(part);
     if ((tid & 63) == 0 && part) atomicAdd(&scratch[19], part);
 
     // rank-table entries of the first row's ids (second round trip)
@@ -258,8 +257,7 @@ __device__ __forceinline__ void recv_index_body(
     {
         uint32_t a = 0;
         for (uint32_t w = tid; w < wpl; w += nthr) a += __popc(addr[w]);
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) a += __shfl_xor(a, d, 64);     // one LDS atomic per wave
+        a = mw_wave_sum(a);                          // one LDS atomic per wave
         if ((tid & 63) == 0 && a) atomicAdd(&scratch[18], a);
     }
 
@@ -617,8 +615,7 @@ __device__ __forceinline__ void recv_index_small(const mw_index_args &a, uint32_
     {
         uint32_t n = 0;
         for (uint32_t w = tid; w < wa; w += nthr) n += __popc(addr[w]);
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) n += __shfl_xor(n, d, 64);
+        n = mw_wave_sum(n);
         if ((tid & 63u) == 0 && n) atomicAdd(&scratch[18], n);
         if (L == 0) for (uint32_t w = tid; w < wa; w += nthr) if (addr[w]) err |= MW_FLAG_NO_LOCAL_EXPERT;
     }
