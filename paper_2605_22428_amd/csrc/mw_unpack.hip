@@ -8,9 +8,9 @@
 // which local experts get the row follows from the row's top-k ids and the rank table.
 //
 // Two launches on the caller's stream:
-//   k_recv_index  one workgroup per peer.  Marks addressed rows from the descriptor
-//                 bitmaps, then for every local expert builds an LDS bitmap over the
-//                 peer's source-token indices.  A prefix of popcounts over that bitmap
+//   k_recv_index  one workgroup per peer (a few where a peer has many experts here).  Marks
+//                 addressed rows from the descriptor bitmaps, then for every local expert
+//                 builds an LDS bitmap over the peer's source-token indices.  A prefix of popcounts over that bitmap
 //                 is the stable rank of a row among the peer's rows for that expert,
 //                 whatever order the rows were packed in -- no sort, no order-dependent
 //                 atomics (LDS atomic ORs only set bits).  Emits per-(expert, peer)
@@ -99,117 +99,152 @@ struct mw_index_args {
     uint32_t *cnt, *row_base, *addr_cnt; mw_row_rec *recs; mw_hit *hits; uint32_t *base;
     int64_t *expert_offsets; mw_recv_stats *stats; uint32_t *flags;
     uint32_t dedup;     // 1: of the rows of one peer that carry the same source token only one is taken
+    uint32_t parts;     // workgroups per peer: part j takes the expert chunks j, j + parts, ... of Lc experts each
+    uint32_t tab_words; // LDS words of the table of local slots (0: the rank table in memory is looked up)
 };
 
-// The work of workgroup `p` (peer p) of the index; any workgroup size that is a multiple of 64.
-// kCache: every thread keeps its first row (ids, rank-table entries, hits, record) in registers
-// from the first request to the final store, which takes two memory round trips off the chain
-// -- and about thirty registers; the launches that run the index beside the row movers and
-// must stay small do without (kCache = false).
-template <bool kPackets, bool kCache = true>
-__device__ __forceinline__ void recv_index_body(
-    const void *__restrict__ peers_v, int P, const int32_t *__restrict__ eslot,
-    int E, int K, int Kd, int my_rank, int L, int Lc,
-    uint32_t max_tokens, uint32_t wpl, uint32_t cap_rows, uint64_t row_bytes, uint32_t header_bytes, int64_t out_cap,
-    uint32_t *cnt, uint32_t *row_base, uint32_t *addr_cnt, mw_row_rec *__restrict__ recs,
-    mw_hit *__restrict__ hits, uint32_t *__restrict__ base, int64_t *__restrict__ expert_offsets,
-    mw_recv_stats *__restrict__ stats, uint32_t *flags, const uint32_t dedup, const int p)
+constexpr uint32_t kNotLocal = 0xffu;     // table entry of an expert that lives elsewhere; local slots are below 255
+
+// LDS words of an index workgroup that handles Lc experts at a time.
+static inline size_t mw_index_lds_words(uint32_t wpl, uint32_t Lc, uint32_t tab_words, bool dedup)
+{
+    const size_t n = (size_t)Lc * wpl;
+    return wpl + tab_words + n + (n + 1) / 2 + 64 + (dedup ? wpl : 0);
+}
+
+// The work of workgroup `part` of peer p; any workgroup size that is a multiple of 64.
+// A workgroup looks at all rows of its peer and at the experts of its chunks: it sets the bit
+// (expert, source token) of every row, scans the popcounts, and a row's rank is a lookup.  Chunks are
+// independent of one another (a row's hit k belongs to the workgroup that has the hit's expert, the row's
+// record to the one that has hit 0), so a peer with many experts here is spread over workgroups that
+// never talk.  Bound by latency: one wave issues a dependent vector instruction every 3.4 ns, so what
+// counts is instructions per row and round trips per lane.  A row costs about fifty instructions (ids by
+// 16-byte loads, one table byte per id, the local ones as a bit set that is walked) where a walk
+// over all eight ids with the hits in an array of registers took several hundred.  Measured, with that walk and
+// with this: 16 peers of 429 rows 16.9 -> 8.3 us, 64 peers of 481 rows 14.0 -> 9.4, 8 peers of 681 rows and
+// 32 experts 23.8 -> 8.6, of 2720 rows 34.6 -> 13.6; riding beside the expander with two waves a peer (8 peers of
+// 1360 rows, 32 experts) the step 170 -> 83 us, because the index no longer outlasts the movers.
+// kB: rows a lane requests together.  kKeep: what the lane's first kB rows parsed to stays in registers
+// for the second pass (top_k <= 8); else the rows are requested again, which the launches that
+// run the index beside the row movers do to stay small in registers.
+template <bool kPackets, bool kGeneral, int kB, bool kKeep>
+__device__ __forceinline__ void recv_index_body(const mw_index_args &a, const uint32_t p, const uint32_t part)
 {
     extern __shared__ uint32_t lds[];
-    uint32_t *addr = lds;                       // [wpl]      bit i: row i's group names this rank
-    uint32_t *bits = addr + wpl;                // [Lc][wpl]  bit s of expert l: a row with source token s
-    uint32_t *pre = bits + (size_t)Lc * wpl;    // [Lc][wpl]  running popcount before each word
-    uint32_t *scratch = pre + (size_t)Lc * wpl; // [17] scan scratch, [17] "I am last", [18] addressed rows,
-                                                // [19] rows of the peers before this one, [20] repeats dropped
-    uint32_t *seen = scratch + 64;              // [wpl]      (dedup only) bit s: a row with source token s was taken
+    const uint32_t tid = threadIdx.x, nthr = blockDim.x;
+    const uint32_t wpl = a.wpl, K = (uint32_t)a.K, Kd = (uint32_t)a.Kd, E = (uint32_t)a.E, L = (uint32_t)a.L, Lc = (uint32_t)a.Lc;
+    const uint32_t P = (uint32_t)a.P, my_rank = (uint32_t)a.my_rank, max_tokens = a.max_tokens, dedup = a.dedup;
+    const bool use_tab = !kGeneral || a.tab_words != 0;
+    uint32_t *addr = lds;                                       // [wpl]      bit i: row i's group names this rank
+    unsigned char *tab = (unsigned char *)(addr + wpl);         // [E + 1]    local slot of expert e or kNotLocal
+    uint32_t *bits = addr + wpl + a.tab_words;                  // [Lc][wpl]  bit s of expert l: a row with source token s
+    uint16_t *pre = (uint16_t *)(bits + (size_t)Lc * wpl);      // [Lc][wpl]  running popcount before each word (modulo 2^16)
+    uint32_t *scratch = bits + (size_t)Lc * wpl + ((size_t)Lc * wpl + 1) / 2;  // [17] scans, [17] "I am last", [18] addressed
+                                                                // rows, [19] repeats dropped, [20..35] waves' sums
+    uint32_t *seen_tok = scratch + 64;                          // [wpl]      (dedup only) bit s: a row with source token s was taken
 
-    const int tid = threadIdx.x, nthr = blockDim.x;
+    // ---- everything that depends on the peer record alone is requested before the first wait:
+    // the lane's first rows (source token, first eight expert ids), its first descriptor and the
+    // row counts of the peers before this one.  The kernel is a chain of memory round trips; beside a
+    // bandwidth-bound kernel each of them takes several times longer.
+    const int32_t slot0 = (use_tab && tid < E) ? a.eslot[tid] : 0;
     mw_recv_peer pr;
     if constexpr (kPackets) {
-        const mw_recv_packets q = ((const mw_recv_packets *)peers_v)[p];
+        const mw_recv_packets q = ((const mw_recv_packets *)a.peers)[p];
         const char *first_packet = (const char *)q.packets;
         pr.desc = nullptr; pr.n_desc = q.n_rows; pr.n_rows = q.n_rows;
-        pr.rows = first_packet + header_bytes;
+        pr.rows = first_packet + a.header_bytes;
         pr.row_src_token = (const int32_t *)(first_packet + 32);
         pr.row_topk = (const int32_t *)(first_packet + 40);
     } else {
-        pr = ((const mw_recv_peer *)peers_v)[p];
+        pr = ((const mw_recv_peer *)a.peers)[p];
     }
-    auto ids_of = [&](uint32_t i) -> const int32_t * {
-        if constexpr (kPackets) return (const int32_t *)((const char *)pr.row_topk + (size_t)i * row_bytes);
+    const uint32_t mine = min(pr.n_rows, max_tokens);
+    // expert ids by 16-byte loads: id lists of whole 16-byte units that start on one
+    const bool wide_ids = !kPackets && (K & 3u) == 0 && ((uintptr_t)pr.row_topk & 15u) == 0;
+    auto ids_of = [&](uint32_t i) __attribute__((always_inline)) -> const int32_t * {
+        if constexpr (kPackets) return (const int32_t *)((const char *)pr.row_topk + (size_t)i * a.row_bytes);
         else return pr.row_topk + (size_t)i * K;
     };
-    auto token_of = [&](uint32_t i) -> uint32_t {
-        if constexpr (kPackets) return (uint32_t)*(const int32_t *)((const char *)pr.row_src_token + (size_t)i * row_bytes);
-        else return (uint32_t)pr.row_src_token[i];
-    };
-    auto rows_of_peer = [&](int q) -> uint32_t {
-        if constexpr (kPackets) return ((const mw_recv_packets *)peers_v)[q].n_rows;
-        else return ((const mw_recv_peer *)peers_v)[q].n_rows;
-    };
-    const uint32_t mine = min(pr.n_rows, max_tokens);
-    // All experts' bitmaps fit in LDS at once (the usual case): marking is fused into the row
-    // parse and the thread's first row never leaves its registers.
-    const bool one_chunk = Lc >= L;
-    uint32_t err = 0;
-
-    // ---- everything that depends on the peer record alone is requested before the first wait:
-    // the thread's first row (source token, first eight expert ids), its first descriptor and
-    // the row counts of the peers before this one.  The kernel is a chain of memory round
-    // trips; beside a bandwidth-bound kernel each of them takes several times longer.
-    const int32_t *tk_c = ids_of((uint32_t)tid);
-    uint32_t s_c = 0;
-    int32_t e_c[8];
+    // source token and first eight ids of row i (a row the peer has)
+    auto load_row = [&](uint32_t i, uint32_t &s, int32_t (&e)[8]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int u = 0; u < 8; ++u) e_c[u] = -1;
-    if (kCache && (uint32_t)tid < mine) {
-        s_c = token_of((uint32_t)tid);
+        for (int u = 0; u < 8; ++u) e[u] = -1;
+        if constexpr (kPackets) {
+            // header bytes 32..79: token, id count, ids (the header is at least 128 bytes, the packet 16-byte aligned)
+            const u32x4 *h = (const u32x4 *)((const char *)pr.rows - a.header_bytes + (size_t)i * a.row_bytes) + 2;
+            const u32x4 h0 = h[0], h1 = h[1], h2 = h[2];
+            s = h0.x;
+            e[0] = (int32_t)h0.z; e[1] = (int32_t)h0.w; e[2] = (int32_t)h1.x; e[3] = (int32_t)h1.y;
+            e[4] = (int32_t)h1.z; e[5] = (int32_t)h1.w; e[6] = (int32_t)h2.x; e[7] = (int32_t)h2.y;
+        } else {
+            s = (uint32_t)pr.row_src_token[i];
+            const int32_t *tk = pr.row_topk + (size_t)i * K;
+            if (wide_ids) {
+                const u32x4 q0 = *(const u32x4 *)tk;
+                e[0] = (int32_t)q0.x; e[1] = (int32_t)q0.y; e[2] = (int32_t)q0.z; e[3] = (int32_t)q0.w;
+                if (K > 4) {
+                    const u32x4 q1 = *((const u32x4 *)tk + 1);
+                    e[4] = (int32_t)q1.x; e[5] = (int32_t)q1.y; e[6] = (int32_t)q1.z; e[7] = (int32_t)q1.w;
+                }
+            } else {
 #pragma unroll
-        for (int u = 0; u < 8; ++u) if (u < K) e_c[u] = tk_c[u];
+                for (int u = 0; u < 8; ++u) if ((uint32_t)u < K) e[u] = tk[u];
+            }
+        }
+    };
+    uint32_t s_c[kB];
+    int32_t e_c[kB][8];
+#pragma unroll
+    for (int c = 0; c < kB; ++c) {
+        s_c[c] = 0;
+        if ((uint32_t)c * nthr < mine) load_row(min(tid + (uint32_t)c * nthr, mine - 1u), s_c[c], e_c[c]);
     }
     uint64_t dmask_c = 0;
     uint32_t doff_c = 0, dcnt_c = 0;       // packets: dcnt_c holds the header's id count
-    if ((uint32_t)tid < pr.n_desc) {
+    auto load_desc = [&](uint32_t g, uint64_t &dm, uint32_t &off, uint32_t &cnt) __attribute__((always_inline)) {
         if constexpr (kPackets) {
-            const char *hd = (const char *)pr.rows - header_bytes + (size_t)tid * row_bytes;
-            dmask_c = ((const uint64_t *)hd)[my_rank >> 6];
-            dcnt_c = *(const uint32_t *)(hd + 36);
+            const char *hd = (const char *)pr.rows - a.header_bytes + (size_t)g * a.row_bytes;
+            dm = ((const uint64_t *)hd)[my_rank >> 6];
+            cnt = *(const uint32_t *)(hd + 36);
         } else {
-            const mw_group_desc *d = pr.desc + tid;
-            dmask_c = d->mask[my_rank >> 6];
-            doff_c = d->row_offset;
-            dcnt_c = d->row_count;
+            const mw_group_desc *d = pr.desc + g;
+            dm = d->mask[my_rank >> 6];
+            off = d->row_offset;
+            cnt = d->row_count;
+        }
+    };
+    if (tid < pr.n_desc) load_desc(tid, dmask_c, doff_c, dcnt_c);
+    auto rows_of_peer = [&](uint32_t q) __attribute__((always_inline)) -> uint32_t {
+        if constexpr (kPackets) return ((const mw_recv_packets *)a.peers)[q].n_rows;
+        else return ((const mw_recv_peer *)a.peers)[q].n_rows;
+    };
+    uint32_t before = 0;
+    for (uint32_t q = tid; q < p; q += nthr) before += min(rows_of_peer(q), max_tokens);
+
+    uint32_t le0 = part * Lc, lc = le0 < L ? min(Lc, L - le0) : 0u;
+    for (uint32_t w = tid; w < wpl; w += nthr) addr[w] = 0;
+    if (dedup) for (uint32_t w = tid; w < wpl; w += nthr) seen_tok[w] = 0;
+    for (uint32_t w = tid; w < lc * wpl; w += nthr) bits[w] = 0;
+    if (tid < 2) scratch[18 + tid] = 0;
+    if (use_tab) {
+        for (uint32_t e = tid; e <= E; e += nthr) {
+            const int32_t q = e < nthr ? slot0 : (e < E ? a.eslot[e] : 0);
+            tab[e] = (e < E && (uint32_t)(q >> 16) == my_rank) ? (unsigned char)(q & 0xff) : (unsigned char)kNotLocal;
         }
     }
-    uint32_t part = 0;
-    for (int q = tid; q < p; q += nthr) part += min(rows_of_peer(q), max_tokens);
-
-    for (uint32_t w = tid; w < wpl; w += nthr) addr[w] = 0;
-    if (dedup) for (uint32_t w = tid; w < wpl; w += nthr) seen[w] = 0;
-    if (one_chunk) for (uint32_t w = tid; w < (uint32_t)L * wpl; w += nthr) bits[w] = 0;
-    if (tid < 3) scratch[18 + tid] = 0;
+    // at most 256 peers of at most 65536 rows, so 32 bits are enough
+    before = mw_wave_sum(before);
+    if ((tid & 63u) == 0) scratch[20 + (tid >> 6)] = before;
     mw_lds_barrier();
-    // at most 256 peers of at most 65536 rows, so 32 bits are enough; a sum, so order-free
-    part = mw_wave_sum(part);
-    if ((tid & 63) == 0 && part) atomicAdd(&scratch[19], part);
-
-    // rank-table entries of the first row's ids (second round trip)
-    int32_t q_c[8];
-    bool bad_c = false;
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-        const bool ok = kCache && (uint32_t)e_c[u] < (uint32_t)E;
-        bad_c |= (kCache && e_c[u] != -1 && !ok);
-        q_c[u] = ok ? eslot[e_c[u]] : -1;
-    }
-    mw_lds_barrier();
-    const uint32_t before = scratch[19];
-    if (pr.n_rows > max_tokens || before + mine > cap_rows) err |= MW_FLAG_RECV_CAPACITY;
-    const uint32_t rb = min(before, cap_rows);
-    const uint32_t n_rows = min(before + mine, cap_rows) - rb;
-    if (tid == 0) {
-        row_base[p] = rb;
-        if (p == P - 1) st_agent(&row_base[P], rb + n_rows);    // (also read by the last workgroup)
+    before = mw_wave_sum((tid & 63u) < (nthr >> 6) ? scratch[20 + (tid & 63u)] : 0u);
+    uint32_t err = 0;
+    if (pr.n_rows > max_tokens || before + mine > a.cap_rows) err |= MW_FLAG_RECV_CAPACITY;
+    const uint32_t rb = min(before, a.cap_rows);
+    const uint32_t n_rows = min(before + mine, a.cap_rows) - rb;
+    if (tid == 0 && part == 0) {
+        a.row_base[p] = rb;
+        if (p == P - 1u) st_agent(&a.row_base[P], rb + n_rows);    // (also read by the last workgroup)
     }
 
     // ---- addressed rows: groups whose bitmap has this rank's bit
@@ -218,243 +253,279 @@ __device__ __forceinline__ void recv_index_body(
         // word of the addressed-rows bitmap and its first lane stores it (no atomics)
         for (uint32_t g0 = 0; g0 < pr.n_desc; g0 += nthr) {
             const uint32_t g = g0 + tid;
-            bool a = false;
+            bool ad = false;
             if (g < pr.n_desc) {
                 uint64_t dm = dmask_c;
-                uint32_t hk = dcnt_c;
-                if (g != (uint32_t)tid) {
-                    const char *hd = (const char *)pr.rows - header_bytes + (size_t)g * row_bytes;
-                    dm = ((const uint64_t *)hd)[my_rank >> 6];
-                    hk = *(const uint32_t *)(hd + 36);
-                }
-                a = (dm >> (my_rank & 63)) & 1ull;
-                if (a && (hk != (uint32_t)K || g >= n_rows)) { err |= MW_FLAG_BAD_DESC; a = false; }
+                uint32_t hk = dcnt_c, unused = 0;
+                if (g0) load_desc(g, dm, unused, hk);
+                ad = (dm >> (my_rank & 63u)) & 1ull;
+                if (ad && (hk != K || g >= n_rows)) { err |= MW_FLAG_BAD_DESC; ad = false; }
             }
-            const uint64_t bal = __ballot(a);
-            if ((tid & 31) == 0 && (g >> 5) < wpl) addr[g >> 5] = (uint32_t)(bal >> (tid & 32));
+            const uint64_t bal = __ballot(ad);
+            if ((tid & 31u) == 0 && (g >> 5) < wpl) addr[g >> 5] = (uint32_t)(bal >> (tid & 32u));
         }
-    } else
-    for (uint32_t g = tid; g < pr.n_desc; g += nthr) {
-        uint64_t dm = dmask_c;
-        uint64_t b = doff_c, e = (uint64_t)doff_c + dcnt_c;
-        if (g != (uint32_t)tid) {
-            const mw_group_desc *d = pr.desc + g;
-            dm = d->mask[my_rank >> 6];
-            b = d->row_offset; e = b + d->row_count;
-        }
-        if (!((dm >> (my_rank & 63)) & 1ull)) continue;
-        if (e > n_rows) { err |= MW_FLAG_BAD_DESC; continue; }
-        if (e <= b) continue;
-        for (uint64_t w = b >> 5; w <= ((e - 1) >> 5); ++w) {
-            const uint64_t wlo = w << 5;
-            uint32_t m = 0xffffffffu;
-            if (b > wlo) m &= 0xffffffffu << (b - wlo);
-            if (e < wlo + 32) m &= 0xffffffffu >> (wlo + 32 - e);
-            atomicOr(&addr[w], m);
+    } else {
+        auto address = [&](uint64_t dm, uint64_t b, uint64_t cnt) __attribute__((always_inline)) {
+            const uint64_t e = b + cnt;
+            if (!((dm >> (my_rank & 63u)) & 1ull)) return;
+            if (e > n_rows) { err |= MW_FLAG_BAD_DESC; return; }
+            if (e <= b) return;
+            for (uint32_t w = (uint32_t)b >> 5; w <= ((uint32_t)e - 1u) >> 5; ++w) {     // (e <= n_rows <= 65536)
+                const uint32_t wlo = w << 5;
+                uint32_t m = 0xffffffffu;
+                if ((uint32_t)b > wlo) m &= 0xffffffffu << ((uint32_t)b - wlo);
+                if ((uint32_t)e < wlo + 32u) m &= 0xffffffffu >> (wlo + 32u - (uint32_t)e);
+                atomicOr(&addr[w], m);
+            }
+        };
+        if (tid < pr.n_desc) address(dmask_c, doff_c, dcnt_c);
+        for (uint32_t g0 = nthr; g0 < pr.n_desc; g0 += 2u * nthr) {      // two descriptors a lane in flight
+            uint64_t dm[2] = {0, 0};
+            uint32_t off[2] = {0, 0}, cnt[2] = {0, 0};
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                const uint32_t g = g0 + tid + (uint32_t)c * nthr;
+                if (g < pr.n_desc) load_desc(g, dm[c], off[c], cnt[c]);
+            }
+#pragma unroll
+            for (int c = 0; c < 2; ++c) address(dm[c], off[c], cnt[c]);      // (no bit set past the last one)
         }
     }
     mw_lds_barrier();
     {
-        uint32_t a = 0;
-        for (uint32_t w = tid; w < wpl; w += nthr) a += __popc(addr[w]);
-        a = mw_wave_sum(a);                          // one LDS atomic per wave
-        if ((tid & 63) == 0 && a) atomicAdd(&scratch[18], a);
+        uint32_t n = 0;
+        for (uint32_t w = tid; w < wpl; w += nthr) n += __popc(addr[w]);
+        n = mw_wave_sum(n);                          // one LDS atomic per wave
+        if ((tid & 63u) == 0 && n) atomicAdd(&scratch[18], n);
+        // no expert lives here: any addressed row is inconsistent
+        if (L == 0 && n) err |= MW_FLAG_NO_LOCAL_EXPERT;
+        if (dedup) mw_lds_barrier();                 // (repeats are taken out of the bitmap below)
     }
 
-    // ---- per row: its distinct local experts in top-k order (duplicate ids count once).
-    // Slot k of the row's hit slots receives expert k; the first eight also stay in f[].
-    // A thread always handles the same rows (i = tid, tid + nthr, ...), so what it wrote for a
-    // row it may read back later without a barrier.
-    auto parse = [&](uint32_t i, bool first, int (&f)[8]) -> int {
-        mw_hit *h = hits + (size_t)(rb + i) * Kd;
-        const int32_t *tk = ids_of(i);
-        int nk = 0;
-        uint64_t seen = 0;                         // (kCache) local experts below 64 the row has named so far
-        constexpr int kB = kCache ? 8 : 4;         // ids looked up together
-        for (int j0 = 0; j0 < K; j0 += kB) {
-            int32_t q[kB];
-            if (first && j0 == 0) {
+    // ---- per row: its distinct local experts in the order of its id list (repeated ids count once).
+    // classify: which of ids j0 .. j0 + 7 are local (bit u), and -- with the LDS table -- their slots, a byte each.
+    auto classify = [&](const int32_t (&e)[8], uint32_t j0, uint32_t &local, uint64_t &slots) __attribute__((always_inline)) {
+        local = 0; slots = 0;
+        uint32_t top = 0;                            // E: some id is outside [0, E)
+        uint32_t x[8];
 #pragma unroll
-                for (int u = 0; u < kB; ++u) q[u] = q_c[u];
-                if (bad_c) err |= MW_FLAG_BAD_EXPERT;
+        for (int u = 0; u < 8; ++u) {
+            x[u] = min((uint32_t)e[u], E);
+            if (j0 + u >= K) x[u] = E; else top = max(top, x[u]);
+        }
+        if (use_tab) {
+            uint32_t q[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) q[u] = tab[x[u]];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                local |= (q[u] != kNotLocal) ? 1u << u : 0u;
+                slots |= (uint64_t)q[u] << (8 * u);
+            }
+        } else {
+            int32_t q[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) q[u] = x[u] < E ? a.eslot[x[u]] : -1;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) local |= (q[u] >= 0 && (uint32_t)(q[u] >> 16) == my_rank) ? 1u << u : 0u;
+        }
+        if (top == E) {
+#pragma unroll
+            for (int u = 0; u < 8; ++u) if (j0 + u < K && e[u] != -1 && (uint32_t)e[u] >= E) err |= MW_FLAG_BAD_EXPERT;
+        }
+    };
+    // walk: calls act(k, expert slot) for every distinct local expert among ids j0 .. j0 + 7
+    auto walk = [&](uint32_t i, uint32_t j0, uint32_t local, uint64_t slots, uint32_t &nk, uint64_t &named, auto act) __attribute__((always_inline)) {
+        while (local) {
+            const uint32_t u = (uint32_t)__ffs((int)local) - 1u;
+            local &= local - 1u;
+            const uint32_t le = use_tab ? (uint32_t)(slots >> (8u * u)) & 0xffu
+                                        : (uint32_t)a.eslot[ids_of(i)[j0 + u]] & 0xffffu;
+            if (!kGeneral || L <= 64) {
+                const uint64_t bit = 1ull << le;
+                if (named & bit) continue;
+                named |= bit;
             } else {
-                int32_t e[kB];
-#pragma unroll
-                for (int u = 0; u < kB; ++u) e[u] = (j0 + u < K) ? tk[j0 + u] : -1;
-#pragma unroll
-                for (int u = 0; u < kB; ++u) {
-                    const bool ok = (uint32_t)e[u] < (uint32_t)E;
-                    if (e[u] != -1 && !ok) err |= MW_FLAG_BAD_EXPERT;
-                    q[u] = ok ? eslot[e[u]] : -1;
-                }
+                const int32_t *tk = ids_of(i);
+                const int32_t e = tk[j0 + u];
+                bool repeated = false;
+                for (uint32_t j = 0; j < j0 + u; ++j) repeated |= tk[j] == e;
+                if (repeated) continue;
             }
+            act(nk++, le);
+        }
+    };
+    // all of a row's hits; (local, slots) are what its first eight ids parsed to
+    auto walk_row = [&](uint32_t i, uint32_t local, uint64_t slots, auto act) __attribute__((always_inline)) -> uint32_t {
+        uint32_t nk = 0;
+        uint64_t named = 0;
+        walk(i, 0, local, slots, nk, named, act);
+        if constexpr (kGeneral)
+        for (uint32_t j0 = 8; j0 < K; j0 += 8) {
+            int32_t e[8];
+            const int32_t *tk = ids_of(i);
 #pragma unroll
-            for (int u = 0; u < kB; ++u) {
-                if (q[u] < 0 || (q[u] >> 16) != my_rank) continue;
-                const int le = q[u] & 0xffff;
-                bool dup = false;
-                if (kCache && le < 64) {               // one bit test instead of a walk over the row's experts
-                    dup = (seen >> le) & 1ull;
-                    seen |= 1ull << le;
-                } else {
-#pragma unroll
-                    for (int k = 0; k < 8; ++k) dup |= (k < nk && f[k] == le);
-                    for (int k = 8; k < nk; ++k) dup |= (h[k].le == le);
-                }
-                if (dup) continue;
-#pragma unroll
-                for (int k = 0; k < 8; ++k) if (k == nk) f[k] = le;
-                h[nk++] = mw_hit{le, 0};
-            }
+            for (int u = 0; u < 8; ++u) e[u] = (j0 + u < K) ? tk[j0 + u] : -1;
+            classify(e, j0, local, slots);
+            walk(i, j0, local, slots, nk, named, act);
         }
         return nk;
     };
-    // sets the (expert, source token) bits of one row for the experts [le0, le0 + lc)
-    auto mark = [&](uint32_t i, uint32_t s, int nk, const int (&f)[8], int le0, int lc) {
-        const mw_hit *h = hits + (size_t)(rb + i) * Kd;
-        for (int k = 0; k < nk; ++k) {
-            int le = 0;
-#pragma unroll
-            for (int k8 = 0; k8 < 8; ++k8) if (k8 == k) le = f[k8];
-            if (k >= 8) le = h[k].le;
-            const int l = le - le0;
-            if (l < 0 || l >= lc) continue;
-            const uint32_t old = atomicOr(&bits[(uint32_t)l * wpl + (s >> 5)], 1u << (s & 31));
-            if ((old >> (s & 31)) & 1u) err |= MW_FLAG_DUP_SRC_TOKEN;
-        }
-    };
-    // a row's state as the parse left it in memory
-    auto reload = [&](uint32_t i, uint32_t &s, int &nk, int (&f)[8]) {
-        const mw_row_rec *rc = recs + rb + i;
-        const mw_hit *h = hits + (size_t)(rb + i) * Kd;
-        s = (uint32_t)rc->src_token; nk = rc->n_hits;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) f[k] = (k < nk) ? h[k].le : 0;
-    };
 
-    int nk_c = 0;
-    int f_c[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    mw_row_rec rec_c = {nullptr, 0, p, 0, 0, 0, 0};
-    for (uint32_t i = tid; i < n_rows; i += nthr) {
-        const bool first = kCache && i == (uint32_t)tid;
-        mw_row_rec rec = {nullptr, 0, p, 0, 0, 0, 0};
-        if ((addr[i >> 5] >> (i & 31)) & 1u) {
-            const uint32_t s = first ? s_c : token_of(i);
-            if (s >= max_tokens) {
-                err |= MW_FLAG_BAD_SRC_TOKEN;
-            } else if (dedup && ((atomicOr(&seen[s >> 5], 1u << (s & 31)) >> (s & 31)) & 1u)) {
+    // ---- pass 1: the (expert, source token) bits of every row.  mark: rows i0 + tid, i0 + tid + nthr, ... as load_row
+    // left them; (local, slots) say what their first eight ids parsed to.
+    auto mark = [&](uint32_t i0, const uint32_t (&s_r)[kB], const int32_t (&e_r)[kB][8], bool first_chunk,
+                    uint32_t (&local_r)[kB], uint64_t (&slots_r)[kB]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int c = 0; c < kB; ++c) {
+            const uint32_t i = i0 + tid + (uint32_t)c * nthr, s = s_r[c];
+            local_r[c] = 0; slots_r[c] = 0;
+            if (i >= n_rows || !((addr[i >> 5] >> (i & 31u)) & 1u)) continue;
+            if (s >= max_tokens) { err |= MW_FLAG_BAD_SRC_TOKEN; continue; }
+            if (dedup && first_chunk && ((atomicOr(&seen_tok[s >> 5], 1u << (s & 31u)) >> (s & 31u)) & 1u)) {
                 // a repeat of a row already taken (a relay forwarded without updating the metadata,
                 // Section 4.1): dropped.  Repeats are copies, so which of them is taken does not matter.
                 err |= MW_FLAG_DUPLICATE_DROPPED;
-                atomicAdd(&scratch[20], 1u);
-            } else {
-                int f[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-                const int nk = parse(i, first, f);
-                if (nk == 0) err |= MW_FLAG_NO_LOCAL_EXPERT;
-                rec.src = (const char *)pr.rows + (size_t)i * row_bytes;
-                rec.src_token = (int32_t)s;
-                rec.n_hits = nk;
-                rec.le0 = f[0];
-                if (one_chunk) mark(i, s, nk, f, 0, L);
-                if (first) {
-                    nk_c = nk;
+                atomicAdd(&scratch[19], 1u);
+                atomicAnd(&addr[i >> 5], ~(1u << (i & 31u)));
+                continue;
+            }
+            classify(e_r[c], 0, local_r[c], slots_r[c]);
+            const uint32_t nk = walk_row(i, local_r[c], slots_r[c], [&](uint32_t, uint32_t le) __attribute__((always_inline)) {
+                const uint32_t l = le - le0;
+                if (l >= lc) return;
+                const uint32_t old = atomicOr(&bits[l * wpl + (s >> 5)], 1u << (s & 31u));
+                if ((old >> (s & 31u)) & 1u) err |= MW_FLAG_DUP_SRC_TOKEN;
+            });
+            if (nk == 0) err |= MW_FLAG_NO_LOCAL_EXPERT;
+        }
+    };
+    const uint32_t step = (uint32_t)kB * nthr;
+    auto load_rows = [&](uint32_t i0, uint32_t (&s_r)[kB], int32_t (&e_r)[kB][8]) __attribute__((always_inline)) {
 #pragma unroll
-                    for (int k = 0; k < 8; ++k) f_c[k] = f[k];
+        for (int c = 0; c < kB; ++c) {
+            s_r[c] = 0;
+            if (i0 + (uint32_t)c * nthr < n_rows) load_row(min(i0 + tid + (uint32_t)c * nthr, n_rows - 1u), s_r[c], e_r[c]);
+        }
+    };
+    auto mark_from = [&](uint32_t i0, bool first_chunk) __attribute__((always_inline)) {
+        for (; i0 < n_rows; i0 += step) {
+            uint32_t s_r[kB], local_r[kB];
+            uint64_t slots_r[kB];
+            int32_t e_r[kB][8];
+            load_rows(i0, s_r, e_r);
+            mark(i0, s_r, e_r, first_chunk, local_r, slots_r);
+        }
+    };
+    uint32_t local_c[kB];                            // (kKeep) the first rows as they parsed
+    uint64_t slots_c[kB];
+    mark(0, s_c, e_c, true, local_c, slots_c);
+    bool first_chunk = true;
+    mark_from(step, true);
+    while (true) {
+        mw_lds_barrier();
+
+        // ---- running popcounts over the chunk's words (expert-major): consecutive words per lane, one scan
+        // of the lanes' sums.  Only differences inside one expert's words are used, and those are below
+        // 65536, so sixteen bits hold them.
+        {
+            const uint32_t n_words = lc * wpl, per = (n_words + nthr - 1u) / nthr;
+            const uint32_t w0 = min(n_words, tid * per), w1 = min(n_words, w0 + per);
+            uint32_t sum = 0, tot;
+            for (uint32_t w = w0; w < w1; ++w) sum += __popc(bits[w]);
+            uint32_t run = mw_block_exscan(sum, scratch, &tot);
+            for (uint32_t w = w0; w < w1; ++w) { pre[w] = (uint16_t)run; run += __popc(bits[w]); }
+        }
+        mw_lds_barrier();
+        for (uint32_t l = tid; l < lc; l += nthr) {
+            uint32_t n = 0;
+            if (wpl) {
+                const uint32_t w = (l + 1u) * wpl - 1u;
+                n = (uint32_t)(uint16_t)(pre[w] - pre[l * wpl]) + __popc(bits[w]);
+            }
+            st_agent(&a.cnt[(size_t)(le0 + l) * P + p], n);
+        }
+
+        // ---- pass 2: stable rank of every row among the peer's rows for each of its experts in the chunk;
+        // hit k is written by the workgroup that has its expert, the record by the one that has hit 0
+        auto rank = [&](uint32_t i0, const uint32_t (&s_r)[kB], const uint32_t (&local_r)[kB], const uint64_t (&slots_r)[kB])
+            __attribute__((always_inline)) {
+#pragma unroll
+            for (int c = 0; c < kB; ++c) {
+                const uint32_t i = i0 + tid + (uint32_t)c * nthr, s = s_r[c];
+                if (i >= n_rows) continue;
+                uint32_t nk = 0;
+                int32_t first_le = -1, first_rank = 0;
+                if (((addr[i >> 5] >> (i & 31u)) & 1u) && s < max_tokens) {
+                    mw_hit *h = a.hits + (size_t)(rb + i) * Kd;
+                    nk = walk_row(i, local_r[c], slots_r[c], [&](uint32_t k, uint32_t le) __attribute__((always_inline)) {
+                        const uint32_t l = le - le0;
+                        if (l >= lc) return;
+                        const uint32_t w = l * wpl + (s >> 5);
+                        const int32_t rk = (int32_t)((uint32_t)(uint16_t)(pre[w] - pre[l * wpl]) +
+                                                     __popc(bits[w] & ((1u << (s & 31u)) - 1u)));
+                        if (k > 0) h[k] = mw_hit{(int32_t)le, rk};
+                        else { first_le = (int32_t)le; first_rank = rk; }
+                    });
                 }
+                if (first_le >= 0)
+                    a.recs[rb + i] = mw_row_rec{(const char *)pr.rows + (size_t)i * a.row_bytes, (int32_t)s, (int32_t)p,
+                                                (int32_t)nk, first_le, first_rank, 0};
+                else if (nk == 0 && part == 0 && first_chunk)
+                    a.recs[rb + i] = mw_row_rec{nullptr, 0, (int32_t)p, 0, 0, 0, 0};
             }
-        }
-        if (first && one_chunk) rec_c = rec;     // written once its rank is known
-        else recs[rb + i] = rec;
-    }
-
-    for (int le0 = 0; le0 < L; le0 += Lc) {
-        const int lc = min(Lc, L - le0);
-        const uint32_t n_words = (uint32_t)lc * wpl;
-        if (!one_chunk) {
-            if (le0 > 0) mw_lds_barrier();           // the previous chunk's ranks have been read
-            for (uint32_t f = tid; f < n_words; f += nthr) bits[f] = 0;
-            mw_lds_barrier();
-            for (uint32_t i = tid; i < n_rows; i += nthr) {
-                uint32_t s; int nk; int f[8];
-                reload(i, s, nk, f);
-                mark(i, s, nk, f, le0, lc);
-            }
-        }
-        mw_lds_barrier();
-
-        // running popcounts over the chunk's words (expert-major), one flat scan
-        uint32_t carry = 0;
-        for (uint32_t f0 = 0; f0 < n_words; f0 += nthr) {
-            const uint32_t f = f0 + tid;
-            const uint32_t v = (f < n_words) ? __popc(bits[f]) : 0u;
-            uint32_t tot;
-            const uint32_t ex = mw_block_exscan(v, scratch, &tot);
-            if (f < n_words) pre[f] = carry + ex;
-            carry += tot;
-        }
-        mw_lds_barrier();
-        for (int l = tid; l < lc; l += nthr) {
-            const uint32_t end = (l + 1 < lc) ? pre[(uint32_t)(l + 1) * wpl] : carry;
-            st_agent(&cnt[(size_t)(le0 + l) * P + p], end - pre[(uint32_t)l * wpl]);
-        }
-
-        // stable rank of the row among the peer's rows for each of its experts in the chunk
-        for (uint32_t i = tid; i < n_rows; i += nthr) {
-            const bool cached = kCache && one_chunk && i == (uint32_t)tid;
-            mw_hit *h = hits + (size_t)(rb + i) * Kd;
-            uint32_t s = s_c; int nk = nk_c; int f[8];
+        };
+        uint32_t i0 = 0;
+        if (kKeep && first_chunk) { rank(0, s_c, local_c, slots_c); i0 = step; }
+        for (; i0 < n_rows; i0 += step) {
+            uint32_t s_r[kB], local_r[kB];
+            uint64_t slots_r[kB];
+            int32_t e_r[kB][8];
+            load_rows(i0, s_r, e_r);
 #pragma unroll
-            for (int k = 0; k < 8; ++k) f[k] = f_c[k];
-            if (!cached) reload(i, s, nk, f);
-            for (int k = 0; k < nk; ++k) {
-                int le = 0;
-#pragma unroll
-                for (int k8 = 0; k8 < 8; ++k8) if (k8 == k) le = f[k8];
-                if (k >= 8) le = h[k].le;
-                const int l = le - le0;
-                if (l < 0 || l >= lc) continue;
-                const uint32_t wi = (uint32_t)l * wpl + (s >> 5);
-                const int32_t rk = (int32_t)(pre[wi] - pre[(uint32_t)l * wpl] + __popc(bits[wi] & ((1u << (s & 31)) - 1u)));
-                if (k > 0) h[k].rank = rk;
-                else if (cached) rec_c.rank0 = rk;
-                else recs[rb + i].rank0 = rk;
+            for (int c = 0; c < kB; ++c) {
+                local_r[c] = 0; slots_r[c] = 0;
+                if (i0 + (uint32_t)c * nthr < n_rows) classify(e_r[c], 0, local_r[c], slots_r[c]);
             }
+            rank(i0, s_r, local_r, slots_r);
         }
+        le0 += a.parts * Lc;
+        if (le0 >= L) break;
+        first_chunk = false;
+        lc = min(Lc, L - le0);
+        mw_lds_barrier();                            // this chunk's ranks have been read
+        for (uint32_t w = tid; w < lc * wpl; w += nthr) bits[w] = 0;
+        mw_lds_barrier();
+        mark_from(0, false);
     }
-    if (kCache && one_chunk && (uint32_t)tid < n_rows) recs[rb + tid] = rec_c;
-    if (L == 0) {
-        // no expert lives here: any addressed row is inconsistent
-        for (uint32_t w = tid; w < wpl; w += nthr) if (addr[w]) err |= MW_FLAG_NO_LOCAL_EXPERT;
-    }
-    if (err) __hip_atomic_fetch_or(&flags[1], err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (tid == 0) st_agent(&addr_cnt[p], scratch[18] - scratch[20]);    // (both complete: barriers in between)
+    if (err) __hip_atomic_fetch_or(&a.flags[1], err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (tid == 0 && part == 0) st_agent(&a.addr_cnt[p], scratch[18] - scratch[19]);    // (both complete: barriers in between)
 
     // ---- the workgroup that finishes last turns the counts into output bases ----------
     // Everything the last workgroup reads (counts, addressed-row counts, flags) is written and
     // read with device-scope atomics, and every workgroup reports through one counter when all
     // its lanes are done (publication rules in mw_internal.h); the workgroup whose report is the
-    // P-th has thereby acquired what all the others released.  The row records and hit slots,
+    // last has thereby acquired what all the others released.  The row records and hit slots,
     // written with ordinary stores, are read by the next kernel only.
     mw_publish_barrier();
-    if (tid == 0) scratch[17] = mw_report(&flags[2]) == (uint32_t)P - 1u ? 1u : 0u;
+    if (tid == 0) scratch[17] = mw_report(&a.flags[2]) == P * a.parts - 1u ? 1u : 0u;
     __syncthreads();
     if (!scratch[17]) return;
-    mw_finish_counts(cnt, addr_cnt, flags, row_base, (uint32_t)L, (uint32_t)P, out_cap, base, expert_offsets, stats,
-                     scratch);
+    mw_finish_counts(a.cnt, a.addr_cnt, a.flags, a.row_base, L, P, a.out_cap, a.base, a.expert_offsets, a.stats, scratch);
 }
 
-template <bool kPackets, bool kCache = true>
-__device__ __forceinline__ void recv_index_of(const mw_index_args &a, int p)
+// Workgroup w of the index of a batch that rides in a launch of row movers: a row a lane at a time,
+// nothing kept between the passes, which fits 58 vector registers without scratch (see kLean below).
+__device__ __forceinline__ void recv_index_rider(const mw_index_args &a, const uint32_t w)
 {
-    recv_index_body<kPackets, kCache>(a.peers, a.P, a.eslot, a.E, a.K, a.Kd, a.my_rank, a.L, a.Lc, a.max_tokens, a.wpl,
-                              a.cap_rows, a.row_bytes, a.header_bytes, a.out_cap, a.cnt, a.row_base, a.addr_cnt, a.recs,
-                              a.hits, a.base, a.expert_offsets, a.stats, a.flags, a.dedup, p);
+    const uint32_t part = w / (uint32_t)a.P;
+    recv_index_body<false, false, 1, false>(a, w - part * (uint32_t)a.P, part);
 }
 
-template <bool kPackets>
+template <bool kPackets, bool kGeneral, int kB>
 __global__ __launch_bounds__(kIndexBlock) void k_recv_index(const mw_index_args a)
 {
-    recv_index_of<kPackets>(a, blockIdx.x);
+    recv_index_body<kPackets, kGeneral, kB, !kGeneral>(a, blockIdx.x, blockIdx.y);
 }
 
 // ---- the index of a SMALL batch in one workgroup ------------------------------------------------
@@ -846,7 +917,6 @@ __global__ __launch_bounds__(1024) void k_expand(
 // in a lean form that fits 56 registers without spilling (no first-row cache in the index, fewer
 // counters in flight in the plan's second half): a few microseconds slower, long inside the
 // movers' shadow.  Beside a small batch, where the riders ARE the step, they keep the fast form.
-template <bool kLean>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_expand_index_next(
     const uint32_t first_expand_row, const uint32_t unused0, const mw_row_rec *__restrict__ recs,
     const uint32_t *__restrict__ row_base, const uint32_t *__restrict__ base, const mw_hit *__restrict__ hits,
@@ -859,7 +929,8 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
                     blockIdx.y - first_expand_row, gridDim.y - first_expand_row);
         return;
     }
-    if (blockIdx.x == 0) recv_index_of<false, !kLean>(next, (int)blockIdx.y);
+    const uint32_t w = blockIdx.y * gridDim.x + blockIdx.x;
+    if (w < (uint32_t)next.P * next.parts) recv_index_rider(next, w);
 }
 
 // The same launch with the PLAN of the next batch riding along as well (Section 5.1, send
@@ -900,13 +971,13 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
                      pack.row_src_token, pack.row_topk, blockIdx.x, blockIdx.y - y_pack, y_expand - y_pack);
         return;
     }
-    const uint32_t n_index = (uint32_t)next.P;
-    if (blockIdx.y < n_index) {
-        if (blockIdx.x == 0) recv_index_of<false, !kLean>(next, (int)blockIdx.y);
+    const uint32_t w = blockIdx.y * gridDim.x + blockIdx.x, n_index = (uint32_t)next.P * next.parts;
+    if (w < n_index) {
+        recv_index_rider(next, w);
         return;
     }
     extern __shared__ uint64_t plan_lds[];
-    mw_plan_ride<W, kKeyed, kLean ? 8 : 16>(plan, (blockIdx.y - n_index) * gridDim.x + blockIdx.x, plan_lds);
+    mw_plan_ride<W, kKeyed, kLean ? 8 : 16>(plan, w - n_index, plan_lds);
 }
 
 // A whole step of a stream of SMALL batches in one launch (the batch sizes of Section 6.3's
@@ -1036,31 +1107,54 @@ __global__ __launch_bounds__(1024) void k_combine(
 
 }  // namespace
 
-// Index arguments of `ctx` for a launch whose workgroups may use `lds_budget_words` words of LDS
-// each: the addressed-rows bitmap plus two arrays per expert of a chunk (experts beyond the
-// budget are handled in further passes).  Returns false if not even one expert fits.
+// Index arguments of `ctx` for a launch whose workgroups may use `lds_words` words of LDS each: the
+// addressed-rows bitmap, the table of local slots if there is room for it, and one and a half words per
+// 32 source tokens for every expert of a chunk.  The chunks go to `parts` workgroups a peer, at most
+// max_parts (further chunks by further passes), at least min_parts where the experts allow it.
+// Returns false if max_tokens is beyond what the call takes (accept_words: the limit it states,
+// three arrays of a bit per token).
 static bool make_index_args(mw_ctx *ctx, const void *peers, bool packets, int32_t P, int64_t cap,
-                            int64_t *expert_offsets, mw_recv_stats *stats, uint32_t lds_budget_words,
-                            mw_index_args *a, size_t *lds_bytes)
+                            int64_t *expert_offsets, mw_recv_stats *stats, uint32_t accept_words, uint32_t lds_words,
+                            uint32_t min_parts, uint32_t max_parts, mw_index_args *a, size_t *lds_bytes)
 {
     const mw_config &c = ctx->cfg;
-    const int L = ctx->n_local;
+    const uint32_t L = (uint32_t)ctx->n_local;
     const uint32_t wpl = ((uint32_t)c.max_tokens + 31u) / 32u;
     const uint32_t dedup = (ctx->options & MW_OPT_RECV_DEDUP) ? 1u : 0u;
-    if (dedup) lds_budget_words = lds_budget_words > wpl ? lds_budget_words - wpl : 0;     // the "taken" bitmap
-    if (lds_budget_words < 3 * wpl + 64) return false;
-    int Lc = (int)((lds_budget_words - 64 - wpl) / (2 * wpl));
-    if (Lc < 1) return false;
-    if (Lc > L) Lc = L > 0 ? L : 1;
-    *lds_bytes = ((size_t)wpl + 2 * (size_t)Lc * wpl + 64 + (dedup ? wpl : 0)) * sizeof(uint32_t);
+    if (accept_words < 3 * wpl + 64 + (dedup ? wpl : 0)) return false;
+    uint32_t tab_words = ((uint32_t)c.n_experts + 4u) / 4u;             // a byte per expert and one for ids outside the range
+    if (L > kNotLocal || tab_words > lds_words / 4 || mw_index_lds_words(wpl, 1, tab_words, dedup) > lds_words) tab_words = 0;
+    uint32_t Lc = L > 0 ? L : 1;
+    if (dedup) min_parts = max_parts = 1;            // one workgroup decides which of the repeats is taken
+    if (L >= 2 * min_parts) Lc = (L + min_parts - 1) / min_parts;
+    if (wpl > 0) {
+        const size_t fixed = mw_index_lds_words(wpl, 0, tab_words, dedup);
+        const size_t fit = lds_words > fixed ? 2 * (lds_words - fixed) / (3 * (size_t)wpl) : 0;
+        if (fit < 1) return false;
+        if (Lc > fit) Lc = (uint32_t)fit;
+        while (Lc > 1 && mw_index_lds_words(wpl, Lc, tab_words, dedup) > lds_words) --Lc;
+    }
+    const uint32_t n_chunks = L > 0 ? (L + Lc - 1) / Lc : 1;
+    *lds_bytes = mw_index_lds_words(wpl, Lc, tab_words, dedup) * sizeof(uint32_t);
     const uint32_t hb = packets ? (uint32_t)mw_packet_header_bytes_of(c.top_k) : 0u;
-    *a = mw_index_args{peers, P, ctx->d_eslot, c.n_experts, c.top_k, ctx->hit_slots, c.my_rank, L, Lc,
+    *a = mw_index_args{peers, P, ctx->d_eslot, c.n_experts, c.top_k, ctx->hit_slots, c.my_rank, (int)L, (int)Lc,
                        (uint32_t)c.max_tokens, wpl, (uint32_t)c.max_recv_rows,
                        (uint64_t)(packets ? hb + ctx->row_bytes : ctx->row_stride), hb, cap,
                        ctx->d_cnt, ctx->d_row_base, ctx->d_addr_cnt, ctx->d_recs, ctx->d_hits, ctx->d_base,
-                       expert_offsets, stats, ctx->d_flags, dedup};
+                       expert_offsets, stats, ctx->d_flags, dedup, n_chunks < max_parts ? n_chunks : max_parts, tab_words};
     return true;
 }
+
+// Id lists of at most eight, at most 64 local experts and a table of their slots in LDS: a row's ids are
+// one request and its distinct experts a 64-bit set, all in registers.  Anything beyond takes
+// the general form, a row a lane at a time.
+static bool index_is_general(const mw_index_args &a) { return a.K > 8 || a.L > 64 || a.tab_words == 0; }
+
+// LDS words a workgroup of `bs` lanes may reserve in a launch whose row movers should keep every wave
+// slot: its share of a CU's 160 KiB when 2048 lanes are resident.
+static uint32_t rider_lds_words(int bs) { return (uint32_t)bs * 20u; }
+constexpr uint32_t kRiderAcceptWords = 1280, kIndexAcceptWords = 12288;   // limits on max_tokens the entry points state
+constexpr uint32_t kMaxIndexParts = 16;
 
 // the index of `P` peers' regions on `ctx` fits the one-workgroup form
 static bool small_index_fits(const mw_ctx *ctx, int32_t P)
@@ -1087,11 +1181,19 @@ int32_t mw_launch_unpack_index(mw_ctx *ctx, const void *peers, bool packets, int
 {
     mw_index_args a;
     size_t lds_index;
-    if (!make_index_args(ctx, peers, packets, P, cap, expert_offsets, stats, 12288, &a, &lds_index))
+    // A few peers with many experts each: up to four workgroups a peer (8 peers of 2720 rows, 32 experts:
+    // 14.5 us with four, 16.1 with one, 14.5 with eight; no difference where a peer has fewer rows than lanes).
+    uint32_t min_parts = 1;
+    while (min_parts < 4 && (uint32_t)P * min_parts < 32) min_parts *= 2;
+    if (!make_index_args(ctx, peers, packets, P, cap, expert_offsets, stats, kIndexAcceptWords, 16384, min_parts,
+                         kMaxIndexParts, &a, &lds_index))
         return MW_ERR_UNSUPPORTED;
-    // A peer seldom sends more than a fraction of its tokens to one rank: for small batches a
-    // quarter of the lanes do, with shorter barriers and scans (about a microsecond of 11).
-    const int ib = ctx->cfg.max_tokens <= 2048 ? 256 : kIndexBlock;
+    // A lane per row as long as a workgroup has that many (a peer seldom sends more than a fraction of its
+    // tokens to one rank): fewer lanes have shorter barriers and scans, more of them fewer rows each.  With
+    // more rows than lanes three a lane are requested together (8 peers of 2720 rows: 13.6 us, one at a time
+    // 14.5), with fewer one (16 peers of 429 rows: 8.3 us, with room for three 8.7).
+    const int64_t rows_of_peer = ctx->recv_rows_hint > 0 ? (ctx->recv_rows_hint + P - 1) / P : ctx->cfg.max_tokens / 2;
+    const int ib = rows_of_peer <= 256 ? 256 : rows_of_peer <= 512 ? 512 : kIndexBlock;
     {
         mw_timed tm(ctx, MW_KERNEL_RECV_INDEX, s);
         const int64_t expected = ctx->recv_rows_hint > 0 ? ctx->recv_rows_hint : (int64_t)P * ctx->cfg.max_tokens;
@@ -1104,8 +1206,17 @@ int32_t mw_launch_unpack_index(mw_ctx *ctx, const void *peers, bool packets, int
             if (small_index_few_rows(ctx, P)) hipLaunchKernelGGL(k_recv_index_small<2>, dim3(1), dim3(kSmallLanes), lds, s, a);
             else hipLaunchKernelGGL(k_recv_index_small<4>, dim3(1), dim3(kSmallLanes), lds, s, a);
         } else
-        if (packets) hipLaunchKernelGGL(k_recv_index<true>, dim3(P), dim3(ib), lds_index, s, a);
-        else hipLaunchKernelGGL(k_recv_index<false>, dim3(P), dim3(ib), lds_index, s, a);
+        {
+#define MW_INDEX(GENERAL_, ROWS_)                                                                                              \
+    do {                                                                                                                       \
+        if (packets) hipLaunchKernelGGL((k_recv_index<true, GENERAL_, ROWS_>), dim3(P, a.parts), dim3(ib), lds_index, s, a);   \
+        else hipLaunchKernelGGL((k_recv_index<false, GENERAL_, ROWS_>), dim3(P, a.parts), dim3(ib), lds_index, s, a);          \
+    } while (0)
+            if (index_is_general(a)) MW_INDEX(true, 1);
+            else if (rows_of_peer <= ib) MW_INDEX(false, 1);
+            else MW_INDEX(false, 3);
+#undef MW_INDEX
+        }
     }
     MW_HIP_CHECK(hipGetLastError());
     return MW_OK;
@@ -1222,36 +1333,35 @@ int32_t mw_launch_unpack_expand_index_next(mw_ctx *ctx, int32_t P, void *out_row
 {
     const mw_config &c = ctx->cfg;
     if (c.max_recv_rows < 1) return MW_ERR_UNSUPPORTED;       // nothing to ride on
-    // Every workgroup of the launch reserves the index's LDS, the expander's included: at most
-    // 5 KiB, so that a CU's 160 KiB still hold a full set of 32 single-wave expander workgroups.
-    mw_index_args a;
-    size_t lds_index;
-    if (!make_index_args(next, next_peers, false, next_P, next_cap, next_expert_offsets, next_stats, 1280, &a,
-                         &lds_index))
-        return MW_ERR_UNSUPPORTED;
-    if (small_step_fits(ctx, next, next_P, 0, nullptr, expand_grid_rows(ctx)))
-        return launch_small_step(ctx, P, out_rows, out_scales, cap, out_src_peer, out_src_token, next, a, false, nullptr,
-                                 0, nullptr, nullptr, nullptr, nullptr, nullptr, expand_grid_rows(ctx), s);
     const int xc = (int)(ctx->x_row_bytes / 16), sc = (int)(ctx->s_row_bytes / 16);
     mw_row_shape shape = mw_row_shape_of(xc + sc);
     // Rows of whole cache lines: two-wave workgroups here.  The expander runs as fast with them
     // as with single waves (138.8 against 139.4 us at 30590 rows of 14336 bytes), and the riding
     // index gets two waves per peer: with one it outlasts the expander (142 against 139 us).
     if (shape.bs == 64 && (xc + sc) % 16 == 0) { shape.bs = 128; shape.nseg = (xc + sc) / 128 + ((xc + sc) % 128 ? 1 : 0); }
+    // Every workgroup of the launch reserves the index's LDS, the expander's included: no more than
+    // leaves a CU a full set of the expander's waves.
+    mw_index_args a;
+    size_t lds_index;
+    if (!make_index_args(next, next_peers, false, next_P, next_cap, next_expert_offsets, next_stats, kRiderAcceptWords,
+                         rider_lds_words(shape.bs), 1, kMaxIndexParts, &a, &lds_index))
+        return MW_ERR_UNSUPPORTED;
     const uint32_t gy = expand_grid_rows(ctx);
+    if (small_step_fits(ctx, next, next_P, 0, nullptr, gy))
+        return launch_small_step(ctx, P, out_rows, out_scales, cap, out_src_peer, out_src_token, next, a, false, nullptr,
+                                 0, nullptr, nullptr, nullptr, nullptr, nullptr, gy, s);
+    if (index_is_general(a)) {                                // not a form that rides: a launch of its own in front
+        const int32_t rc = mw_launch_unpack_index(next, next_peers, false, next_P, next_cap, next_expert_offsets, next_stats, s);
+        if (rc != MW_OK) return rc;
+        return mw_launch_unpack_expand(ctx, P, out_rows, out_scales, cap, out_src_peer, out_src_token, s);
+    }
+    const uint32_t index_rows = ((uint32_t)next_P * a.parts + (uint32_t)shape.nseg - 1) / (uint32_t)shape.nseg;
     {
         mw_timed tm(ctx, MW_KERNEL_EXPAND, s);
         const uint32_t cap32 = (uint32_t)(cap < 0x7fffffffLL ? cap : 0x7fffffffLL);
-        if (riders_lean(ctx, gy))
-            hipLaunchKernelGGL(k_expand_index_next<true>, dim3(shape.nseg, gy + (uint32_t)next_P), dim3(shape.bs), lds_index,
-                               s, (uint32_t)next_P, 0u, ctx->d_recs, ctx->d_row_base, ctx->d_base, ctx->d_hits, P,
-                               ctx->hit_slots, xc, sc, (u32x4 *)out_rows, (u32x4 *)out_scales, cap32, out_src_peer,
-                               out_src_token, a);
-        else
-            hipLaunchKernelGGL(k_expand_index_next<false>, dim3(shape.nseg, gy + (uint32_t)next_P), dim3(shape.bs), lds_index,
-                               s, (uint32_t)next_P, 0u, ctx->d_recs, ctx->d_row_base, ctx->d_base, ctx->d_hits, P,
-                               ctx->hit_slots, xc, sc, (u32x4 *)out_rows, (u32x4 *)out_scales, cap32, out_src_peer,
-                               out_src_token, a);
+        hipLaunchKernelGGL(k_expand_index_next, dim3(shape.nseg, gy + index_rows), dim3(shape.bs), lds_index, s, index_rows, 0u,
+                           ctx->d_recs, ctx->d_row_base, ctx->d_base, ctx->d_hits, P, ctx->hit_slots, xc, sc,
+                           (u32x4 *)out_rows, (u32x4 *)out_scales, cap32, out_src_peer, out_src_token, a);
     }
     MW_HIP_CHECK(hipGetLastError());
     return MW_OK;
@@ -1268,18 +1378,24 @@ int32_t mw_launch_unpack_expand_index_plan_next(mw_ctx *ctx, int32_t P, void *ou
     const mw_config &c = ctx->cfg;
     if (c.max_recv_rows < 1) return MW_ERR_UNSUPPORTED;       // nothing to ride on
     if (next_T > MW_RIDE_MAX_TOKENS) return MW_ERR_UNSUPPORTED;
+    const int xc = (int)(ctx->x_row_bytes / 16), sc = (int)(ctx->s_row_bytes / 16);
+    mw_row_shape shape = mw_row_shape_of(xc + sc);
+    if (shape.bs == 64 && (xc + sc) % 16 == 0) { shape.bs = 128; shape.nseg = (xc + sc) / 128 + ((xc + sc) % 128 ? 1 : 0); }
     mw_index_args a;
     size_t lds_index;
-    if (!make_index_args(next, next_peers, false, next_P, next_cap, next_expert_offsets, next_stats, 1280, &a,
-                         &lds_index))
+    if (!make_index_args(next, next_peers, false, next_P, next_cap, next_expert_offsets, next_stats, kRiderAcceptWords,
+                         rider_lds_words(shape.bs), 1, kMaxIndexParts, &a, &lds_index))
         return MW_ERR_UNSUPPORTED;
     const uint32_t gy = expand_grid_rows(ctx);
     if (small_step_fits(ctx, next, next_P, next_T, pk, gy))
         return launch_small_step(ctx, P, out_rows, out_scales, cap, out_src_peer, out_src_token, next, a, true, next_topk,
                                  next_T, next_mask, next_perm, next_desc, next_send_stats, pk, gy, s);
-    const int xc = (int)(ctx->x_row_bytes / 16), sc = (int)(ctx->s_row_bytes / 16);
-    mw_row_shape shape = mw_row_shape_of(xc + sc);
-    if (shape.bs == 64 && (xc + sc) % 16 == 0) { shape.bs = 128; shape.nseg = (xc + sc) / 128 + ((xc + sc) % 128 ? 1 : 0); }
+
+    if (index_is_general(a)) {                                // not a form that rides: a launch of its own in front
+        const int32_t rc = mw_launch_unpack_index(next, next_peers, false, next_P, next_cap, next_expert_offsets, next_stats, s);
+        if (rc != MW_OK) return rc;
+        a.parts = 0;
+    }
 
     // the riding plan: workgroups of the launch's size
     const int K = next->cfg.top_k, W = next->mask_words;
@@ -1303,7 +1419,8 @@ int32_t mw_launch_unpack_expand_index_plan_next(mw_ctx *ctx, int32_t P, void *ou
     pl.finish_rows = mw_plan_finish_rows(shape.bs);
     pl.n_finish = next_T > 0 ? ((uint32_t)next_T + pl.finish_rows - 1) / pl.finish_rows : 1u;
     pl.wait_limit = next->ride_wait_limit;
-    const uint32_t n_plan_rows = (pl.n_rank + pl.n_finish + (uint32_t)shape.nseg - 1) / (uint32_t)shape.nseg;
+    const uint32_t rider_rows = ((uint32_t)next_P * a.parts + pl.n_rank + pl.n_finish + (uint32_t)shape.nseg - 1) /
+                                (uint32_t)shape.nseg;
     size_t lds_plan = (size_t)pl.slice * key_bytes;
     if (lds_plan < mw_plan_finish_lds(shape.bs)) lds_plan = mw_plan_finish_lds(shape.bs);
     const size_t lds = lds_index > lds_plan ? lds_index : lds_plan;
@@ -1320,15 +1437,14 @@ int32_t mw_launch_unpack_expand_index_plan_next(mw_ctx *ctx, int32_t P, void *ou
             n_pack_rows = (uint32_t)pk->n_tokens < 16384u ? (uint32_t)pk->n_tokens : 16384u;   // more by striding
         }
         // a grid has at most 65535 rows: the expander takes what the riders leave (more by striding)
-        const uint32_t riders = (uint32_t)next_P + n_plan_rows + n_pack_rows;      // <= 256 + 8192 + 16384
+        const uint32_t riders = rider_rows + n_pack_rows;                         // <= 4096 + 8192 + 16384
         const uint32_t gy_fit = gy < 65535u - riders ? gy : 65535u - riders;
         const dim3 grid(shape.nseg, gy_fit + riders), block(shape.bs);
         const uint32_t cap32 = (uint32_t)(cap < 0x7fffffffLL ? cap : 0x7fffffffLL);
         const bool lean = riders_lean(ctx, gy_fit);
 #define MW_RIDE_(W_, KEYED_, LEAN_)                                                                                \
     hipLaunchKernelGGL((k_expand_index_plan_next<W_, KEYED_, LEAN_>), grid, block, lds, s,                          \
-                       (uint32_t)next_P + n_plan_rows, (uint32_t)next_P + n_plan_rows + n_pack_rows, ctx->d_recs,   \
-                       ctx->d_row_base, P, xc, pa.perm, pa.stats, sc, ctx->hit_slots, ctx->d_base, ctx->d_hits,     \
+                       rider_rows, rider_rows + n_pack_rows, ctx->d_recs, ctx->d_row_base, P, xc, pa.perm, pa.stats, sc, ctx->hit_slots, ctx->d_base, ctx->d_hits,     \
                        (u32x4 *)out_rows, (u32x4 *)out_scales, cap32, out_src_peer, out_src_token, a, pl, pa)
 #define MW_RIDE(W_, KEYED_) do { if (lean) MW_RIDE_(W_, KEYED_, true); else MW_RIDE_(W_, KEYED_, false); } while (0)
         if (keyed) MW_RIDE(4, true);
