@@ -69,6 +69,8 @@ struct mw_ctx {
     int32_t *d_eslot;       // [E] (rank << 16) | slot of expert e among the experts of its rank
     uint64_t *d_plan_cnt;       // [max_tokens] packed per-token counters; zero between plans
     uint32_t *d_plan_state;     // [MW_PLAN_STATE_WORDS] rows per destination, kept tokens, flags, workgroups done; zero between plans
+    uint64_t *d_plan_keys;      // [min(max_tokens, 8192)] keys of the plan's two-launch form
+    uint32_t *d_plan_bad;       // [64] its workgroups that saw an id outside the range
     uint64_t *d_sort_key;       // [max_tokens rounded up to 1024] sorted chunks of the large-batch plan (or null)
     uint32_t *d_sort_sec;       // same count: second sort word
     uint32_t *d_chunk_kept;     // [64] kept tokens per chunk

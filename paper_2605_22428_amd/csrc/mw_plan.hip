@@ -7,29 +7,29 @@
 // C(64,8) sets at EP=64/top-8); the accounting is Section 1's "one copy however many
 // destinations" against one copy per destination.
 //
-// Two launches on the caller's stream, no host synchronisation:
-//   k_rank    A workgroup owns 256 tokens and a slice of all tokens.  It builds the
-//             bitmaps of both from the top-k ids (one lane per token, K rank bits ORed
-//             into four 64-bit words; the slice goes to LDS), then every lane counts, over
-//             the slice, the tokens whose (bitmap, index) is smaller than its own, and how
-//             many carry an equal bitmap before / at-or-after it.  Slices are spread over
-//             the whole chip and combined with one 64-bit integer atomic add per lane (a
-//             sum, so the result does not depend on arrival order).  For the batch sizes
-//             of a dispatch (<= 8k tokens) this beats a multi-pass radix sort of 256-bit
-//             keys, which would be launch- and barrier-bound.  The workgroups of slice 0
-//             also write the bitmaps out and turn 64 tokens' bitmaps into per-rank counts
-//             with wavefront ballots and popcounts.
-//   k_groups  Workgroup b owns packed rows [256 b, 256 b + 256): it finds their tokens
-//             from the counts (predecessor count = packed row), writes perm, ranks the
-//             group starts (tokens with no equal bitmap before them) and writes their
-//             descriptors; a group's row count is the number of equal bitmaps.  Writing is
-//             spread over many workgroups because one CU retires only about one cache line
-//             of scattered stores per cycle.
+// No host synchronisation, launches on the caller's stream only:
+//   k_plan_order  batches of up to 8192 tokens whose bitmaps have a 64-bit key (one word, or at most
+//                 eight ids a token): every workgroup holds all keys and finishes a few tokens, nothing is
+//                 exchanged between workgroups.  Above 2048 tokens k_plan_keys makes the keys first.
+//   k_rank        otherwise (several words, more than eight ids): a workgroup owns 256 tokens and a
+//                 slice of all tokens.  It builds the bitmaps of both from the top-k ids (one lane per
+//                 token; the slice goes to LDS), then every lane counts, over the slice, the tokens whose
+//                 (bitmap, index) is smaller than its own, and how many carry an equal bitmap before /
+//                 at-or-after it.  Slices are spread over the whole chip and combined with one 64-bit
+//                 integer atomic add per lane (a sum, so the result does not depend on arrival order).
+//                 The workgroups of slice 0 also write the bitmaps out and turn 64 tokens'
+//                 bitmaps into per-rank counts with wavefront ballots and popcounts.
+//   k_groups      behind k_rank and the sorted chunks: workgroup b owns packed rows [256 b, 256 b + 256): it
+//                 finds their tokens from the counts (predecessor count = packed row), writes perm, ranks
+//                 the group starts (tokens with no equal bitmap before them) and writes their
+//                 descriptors; a group's row count is the number of equal bitmaps.  Writing is
+//                 spread over many workgroups because one CU retires only about one cache line
+//                 of scattered stores per cycle.
 // The count and histogram buffers are zero between plans: the k_groups workgroup that is the
 // last to have read them clears them, so there is no clearing launch and no host-side state
 // (a captured mw_plan can be replayed).
-// Batches above 8192 tokens replace k_rank by k_chunk_sort + k_merge_rank (sorted chunks,
-// ranks by binary search: T log T instead of T^2); batches of at most 256 tokens can take
+// Batches above 8192 tokens with keys take k_chunk_sort + k_merge_rank (sorted chunks, ranks by
+// binary search: T log T instead of T^2) in k_rank's place; batches of at most 256 tokens can take
 // k_plan_pack, which plans and packs in one launch.
 #include "mw_internal.h"
 #include "mw_plan_dev.h"
@@ -37,7 +37,7 @@
 namespace {
 
 constexpr int kBlock = 256;
-template <int W, bool kKeyed>
+template <int W>
 __global__ __launch_bounds__(kBlock) void k_rank(const int32_t *__restrict__ topk, int T, int K,
                                                  const int32_t *__restrict__ eslot, int E, int slice,
                                                  uint64_t *__restrict__ mask_out,
@@ -45,7 +45,7 @@ __global__ __launch_bounds__(kBlock) void k_rank(const int32_t *__restrict__ top
                                                  uint32_t *__restrict__ pstate)
 {
     extern __shared__ uint64_t smask[];
-    mw_rank_body<W, kKeyed>(topk, T, K, eslot, E, slice, mask_out, cnt, pstate, blockIdx.x, blockIdx.y, kBlock, smask);
+    mw_rank_body<W, false>(topk, T, K, eslot, E, slice, mask_out, cnt, pstate, blockIdx.x, blockIdx.y, kBlock, smask);
 }
 
 // For very large batches the walk below (every workgroup over every token's counters) is
@@ -189,6 +189,483 @@ __global__ __launch_bounds__(kBlock) void k_groups(const uint64_t *__restrict__ 
     for (int r = tid; r < MW_PLAN_STATE_WORDS; r += kBlock) pstate[r] = 0;
 }
 
+// ---- the plan of a batch whose bitmaps have a 64-bit order-preserving key, at most 8192 tokens -------
+// (bitmaps of one word, or of up to eight ranks anywhere: top_k <= 8.)  Every workgroup holds the keys of ALL
+// tokens, a few a lane in registers, and finishes the tokens [wg n_own, wg n_own + n_own) by itself:
+//   packed row   the number of tokens with (key, index) below: one 64-bit compare per 64 tokens, whose
+//                result mask is counted by scalar instructions;
+//   group index  the number of DISTINCT keys below: a hash table in LDS makes one token of every key its
+//                representative, and the same compare masks are counted under the representatives' mask.
+// So no workgroup waits for another, nothing is summed up in global memory, nothing has to be cleared and
+// one launch does it all; what it costs is that the keys are made once per workgroup.  Up to kKeysFrom
+// tokens each workgroup makes them from the ids; beyond, a first launch makes them once
+// (k_plan_keys) and the workgroups only load them: 8 instead of 4 top_k bytes a token, no look-ups.
+// Bound by latency (a dependent instruction 3.4 ns, a block barrier with its LDS traffic about 0.1 us).
+// Before, with per-slice counts joined by global atomics and a second launch that inverted them (mw_plan
+// alone, us): 1000 tokens 15.0 -> 7.4, 2048 15.8 -> 8.8, 4096 19.2 -> 12.3, 8192 33.9 -> 21.3 (256 ranks 37.3 -> 21.8).
+//
+// The key of a multi-word bitmap: its rank positions, highest first, a byte each; the highest as it
+// is, the others plus one (they are at most 254, since a higher one precedes them), zero for "no further
+// rank".  Comparing keys is comparing the bitmaps as numbers, and different bitmaps have different
+// keys.  The key of a one-word bitmap is the word.
+constexpr int kOrderBlock = 1024, kOrderMaxTokens = 8192, kOwnMax = 32;
+
+template <bool kBytes> struct mw_order_key {
+    // a value no kept token's key has: marks free slots of the hash table.  (One word: 0 is the empty
+    // bitmap.  Bytes: the third byte from the top is at most 254.)
+    static constexpr uint64_t kNone = kBytes ? ~0ull : 0ull;
+};
+
+// Key of one token from its ranks plus one (0: no rank).
+template <bool kBytes>
+__device__ __forceinline__ uint64_t order_key_of(uint32_t (&v)[8])
+{
+    static_assert(kBytes, "one-word bitmaps are their own keys");
+#define MW_CE(i, j) do { const uint32_t hi_ = max(v[i], v[j]), lo_ = min(v[i], v[j]); v[i] = hi_; v[j] = lo_; } while (0)
+    MW_CE(0, 1); MW_CE(2, 3); MW_CE(4, 5); MW_CE(6, 7);          // odd-even merge sort of eight, descending
+    MW_CE(0, 2); MW_CE(1, 3); MW_CE(4, 6); MW_CE(5, 7);
+    MW_CE(1, 2); MW_CE(5, 6);
+    MW_CE(0, 4); MW_CE(1, 5); MW_CE(2, 6); MW_CE(3, 7);
+    MW_CE(2, 4); MW_CE(3, 5);
+    MW_CE(1, 2); MW_CE(3, 4); MW_CE(5, 6);
+#undef MW_CE
+    uint64_t key = 0;
+    int n = 0;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const bool take = v[j] != 0 && (j == 0 || v[j] != v[j - 1]);       // a rank named twice counts once
+        const uint32_t byte = n == 0 ? v[j] - 1u : v[j];
+        key |= take ? (uint64_t)byte << (56 - 8 * n) : 0ull;
+        n += take ? 1 : 0;
+    }
+    return n ? key : mw_order_key<true>::kNone;
+}
+
+// The bitmap a key stands for.
+template <bool kBytes>
+__device__ __forceinline__ void mask_of_key(uint64_t key, uint64_t (&m)[MW_MASK_WORDS])
+{
+#pragma unroll
+    for (int q = 0; q < MW_MASK_WORDS; ++q) m[q] = 0;
+    if (key == mw_order_key<kBytes>::kNone) return;
+    if constexpr (!kBytes) {
+        m[0] = key;
+    } else {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const uint32_t b = (uint32_t)(key >> (56 - 8 * j)) & 0xffu;
+            if (j > 0 && b == 0) continue;
+            const uint32_t r = j > 0 ? b - 1u : b;
+#pragma unroll
+            for (int q = 0; q < MW_MASK_WORDS; ++q) m[q] |= (r >> 6) == (uint32_t)q ? 1ull << (r & 63u) : 0ull;
+        }
+    }
+}
+
+// The first eight ids of kN tokens t, t + stride, ... of one lane, all requested together (past the last token
+// the last one is read again: T > 0).
+template <int kN>
+__device__ __forceinline__ void load_ids(const int32_t *__restrict__ topk, int T, int K, int j0, int t, int stride, int32_t (&e)[kN][8])
+{
+    const bool wide = (K & 3) == 0 && ((uintptr_t)topk & 15u) == 0;        // id lists of whole 16-byte units
+#pragma unroll
+    for (int n = 0; n < kN; ++n) {
+        const int32_t *row = topk + (size_t)min(t + n * stride, T - 1) * K + j0;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) e[n][k] = -1;
+        if (wide) {
+            const u32x4 q = *(const u32x4 *)row;
+            e[n][0] = (int32_t)q.x; e[n][1] = (int32_t)q.y; e[n][2] = (int32_t)q.z; e[n][3] = (int32_t)q.w;
+            if (j0 + 4 < K) {
+                const u32x4 p = *((const u32x4 *)row + 1);
+                e[n][4] = (int32_t)p.x; e[n][5] = (int32_t)p.y; e[n][6] = (int32_t)p.z; e[n][7] = (int32_t)p.w;
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) if (j0 + k < K) e[n][k] = row[k];
+        }
+    }
+}
+
+// Their keys.  `tab`: LDS table of rank + 1 per expert (0: none), entry E for ids outside [0, E); null: the rank
+// table in memory.
+template <bool kBytes, int kN>
+__device__ __forceinline__ void keys_of_ids(int32_t (&e)[kN][8], const int32_t *__restrict__ topk, int T, int K,
+                                            const int32_t *__restrict__ eslot, int E, const uint16_t *tab, int t, int stride,
+                                            uint64_t (&key)[kN], bool &bad)
+{
+#pragma unroll
+    for (int n = 0; n < kN; ++n) key[n] = 0;
+    for (int j0 = 0; j0 < K; j0 += 8) {                                     // (one turn where keys are bytes)
+        if (j0 > 0) load_ids<kN>(topk, T, K, j0, t, stride, e);
+#pragma unroll
+        for (int n = 0; n < kN; ++n) {
+            uint32_t v[8], out = 0;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const uint32_t x = min((uint32_t)e[n][k], (uint32_t)E);
+                if (tab) v[k] = tab[x];
+                else { const int32_t q = x < (uint32_t)E ? eslot[x] : -1; v[k] = q < 0 ? 0u : (uint32_t)(q >> 16) + 1u; }
+                out |= (x == (uint32_t)E && e[n][k] != -1) ? 1u : 0u;
+            }
+            bad |= out != 0 && t + n * stride < T;
+            if constexpr (kBytes) {
+                key[n] = order_key_of<true>(v);
+            } else {
+#pragma unroll
+                for (int k = 0; k < 8; ++k) key[n] |= v[k] ? 1ull << ((v[k] - 1u) & 63u) : 0ull;
+            }
+        }
+    }
+#pragma unroll
+    for (int n = 0; n < kN; ++n) if (t + n * stride >= T) key[n] = mw_order_key<kBytes>::kNone;
+}
+
+// Bucket of a key among kBuckets, never decreasing with the key, fine where keys are dense: up to twelve ranks
+// the bitmap itself, up to 24 the highest rank and the six bits below it, beyond (few of many ranks
+// named) the two highest ranks; of a byte key the highest rank and the upper half of the second's byte.
+constexpr int kBuckets = 4096;
+template <bool kBytes>
+__device__ __forceinline__ uint32_t bucket_of(uint64_t key, int R)
+{
+    if constexpr (kBytes) return (uint32_t)(key >> 52);
+    if (R <= 12) return (uint32_t)key & (kBuckets - 1u);
+    const int h = 63 - __clzll((long long)(key | 1ull));
+    const uint64_t rest = key & ~(1ull << h);
+    if (R <= 24) return (uint32_t)h * 64u + (uint32_t)((h >= 6 ? rest >> (h - 6) : rest << (6 - h)) & 63ull);
+    return (uint32_t)h * 64u + (rest ? 64u - (uint32_t)__clzll((long long)rest) : 0u);
+}
+
+// LDS table of rank + 1 per expert: needs (E + 1) halfwords; entry E is 0.
+__device__ __forceinline__ void fill_rank_table(uint16_t *tab, const int32_t *__restrict__ eslot, int E)
+{
+    for (int e = threadIdx.x; e <= E; e += (int)blockDim.x) {
+        const int32_t q = e < E ? eslot[e] : -1;
+        tab[e] = q < 0 ? (uint16_t)0 : (uint16_t)((q >> 16) + 1);
+    }
+}
+constexpr int kTableExperts = 4095;        // experts of the LDS table (8 KiB); more: look-ups in memory
+
+// First launch of the two-launch form: a token a lane.  bad[wg]: one of its ids was outside [0, E).
+constexpr int kKeysBlock = 128;
+template <bool kBytes>
+__global__ __launch_bounds__(kKeysBlock) void k_plan_keys(const int32_t *__restrict__ topk, int T, int K,
+                                                          const int32_t *__restrict__ eslot, int E,
+                                                          uint64_t *__restrict__ keys, uint32_t *__restrict__ bad_out)
+{
+    extern __shared__ uint64_t keys_lds[];
+    uint16_t *tab = E <= kTableExperts ? (uint16_t *)keys_lds : nullptr;
+    __shared__ uint32_t any_bad;
+    if (threadIdx.x == 0) any_bad = 0;
+    const int t = blockIdx.x * kKeysBlock + threadIdx.x;
+    int32_t e[1][8];
+    load_ids<1>(topk, T, K, 0, t, 0, e);
+    if (tab) fill_rank_table(tab, eslot, E);
+    mw_lds_barrier();
+    uint64_t key[1];
+    bool bad = false;
+    keys_of_ids<kBytes, 1>(e, topk, T, K, eslot, E, tab, t, 0, key, bad);
+    if (t < T) keys[t] = key[0];
+    if (bad) any_bad = 1;
+    mw_lds_barrier();
+    if (threadIdx.x == 0) bad_out[blockIdx.x] = any_bad;
+}
+
+// kU: tokens a lane holds (T <= kU blockDim.x).  kFromKeys: keys and bad[n_bad] come from k_plan_keys.
+// pstate: only its flag word is looked at (mw_plan_static reports bad table entries there).
+// kByBucket: keys are first counted into buckets (LDS), the bucket's start gives most of a token's packed row and group
+// index, and only the keys of its own bucket are compared with it -- where a workgroup's tokens times all
+// tokens would be the time (8192 tokens: 34 us of compares).
+template <bool kBytes, int kU, bool kFromKeys, bool kByBucket>
+__global__ __launch_bounds__(kOrderBlock) void k_plan_order(
+    const int32_t *__restrict__ topk, int T, int K, const int32_t *__restrict__ eslot, int E, int R, int n_own, int slots_log,
+    const uint64_t *__restrict__ keys, const uint32_t *__restrict__ bad_in, int n_bad, const uint32_t *__restrict__ pstate,
+    uint64_t row_bytes, uint64_t *__restrict__ mask_out, int32_t *__restrict__ perm, mw_group_desc *__restrict__ desc,
+    mw_send_stats *__restrict__ stats)
+{
+    constexpr uint64_t kNone = mw_order_key<kBytes>::kNone;
+    extern __shared__ __align__(16) uint64_t order_lds[];
+    unsigned long long *slot = (unsigned long long *)order_lds;       // [1 << slots_log] hash table of keys
+    const uint32_t n_slots = 1u << slots_log;
+    uint64_t *own = order_lds + n_slots;                              // [kOwnMax]          keys of this workgroup's tokens
+    uint2 *part = (uint2 *)(own + kOwnMax);                           // [16][kOwnMax]      the waves' counts for them
+    uint32_t *wave_n = (uint32_t *)(part + 16 * kOwnMax);             // [16][4]            kept, distinct, destinations, bad
+    uint32_t *wave_r = wave_n + 64;                                   // [16][4]            tokens that name rank r
+    uint32_t *bins = wave_r + 64;                                     // [kBuckets]         (by bucket) tokens and representatives
+    uint16_t *tab = kFromKeys || E > kTableExperts ? nullptr : (uint16_t *)(bins + (kByBucket ? kBuckets : 0));
+    const int tid = threadIdx.x, bs = blockDim.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), n_wave = bs >> 6;
+    const int wg = blockIdx.x, n_wg = gridDim.x, t0 = wg * n_own;
+    __shared__ uint32_t scan[kByBucket ? 17 : 1];
+
+    uint64_t key[kU];
+    int32_t e[kFromKeys ? 1 : kU][8];
+    bool bad = false;
+    if constexpr (kFromKeys) {
+#pragma unroll
+        for (int j = 0; j < kU; ++j) key[j] = tid + j * bs < T ? keys[tid + j * bs] : kNone;
+        bad = wg == 0 && tid < n_bad && bad_in[tid] != 0;
+    } else if (T > 0) {
+        load_ids<kU>(topk, T, K, 0, tid, bs, e);
+    }
+    if (tab) fill_rank_table(tab, eslot, E);
+    for (uint32_t s = tid; s < n_slots / 2; s += bs) ((ulonglong2 *)slot)[s] = make_ulonglong2(kNone, kNone);
+    if constexpr (kByBucket) for (uint32_t b = tid; b < kBuckets / 4; b += bs) ((uint4 *)bins)[b] = make_uint4(0, 0, 0, 0);
+    mw_lds_barrier();
+    if constexpr (!kFromKeys) {
+        if (T > 0) {
+            keys_of_ids<kBytes, kU>(e, topk, T, K, eslot, E, tab, tid, bs, key, bad);
+        } else {                                                      // an empty batch has no ids to read
+#pragma unroll
+            for (int j = 0; j < kU; ++j) key[j] = kNone;
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < kU; ++j) {
+        const int o = tid + j * bs - t0;
+        if (o >= 0 && o < n_own) own[o] = key[j];
+    }
+
+    // ---- one representative per distinct key: the token whose key takes the slot.  A lane's probes go out together,
+    // round after round until the longest chain has ended (at least half of the slots stay free).  A wave whose
+    // tokens all have one key sends one lane: thousands of compare-and-swaps on one address would queue.
+    uint64_t kept[kU], rep[kU];                                       // wave masks
+    uint64_t hit[kU];                                                 // what the token's slot held: kNone for a representative
+    uint32_t at[kU], stride[kU];
+    bool same[kU];                                                    // (uniform) the wave's kept tokens have one key
+#pragma unroll
+    for (int j = 0; j < kU; ++j) {
+        const bool k = key[j] != kNone;
+        kept[j] = __ballot(k);
+        const int first = kept[j] ? (int)__builtin_ctzll(kept[j]) : 0;
+        const uint64_t fk = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)key[j], first) |
+                            (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(key[j] >> 32), first) << 32;
+        same[j] = __ballot(key[j] == fk) == kept[j];
+        const uint32_t h = ((uint32_t)key[j] ^ ((uint32_t)(key[j] >> 32) * 0x9E3779B1u)) * 0x85EBCA6Bu;
+        at[j] = h >> (32 - slots_log);
+        stride[j] = (h >> 3) | 1u;                                    // odd: visits every slot
+        hit[j] = key[j];
+        if (k && (!same[j] || lane == first))
+            hit[j] = atomicCAS(&slot[at[j]], (unsigned long long)kNone, (unsigned long long)key[j]);
+    }
+    while (true) {
+        bool more = false;
+#pragma unroll
+        for (int j = 0; j < kU; ++j) more |= hit[j] != kNone && hit[j] != key[j];
+        if (!__any(more)) break;
+#pragma unroll
+        for (int j = 0; j < kU; ++j) {
+            if (hit[j] != kNone && hit[j] != key[j]) {                // taken by another key
+                at[j] = (at[j] + stride[j]) & (n_slots - 1u);
+                hit[j] = atomicCAS(&slot[at[j]], (unsigned long long)kNone, (unsigned long long)key[j]);
+            }
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < kU; ++j) rep[j] = __ballot(hit[j] == kNone) & kept[j];   // (a lane without a key: hit == key == kNone)
+
+    // ---- totals (workgroup 0) and rows per destination (rank r: workgroup r modulo the grid)
+    if (lane == 0) {
+        uint32_t n = 0, g = 0;
+#pragma unroll
+        for (int j = 0; j < kU; ++j) { n += (uint32_t)__popcll(kept[j]); g += (uint32_t)__popcll(rep[j]); }
+        wave_n[wave * 4] = n;
+        wave_n[wave * 4 + 1] = g;
+    }
+    if (wg == 0) {
+        uint32_t d = 0;
+#pragma unroll
+        for (int j = 0; j < kU; ++j) {
+            if constexpr (!kBytes) {
+                d += (uint32_t)__popcll(key[j]);
+            } else if (key[j] != kNone) {
+                uint64_t x = key[j] & 0x00ffffffffffffffull;          // its non-zero bytes, and the first rank
+                x |= x >> 4; x |= x >> 2; x |= x >> 1;
+                d += 1u + (uint32_t)__popcll(x & 0x0001010101010101ull);
+            }
+        }
+        d = mw_wave_sum(d);
+        const uint64_t any_bad = __ballot(bad);
+        if (lane == 0) { wave_n[wave * 4 + 2] = d; wave_n[wave * 4 + 3] = any_bad ? 1u : 0u; }
+    }
+    for (int q = 0, r = wg; q < 4 && r < R; ++q, r += n_wg) {         // (the grid has at least R / 4 workgroups)
+        uint32_t n = 0;
+#pragma unroll
+        for (int j = 0; j < kU; ++j) {
+            bool names;
+            if constexpr (!kBytes) {
+                names = (key[j] >> r) & 1ull;
+            } else {
+                const uint64_t x = (key[j] | 0xff00000000000000ull) ^ (0x0001010101010101ull * (uint64_t)((r + 1) & 0xff));
+                const bool low = (((x - 0x0001010101010101ull) & ~x & 0x0080808080808080ull) != 0) && r < 255;
+                names = key[j] != kNone && (low || (uint32_t)(key[j] >> 56) == (uint32_t)r);
+            }
+            n += (uint32_t)__popcll(__ballot(names));
+        }
+        if (lane == 0) wave_r[wave * 4 + q] = n;
+    }
+    uint32_t bucket[kU], pos[kU];
+    if constexpr (kByBucket) {
+#pragma unroll
+        for (int j = 0; j < kU; ++j) {
+            bucket[j] = bucket_of<kBytes>(key[j], R);
+            if (same[j]) {                                            // one add for the wave's tokens
+                const int first = kept[j] ? (int)__builtin_ctzll(kept[j]) : 0;
+                uint32_t p = 0;
+                if (kept[j] && lane == first)
+                    p = atomicAdd(&bins[bucket[j]], (uint32_t)__popcll(kept[j]) | (uint32_t)__popcll(rep[j]) << 16);
+                pos[j] = ((uint32_t)__builtin_amdgcn_readlane((int)p, first) & 0xffffu) +
+                         (uint32_t)__popcll(kept[j] & ((1ull << lane) - 1ull));
+            } else if (key[j] != kNone) {
+                pos[j] = atomicAdd(&bins[bucket[j]], 1u | (hit[j] == kNone ? 0x10000u : 0u)) & 0xffffu;
+            }
+        }
+    }
+    mw_lds_barrier();
+
+    if constexpr (kByBucket) {
+        // ---- bucket starts (both counts at once, halves stay below 2^16), then the keys bucket by bucket in the hash
+        // table's place; the order inside a bucket does not matter
+        unsigned long long *lkey = slot;                              // [T]
+        uint16_t *lidx = (uint16_t *)(lkey + T);                      // [T]    token, bit 15: representative
+        static_assert(kBuckets == 4 * kOrderBlock, "four buckets a lane");
+        {
+            uint4 c = ((uint4 *)bins)[tid];
+            uint32_t total;
+            uint32_t run = mw_block_exscan(c.x + c.y + c.z + c.w, scan, &total);
+            const uint4 st = make_uint4(run, run + c.x, run + c.x + c.y, run + c.x + c.y + c.z);
+            ((uint4 *)bins)[tid] = st;
+        }
+        mw_lds_barrier();
+#pragma unroll
+        for (int j = 0; j < kU; ++j) {
+            if (key[j] == kNone) continue;
+            const uint32_t i = (bins[bucket[j]] & 0xffffu) + pos[j];
+            lkey[i] = key[j];
+            lidx[i] = (uint16_t)((uint32_t)(tid + j * bs) | (hit[j] == kNone ? 0x8000u : 0u));
+        }
+        mw_lds_barrier();
+        // ---- a wave per own token
+        uint32_t n_kept = 0, n_distinct = 0;
+        for (int w = 0; w < n_wave; ++w) { n_kept += wave_n[w * 4]; n_distinct += wave_n[w * 4 + 1]; }
+        for (int o = wave; o < n_own && t0 + o < T; o += n_wave) {
+            const uint64_t k = own[o];
+            if (k == kNone) continue;
+            const uint32_t b = bucket_of<kBytes>(k, R), st = bins[b];
+            const uint32_t end = b + 1 < kBuckets ? bins[b + 1] : n_kept | n_distinct << 16;
+            const uint32_t from = st & 0xffffu, to = end & 0xffffu;
+            uint32_t below = from, distinct = st >> 16, before = 0, after = 0;
+            uint32_t i0 = from;
+            if ((end >> 16) - distinct == 1) {                        // one key in the bucket: only the tokens' order counts
+                for (; i0 + 256 <= to; i0 += 256) {
+                    uint32_t id[4];
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) id[c] = lidx[i0 + 64u * c + lane];
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) before += (uint32_t)__popcll(__ballot((int)(id[c] & 0x7fffu) < t0 + o));
+                }
+                after = i0 - from - before;
+            }
+            auto count = [&](uint64_t q, uint32_t id, uint64_t in) __attribute__((always_inline)) {
+                const uint64_t lt = __ballot(q < k) & in, eq = __ballot(q == k) & in;
+                below += (uint32_t)__popcll(lt);
+                distinct += (uint32_t)__popcll(lt & __ballot(id > 0x7fffu));
+                if (eq) {
+                    const uint64_t ahead = __ballot((int)(id & 0x7fffu) < t0 + o);
+                    before += (uint32_t)__popcll(eq & ahead);
+                    after += (uint32_t)__popcll(eq & ~ahead);
+                }
+            };
+            for (; i0 + 256 <= to; i0 += 256) {                       // a crowded bucket: four reads in flight
+                uint64_t q[4];
+                uint32_t id[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) { q[c] = lkey[i0 + 64u * c + lane]; id[c] = lidx[i0 + 64u * c + lane]; }
+#pragma unroll
+                for (int c = 0; c < 4; ++c) count(q[c], id[c], ~0ull);
+            }
+            for (; i0 < to; i0 += 64) {
+                const uint32_t i = min(i0 + (uint32_t)lane, to - 1u), left = to - i0;
+                count(lkey[i], lidx[i], left >= 64 ? ~0ull : (1ull << left) - 1ull);
+            }
+            if (lane == 0) part[o] = make_uint2(below | distinct << 16, before | after << 16);
+        }
+    } else
+    // ---- counts for the workgroup's own tokens
+    if (t0 < T) {
+        const uint64_t mine = lane < kOwnMax ? own[lane] : kNone;     // (entries past n_own are not used)
+        uint32_t c0 = 0, c1 = 0;                                      // lane o: (below, distinct below), (equal before, equal at or after)
+#pragma unroll
+        for (int j = 0; j < kU; ++j) if (key[j] == kNone) key[j] = ~0ull;      // below no token; equals are masked by `kept`
+        const int n = min(n_own, T - t0);
+        for (int o = 0; o < n; ++o) {
+            const uint64_t k = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)mine, o) |
+                               (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(mine >> 32), o) << 32;
+            uint32_t below = 0, distinct = 0, before = 0, after = 0;
+#pragma unroll
+            for (int j = 0; j < kU; ++j) {
+                const uint64_t lt = __ballot(key[j] < k);
+                below += (uint32_t)__popcll(lt);
+                distinct += (uint32_t)__popcll(lt & rep[j]);
+                const uint64_t eq = __ballot(key[j] == k) & kept[j];
+                if (eq) {
+                    const int ahead = t0 + o - (j * bs + wave * 64);  // tokens of this wave's 64 that come before
+                    const uint64_t m = ahead <= 0 ? 0ull : ahead >= 64 ? ~0ull : (1ull << ahead) - 1ull;
+                    before += (uint32_t)__popcll(eq & m);
+                    after += (uint32_t)__popcll(eq & ~m);
+                }
+            }
+            if (lane == o) { c0 = below | distinct << 16; c1 = before | after << 16; }
+        }
+        if (lane < n) part[wave * kOwnMax + lane] = make_uint2(c0, c1);
+    }
+    mw_lds_barrier();
+    if (tid < n_own && t0 + tid < T) {
+        const int t = t0 + tid;
+        uint32_t c0 = 0, c1 = 0;
+        for (int w = 0; w < (kByBucket ? 1 : n_wave); ++w) { const uint2 c = part[w * kOwnMax + tid]; c0 += c.x; c1 += c.y; }     // (halves stay below 2^16)
+        uint64_t m[MW_MASK_WORDS];
+        const uint64_t k = own[tid];
+        mask_of_key<kBytes>(k, m);
+        uint64_t *mo = mask_out + (size_t)t * MW_MASK_WORDS;
+#pragma unroll
+        for (int q = 0; q < MW_MASK_WORDS; ++q) mo[q] = m[q];
+        if (k != kNone) {
+            const uint32_t below = c0 & 0xffffu, distinct = c0 >> 16, before = c1 & 0xffffu, after = c1 >> 16;
+            const uint32_t row = below + before;
+            perm[row] = t;
+            if (before == 0) {
+                mw_group_desc d;
+                uint32_t nd = 0;
+#pragma unroll
+                for (int q = 0; q < MW_MASK_WORDS; ++q) { d.mask[q] = m[q]; nd += (uint32_t)__popcll(m[q]); }
+                d.row_offset = row; d.row_count = after; d.n_dest = nd; d.reserved0 = 0;
+                desc[distinct] = d;
+            }
+        }
+    }
+    if (tid < 4 && wg + tid * n_wg < R) {
+        uint32_t n = 0;
+        for (int w = 0; w < n_wave; ++w) n += wave_r[w * 4 + tid];
+        stats->rows_per_dest[wg + tid * n_wg] = n;
+    }
+    if (wg == 0) {
+        for (int r = R + tid; r < MW_MAX_RANKS; r += bs) stats->rows_per_dest[r] = 0;
+        if (tid == 0) {
+            uint32_t n = 0, g = 0, d = 0, b = 0;
+            for (int w = 0; w < n_wave; ++w) {
+                n += wave_n[w * 4]; g += wave_n[w * 4 + 1]; d += wave_n[w * 4 + 2]; b |= wave_n[w * 4 + 3];
+            }
+            stats->n_rows = n;
+            stats->n_groups = g;
+            stats->multicast_bytes = (uint64_t)n * row_bytes;
+            stats->unicast_bytes = (uint64_t)d * row_bytes;
+            stats->error_flags = pstate[kPsFlags] | (b ? MW_FLAG_BAD_EXPERT : 0u);
+            stats->reserved0 = 0;
+        }
+    }
+}
+
 __global__ __launch_bounds__(256) void k_plan_allgather(int R, uint64_t shard_bytes, mw_group_desc *desc,
                                                         mw_send_stats *stats)
 {
@@ -274,7 +751,7 @@ __global__ __launch_bounds__(kBlock) void k_plan_pack(const int32_t *__restrict_
 // ---- ordering of large batches: sorted chunks, then ranks by binary search ------------------
 // The all-pairs walk of k_rank costs T^2 compares: 84 us at 16 k tokens, 220 us at 32 k, 700 us
 // at 64 k (one-word bitmaps; 120 / 335 / 1085 us with short keys).  This path: 48 / 68 / 97 us
-// (53 / 74 / 107 us).  For large batches (switch points below) whose bitmaps have a 64-bit order-preserving key (one word, or
+// (53 / 74 / 107 us).  For batches beyond k_plan_order's whose bitmaps have a 64-bit order-preserving key (one word, or
 // short keys) the same counters are produced in T log T work:
 //   k_chunk_sort   one workgroup per chunk of 1024 tokens: bitmaps, keys, a bitonic sort of
 //                  (key, second word) pairs in LDS; the sorted chunk goes to the workspace.
@@ -288,9 +765,6 @@ __global__ __launch_bounds__(kBlock) void k_plan_pack(const int32_t *__restrict_
 // tokens without a destination and the padding of the last chunk carry the largest key and a
 // second word above every kept token's, so they sort behind all kept tokens of the chunk.
 constexpr int kChunk = 1024;
-// Switch points, measured: one-word bitmaps tie at 8192 tokens (35 us either way); with short
-// keys (a costlier compare per pair) sorting is ahead from about 6144 (8192 tokens: 39 against 48 us).
-constexpr int kChunkFromOneWord = 8193, kChunkFromKeyed = 6145;
 constexpr int kRowsFrom = 24576;       // from here k_groups works on row-indexed arrays
 constexpr uint32_t kSecEmpty = 0x40000000u, kSecPad = 0x7fffffffu;
 
@@ -443,6 +917,52 @@ int32_t mw_launch_plan_allgather_split(mw_ctx *ctx, int64_t shard_bytes, int64_t
     return MW_OK;
 }
 
+// Tokens from which the keys get a launch of their own, and from which a token is compared with its bucket only
+// (mw_plan alone, us).  Keys: 64 ranks, 2048 tokens 8.8 in one launch, 9.9 in two; 3000 tokens 13.3 / 10.9, 8192
+// tokens 37.6 / 21.3 (256 ranks 41.2 / 21.8).  Buckets: up to one token a lane the buckets' two scans cost what the
+// compares do, with 4096 tokens 18 us without them and 12.3 with, with 8192 36 and 21.3.
+constexpr int kKeysFrom = 2049;
+constexpr int kBucketsFrom = 1025;
+
+template <bool kBytes>
+static void launch_plan_order(mw_ctx *ctx, const int32_t *topk, int32_t T, uint64_t *mask, int32_t *perm, mw_group_desc *desc,
+                              mw_send_stats *stats, hipStream_t s)
+{
+    const int K = ctx->cfg.top_k, E = ctx->cfg.n_experts, R = ctx->cfg.n_ranks;
+    const bool from_keys = T >= kKeysFrom;
+    const int bs = T <= 256 ? 256 : T <= 512 ? 512 : kOrderBlock;
+    // about a workgroup per CU, and enough of them that each counts at most four ranks
+    int n_own = (T + 255) / 256;
+    if (n_own < 1) n_own = 1;
+    int n_wg = (T + n_own - 1) / n_own;
+    if (n_wg < (R + 3) / 4) n_wg = (R + 3) / 4;
+    // four slots a token up to 4096 tokens, then the two that LDS has room for: half the slots taken means probe
+    // chains of up to ten, and every wave waits for the longest
+    int slots_log = 6;
+    while ((1 << slots_log) < 2 * T || ((1 << slots_log) < 4 * T && slots_log < 14)) ++slots_log;
+    const size_t tab = E <= kTableExperts ? ((size_t)E + 4) / 4 * 8 : 0;
+    const bool by_bucket = T >= kBucketsFrom;
+    const size_t lds = ((size_t)8 << slots_log) + 8 * kOwnMax + 8 * 16 * kOwnMax + 4 * 128 + (by_bucket ? 4 * kBuckets : 0) +
+                       (from_keys ? 0 : tab);
+    const int n_key_wg = (T + kKeysBlock - 1) / kKeysBlock;
+    if (from_keys) {
+        mw_timed tm(ctx, MW_KERNEL_PLAN_RANK, s);
+        hipLaunchKernelGGL(k_plan_keys<kBytes>, dim3(n_key_wg), dim3(kKeysBlock), tab, s, topk, T, K, ctx->d_eslot, E,
+                           ctx->d_plan_keys, ctx->d_plan_bad);
+    }
+    mw_timed tm(ctx, from_keys ? MW_KERNEL_PLAN_GROUPS : MW_KERNEL_PLAN_RANK, s);
+#define MW_ORDER(U_, KEYS_, BUCKET_)                                                                                    \
+    hipLaunchKernelGGL((k_plan_order<kBytes, U_, KEYS_, BUCKET_>), dim3(n_wg), dim3(bs), lds, s, topk, T, K, ctx->d_eslot, E, R, \
+                       n_own, slots_log, ctx->d_plan_keys, ctx->d_plan_bad, n_key_wg, ctx->d_plan_state,                      \
+                       (uint64_t)ctx->row_bytes, mask, perm, desc, stats)
+    static_assert(kBucketsFrom == kOrderBlock + 1 && kKeysFrom == 2 * kOrderBlock + 1, "tokens a lane of each form");
+    if (!by_bucket) MW_ORDER(1, false, false);
+    else if (!from_keys) MW_ORDER(2, false, true);
+    else if (T <= 4 * kOrderBlock) MW_ORDER(4, true, true);
+    else MW_ORDER(8, true, true);
+#undef MW_ORDER
+}
+
 int32_t mw_launch_plan(mw_ctx *ctx, const int32_t *topk, int32_t T, uint64_t *mask, int32_t *perm,
                        mw_group_desc *desc, mw_send_stats *stats, hipStream_t s)
 {
@@ -452,7 +972,15 @@ int32_t mw_launch_plan(mw_ctx *ctx, const int32_t *topk, int32_t T, uint64_t *ma
     uint32_t *pstate = ctx->d_plan_state;
     const int tb = (T + kBlock - 1) / kBlock;
     const bool has_key = ctx->mask_words == 1 || K <= 8;
-    if (T >= (ctx->mask_words == 1 ? kChunkFromOneWord : kChunkFromKeyed) && has_key && ctx->d_sort_key) {
+    if (has_key && T <= kOrderMaxTokens) {
+        if (ctx->mask_words == 1) launch_plan_order<false>(ctx, topk, T, mask, perm, desc, stats, s);
+        else launch_plan_order<true>(ctx, topk, T, mask, perm, desc, stats, s);
+        // (the other kernel's event pair, where a caller has set one, brackets nothing)
+        if (T < kKeysFrom) { mw_timed tm(ctx, MW_KERNEL_PLAN_GROUPS, s); }
+        MW_HIP_CHECK(hipGetLastError());
+        return MW_OK;
+    }
+    if (T > kOrderMaxTokens && has_key && ctx->d_sort_key) {
         const int nc = (T + kChunk - 1) / kChunk;
         // split every chunk's walk over the other chunks into parts so that the grid fills the chip
         int parts = (2 * ctx->n_cu + nc - 1) / nc;
@@ -471,13 +999,9 @@ int32_t mw_launch_plan(mw_ctx *ctx, const int32_t *topk, int32_t T, uint64_t *ma
                                ctx->d_sort_key, ctx->d_sort_sec, ctx->d_chunk_kept, cnt);
         }
     } else if (T > 0) {
-        // split the predecessor walk into slices so that about 2 workgroups land on every CU when
-        // a compare is one word (4 when it is a key and a flag: more compare work per pair); a
-        // slice's bitmaps must fit in LDS.  Fewer, longer workgroups mean fewer atomics and less
-        // disturbance of a bandwidth-bound kernel running beside the plan (the expander of the
-        // batch before: 88 -> 85 us per launch with fp8 rows), at the same latency.
-        const int per_cu = ctx->mask_words == 1 ? 2 : 4;
-        int ns = (per_cu * ctx->n_cu + tb - 1) / tb;
+        // Bitmaps of more than one word and more than eight ids: no 64-bit key.  Split the predecessor walk into
+        // slices so that about 4 workgroups land on every CU; a slice's bitmaps must fit in LDS.
+        int ns = (4 * ctx->n_cu + tb - 1) / tb;
         if (ns < 1) ns = 1;
         int slice = (T + ns - 1) / ns;
         if (slice < 64) slice = 64;
@@ -485,17 +1009,13 @@ int32_t mw_launch_plan(mw_ctx *ctx, const int32_t *topk, int32_t T, uint64_t *ma
         ns = (T + slice - 1) / slice;
         const dim3 grid(tb, ns), block(kBlock);
         const int W = ctx->mask_words;
-        const bool keyed = W > 1 && K <= 8;         // at most eight bits per bitmap: short keys
-        const size_t lds = keyed ? (size_t)slice * sizeof(mw_short_key) : (size_t)slice * W * sizeof(uint64_t);
+        const size_t lds = (size_t)slice * W * sizeof(uint64_t);
         mw_timed tm(ctx, MW_KERNEL_PLAN_RANK, s);
-#define MW_RANK(W_, KEYED_)                                                                                 \
-    hipLaunchKernelGGL((k_rank<W_, KEYED_>), grid, block, lds, s, topk, T, K, ctx->d_eslot, E, slice, mask, cnt, \
-                       pstate)
-        if (keyed) MW_RANK(4, true);
-        else if (W == 1) MW_RANK(1, false);
-        else if (W == 2) MW_RANK(2, false);
-        else if (W == 3) MW_RANK(3, false);
-        else MW_RANK(4, false);
+#define MW_RANK(W_)                                                                                         \
+    hipLaunchKernelGGL(k_rank<W_>, grid, block, lds, s, topk, T, K, ctx->d_eslot, E, slice, mask, cnt, pstate)
+        if (W == 2) MW_RANK(2);
+        else if (W == 3) MW_RANK(3);
+        else MW_RANK(4);
 #undef MW_RANK
     }
     {
