@@ -91,8 +91,8 @@ struct mw_ctx {
     int32_t n_hops;         // 0 until mw_set_forwarding
     uint64_t *d_hop_bits;   // [MW_MAX_HOPS][4] ranks served through each next hop
     int32_t *d_group_of_row;// [max_tokens]
-    uint32_t *d_child_pos;  // [max_tokens][MW_MAX_HOPS] first child row of (group, hop) or kNoChild
-    uint32_t *d_relay_flags;// [1]
+    uint32_t *d_child_pos;  // [max_tokens][16, 32 or 64 by the hops] first child row of (group, hop) or kNoChild
+    uint32_t *d_relay_flags;// flag word and the accounting sums behind it (mw_relay_acc)
     // measurement hook: optional event pairs recorded around single kernels
     hipEvent_t ev_start[MW_KERNEL_COUNT];
     hipEvent_t ev_stop[MW_KERNEL_COUNT];

@@ -10,11 +10,12 @@
 // the remote server replicates a token to the targets inside that server.
 //
 // Two launches on the caller's stream:
-//   k_relay_index  workgroup h < n_hops builds child h's descriptor table: a group is kept
+//   k_relay_index  workgroup (h, c) builds chunk c of child h's descriptor table: a group is kept
 //                  if its bitmap intersects the hop's rank set; kept groups are ranked with
 //                  block scans (group index, first row), so the child is in parent order
-//                  whatever the timing.  The (group, hop) -> first child row table feeds the
-//                  copy.  One more workgroup maps rows to groups and does the byte accounting.
+//                  whatever the timing.  What the chunks before it keep a workgroup counts for itself.
+//                  The (group, hop) -> first child row table feeds the
+//                  copy.  Further workgroups map rows to groups and do the byte accounting.
 //   k_relay_copy   small workgroups (a single wave for cache-line-sized rows), each moving
 //                  consecutive 16-byte chunks of one input row: read once, stored once per next hop that keeps the row's group
 //                  (lane h of every wave holds hop h's position; a ballot lists the hops).  Bound by HBM
@@ -23,9 +24,17 @@
 
 namespace {
 
-constexpr int kBlock = 1024;
+constexpr int kBlock = 512;                  // lanes of an index workgroup in a launch of its own
 constexpr uint32_t kNoChild = 0xffffffffu;
-constexpr uint32_t kLongGroup = 32;          // rows; longer groups are filled cooperatively
+constexpr uint32_t kLongGroup = 32;          // rows; longer groups are filled by their whole wave
+constexpr uint32_t kMaxChunks = 16;          // workgroups per hop
+
+// Entries from one group's (packet's) child positions to the next one's: a power of two from 16, so that
+// a group's positions are one or two cache lines.
+__host__ __device__ __forceinline__ uint32_t relay_pos_stride(int n_hops) { return n_hops <= 16 ? 16u : n_hops <= 32 ? 32u : 64u; }
+// Words behind the relay flags in the workspace: what the accounting workgroups of one index add up (zero between
+// indexes; the workgroup that reports last writes the statistics and clears them).
+struct mw_relay_acc { uint32_t flags, groups, done, reserved0; unsigned long long rows, dest_rows; };
 
 // Everything the index of one relay step needs (one kernel argument).
 struct mw_relay_index_args {
@@ -33,6 +42,7 @@ struct mw_relay_index_args {
     uint32_t max_tokens, cap; uint64_t row_bytes; const uint64_t *hop_bits;
     int32_t *group_of_row; uint32_t *child_pos; uint32_t *relay_flags; mw_relay_stats *stats;
     uint32_t keep_metadata;     // 1: children carry the parent's bitmaps (Section 4.1: the update may be omitted)
+    uint32_t chunks;            // workgroups per hop
 };
 
 // The bitmap of ranks below n_ranks, word w.
@@ -42,205 +52,225 @@ __device__ __forceinline__ uint64_t valid_rank_word(int n_ranks, int w)
     return (n_ranks >= lo + 64) ? ~0ull : (n_ranks > lo ? ((1ull << (n_ranks - lo)) - 1ull) : 0ull);
 }
 
-// Child descriptor table of next hop h, by one workgroup.  A lane takes KP consecutive groups a
-// step and reads of each what the ranking needs: the NW bitmap words that can name a rank
-// (ranks < 64 NW; the hop's rank set and the valid ranks have nothing above them), the row range,
-// and the end of the range in front (a descriptor is valid if its row range is not empty, lies
-// inside the buffer and starts at or after the end of the previous descriptor's).  All of a step's loads are
-// issued before the first is used -- addresses are clamped instead of branched around -- so a
-// step is one memory round trip whatever KP; then one scan of the lanes' kept groups and one
-// of their rows place every kept group in parent order.
-template <int NW, int KP>
+// Sum of one value per lane over the workgroup; scratch of 17 words.
+__device__ __forceinline__ uint32_t relay_block_sum(uint32_t v, uint32_t *scratch)
+{
+    uint32_t total;
+    mw_block_exscan(v, scratch, &total);
+    return total;
+}
+
+// Chunk c of `chunks` of next hop h's child descriptor table, by one workgroup.  Of a descriptor the
+// ranking needs the NW bitmap words that can name a rank (ranks < 64 NW; the hop's rank set and the valid
+// ranks have nothing above them), the row range, and the end of the range in front (a descriptor is valid
+// if its row range is not empty, lies inside the buffer and starts at or after the end of the previous
+// descriptor's).  A workgroup first counts what the hop keeps of all groups before its chunk -- four of them a lane
+// in flight, nothing to scan -- and then places its own, a group a lane, with one scan of the kept groups
+// and one of their rows.  Bound by latency: one workgroup a hop, walking all groups three a lane and step, took
+// 3.5 us a step plus the scans (4096 groups, 15 hops: the index 14.7 us, now 7 us).
+template <int NW>
 __device__ __forceinline__ uint32_t relay_index_hop(
     const mw_recv_peer &src, const uint32_t G, const uint32_t n_rows, mw_group_desc *__restrict__ cdesc, const int h,
-    const int n_ranks, const uint32_t cap, const uint64_t *__restrict__ hop_bits, uint32_t *__restrict__ child_pos,
-    mw_relay_stats *__restrict__ stats, const uint32_t keep_metadata, uint32_t *scratch, uint32_t *fit)
+    const uint32_t c, const uint32_t chunks, const int n_ranks, const uint32_t cap, const uint64_t *__restrict__ hop_bits,
+    uint32_t *__restrict__ child_pos, const uint32_t pos_stride, mw_relay_stats *__restrict__ stats,
+    const uint32_t keep_metadata, uint32_t *scratch, uint32_t *fit)
 {
     const uint32_t bs = blockDim.x, tid = threadIdx.x;
+    const uint32_t per = ((G + chunks - 1) / chunks + bs - 1) / bs * bs;
+    const uint32_t g_first = min(G, c * per), g_end = min(G, g_first + per);
+    if (g_first >= G && c + 1 < chunks) return 0;                            // (the last chunk reports the totals)
     uint32_t err = 0;
-    uint64_t hb[NW], ok[NW];
+    uint64_t hb[NW];
 #pragma unroll
-    for (int w = 0; w < NW; ++w) { hb[w] = hop_bits[(size_t)h * MW_MASK_WORDS + w]; ok[w] = valid_rank_word(n_ranks, w); }
-    if (tid < 2) fit[tid] = 0;
-    mw_lds_barrier();
+    for (int w = 0; w < NW; ++w) hb[w] = hop_bits[(size_t)h * MW_MASK_WORDS + w];
+    uint64_t m[NW];
+    uint2 oc, po;
+    auto load = [&](uint32_t g, uint64_t (&mm)[NW], uint2 &o, uint2 &p) __attribute__((always_inline)) {
+        const mw_group_desc *d = src.desc + g;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) mm[w] = d->mask[w];
+        o = *(const uint2 *)&d->row_offset;          // (row_offset, row_count)
+        p = *(const uint2 *)&src.desc[g > 0 ? g - 1u : 0u].row_offset;
+        if (g == 0) p = make_uint2(0u, 0u);
+    };
+    auto valid = [&](uint2 o, uint2 p) __attribute__((always_inline)) {
+        return o.y >= 1 && (uint64_t)o.x + o.y <= n_rows && o.x >= (uint64_t)p.x + p.y;
+    };
+    auto kept = [&](const uint64_t (&mm)[NW]) __attribute__((always_inline)) {
+        uint64_t any = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) any |= mm[w] & hb[w];
+        return any != 0;
+    };
+    const bool work = g_first < g_end;
+    if (work) load(min(g_first + tid, g_end - 1u), m, oc, po);               // in flight beside the counting
     uint32_t carry_g = 0, carry_r = 0;
-    for (uint32_t g0 = 0; g0 < G; g0 += bs * KP) {
-        const uint32_t gl = g0 + tid * KP;           // this lane's first group
-        uint64_t m[KP][NW];
-        uint2 oc[KP];
+    constexpr int kFly = NW == 1 ? 4 : NW == 2 ? 3 : 1;                      // (within the 64 registers of the riding form)
+    for (uint32_t g0 = 0; g0 < g_first; g0 += (uint32_t)kFly * bs) {
+        uint64_t mm[kFly][NW];
+        uint2 o[kFly], p[kFly];
 #pragma unroll
-        for (int k = 0; k < KP; ++k) {
-            const mw_group_desc *d = src.desc + min(gl + (uint32_t)k, G - 1u);
+        for (int k = 0; k < kFly; ++k)
+            if (g0 + (uint32_t)k * bs < g_first) load(min(g0 + (uint32_t)k * bs + tid, g_first - 1u), mm[k], o[k], p[k]);
 #pragma unroll
-            for (int w = 0; w < NW; ++w) m[k][w] = d->mask[w];
-            oc[k] = *(const uint2 *)&d->row_offset;  // (row_offset, row_count)
+        for (int k = 0; k < kFly; ++k) {
+            if (g0 + (uint32_t)k * bs + tid < g_first && kept(mm[k]) && valid(o[k], p[k])) { ++carry_g; carry_r += o[k].y; }
         }
-        const uint2 po = *(const uint2 *)&src.desc[min(gl > 0 ? gl - 1u : 0u, G - 1u)].row_offset;
-        uint64_t prev_end = gl > 0 ? (uint64_t)po.x + po.y : 0ull;
-        bool keep[KP];
-        uint32_t nd[KP], lg = 0, lr = 0;
-#pragma unroll
-        for (int k = 0; k < KP; ++k) {
-            const uint32_t off = oc[k].x, cnt = oc[k].y;
-            const bool valid = gl + k < G && cnt >= 1 && (uint64_t)off + cnt <= n_rows && off >= prev_end;
-            prev_end = (uint64_t)off + cnt;
-            uint32_t n = 0;
-#pragma unroll
-            for (int w = 0; w < NW; ++w) n += (uint32_t)__popcll(m[k][w] & hb[w]);
-            keep[k] = valid && n > 0;
-            if (keep_metadata) {                     // the copy carries every destination the parent named
-                n = 0;
-#pragma unroll
-                for (int w = 0; w < NW; ++w) { m[k][w] &= ok[w]; n += (uint32_t)__popcll(m[k][w]); }
-            } else {
-#pragma unroll
-                for (int w = 0; w < NW; ++w) m[k][w] &= hb[w];
-            }
-            nd[k] = n;
-            lg += keep[k] ? 1u : 0u;
-            lr += keep[k] ? cnt : 0u;
-        }
+    }
+    if (g_first > 0) { carry_g = relay_block_sum(carry_g, scratch); carry_r = relay_block_sum(carry_r, scratch); }
+    const uint32_t before_r = carry_r;
+    if (tid == 0) { fit[0] = carry_g; fit[1] = carry_r; }
+    for (uint32_t g0 = g_first; g0 < g_end; g0 += bs) {
+        const uint32_t g = g0 + tid;
+        if (g0 > g_first) load(min(g, g_end - 1u), m, oc, po);
+        const uint32_t cnt = oc.y;
+        const bool keep = g < g_end && valid(oc, po) && kept(m);
         uint32_t tot_g, tot_r;
-        uint32_t cg = carry_g + mw_block_exscan(lg, scratch, &tot_g);
-        uint32_t cr = carry_r + mw_block_exscan(lr, scratch, &tot_r);
-        uint32_t fit_g = 0, fit_r = 0;
+        const uint32_t cg = carry_g + mw_block_exscan(keep ? 1u : 0u, scratch, &tot_g);
+        const uint32_t cr = carry_r + mw_block_exscan(keep ? cnt : 0u, scratch, &tot_r);
+        uint32_t pos = kNoChild, fit_g = 0, fit_r = 0;
+        if (keep) {
+            if ((uint64_t)cr + cnt <= cap) {
+                mw_group_desc d;
+                uint32_t n = 0;
 #pragma unroll
-        for (int k = 0; k < KP; ++k) {
-            if (gl + k >= G) continue;
-            const uint32_t cnt = oc[k].y;
-            uint32_t pos = kNoChild;
-            if (keep[k]) {
-                if ((uint64_t)cr + cnt <= cap) {
-                    mw_group_desc d;
+                for (int w = 0; w < MW_MASK_WORDS; ++w) d.mask[w] = 0;
 #pragma unroll
-                    for (int w = 0; w < MW_MASK_WORDS; ++w) d.mask[w] = 0;
-#pragma unroll
-                    for (int w = 0; w < NW; ++w) d.mask[w] = m[k][w];
-                    d.row_offset = cr; d.row_count = cnt; d.n_dest = nd[k]; d.reserved0 = 0;
-                    cdesc[cg] = d;
-                    pos = cr;
-                    fit_g = cg + 1u; fit_r = cr + cnt;
-                } else {
-                    err |= MW_FLAG_OUT_CAPACITY;
+                for (int w = 0; w < NW; ++w) {
+                    d.mask[w] = m[w] & (keep_metadata ? valid_rank_word(n_ranks, w) : hb[w]);   // (keep: every destination the parent named)
+                    n += (uint32_t)__popcll(d.mask[w]);
                 }
-                ++cg; cr += cnt;
+                d.row_offset = cr; d.row_count = cnt; d.n_dest = n; d.reserved0 = 0;
+                cdesc[cg] = d;
+                pos = cr;
+                fit_g = cg + 1u; fit_r = cr + cnt;
+            } else {
+                err |= MW_FLAG_OUT_CAPACITY;
             }
-            child_pos[(size_t)(gl + k) * MW_MAX_HOPS + h] = pos;
         }
-        // kept groups that fit are a prefix of the kept groups: the largest (index + 1, end
-        // row) pair describes the child.  Reduced over the wave first: same-address LDS
-        // atomics of a whole workgroup would serialise.
-        fit_g = mw_wave_max(fit_g);
-        fit_r = mw_wave_max(fit_r);
-        if ((tid & 63) == 0 && fit_g) { atomicMax(&fit[0], fit_g); atomicMax(&fit[1], fit_r); }
+        if (g < g_end) child_pos[(size_t)g * pos_stride + h] = pos;
         carry_g += tot_g; carry_r += tot_r;
+        // kept groups that fit are a prefix of the kept groups: the largest (index + 1, end row) pair describes
+        // the child where its capacity ends inside this chunk
+        if (carry_r > cap) {
+            fit_g = mw_wave_max(fit_g);
+            fit_r = mw_wave_max(fit_r);
+            if ((tid & 63) == 0 && fit_g) { atomicMax(&fit[0], fit_g); atomicMax(&fit[1], fit_r); }
+        } else if (tid == 0) {
+            fit[0] = carry_g; fit[1] = carry_r;      // everything so far fits
+        }
     }
     mw_lds_barrier();
-    if (tid == 0) { stats->groups_per_hop[h] = fit[0]; stats->rows_per_hop[h] = fit[1]; }
+    // the capacity ends in exactly one chunk, or nowhere: then the last chunk has the totals
+    if (tid == 0) {
+        if (before_r <= cap && carry_r > cap) {
+            stats->groups_per_hop[h] = fit[0];
+            stats->rows_per_hop[h] = fit[1];
+        } else if (c + 1 == chunks && carry_r <= cap) {
+            stats->groups_per_hop[h] = carry_g;
+            stats->rows_per_hop[h] = carry_r;
+        }
+    }
     return err;
 }
 
-// Workgroup `wg` of the relay index: wg < n_hops builds child wg's descriptor table, wg == n_hops
-// maps rows to groups and does the accounting.  Any workgroup size that is a multiple of 64.
-__device__ __forceinline__ void relay_index_body(
-    const mw_recv_peer *__restrict__ in, const mw_relay_child *__restrict__ children, int n_hops, int n_ranks,
-    uint32_t max_tokens, uint32_t cap, uint64_t row_bytes, const uint64_t *__restrict__ hop_bits,
-    int32_t *__restrict__ group_of_row, uint32_t *__restrict__ child_pos, uint32_t *relay_flags,
-    mw_relay_stats *__restrict__ stats, const uint32_t keep_metadata, const int wg)
+// What the accounting workgroups of one index found, added up in the workspace; the one that reports last
+// writes the statistics (publication rules in mw_internal.h) and leaves the sums zero.  `groups`, `rows` and
+// `dests`: this lane's.
+__device__ __forceinline__ void relay_account_finish(uint32_t groups, uint32_t rows, uint32_t dests, uint32_t chunks,
+                                                     uint64_t row_bytes, mw_relay_acc *acc, mw_relay_stats *__restrict__ stats,
+                                                     uint32_t *scratch)
 {
-    const uint32_t bs = blockDim.x;
+    groups = relay_block_sum(groups, scratch);
+    rows = relay_block_sum(rows, scratch);
+    dests = relay_block_sum(dests, scratch);
+    if (threadIdx.x == 0) {
+        __hip_atomic_fetch_add(&acc->groups, groups, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_fetch_add(&acc->rows, (unsigned long long)rows, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_fetch_add(&acc->dest_rows, (unsigned long long)dests, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    mw_publish_barrier();
+    if (threadIdx.x != 0 || mw_report(&acc->done) != chunks - 1u) return;
+    stats->n_groups_in = __hip_atomic_load(&acc->groups, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    stats->n_rows_in = (uint32_t)__hip_atomic_load(&acc->rows, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    stats->unicast_bytes = (uint64_t)__hip_atomic_load(&acc->dest_rows, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) * row_bytes;
+    stats->reserved0 = 0;
+    __hip_atomic_store(&acc->groups, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&acc->done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&acc->rows, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&acc->dest_rows, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Workgroup `wg` of the relay index, of (n_hops + 1) chunks: wg / chunks < n_hops builds a chunk of that child's
+// descriptor table, the last `chunks` map rows to groups and do the accounting.  Any workgroup size that is a multiple of 64.
+__device__ __forceinline__ void relay_index_body(const mw_relay_index_args &a, const uint32_t wg)
+{
+    const uint32_t bs = blockDim.x, tid = threadIdx.x, lane = tid & 63u;
     __shared__ uint32_t scratch[17];
     __shared__ uint32_t fit[2];                  // groups, rows of the child that fit its capacity
-    __shared__ unsigned long long acc[2];        // rows taken, rows * destinations
-    __shared__ uint32_t n_long;
-    __shared__ uint32_t long_groups[65536 / kLongGroup];
-    const uint32_t tid = threadIdx.x;
-    const mw_recv_peer src = in[0];
-    const uint32_t G = min(src.n_desc, max_tokens), n_rows = min(src.n_rows, max_tokens);
-    uint32_t err = (src.n_desc > max_tokens || src.n_rows > max_tokens) ? MW_FLAG_BAD_DESC : 0u;
+    const uint32_t chunks = a.chunks, h = wg / chunks, c = wg - h * chunks;
+    const mw_recv_peer src = a.in[0];
+    const uint32_t G = min(src.n_desc, a.max_tokens), n_rows = min(src.n_rows, a.max_tokens);
+    const uint32_t pos_stride = relay_pos_stride(a.n_hops);
+    uint32_t err = (src.n_desc > a.max_tokens || src.n_rows > a.max_tokens) ? MW_FLAG_BAD_DESC : 0u;
 
-    if (wg < n_hops) {
-        // ---- child descriptor table of next hop wg: three groups a lane and step where one bitmap
-        // word holds every rank, two for two words
-        mw_group_desc *cdesc = children[wg].desc;
-        if (n_ranks <= 64)
-            err |= relay_index_hop<1, 3>(src, G, n_rows, cdesc, wg, n_ranks, cap, hop_bits, child_pos, stats, keep_metadata, scratch, fit);
-        else if (n_ranks <= 128)
-            err |= relay_index_hop<2, 2>(src, G, n_rows, cdesc, wg, n_ranks, cap, hop_bits, child_pos, stats, keep_metadata, scratch, fit);
-        else
-            err |= relay_index_hop<MW_MASK_WORDS, 1>(src, G, n_rows, cdesc, wg, n_ranks, cap, hop_bits, child_pos, stats, keep_metadata, scratch, fit);
+    if (h < (uint32_t)a.n_hops) {
+        mw_group_desc *cdesc = a.children[h].desc;
+#define MW_HOP(NW_)                                                                                                      \
+    relay_index_hop<NW_>(src, G, n_rows, cdesc, (int)h, c, chunks, a.n_ranks, a.cap, a.hop_bits, a.child_pos, pos_stride, a.stats, \
+                         a.keep_metadata, scratch, fit)
+        if (a.n_ranks <= 64) err |= MW_HOP(1);
+        else if (a.n_ranks <= 128) err |= MW_HOP(2);
+        else err |= MW_HOP(MW_MASK_WORDS);
+#undef MW_HOP
     } else {
-        // ---- rows -> groups, accounting, two groups a lane and step.  A group's thread writes the
-        // group's index over its rows; groups longer than kLongGroup rows are queued in LDS and
-        // filled by the whole workgroup.  Rows of no valid group keep whatever the array held: the
-        // copy kernel checks every entry against the descriptors.
-        if (tid < 2) acc[tid] = 0;
-        if (tid == 0) n_long = 0;
-        mw_lds_barrier();
-        uint64_t valid_ranks[MW_MASK_WORDS];
+        // ---- rows -> groups, accounting, a group a lane.  A group's lane writes the group's index over its
+        // rows; groups longer than kLongGroup rows are filled by their wave.  Rows of no valid group keep whatever
+        // the array held: the copy kernel checks every entry against the descriptors.
+        const uint32_t per = ((G + chunks - 1) / chunks + bs - 1) / bs * bs;
+        const uint32_t g_first = min(G, c * per), g_end = min(G, g_first + per);
+        uint32_t groups = 0, rows = 0, dests = 0;
+        for (uint32_t g0 = g_first; g0 < g_end; g0 += bs) {
+            const uint32_t g = g0 + tid, gl = min(g, g_end - 1u);
+            const mw_group_desc *d = src.desc + gl;
+            uint64_t m[MW_MASK_WORDS];
 #pragma unroll
-        for (int w = 0; w < MW_MASK_WORDS; ++w) valid_ranks[w] = valid_rank_word(n_ranks, w);
-        unsigned long long rows_in = 0, dest_rows = 0;
-        uint32_t groups_in = 0;
-        constexpr int KA = 2;
-        for (uint32_t g0 = 0; g0 < G; g0 += bs * KA) {
-            const uint32_t gl = g0 + tid * KA;
-            uint64_t m[KA][MW_MASK_WORDS];
-            uint2 oc[KA];
-#pragma unroll
-            for (int k = 0; k < KA; ++k) {
-                const mw_group_desc *d = src.desc + min(gl + (uint32_t)k, G - 1u);
-#pragma unroll
-                for (int w = 0; w < MW_MASK_WORDS; ++w) m[k][w] = d->mask[w];
-                oc[k] = *(const uint2 *)&d->row_offset;
-            }
-            const uint2 po = *(const uint2 *)&src.desc[min(gl > 0 ? gl - 1u : 0u, G - 1u)].row_offset;
-            uint64_t prev_end = gl > 0 ? (uint64_t)po.x + po.y : 0ull;
-#pragma unroll
-            for (int k = 0; k < KA; ++k) {
-                const uint32_t g = gl + k, off = oc[k].x, cnt = oc[k].y;
-                const bool valid = cnt >= 1 && (uint64_t)off + cnt <= n_rows && off >= prev_end;
-                prev_end = (uint64_t)off + cnt;
-                if (g >= G) continue;
-                if (!valid) { err |= MW_FLAG_BAD_DESC; continue; }
+            for (int w = 0; w < MW_MASK_WORDS; ++w) m[w] = d->mask[w];
+            const uint2 oc = *(const uint2 *)&d->row_offset;
+            uint2 po = *(const uint2 *)&src.desc[gl > 0 ? gl - 1u : 0u].row_offset;
+            if (gl == 0) po = make_uint2(0u, 0u);
+            const uint32_t off = oc.x, cnt = oc.y;
+            const bool valid = g < g_end && cnt >= 1 && (uint64_t)off + cnt <= n_rows && off >= (uint64_t)po.x + po.y;
+            if (g < g_end && !valid) err |= MW_FLAG_BAD_DESC;
+            if (valid) {
                 uint32_t nd = 0;
 #pragma unroll
                 for (int w = 0; w < MW_MASK_WORDS; ++w) {
-                    if (m[k][w] & ~valid_ranks[w]) err |= MW_FLAG_BAD_RANK;
-                    nd += (uint32_t)__popcll(m[k][w] & valid_ranks[w]);
+                    const uint64_t ok = valid_rank_word(a.n_ranks, w);
+                    if (m[w] & ~ok) err |= MW_FLAG_BAD_RANK;
+                    nd += (uint32_t)__popcll(m[w] & ok);
                 }
-                if (cnt <= kLongGroup) {
-                    for (uint32_t r = 0; r < cnt; ++r) group_of_row[off + r] = (int32_t)g;
-                } else {
-                    long_groups[atomicAdd(&n_long, 1u)] = g;      // at most max_tokens / kLongGroup of them
-                }
-                rows_in += cnt; dest_rows += (unsigned long long)cnt * nd; ++groups_in;
+                ++groups; rows += cnt; dests += cnt * nd;
+                if (cnt <= kLongGroup) for (uint32_t r = 0; r < cnt; ++r) a.group_of_row[off + r] = (int32_t)g;
+            }
+            uint64_t longs = __ballot(valid && cnt > kLongGroup);
+            while (longs) {
+                const int l = (int)__builtin_ctzll(longs);
+                longs &= longs - 1;
+                const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)off, l), lc = (uint32_t)__builtin_amdgcn_readlane((int)cnt, l);
+                const int32_t lg = __builtin_amdgcn_readlane((int)g, l);
+                for (uint32_t r = lane; r < lc; r += 64u) a.group_of_row[lo + r] = lg;
             }
         }
-        if (rows_in) atomicAdd(&acc[0], rows_in);            // integer sums: order-free
-        if (dest_rows) atomicAdd(&acc[1], dest_rows);
-        uint32_t tot_groups;
-        mw_block_exscan(groups_in, scratch, &tot_groups);     // (its barriers also publish the queue)
-        for (uint32_t q = 0; q < n_long; ++q) {
-            const uint32_t g = long_groups[q];
-            const uint32_t off = src.desc[g].row_offset, cnt = src.desc[g].row_count;
-            for (uint32_t r = tid; r < cnt; r += bs) group_of_row[off + r] = (int32_t)g;
-        }
-        if (tid == 0) {
-            stats->n_groups_in = tot_groups;
-            stats->n_rows_in = (uint32_t)acc[0];
-            stats->unicast_bytes = (uint64_t)acc[1] * row_bytes;
-            stats->reserved0 = 0;
-        }
-        for (int h = n_hops + (int)tid; h < MW_MAX_HOPS; h += (int)bs) { stats->groups_per_hop[h] = 0; stats->rows_per_hop[h] = 0; }
+        if (c == 0) for (uint32_t q = (uint32_t)a.n_hops + tid; q < MW_MAX_HOPS; q += bs) { a.stats->groups_per_hop[q] = 0; a.stats->rows_per_hop[q] = 0; }
+        relay_account_finish(groups, rows, dests, chunks, a.row_bytes, (mw_relay_acc *)a.relay_flags, a.stats, scratch);
     }
-    if (err) atomicOr(relay_flags, err);
+    if (err) atomicOr(a.relay_flags, err);
 }
 
 __global__ __launch_bounds__(kBlock) void k_relay_index(const mw_relay_index_args a)
 {
-    relay_index_body(a.in, a.children, a.n_hops, a.n_ranks, a.max_tokens, a.cap, a.row_bytes, a.hop_bits,
-                     a.group_of_row, a.child_pos, a.relay_flags, a.stats, a.keep_metadata, (int)blockIdx.x);
+    relay_index_body(a, blockIdx.x);
 }
 
 // blockIdx.x selects a segment of blockDim.x chunks of a row; rows i_first, i_first + i_stride, ...
@@ -264,7 +294,7 @@ __device__ __forceinline__ void relay_copy_body(
         if (g < 0 || (uint32_t)g >= n_desc) continue;        // (stale or never written)
         const uint32_t off = i - src.desc[g].row_offset;
         if (off >= src.desc[g].row_count) continue;          // behind its group's end: in no valid group
-        const uint32_t p = (lane < n_hops) ? child_pos[(size_t)g * MW_MAX_HOPS + lane] : kNoChild;
+        const uint32_t p = (lane < n_hops) ? child_pos[(size_t)g * relay_pos_stride(n_hops) + lane] : kNoChild;
         int32_t tk = 0;
         if ((int)threadIdx.x < K && blockIdx.x == 0) tk = src.row_topk[(size_t)i * K + threadIdx.x];
         uint64_t hops = __ballot(p != kNoChild);              // the same in every wave
@@ -299,8 +329,8 @@ __global__ __launch_bounds__(1024) void k_relay_copy(
 }
 
 // A stream of relay steps on one stream (Section 4.3.3; the relay module of Section 5.1 handles
-// one buffer after the other): the copy of this step's buffer and, in the first next.n_hops + 1
-// workgroup rows of the grid, the index of the NEXT step's buffer, written to another context's
+// one buffer after the other): the copy of this step's buffer and, in the first
+// rows of the grid, the index of the NEXT step's buffer, written to another context's
 // workspace.  The index is a chain of memory round trips that moves almost nothing; as a launch
 // of its own it costs about 15 us in front of every copy.  Held to 64 registers so that the copy
 // keeps every wave slot.
@@ -316,10 +346,8 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
                         relay_flags, stats, blockIdx.y - first_copy_row, gridDim.y - first_copy_row);
         return;
     }
-    if (blockIdx.x == 0)
-        relay_index_body(next.in, next.children, next.n_hops, next.n_ranks, next.max_tokens, next.cap, next.row_bytes,
-                         next.hop_bits, next.group_of_row, next.child_pos, next.relay_flags, next.stats,
-                         next.keep_metadata, (int)blockIdx.y);
+    const uint32_t w = blockIdx.y * gridDim.x + blockIdx.x;
+    if (w < ((uint32_t)next.n_hops + 1u) * next.chunks) relay_index_body(next, w);
 }
 
 // Several buffers in one launch (mw_relay_batch): the copies of n_copy buffers, `rows_per_copy`
@@ -346,13 +374,12 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
                         c.relay_flags, c.stats, y - j * rows_per_copy, rows_per_copy);
         return;
     }
-    if (blockIdx.x != 0) return;
     int k = 0;
 #pragma unroll
     for (int q = 1; q < MW_RELAY_BATCH_MAX; ++q) k += (blockIdx.y >= b.index_first_row[q]) ? 1 : 0;
     const mw_relay_index_args &a = b.index[k];
-    relay_index_body(a.in, a.children, a.n_hops, a.n_ranks, a.max_tokens, a.cap, a.row_bytes, a.hop_bits, a.group_of_row,
-                     a.child_pos, a.relay_flags, a.stats, a.keep_metadata, (int)(blockIdx.y - b.index_first_row[k]));
+    const uint32_t w = (blockIdx.y - b.index_first_row[k]) * gridDim.x + blockIdx.x;
+    if (w < ((uint32_t)a.n_hops + 1u) * a.chunks) relay_index_body(a, w);
 }
 
 // ---- the same step for packets (Section 4.1, "Replication and forwarding": the relay parses the
@@ -365,134 +392,120 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
 struct mw_relay_packets_index_args {
     const mw_recv_packets *in; int n_hops, n_ranks; uint32_t K, max_tokens, cap; uint64_t packet_bytes;
     const uint64_t *hop_bits; uint32_t *child_pos; uint32_t *relay_flags; mw_relay_stats *stats;
+    uint32_t chunks;            // workgroups per hop
 };
 
-// Positions of the packets that next hop h keeps, by one workgroup: KP consecutive packets a
-// lane and step, of each header the NW bitmap words that can name a rank and the id count, all
-// loads of a step issued before the first is used (as relay_index_hop).
-template <int NW, int KP>
+// Positions of the packets of chunk c that next hop h keeps: what the hop keeps of the chunks before is counted
+// first, four headers a lane in flight, then a packet a lane (as relay_index_hop).  Of a header: the NW
+// bitmap words that can name a rank and the id count.
+template <int NW>
 __device__ __forceinline__ uint32_t relay_packets_index_hop(
     const char *__restrict__ packets, const uint64_t packet_bytes, const uint32_t n_rows, const uint32_t K, const int h,
-    const uint32_t cap, const uint64_t *__restrict__ hop_bits, uint32_t *__restrict__ child_pos,
-    mw_relay_stats *__restrict__ stats, uint32_t *scratch)
+    const uint32_t c, const uint32_t chunks, const uint32_t cap, const uint64_t *__restrict__ hop_bits,
+    uint32_t *__restrict__ child_pos, const uint32_t pos_stride, mw_relay_stats *__restrict__ stats, uint32_t *scratch)
 {
     const uint32_t tid = threadIdx.x, bs = blockDim.x;
+    const uint32_t per = ((n_rows + chunks - 1) / chunks + bs - 1) / bs * bs;
+    const uint32_t first = min(n_rows, c * per), end = min(n_rows, first + per);
+    if (first >= n_rows && c + 1 < chunks) return 0;
     uint32_t err = 0;
     uint64_t hb[NW];
 #pragma unroll
     for (int w = 0; w < NW; ++w) hb[w] = hop_bits[(size_t)h * MW_MASK_WORDS + w];
+    auto load = [&](uint32_t i, uint64_t (&m)[NW], uint32_t &nid) __attribute__((always_inline)) {
+        const char *hd = packets + (size_t)i * packet_bytes;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) m[w] = *(const uint64_t *)(hd + 8 * w);
+        nid = *(const uint32_t *)(hd + 36);
+    };
+    auto kept = [&](const uint64_t (&m)[NW], uint32_t nid) __attribute__((always_inline)) {
+        uint64_t any = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) any |= m[w] & hb[w];
+        return any != 0 && nid == K;
+    };
+    uint64_t m[NW];
+    uint32_t nid = 0;
+    if (first < end) load(min(first + tid, end - 1u), m, nid);
     uint32_t carry = 0;
-    for (uint32_t i0 = 0; i0 < n_rows; i0 += bs * KP) {
-        const uint32_t il = i0 + tid * KP;
-        uint64_t m[KP][NW];
-        uint32_t nid[KP];
+    for (uint32_t i0 = 0; i0 < first; i0 += 4u * bs) {
+        uint64_t mm[4][NW];
+        uint32_t nn[4];
 #pragma unroll
-        for (int k = 0; k < KP; ++k) {
-            const char *hd = packets + (size_t)min(il + (uint32_t)k, n_rows - 1u) * packet_bytes;
+        for (int k = 0; k < 4; ++k)
+            if (i0 + (uint32_t)k * bs < first) load(min(i0 + (uint32_t)k * bs + tid, first - 1u), mm[k], nn[k]);
 #pragma unroll
-            for (int w = 0; w < NW; ++w) m[k][w] = *(const uint64_t *)(hd + 8 * w);
-            nid[k] = *(const uint32_t *)(hd + 36);
-        }
-        bool keep[KP];
-        uint32_t lk = 0;
-#pragma unroll
-        for (int k = 0; k < KP; ++k) {
-            bool any = false;
-#pragma unroll
-            for (int w = 0; w < NW; ++w) any |= (m[k][w] & hb[w]) != 0;
-            keep[k] = any && il + k < n_rows && nid[k] == K;
-            lk += keep[k] ? 1u : 0u;
-        }
+        for (int k = 0; k < 4; ++k)
+            if (i0 + (uint32_t)k * bs + tid < first && kept(mm[k], nn[k])) ++carry;
+    }
+    if (first > 0) carry = relay_block_sum(carry, scratch);
+    for (uint32_t i0 = first; i0 < end; i0 += bs) {
+        const uint32_t i = i0 + tid;
+        if (i0 > first) load(min(i, end - 1u), m, nid);
+        const bool keep = i < end && kept(m, nid);
         uint32_t tot;
-        uint32_t pos = carry + mw_block_exscan(lk, scratch, &tot);
-#pragma unroll
-        for (int k = 0; k < KP; ++k) {
-            if (il + k >= n_rows) continue;
-            const bool fits = keep[k] && pos < cap;
-            if (keep[k] && !fits) err |= MW_FLAG_OUT_CAPACITY;
-            child_pos[(size_t)(il + k) * MW_MAX_HOPS + h] = fits ? pos : kNoChild;
-            pos += keep[k] ? 1u : 0u;
-        }
+        const uint32_t pos = carry + mw_block_exscan(keep ? 1u : 0u, scratch, &tot);
+        const bool fits = keep && pos < cap;
+        if (keep && !fits) err |= MW_FLAG_OUT_CAPACITY;
+        if (i < end) child_pos[(size_t)i * pos_stride + h] = fits ? pos : kNoChild;
         carry += tot;
     }
-    if (tid == 0) {
+    if (tid == 0 && c + 1 == chunks) {
         const uint32_t fit = min(carry, cap);      // the packets that fit are a prefix of the kept ones
         stats->groups_per_hop[h] = fit; stats->rows_per_hop[h] = fit;
     }
     return err;
 }
 
-// Workgroup `wg` of the packets' relay index (wg < n_hops: hop wg's positions; wg == n_hops: the
-// accounting).  Any workgroup size that is a multiple of 64.
-__device__ __forceinline__ void relay_packets_index_body(
-    const mw_recv_packets *__restrict__ in, int n_hops, int n_ranks, uint32_t K, uint32_t max_tokens, uint32_t cap,
-    uint64_t packet_bytes, const uint64_t *__restrict__ hop_bits, uint32_t *__restrict__ child_pos,
-    uint32_t *relay_flags, mw_relay_stats *__restrict__ stats, const int wg)
+// Workgroup `wg` of the packets' relay index, of (n_hops + 1) chunks: positions of a chunk for a hop, then the
+// accounting's chunks.  Any workgroup size that is a multiple of 64.
+__device__ __forceinline__ void relay_packets_index_body(const mw_relay_packets_index_args &a, const uint32_t wg)
 {
     __shared__ uint32_t scratch[17];
-    __shared__ unsigned long long acc[2];        // packets taken, destinations named
     const uint32_t tid = threadIdx.x, bs = blockDim.x;
-    const mw_recv_packets src = in[0];
+    const uint32_t chunks = a.chunks, h = wg / chunks, c = wg - h * chunks;
+    const mw_recv_packets src = a.in[0];
     const char *packets = (const char *)src.packets;
-    const uint32_t n_rows = min(src.n_rows, max_tokens);
-    uint32_t err = src.n_rows > max_tokens ? MW_FLAG_BAD_DESC : 0u;
+    const uint32_t n_rows = min(src.n_rows, a.max_tokens);
+    uint32_t err = src.n_rows > a.max_tokens ? MW_FLAG_BAD_DESC : 0u;
 
-    if (wg < n_hops) {
-        if (n_ranks <= 64)
-            err |= relay_packets_index_hop<1, 4>(packets, packet_bytes, n_rows, K, wg, cap, hop_bits, child_pos, stats, scratch);
-        else if (n_ranks <= 128)
-            err |= relay_packets_index_hop<2, 4>(packets, packet_bytes, n_rows, K, wg, cap, hop_bits, child_pos, stats, scratch);
-        else
-            err |= relay_packets_index_hop<MW_MASK_WORDS, 2>(packets, packet_bytes, n_rows, K, wg, cap, hop_bits, child_pos, stats, scratch);
+    if (h < (uint32_t)a.n_hops) {
+#define MW_HOP(NW_)                                                                                                      \
+    relay_packets_index_hop<NW_>(packets, a.packet_bytes, n_rows, a.K, (int)h, c, chunks, a.cap, a.hop_bits, a.child_pos,   \
+                                 relay_pos_stride(a.n_hops), a.stats, scratch)
+        if (a.n_ranks <= 64) err |= MW_HOP(1);
+        else if (a.n_ranks <= 128) err |= MW_HOP(2);
+        else err |= MW_HOP(MW_MASK_WORDS);
+#undef MW_HOP
     } else {
-        if (tid < 2) acc[tid] = 0;
-        mw_lds_barrier();
-        uint64_t valid_ranks[MW_MASK_WORDS];
-#pragma unroll
-        for (int w = 0; w < MW_MASK_WORDS; ++w) valid_ranks[w] = valid_rank_word(n_ranks, w);
+        const uint32_t per = ((n_rows + chunks - 1) / chunks + bs - 1) / bs * bs;
+        const uint32_t first = min(n_rows, c * per), end = min(n_rows, first + per);
         uint32_t taken = 0, dests = 0;
-        constexpr int KA = 2;                       // two headers a lane in flight
-        for (uint32_t i0 = 0; i0 < n_rows; i0 += bs * KA) {
-            uint64_t m[KA][MW_MASK_WORDS];
-            uint32_t nid[KA];
+        for (uint32_t i0 = first; i0 < end; i0 += bs) {
+            const char *hd = packets + (size_t)min(i0 + tid, end - 1u) * a.packet_bytes;
+            uint64_t m[MW_MASK_WORDS];
 #pragma unroll
-            for (int k = 0; k < KA; ++k) {
-                const char *hd = packets + (size_t)min(i0 + k * bs + tid, n_rows - 1u) * packet_bytes;
+            for (int w = 0; w < MW_MASK_WORDS; ++w) m[w] = *(const uint64_t *)(hd + 8 * w);
+            const uint32_t nid = *(const uint32_t *)(hd + 36);
+            if (i0 + tid >= end) continue;
+            if (nid != a.K) { err |= MW_FLAG_BAD_DESC; continue; }
 #pragma unroll
-                for (int w = 0; w < MW_MASK_WORDS; ++w) m[k][w] = *(const uint64_t *)(hd + 8 * w);
-                nid[k] = *(const uint32_t *)(hd + 36);
+            for (int w = 0; w < MW_MASK_WORDS; ++w) {
+                const uint64_t ok = valid_rank_word(a.n_ranks, w);
+                if (m[w] & ~ok) err |= MW_FLAG_BAD_RANK;
+                dests += (uint32_t)__popcll(m[w] & ok);
             }
-#pragma unroll
-            for (int k = 0; k < KA; ++k) {
-                if (i0 + k * bs + tid >= n_rows) continue;
-                if (nid[k] != K) { err |= MW_FLAG_BAD_DESC; continue; }
-#pragma unroll
-                for (int w = 0; w < MW_MASK_WORDS; ++w) {
-                    if (m[k][w] & ~valid_ranks[w]) err |= MW_FLAG_BAD_RANK;
-                    dests += (uint32_t)__popcll(m[k][w] & valid_ranks[w]);
-                }
-                ++taken;
-            }
+            ++taken;
         }
-        taken = mw_wave_sum(taken);
-        dests = mw_wave_sum(dests);
-        if ((tid & 63) == 0) { atomicAdd(&acc[0], (unsigned long long)taken); atomicAdd(&acc[1], (unsigned long long)dests); }
-        mw_lds_barrier();
-        if (tid == 0) {
-            stats->n_groups_in = (uint32_t)acc[0];
-            stats->n_rows_in = (uint32_t)acc[0];
-            stats->unicast_bytes = (uint64_t)acc[1] * packet_bytes;
-            stats->reserved0 = 0;
-        }
-        for (int h = n_hops + (int)tid; h < MW_MAX_HOPS; h += (int)bs) { stats->groups_per_hop[h] = 0; stats->rows_per_hop[h] = 0; }
+        if (c == 0) for (uint32_t q = (uint32_t)a.n_hops + tid; q < MW_MAX_HOPS; q += bs) { a.stats->groups_per_hop[q] = 0; a.stats->rows_per_hop[q] = 0; }
+        relay_account_finish(taken, taken, dests, chunks, a.packet_bytes, (mw_relay_acc *)a.relay_flags, a.stats, scratch);
     }
-    if (err) atomicOr(relay_flags, err);
+    if (err) atomicOr(a.relay_flags, err);
 }
 
 __global__ __launch_bounds__(kBlock) void k_relay_packets_index(const mw_relay_packets_index_args a)
 {
-    relay_packets_index_body(a.in, a.n_hops, a.n_ranks, a.K, a.max_tokens, a.cap, a.packet_bytes, a.hop_bits,
-                             a.child_pos, a.relay_flags, a.stats, (int)blockIdx.x);
+    relay_packets_index_body(a, blockIdx.x);
 }
 
 // blockIdx.x selects a segment of blockDim.x chunks of a packet; packets i_first, i_first + i_stride, ...
@@ -509,7 +522,7 @@ __device__ __forceinline__ void relay_packets_copy_body(
     for (uint32_t i = i_first; i < n_rows; i += i_stride) {
         u32x4 v = {0u, 0u, 0u, 0u};
         if (c < n_chunks) v = mw_ld16((const u32x4 *)src.packets + (size_t)i * n_chunks + c);
-        const uint32_t p = (lane < n_hops) ? child_pos[(size_t)i * MW_MAX_HOPS + lane] : kNoChild;
+        const uint32_t p = (lane < n_hops) ? child_pos[(size_t)i * relay_pos_stride(n_hops) + lane] : kNoChild;
         uint64_t hops = __ballot(p != kNoChild);              // the same in every wave
         while (hops) {
             const int h = __ffsll((unsigned long long)hops) - 1;
@@ -544,7 +557,7 @@ __global__ __launch_bounds__(1024) void k_relay_packets_copy(
 }
 
 // The packets' form of k_relay_copy_index_next: this buffer's copy with the next buffer's index
-// (another context's workspace) in the first next.n_hops + 1 workgroup rows.  Held to 64 scalar
+// (another context's workspace) in the first rows of the grid.  Held to 64 scalar
 // registers as well: with the 69 the index's branch would take, the copy's step is 6 % longer
 // (56.9 -> 60.4 us; forcing the count up with nothing else changed shows the same), the four
 // values over the limit live in lanes of a vector register instead.
@@ -561,22 +574,16 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8), amd
                                 gridDim.y - first_copy_row);
         return;
     }
-    if (blockIdx.x == 0)
-        relay_packets_index_body(next.in, next.n_hops, next.n_ranks, next.K, next.max_tokens, next.cap,
-                                 next.packet_bytes, next.hop_bits, next.child_pos, next.relay_flags, next.stats,
-                                 (int)blockIdx.y);
+    const uint32_t w = blockIdx.y * gridDim.x + blockIdx.x;
+    if (w < ((uint32_t)next.n_hops + 1u) * next.chunks) relay_packets_index_body(next, w);
 }
 
 }  // namespace
 
 // Workgroup shape of a copy that carries a riding index, for long rows that would otherwise move
-// as single waves.  The index walks the groups a workgroup's width at a time (one memory round
-// trip and two scans per step: 128 lanes took 32 steps for 4096 groups and outlasted the copy by
-// half) and its 8 KiB of LDS per workgroup would leave a CU of single-wave workgroups 19 waves
-// instead of 32, so the launch wants wide workgroups; the copy wants narrow ones.  Measured on
-// 14336-byte rows (per step of a stream, 15 next hops): 128 lanes 80 us, 192: 67, 256: 63, 320: 55.3,
-// 384: 55.8, 448: 57.4, 512: 61, 896: 57.2.  An even number of unequal segments would hand the short
-// segment to the same XCDs every row (256 lanes: four segments, the last half empty).
+// as single waves: wide enough for the index, whose workgroups take a group a lane.  The copy hardly minds:
+// 14336-byte rows, 15 next hops, per step of a stream: 64 lanes 60.5 us, 128: 55.9, 192: 57.1, 320: 55.9 (the copy alone 53).
+// An even number of unequal segments would hand the short segment to the same XCDs every row.
 static mw_row_shape relay_stream_shape(int n_chunks)
 {
     int nseg = (n_chunks + 383) / 384;
@@ -584,8 +591,33 @@ static mw_row_shape relay_stream_shape(int n_chunks)
     return mw_row_shape{((n_chunks + nseg - 1) / nseg + 63) / 64 * 64, nseg};
 }
 
+// Index workgroups of `bs` lanes per hop: one per `bs` groups the buffer may hold, at most kMaxChunks.
+static uint32_t relay_chunks(const mw_ctx *ctx, int bs)
+{
+    const uint32_t n = ((uint32_t)ctx->cfg.max_tokens + (uint32_t)bs - 1u) / (uint32_t)bs;
+    return n < 1 ? 1u : n < kMaxChunks ? n : kMaxChunks;
+}
+// Grid rows of `nseg` workgroups that a riding index takes.
+static uint32_t relay_index_rows(const mw_ctx *next, uint32_t chunks, int nseg)
+{
+    return (((uint32_t)next->n_hops + 1u) * chunks + (uint32_t)nseg - 1u) / (uint32_t)nseg;
+}
+
+// Whether the next buffer's index rides in a copy of `ctx` with `bs`-lane workgroups or gets a launch of its own
+// in front.  A riding workgroup takes about 1.6 us for four groups a lane of those it counts and for every group a lane
+// it places, and narrow workgroups have few lanes; the copy takes at least its rows once in and, say,
+// twice out at 6 TB/s; a launch of its own about 10 us.  (16384 rows of 2048 bytes, 128 lanes: riding 64.5 us a step,
+// apart 48.8; 4096 rows of 14336 bytes, 320 lanes: 55.9 and 60.5.)
+static bool relay_index_rides(const mw_ctx *ctx, const mw_ctx *next, int bs, int64_t row_bytes)
+{
+    const double groups = (double)next->cfg.max_tokens, chunks = (double)relay_chunks(next, bs);
+    const double rider_us = 1.6 * (groups / (4.0 * bs) + groups / (chunks * bs));
+    const double copy_us = 3.0 * (double)ctx->cfg.max_tokens * (double)row_bytes / 6e6;
+    return rider_us < copy_us + 10.0;
+}
+
 static mw_relay_index_args relay_index_args(mw_ctx *ctx, const mw_recv_peer *in, const mw_relay_child *children,
-                                            int64_t cap, mw_relay_stats *stats)
+                                            int64_t cap, mw_relay_stats *stats, int bs)
 {
     mw_relay_index_args a;
     a.in = in; a.children = children; a.n_hops = ctx->n_hops; a.n_ranks = ctx->cfg.n_ranks;
@@ -593,6 +625,7 @@ static mw_relay_index_args relay_index_args(mw_ctx *ctx, const mw_recv_peer *in,
     a.hop_bits = ctx->d_hop_bits; a.group_of_row = ctx->d_group_of_row; a.child_pos = ctx->d_child_pos;
     a.relay_flags = ctx->d_relay_flags; a.stats = stats;
     a.keep_metadata = (ctx->options & MW_OPT_RELAY_KEEP_METADATA) ? 1u : 0u;
+    a.chunks = relay_chunks(ctx, bs);
     return a;
 }
 
@@ -601,8 +634,8 @@ int32_t mw_launch_relay_index(mw_ctx *ctx, const mw_recv_peer *in, const mw_rela
 {
     {
         mw_timed tm(ctx, MW_KERNEL_RELAY_INDEX, s);
-        hipLaunchKernelGGL(k_relay_index, dim3(ctx->n_hops + 1), dim3(kBlock), 0, s,
-                           relay_index_args(ctx, in, children, cap, stats));
+        const mw_relay_index_args a = relay_index_args(ctx, in, children, cap, stats, kBlock);
+        hipLaunchKernelGGL(k_relay_index, dim3(((uint32_t)ctx->n_hops + 1u) * a.chunks), dim3(kBlock), 0, s, a);
     }
     MW_HIP_CHECK(hipGetLastError());
     return MW_OK;
@@ -617,6 +650,16 @@ int32_t mw_launch_relay_copy(mw_ctx *ctx, const mw_recv_peer *in, const mw_relay
     const mw_config &c = ctx->cfg;
     const int n_chunks = (int)(ctx->row_bytes / 16);
     mw_row_shape shape = mw_row_shape_of(n_chunks);
+    if (next) {
+        const mw_row_shape wide = shape.bs == 64 && n_chunks % 16 == 0 ? relay_stream_shape(n_chunks) : shape;
+        if (relay_index_rides(ctx, next, wide.bs, ctx->row_bytes)) {
+            shape = wide;
+        } else {
+            const int32_t rc = mw_launch_relay_index(next, next_in, next_children, next_cap, next_stats, s);
+            if (rc != MW_OK) return rc;
+            next = nullptr;
+        }
+    }
     uint32_t gy = (uint32_t)c.max_tokens < kRowGridMax ? (uint32_t)c.max_tokens : kRowGridMax;
     if (gy < 1) gy = 1;
     {
@@ -626,12 +669,11 @@ int32_t mw_launch_relay_copy(mw_ctx *ctx, const mw_recv_peer *in, const mw_relay
                                c.top_k, n_chunks, (int)(ctx->row_stride / 16), (uint32_t)c.max_tokens,
                                (uint64_t)ctx->row_bytes, ctx->d_group_of_row, ctx->d_child_pos, ctx->d_relay_flags, stats);
         } else {
-            if (shape.bs == 64 && n_chunks % 16 == 0) shape = relay_stream_shape(n_chunks);
-            hipLaunchKernelGGL(k_relay_copy_index_next, dim3(shape.nseg, gy + (uint32_t)next->n_hops + 1u),
-                               dim3(shape.bs), 0, s, (uint32_t)next->n_hops + 1u, 0u, in, children, ctx->n_hops, c.top_k, n_chunks,
+            const mw_relay_index_args a = relay_index_args(next, next_in, next_children, next_cap, next_stats, shape.bs);
+            const uint32_t riders = relay_index_rows(next, a.chunks, shape.nseg);
+            hipLaunchKernelGGL(k_relay_copy_index_next, dim3(shape.nseg, gy + riders), dim3(shape.bs), 0, s, riders, 0u, in, children, ctx->n_hops, c.top_k, n_chunks,
                                (int)(ctx->row_stride / 16), (uint32_t)c.max_tokens, (uint64_t)ctx->row_bytes,
-                               ctx->d_group_of_row, ctx->d_child_pos, ctx->d_relay_flags, stats,
-                               relay_index_args(next, next_in, next_children, next_cap, next_stats));
+                               ctx->d_group_of_row, ctx->d_child_pos, ctx->d_relay_flags, stats, a);
         }
     }
     MW_HIP_CHECK(hipGetLastError());
@@ -660,8 +702,8 @@ int32_t mw_launch_relay_batch(const mw_relay_job *copy, int32_t n_copy, const mw
         b.index_first_row[k] = first;
         if (k < n_index) {
             b.index[k] = relay_index_args(index[k].ctx, index[k].in_dev, index[k].children_dev,
-                                          index[k].child_capacity_rows, index[k].stats_dev);
-            first += (uint32_t)index[k].ctx->n_hops + 1u;
+                                          index[k].child_capacity_rows, index[k].stats_dev, shape.bs);
+            first += relay_index_rows(index[k].ctx, b.index[k].chunks, shape.nseg);
         }
     }
     b.index_first_row[MW_RELAY_BATCH_MAX] = first;
@@ -684,13 +726,14 @@ int32_t mw_launch_relay(mw_ctx *ctx, const mw_recv_peer *in, const mw_relay_chil
 }
 
 static mw_relay_packets_index_args relay_packets_index_args(mw_ctx *ctx, const mw_recv_packets *in, int64_t cap,
-                                                            mw_relay_stats *stats)
+                                                            mw_relay_stats *stats, int bs)
 {
     mw_relay_packets_index_args a;
     a.in = in; a.n_hops = ctx->n_hops; a.n_ranks = ctx->cfg.n_ranks; a.K = (uint32_t)ctx->cfg.top_k;
     a.max_tokens = (uint32_t)ctx->cfg.max_tokens; a.cap = (uint32_t)cap;
     a.packet_bytes = (uint64_t)(mw_packet_header_bytes_of(ctx->cfg.top_k) + ctx->row_bytes);
     a.hop_bits = ctx->d_hop_bits; a.child_pos = ctx->d_child_pos; a.relay_flags = ctx->d_relay_flags; a.stats = stats;
+    a.chunks = relay_chunks(ctx, bs);
     return a;
 }
 
@@ -699,8 +742,8 @@ int32_t mw_launch_relay_packets_index(mw_ctx *ctx, const mw_recv_packets *in, in
 {
     {
         mw_timed tm(ctx, MW_KERNEL_RELAY_INDEX, s);
-        hipLaunchKernelGGL(k_relay_packets_index, dim3(ctx->n_hops + 1), dim3(kBlock), 0, s,
-                           relay_packets_index_args(ctx, in, cap, stats));
+        const mw_relay_packets_index_args a = relay_packets_index_args(ctx, in, cap, stats, kBlock);
+        hipLaunchKernelGGL(k_relay_packets_index, dim3(((uint32_t)ctx->n_hops + 1u) * a.chunks), dim3(kBlock), 0, s, a);
     }
     MW_HIP_CHECK(hipGetLastError());
     return MW_OK;
@@ -716,6 +759,18 @@ int32_t mw_launch_relay_packets_copy(mw_ctx *ctx, const mw_recv_packets *in, voi
     const int n_chunks = (int)(pb / 16);
     const uint32_t keep = (ctx->options & MW_OPT_RELAY_KEEP_METADATA) ? 1u : 0u;
     mw_row_shape shape = mw_row_shape_of(n_chunks);
+    if (next) {
+        // long packets: a few larger workgroups per packet instead of single waves, for the
+        // riding index's sake (see relay_stream_shape); pieces stay whole cache lines
+        const mw_row_shape wide = shape.bs == 64 ? relay_stream_shape(n_chunks) : shape;
+        if (relay_index_rides(ctx, next, wide.bs, (int64_t)pb)) {
+            shape = wide;
+        } else {
+            const int32_t rc = mw_launch_relay_packets_index(next, next_in, next_cap, next_stats, s);
+            if (rc != MW_OK) return rc;
+            next = nullptr;
+        }
+    }
     uint32_t gy = (uint32_t)c.max_tokens < kRowGridMax ? (uint32_t)c.max_tokens : kRowGridMax;
     if (gy < 1) gy = 1;
     {
@@ -725,13 +780,10 @@ int32_t mw_launch_relay_packets_copy(mw_ctx *ctx, const mw_recv_packets *in, voi
                                n_chunks, (uint32_t)c.max_tokens, pb, ctx->d_hop_bits, ctx->d_child_pos,
                                ctx->d_relay_flags, stats, keep);
         } else {
-            // long packets: a few larger workgroups per packet instead of single waves, for the
-            // riding index's sake (see relay_stream_shape); pieces stay whole cache lines
-            if (shape.bs == 64) shape = relay_stream_shape(n_chunks);
-            hipLaunchKernelGGL(k_relay_packets_copy_index_next, dim3(shape.nseg, gy + (uint32_t)next->n_hops + 1u),
-                               dim3(shape.bs), 0, s, (uint32_t)next->n_hops + 1u, 0u, in, children, ctx->n_hops, n_chunks, (uint32_t)c.max_tokens, pb,
-                               ctx->d_hop_bits, ctx->d_child_pos, ctx->d_relay_flags, stats, keep,
-                               relay_packets_index_args(next, next_in, next_cap, next_stats));
+            const mw_relay_packets_index_args a = relay_packets_index_args(next, next_in, next_cap, next_stats, shape.bs);
+            const uint32_t riders = relay_index_rows(next, a.chunks, shape.nseg);
+            hipLaunchKernelGGL(k_relay_packets_copy_index_next, dim3(shape.nseg, gy + riders), dim3(shape.bs), 0, s, riders, 0u, in, children, ctx->n_hops, n_chunks, (uint32_t)c.max_tokens, pb,
+                               ctx->d_hop_bits, ctx->d_child_pos, ctx->d_relay_flags, stats, keep, a);
         }
     }
     MW_HIP_CHECK(hipGetLastError());

@@ -435,3 +435,73 @@ def test_relay_bitmaps_of_more_than_one_word(n_ranks, n_experts, n_hops, keep):
         ch3, st3, _ = gpu_relay(ctx, rec, next_hop, n_hops, w.n_tokens)
         assert int(st3["error_flags"]) & B.MW_FLAG_BAD_RANK
     ctx.close(); ctx2.close()
+
+
+@pytest.mark.parametrize("R,n_hops,T,cap_rows", [(8, 1, 1, 1), (16, 16, 511, 511), (16, 17, 513, 300), (64, 33, 1025, 7),
+                                                (65, 9, 4097, 4097), (129, 64, 2049, 1024), (24, 3, 9000, 4000)])
+def test_index_over_several_workgroups_a_hop(R, n_hops, T, cap_rows):
+    """Child tables whose groups are spread over several workgroups a hop, with the capacity ending inside the first,
+    a middle or no chunk, 16, 32 or 64 positions a group, long groups; on its own, in a stream whose index rides
+    and one whose index does not (16-byte rows: the index would outlast the copy), and the same for packets."""
+    rng = np.random.default_rng(R * 100 + n_hops)
+    E, K, hidden = 2 * R, 3, 8
+    e2r = (np.arange(E) // 2).astype(np.int32)
+    hop = np.concatenate([np.arange(min(n_hops, R)), rng.integers(0, n_hops, max(0, R - n_hops))])[:R].astype(np.int32)
+    tk = rng.integers(0, E, size=(T, K)).astype(np.int32)
+    tk[rng.random(T) < 0.2] = rng.integers(0, E, size=K)          # one long group
+    x = rng.integers(0, 1 << 16, size=(T, hidden), dtype=np.uint16)
+    ctxs = [B.Context(R, E, K, 0, hidden, B.MW_ROW_BF16, T, T, e2r, device=H.DEV, max_hops=n_hops) for _ in range(2)]
+    for c in ctxs:
+        c.mw_set_forwarding(hop, n_hops)
+    mask, perm, desc, _ = ref.plan(tk, e2r, R, 2 * hidden)
+    packed, src, rtk = ref.pack(x, None, tk, perm)
+    rec = dict(desc=H.dev(desc.view(np.uint8)), rows=H.dev(packed), row_src_token=H.dev(src), row_topk=H.dev(rtk),
+               n_desc=len(desc), n_rows=len(perm))
+    table = B.peers_table([rec], H.DEV)
+    kids = [B.RelayChildren(c, n_hops, cap_rows) for c in ctxs]
+    ctxs[0].mw_relay(table, kids[0].table, cap_rows, kids[0].stats)
+    ctxs[1].mw_relay_index(table, kids[1].table, cap_rows, kids[1].stats)
+    ctxs[1].mw_relay_copy_index_next(table, kids[1].table, kids[1].stats, ctxs[0], table, kids[0].table, cap_rows, kids[0].stats)
+    ctxs[0].mw_relay_copy(table, kids[0].table, kids[0].stats)
+    want, overflow, rows_out = [], False, 0
+    for h in range(n_hops):
+        d, r, s, t = ref.relay_child(desc, packed, src, rtk, hop, n_hops, h)
+        end = d["row_offset"] + d["row_count"]
+        fit = int((end <= cap_rows).sum())
+        overflow |= fit < len(d)
+        n = int(end[fit - 1]) if fit else 0
+        rows_out += n
+        want.append((d[:fit], r[:n], s[:n], t[:n]))
+    dests = sum(int(c) * sum(bin(int(w)).count("1") for w in m) for m, c in zip(desc["mask"], desc["row_count"]))
+    for c, k in zip(ctxs, kids):
+        st = c.mw_get_relay_stats(k.stats)
+        assert int(st["error_flags"]) == (B.MW_FLAG_OUT_CAPACITY if overflow else 0)
+        assert (int(st["n_groups_in"]), int(st["n_rows_in"])) == (len(desc), len(perm))
+        assert int(st["unicast_bytes"]) == dests * 2 * hidden and int(st["forward_bytes"]) == rows_out * 2 * hidden
+        for h, (d, r, s, t) in enumerate(want):
+            assert (int(st["groups_per_hop"][h]), int(st["rows_per_hop"][h])) == (len(d), len(s)), h
+            H.assert_same_bytes(H.host(k.desc[h]).reshape(-1).view(B.DESC_DTYPE)[: len(d)].view(np.uint8), d.view(np.uint8), "desc")
+            H.assert_same_bytes(H.host(k.rows[h])[: len(s)], r, "rows")
+            H.assert_same_bytes(H.host(k.row_src_token[h])[: len(s)], s, "row_src_token")
+            H.assert_same_bytes(H.host(k.row_topk[h])[: len(s)], t, "row_topk")
+        assert (np.asarray(st["groups_per_hop"])[n_hops:] == 0).all()
+    # packets
+    pk = ref.pack_packets(x, None, tk, mask, perm)
+    pk_d = H.dev(pk)
+    ptable = B.packets_table([pk_d], [len(pk)], H.DEV)
+    outs, tabs, sts = [], [], []
+    for _ in ctxs:
+        o = torch.zeros((n_hops, max(cap_rows, 1), pk.shape[1]), dtype=torch.uint8, device=H.DEV)
+        outs.append(o)
+        tabs.append(torch.tensor([q.data_ptr() for q in o], dtype=torch.int64, device=H.DEV))
+        sts.append(torch.zeros(B.RELAY_STATS_BYTES, dtype=torch.uint8, device=H.DEV))
+    ctxs[1].mw_relay_packets_index(ptable, cap_rows, sts[1])
+    ctxs[1].mw_relay_packets_copy_index_next(ptable, tabs[1], sts[1], ctxs[0], ptable, cap_rows, sts[0])
+    ctxs[0].mw_relay_packets_copy(ptable, tabs[0], sts[0])
+    for c, o, stats in zip(ctxs, outs, sts):
+        st = c.mw_get_relay_stats(stats)
+        assert (int(st["n_groups_in"]), int(st["n_rows_in"])) == (len(pk), len(pk))
+        for h in range(n_hops):
+            w = ref.relay_packets_child(pk, hop, n_hops, h)[0][:cap_rows]
+            assert int(st["rows_per_hop"][h]) == len(w)
+            H.assert_same_bytes(H.host(o[h])[: len(w)], w, "packets of hop %d" % h)
