@@ -201,7 +201,8 @@ MW_API int32_t mw_ctx_destroy(mw_ctx *ctx);
  * mw_unpack_expand_index_plan_next or mw_stream_step waits for its first half before it gives
  * up; default 2097152.
  * 0 makes it give up unless the first half is already complete when it looks: for tests of
- * that path.  Applies to later calls that plan with this context.
+ * that path.  Applies to later calls that plan with this context; with any value but the default their
+ * plans ride whatever the sizes.
  */
 MW_API int32_t mw_ctx_set_ride_wait_limit(mw_ctx *ctx, int64_t polls);
 
@@ -439,7 +440,10 @@ MW_API int32_t mw_unpack_expand_index_next(mw_ctx *ctx, const mw_recv_batch *rec
  *     mw_pack(batch n);  mw_unpack_expand_index_plan_next(expand n; index n+1; plan n+1);
  *     mw_pack(batch n+1);  ...
  * The plan uses the plan part of next->ctx's workspace (see the conventions above); its outputs
- * are complete when this launch is, i.e. for every later call on the same stream.  The riding
+ * are complete when this launch is, i.e. for every later call on the same stream.  Where the expander
+ * (with mw_stream_step, and the packer) is too short to hide the index or the plan, the library gives them
+ * launches of their own in front, with the same results; a plan always rides on a next context whose
+ * wait limit was set to something else than the default.  The riding
  * plan ranks tokens all-pairs (as mw_plan does up to about 8000 tokens): it stays in the
  * expander's shadow while that takes less time than the expander -- 4096 tokens beside 30000
  * received rows of 14 KiB do, 8192 tokens over 256 ranks beside 20000 such rows do not (use
@@ -758,8 +762,8 @@ MW_API int32_t mw_copy_bytes(void *dst_dev, const void *src_dev, int64_t n_bytes
 
 /* Copy a statistics block to the host.  SYNCHRONISES `stream`.  mw_get_recv_stats also lets
  * the context remember how many rows the peers' buffers held, and the next mw_unpack sizes its
- * launch for about that many rows instead of max_recv_rows (a hint only: any number of rows
- * up to max_recv_rows is still handled). */
+ * launch for about that many rows (without it: for what full batches of evenly drawn ids would
+ * send; a hint only: any number of rows up to max_recv_rows is still handled). */
 MW_API int32_t mw_get_send_stats(mw_ctx *ctx, const mw_send_stats *stats_dev, mw_send_stats *host_out, void *stream);
 MW_API int32_t mw_get_recv_stats(mw_ctx *ctx, const mw_recv_stats *stats_dev, mw_recv_stats *host_out, void *stream);
 MW_API int32_t mw_get_relay_stats(mw_ctx *ctx, const mw_relay_stats *stats_dev, mw_relay_stats *host_out, void *stream);

@@ -53,6 +53,8 @@ static inline mw_row_shape mw_row_shape_of(int chunks)
     return mw_row_shape{b, (chunks + b - 1) / b};
 }
 
+constexpr uint32_t kRideWaitDefault = 1u << 21;      // polls a riding plan's second half waits for its first
+
 // Host-side context.  Every d_* pointer is a slice of the caller's workspace.
 struct mw_ctx {
     mw_config cfg;

@@ -430,11 +430,11 @@ __device__ __forceinline__ void mw_plan_clear(unsigned long long *cnt, uint32_t 
 // n_rank + 1 -- this workgroup if all ranks were done after all, else the rank workgroup that
 // reports last (mw_plan_ride) -- does the clearing.  Either way the launch leaves the context
 // ready for its next plan.
-// `lds`: mw_plan_finish_lds(bs) bytes.  kInFlight: counters a lane requests before it looks at the
-// first (sixteen for the shortest chain; eight where the launch has to stay small in registers).
-template <int kInFlight = 16>
+// `lds`: mw_plan_finish_lds(bs) bytes.  A lane requests eight counters before it looks at the
+// first (sixteen would not fit the launch's registers).
 __device__ __forceinline__ void mw_plan_finish_ride(const mw_plan_args &a, uint32_t fb, uint64_t *lds)
 {
+    constexpr int kInFlight = 8;
     const uint32_t tid = threadIdx.x, bs = blockDim.x;
     const uint32_t rpw = a.finish_rows;
     unsigned long long *tokc = (unsigned long long *)lds;          // [rpw] the row's counters
@@ -550,7 +550,7 @@ __device__ __forceinline__ void mw_plan_finish_ride(const mw_plan_args &a, uint3
 
 // One riding plan workgroup.  `lds` is the launch's dynamic LDS: the slice's keys for a rank
 // workgroup, mw_plan_finish_lds(bs) bytes for a finishing one.
-template <int W, bool kKeyed, int kInFlight = 16>
+template <int W, bool kKeyed>
 __device__ __forceinline__ void mw_plan_ride(const mw_plan_args &a, uint32_t wg, uint64_t *lds)
 {
     if (wg < a.n_rank) {
@@ -568,7 +568,7 @@ __device__ __forceinline__ void mw_plan_ride(const mw_plan_args &a, uint32_t wg,
         return;
     }
     wg -= a.n_rank;
-    if (wg < a.n_finish) mw_plan_finish_ride<kInFlight>(a, wg, lds);
+    if (wg < a.n_finish) mw_plan_finish_ride(a, wg, lds);
 }
 
 }  // namespace

@@ -100,6 +100,7 @@ struct mw_index_args {
     int64_t *expert_offsets; mw_recv_stats *stats; uint32_t *flags;
     uint32_t dedup;     // 1: of the rows of one peer that carry the same source token only one is taken
     uint32_t parts;     // workgroups per peer: part j takes the expert chunks j, j + parts, ... of Lc experts each
+    uint32_t row_parts; // ... times this many: all of them mark every row, each ranks and writes its share of the rows
     uint32_t tab_words; // LDS words of the table of local slots (0: the rank table in memory is looked up)
 };
 
@@ -112,7 +113,7 @@ static inline size_t mw_index_lds_words(uint32_t wpl, uint32_t Lc, uint32_t tab_
     return wpl + tab_words + n + (n + 1) / 2 + 64 + (dedup ? wpl : 0);
 }
 
-// The work of workgroup `part` of peer p; any workgroup size that is a multiple of 64.
+// The work of workgroup (part, row_part) of peer p; any workgroup size that is a multiple of 64.
 // A workgroup looks at all rows of its peer and at the experts of its chunks: it sets the bit
 // (expert, source token) of every row, scans the popcounts, and a row's rank is a lookup.  Chunks are
 // independent of one another (a row's hit k belongs to the workgroup that has the hit's expert, the row's
@@ -128,7 +129,7 @@ static inline size_t mw_index_lds_words(uint32_t wpl, uint32_t Lc, uint32_t tab_
 // for the second pass (top_k <= 8); else the rows are requested again, which the launches that
 // run the index beside the row movers do to stay small in registers.
 template <bool kPackets, bool kGeneral, int kB, bool kKeep>
-__device__ __forceinline__ void recv_index_body(const mw_index_args &a, const uint32_t p, const uint32_t part)
+__device__ __forceinline__ void recv_index_body(const mw_index_args &a, const uint32_t p, const uint32_t part, const uint32_t row_part = 0)
 {
     extern __shared__ uint32_t lds[];
     const uint32_t tid = threadIdx.x, nthr = blockDim.x;
@@ -242,7 +243,7 @@ __device__ __forceinline__ void recv_index_body(const mw_index_args &a, const ui
     if (pr.n_rows > max_tokens || before + mine > a.cap_rows) err |= MW_FLAG_RECV_CAPACITY;
     const uint32_t rb = min(before, a.cap_rows);
     const uint32_t n_rows = min(before + mine, a.cap_rows) - rb;
-    if (tid == 0 && part == 0) {
+    if (tid == 0 && part == 0 && row_part == 0) {
         a.row_base[p] = rb;
         if (p == P - 1u) st_agent(&a.row_base[P], rb + n_rows);    // (also read by the last workgroup)
     }
@@ -437,6 +438,7 @@ __device__ __forceinline__ void recv_index_body(const mw_index_args &a, const ui
             for (uint32_t w = w0; w < w1; ++w) { pre[w] = (uint16_t)run; run += __popc(bits[w]); }
         }
         mw_lds_barrier();
+        if (row_part == 0)
         for (uint32_t l = tid; l < lc; l += nthr) {
             uint32_t n = 0;
             if (wpl) {
@@ -475,9 +477,9 @@ __device__ __forceinline__ void recv_index_body(const mw_index_args &a, const ui
                     a.recs[rb + i] = mw_row_rec{nullptr, 0, (int32_t)p, 0, 0, 0, 0};
             }
         };
-        uint32_t i0 = 0;
-        if (kKeep && first_chunk) { rank(0, s_c, local_c, slots_c); i0 = step; }
-        for (; i0 < n_rows; i0 += step) {
+        uint32_t i0 = row_part * step;
+        if (kKeep && first_chunk && i0 == 0) { rank(0, s_c, local_c, slots_c); i0 = a.row_parts * step; }
+        for (; i0 < n_rows; i0 += a.row_parts * step) {
             uint32_t s_r[kB], local_r[kB];
             uint64_t slots_r[kB];
             int32_t e_r[kB][8];
@@ -499,7 +501,7 @@ __device__ __forceinline__ void recv_index_body(const mw_index_args &a, const ui
         mark_from(0, false);
     }
     if (err) __hip_atomic_fetch_or(&a.flags[1], err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (tid == 0 && part == 0) st_agent(&a.addr_cnt[p], scratch[18] - scratch[19]);    // (both complete: barriers in between)
+    if (tid == 0 && part == 0 && row_part == 0) st_agent(&a.addr_cnt[p], scratch[18] - scratch[19]);    // (both complete: barriers in between)
 
     // ---- the workgroup that finishes last turns the counts into output bases ----------
     // Everything the last workgroup reads (counts, addressed-row counts, flags) is written and
@@ -508,19 +510,20 @@ __device__ __forceinline__ void recv_index_body(const mw_index_args &a, const ui
     // last has thereby acquired what all the others released.  The row records and hit slots,
     // written with ordinary stores, are read by the next kernel only.
     mw_publish_barrier();
-    if (tid == 0) scratch[17] = mw_report(&a.flags[2]) == P * a.parts - 1u ? 1u : 0u;
+    if (tid == 0) scratch[17] = mw_report(&a.flags[2]) == P * a.parts * a.row_parts - 1u ? 1u : 0u;
     __syncthreads();
     if (!scratch[17]) return;
     mw_finish_counts(a.cnt, a.addr_cnt, a.flags, a.row_base, L, P, a.out_cap, a.base, a.expert_offsets, a.stats, scratch);
 }
 
 // Workgroup w of the index of a batch that rides in a launch of row movers: a row a lane at a time,
-// nothing kept between the passes, which fits 58 vector registers without scratch (see kLean below).
+// nothing kept between the passes, which fits 58 vector registers without scratch (see k_expand_index_next).
 __device__ __forceinline__ void recv_index_rider(const mw_index_args &a, const uint32_t w)
 {
-    const uint32_t part = w / (uint32_t)a.P;
-    recv_index_body<false, false, 1, false>(a, w - part * (uint32_t)a.P, part);
+    const uint32_t q = w / (uint32_t)a.P, part = q / a.row_parts;
+    recv_index_body<false, false, 1, false>(a, w - q * (uint32_t)a.P, part, q - part * a.row_parts);
 }
+__device__ __forceinline__ uint32_t index_riders(const mw_index_args &a) { return (uint32_t)a.P * a.parts * a.row_parts; }
 
 template <bool kPackets, bool kGeneral, int kB>
 __global__ __launch_bounds__(kIndexBlock) void k_recv_index(const mw_index_args a)
@@ -909,14 +912,13 @@ __global__ __launch_bounds__(1024) void k_expand(
 // Here it rides along: its workgroups are dispatched first and finish long before the
 // expander's do, and the launch that expands the next batch is ordered after this one by the
 // stream, so no wait, flag or fence is needed.
-// kLean: every wave of a launch is given the registers (and the scratch space for spills) of the
+// Every wave of a launch is given the registers (and the scratch space for spills) of the
 // launch's hungriest path, the row movers' waves included -- and with 64 registers a wave, or
 // with any scratch at all, the dispatcher refills the movers' wave slots more slowly (rocprofv3:
 // SPI_RA_VGPR_SIMD_FULL_CSN and SPI_RA_TMP_STALL_CSN appear, occupancy 7 % down; fp8 step 94.9
-// against 87.4 us with the riders compiled out).  Beside a large batch the riders therefore run
-// in a lean form that fits 56 registers without spilling (no first-row cache in the index, fewer
-// counters in flight in the plan's second half): a few microseconds slower, long inside the
-// movers' shadow.  Beside a small batch, where the riders ARE the step, they keep the fast form.
+// against 87.4 us with the riders compiled out).  The riders therefore come in a lean form that fits
+// 58 registers without spilling (a row a lane at a time in the index, eight counters in flight in the
+// plan's second half); batches too small to hide them give them launches of their own.
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_expand_index_next(
     const uint32_t first_expand_row, const uint32_t unused0, const mw_row_rec *__restrict__ recs,
     const uint32_t *__restrict__ row_base, const uint32_t *__restrict__ base, const mw_hit *__restrict__ hits,
@@ -930,7 +932,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
         return;
     }
     const uint32_t w = blockIdx.y * gridDim.x + blockIdx.x;
-    if (w < (uint32_t)next.P * next.parts) recv_index_rider(next, w);
+    if (w < index_riders(next)) recv_index_rider(next, w);
 }
 
 // The same launch with the PLAN of the next batch riding along as well (Section 5.1, send
@@ -942,7 +944,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
 // on a second stream and one event wait per batch (171 us); fp8 rows of half the size 101
 // against 105 us.  The riding plan is not free: its device-scope atomics and loads take
 // about 4 us of memory-channel time from the expander.
-template <int W, bool kKeyed, bool kLean>
+template <int W, bool kKeyed>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_expand_index_plan_next(
     const uint32_t first_pack_row, const uint32_t first_expand_row, const mw_row_rec *__restrict__ recs,
     const uint32_t *__restrict__ row_base, int P, int xc, const int32_t *__restrict__ pack_perm,
@@ -971,13 +973,13 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
                      pack.row_src_token, pack.row_topk, blockIdx.x, blockIdx.y - y_pack, y_expand - y_pack);
         return;
     }
-    const uint32_t w = blockIdx.y * gridDim.x + blockIdx.x, n_index = (uint32_t)next.P * next.parts;
+    const uint32_t w = blockIdx.y * gridDim.x + blockIdx.x, n_index = index_riders(next);
     if (w < n_index) {
         recv_index_rider(next, w);
         return;
     }
     extern __shared__ uint64_t plan_lds[];
-    mw_plan_ride<W, kKeyed, kLean ? 8 : 16>(plan, w - n_index, plan_lds);
+    mw_plan_ride<W, kKeyed>(plan, w - n_index, plan_lds);
 }
 
 // A whole step of a stream of SMALL batches in one launch (the batch sizes of Section 6.3's
@@ -1107,6 +1109,28 @@ __global__ __launch_bounds__(1024) void k_combine(
 
 }  // namespace
 
+// The part of a peer's tokens that has an expert here, if ids are drawn evenly, and the experts such a token
+// has here on average.
+static double addressed_share(const mw_ctx *ctx, double *copies)
+{
+    const mw_config &c = ctx->cfg;
+    const double share = c.n_experts > 0 ? (double)ctx->n_local / c.n_experts : 0.0;
+    double none = 1.0;
+    for (int k = 0; k < c.top_k; ++k) none *= 1.0 - share;
+    *copies = none < 1.0 ? c.top_k * share / (1.0 - none) : 1.0;
+    return 1.0 - none;
+}
+
+// Rows the peers' buffers will hold: as many as the context saw last, if the caller has asked for the
+// statistics, else what full batches of evenly drawn ids would send.  For launch shapes only.
+static int64_t expected_rows(const mw_ctx *ctx, int32_t P)
+{
+    if (ctx->recv_rows_hint > 0) return ctx->recv_rows_hint;
+    double copies;
+    const double rows = (double)P * ctx->cfg.max_tokens * addressed_share(ctx, &copies);
+    return rows < (double)ctx->cfg.max_recv_rows ? (int64_t)rows : ctx->cfg.max_recv_rows;
+}
+
 // Index arguments of `ctx` for a launch whose workgroups may use `lds_words` words of LDS each: the
 // addressed-rows bitmap, the table of local slots if there is room for it, and one and a half words per
 // 32 source tokens for every expert of a chunk.  The chunks go to `parts` workgroups a peer, at most
@@ -1141,7 +1165,7 @@ static bool make_index_args(mw_ctx *ctx, const void *peers, bool packets, int32_
                        (uint32_t)c.max_tokens, wpl, (uint32_t)c.max_recv_rows,
                        (uint64_t)(packets ? hb + ctx->row_bytes : ctx->row_stride), hb, cap,
                        ctx->d_cnt, ctx->d_row_base, ctx->d_addr_cnt, ctx->d_recs, ctx->d_hits, ctx->d_base,
-                       expert_offsets, stats, ctx->d_flags, dedup, n_chunks < max_parts ? n_chunks : max_parts, tab_words};
+                       expert_offsets, stats, ctx->d_flags, dedup, n_chunks < max_parts ? n_chunks : max_parts, 1u, tab_words};
     return true;
 }
 
@@ -1155,6 +1179,41 @@ static bool index_is_general(const mw_index_args &a) { return a.K > 8 || a.L > 6
 static uint32_t rider_lds_words(int bs) { return (uint32_t)bs * 20u; }
 constexpr uint32_t kRiderAcceptWords = 1280, kIndexAcceptWords = 12288;   // limits on max_tokens the entry points state
 constexpr uint32_t kMaxIndexParts = 16;
+
+// What the row movers of a launch will take, in microseconds: `pack_tokens` rows packed and the received rows
+// read once and written once per local expert, at 5.6 TB/s.
+static double movers_us(const mw_ctx *ctx, int32_t P, int32_t pack_tokens)
+{
+    double copies;
+    addressed_share(ctx, &copies);
+    return ((double)expected_rows(ctx, P) * (1.0 + copies) + 2.0 * pack_tokens) * (double)ctx->row_bytes / 5.6e6;
+}
+
+// Whether the next batch's index rides beside movers of `mover_us` in workgroups of `bs` lanes, and over how many
+// workgroups its rows are then spread.  A rider takes about 1.4 us for every row a lane of each pass; a launch of its own
+// about 12 us.  Measured (us for expander and index; rows of a peer / lanes): 42 rows a lane, expander 80 us: 85.6 riding
+// (110 with the rows not spread), 17 rows a lane, expander 11 us: 44 riding, 23.6 apart.
+static bool index_rides(const mw_ctx *next, double mover_us, int bs, mw_index_args *a)
+{
+    if (index_is_general(*a)) return false;
+    const int64_t rows = (expected_rows(next, a->P) + a->P - 1) / a->P;
+    const int64_t per_lane = (rows + bs - 1) / bs;
+    a->row_parts = a->dedup ? 1u : per_lane >= 8 ? 4u : per_lane >= 4 ? 2u : 1u;
+    return 6.0 + 1.4 * (double)per_lane * (1.0 + 1.0 / a->row_parts) < mover_us + 12.0;
+}
+
+// Whether the next batch's plan rides.  It ranks tokens all-pairs over workgroups that talk through
+// memory: 40 us for 700 tokens, 48 for 1000 and more, a dozen more with keys of several words, free beside movers
+// that take longer; a launch of its own takes 8 (up to 2048 tokens), 13 (4096), 21 us (8192).  Measured (us a
+// step, riding / apart): 1024 tokens beside 26 us of movers 49 / 31; 2000 tokens of 256 ranks beside 34 us 63 / 46;
+// 2048 tokens beside 44 us 48 / 53; 4096 tokens beside 161 us 163 / 174.  A context whose wait limit the caller has set keeps its plans riding.
+static bool plan_rides(const mw_ctx *next, double mover_us, int32_t T, bool keyed)
+{
+    if (T == 0 || next->ride_wait_limit != kRideWaitDefault) return true;
+    const double rider_us = 13.0 + 34.0 * (T < 1024 ? T : 1024) / 1024.0 + (keyed ? 12.0 : 0.0);
+    const double apart_us = T <= 2048 ? 8.0 : T <= 4096 ? 13.0 : 21.0;
+    return rider_us < mover_us + apart_us;
+}
 
 // the index of `P` peers' regions on `ctx` fits the one-workgroup form
 static bool small_index_fits(const mw_ctx *ctx, int32_t P)
@@ -1192,7 +1251,7 @@ int32_t mw_launch_unpack_index(mw_ctx *ctx, const void *peers, bool packets, int
     // tokens to one rank): fewer lanes have shorter barriers and scans, more of them fewer rows each.  With
     // more rows than lanes three a lane are requested together (8 peers of 2720 rows: 13.6 us, one at a time
     // 14.5), with fewer one (16 peers of 429 rows: 8.3 us, with room for three 8.7).
-    const int64_t rows_of_peer = ctx->recv_rows_hint > 0 ? (ctx->recv_rows_hint + P - 1) / P : ctx->cfg.max_tokens / 2;
+    const int64_t rows_of_peer = (expected_rows(ctx, P) + P - 1) / P;
     const int ib = rows_of_peer <= 256 ? 256 : rows_of_peer <= 512 ? 512 : kIndexBlock;
     {
         mw_timed tm(ctx, MW_KERNEL_RECV_INDEX, s);
@@ -1222,24 +1281,15 @@ int32_t mw_launch_unpack_index(mw_ctx *ctx, const void *peers, bool packets, int
     return MW_OK;
 }
 
-// Grid rows of the expander: about as many as the peers held last time (if the caller has
-// asked for the statistics), not the capacity -- workgroups are dispatched at a finite rate,
-// empty ones included.  More rows than that are reached by striding.
-static uint32_t expand_grid_rows(const mw_ctx *ctx)
+// Grid rows of the expander: about as many as the peers will hold, not the capacity -- workgroups are
+// dispatched at a finite rate, empty ones included (16 ranks, 1000 tokens, capacity 16000 rows, 6750 there: mw_plan,
+// mw_pack and mw_unpack 34.3 us for the capacity, 32.0 for the rows).  More rows than that are reached by striding.
+static uint32_t expand_grid_rows(const mw_ctx *ctx, int32_t P)
 {
-    int64_t rows = ctx->cfg.max_recv_rows;
-    if (ctx->recv_rows_hint > 0) {
-        const int64_t want = ctx->recv_rows_hint + ctx->recv_rows_hint / 64 + 64;
-        if (want < rows) rows = want;
-    }
+    int64_t rows = expected_rows(ctx, P);
+    rows += rows / 64 + 64;
+    if (rows > ctx->cfg.max_recv_rows) rows = ctx->cfg.max_recv_rows;
     return (uint32_t)(rows < kRowGridMax ? rows : kRowGridMax);
-}
-
-// Whether a launch that moves `grid_rows` received rows (more by striding) carries its riders in
-// the lean form: from 32 MiB of payload on, where the movers' time dwarfs the riders'.
-static bool riders_lean(const mw_ctx *ctx, uint32_t grid_rows)
-{
-    return (int64_t)grid_rows * ctx->row_bytes >= (32LL << 20);
 }
 
 int32_t mw_launch_unpack_expand(mw_ctx *ctx, int32_t P, void *out_rows, float *out_scales, int64_t cap,
@@ -1249,7 +1299,7 @@ int32_t mw_launch_unpack_expand(mw_ctx *ctx, int32_t P, void *out_rows, float *o
     if (c.max_recv_rows > 0) {
         const int xc = (int)(ctx->x_row_bytes / 16), sc = (int)(ctx->s_row_bytes / 16);
         const mw_row_shape shape = mw_row_shape_of(xc + sc);
-        const uint32_t gy = expand_grid_rows(ctx);
+        const uint32_t gy = expand_grid_rows(ctx, P);
         mw_timed tm(ctx, MW_KERNEL_EXPAND, s);
         hipLaunchKernelGGL(k_expand, dim3(shape.nseg, gy), dim3(shape.bs), 0, s, ctx->d_recs, ctx->d_row_base, ctx->d_base,
                            ctx->d_hits, P, ctx->hit_slots, xc, sc, (u32x4 *)out_rows, (u32x4 *)out_scales,
@@ -1346,16 +1396,16 @@ int32_t mw_launch_unpack_expand_index_next(mw_ctx *ctx, int32_t P, void *out_row
     if (!make_index_args(next, next_peers, false, next_P, next_cap, next_expert_offsets, next_stats, kRiderAcceptWords,
                          rider_lds_words(shape.bs), 1, kMaxIndexParts, &a, &lds_index))
         return MW_ERR_UNSUPPORTED;
-    const uint32_t gy = expand_grid_rows(ctx);
+    const uint32_t gy = expand_grid_rows(ctx, P);
     if (small_step_fits(ctx, next, next_P, 0, nullptr, gy))
         return launch_small_step(ctx, P, out_rows, out_scales, cap, out_src_peer, out_src_token, next, a, false, nullptr,
                                  0, nullptr, nullptr, nullptr, nullptr, nullptr, gy, s);
-    if (index_is_general(a)) {                                // not a form that rides: a launch of its own in front
+    if (!index_rides(next, movers_us(ctx, P, 0), shape.bs, &a)) {      // a launch of its own in front
         const int32_t rc = mw_launch_unpack_index(next, next_peers, false, next_P, next_cap, next_expert_offsets, next_stats, s);
         if (rc != MW_OK) return rc;
         return mw_launch_unpack_expand(ctx, P, out_rows, out_scales, cap, out_src_peer, out_src_token, s);
     }
-    const uint32_t index_rows = ((uint32_t)next_P * a.parts + (uint32_t)shape.nseg - 1) / (uint32_t)shape.nseg;
+    const uint32_t index_rows = ((uint32_t)next_P * a.parts * a.row_parts + (uint32_t)shape.nseg - 1) / (uint32_t)shape.nseg;
     {
         mw_timed tm(ctx, MW_KERNEL_EXPAND, s);
         const uint32_t cap32 = (uint32_t)(cap < 0x7fffffffLL ? cap : 0x7fffffffLL);
@@ -1386,20 +1436,26 @@ int32_t mw_launch_unpack_expand_index_plan_next(mw_ctx *ctx, int32_t P, void *ou
     if (!make_index_args(next, next_peers, false, next_P, next_cap, next_expert_offsets, next_stats, kRiderAcceptWords,
                          rider_lds_words(shape.bs), 1, kMaxIndexParts, &a, &lds_index))
         return MW_ERR_UNSUPPORTED;
-    const uint32_t gy = expand_grid_rows(ctx);
+    const uint32_t gy = expand_grid_rows(ctx, P);
     if (small_step_fits(ctx, next, next_P, next_T, pk, gy))
         return launch_small_step(ctx, P, out_rows, out_scales, cap, out_src_peer, out_src_token, next, a, true, next_topk,
                                  next_T, next_mask, next_perm, next_desc, next_send_stats, pk, gy, s);
 
-    if (index_is_general(a)) {                                // not a form that rides: a launch of its own in front
+    const int K = next->cfg.top_k, W = next->mask_words;
+    const bool keyed = W > 1 && K <= 8;
+    const double mover_us = movers_us(ctx, P, pk ? pk->n_tokens : 0);
+    if (!index_rides(next, mover_us, shape.bs, &a)) {                // a launch of its own in front
         const int32_t rc = mw_launch_unpack_index(next, next_peers, false, next_P, next_cap, next_expert_offsets, next_stats, s);
         if (rc != MW_OK) return rc;
         a.parts = 0;
     }
+    const bool with_plan = plan_rides(next, mover_us, next_T, keyed);
+    if (!with_plan) {
+        const int32_t rc = mw_launch_plan(next, next_topk, next_T, next_mask, next_perm, next_desc, next_send_stats, s);
+        if (rc != MW_OK) return rc;
+    }
 
     // the riding plan: workgroups of the launch's size
-    const int K = next->cfg.top_k, W = next->mask_words;
-    const bool keyed = W > 1 && K <= 8;
     mw_plan_args pl;
     pl.topk = next_topk; pl.T = next_T; pl.K = K; pl.E = next->cfg.n_experts; pl.eslot = next->d_eslot;
     pl.mask_out = next_mask; pl.cnt = (unsigned long long *)next->d_plan_cnt; pl.pstate = next->d_plan_state;
@@ -1419,11 +1475,14 @@ int32_t mw_launch_unpack_expand_index_plan_next(mw_ctx *ctx, int32_t P, void *ou
     pl.finish_rows = mw_plan_finish_rows(shape.bs);
     pl.n_finish = next_T > 0 ? ((uint32_t)next_T + pl.finish_rows - 1) / pl.finish_rows : 1u;
     pl.wait_limit = next->ride_wait_limit;
-    const uint32_t rider_rows = ((uint32_t)next_P * a.parts + pl.n_rank + pl.n_finish + (uint32_t)shape.nseg - 1) /
+    if (!with_plan) pl.n_rank = pl.n_finish = 0;
+    const uint32_t rider_rows = ((uint32_t)next_P * a.parts * a.row_parts + pl.n_rank + pl.n_finish + (uint32_t)shape.nseg - 1) /
                                 (uint32_t)shape.nseg;
     size_t lds_plan = (size_t)pl.slice * key_bytes;
     if (lds_plan < mw_plan_finish_lds(shape.bs)) lds_plan = mw_plan_finish_lds(shape.bs);
-    const size_t lds = lds_index > lds_plan ? lds_index : lds_plan;
+    size_t lds = 0;                                              // of the riders there are
+    if (a.parts > 0) lds = lds_index;
+    if (with_plan && lds < lds_plan) lds = lds_plan;
     {
         mw_timed tm(ctx, MW_KERNEL_EXPAND, s);
         // the packer of this context's own rows, if asked for: same row shape as the expander
@@ -1437,23 +1496,20 @@ int32_t mw_launch_unpack_expand_index_plan_next(mw_ctx *ctx, int32_t P, void *ou
             n_pack_rows = (uint32_t)pk->n_tokens < 16384u ? (uint32_t)pk->n_tokens : 16384u;   // more by striding
         }
         // a grid has at most 65535 rows: the expander takes what the riders leave (more by striding)
-        const uint32_t riders = rider_rows + n_pack_rows;                         // <= 4096 + 8192 + 16384
+        const uint32_t riders = rider_rows + n_pack_rows;                         // <= 16384 + 8192 + 16384
         const uint32_t gy_fit = gy < 65535u - riders ? gy : 65535u - riders;
         const dim3 grid(shape.nseg, gy_fit + riders), block(shape.bs);
         const uint32_t cap32 = (uint32_t)(cap < 0x7fffffffLL ? cap : 0x7fffffffLL);
-        const bool lean = riders_lean(ctx, gy_fit);
-#define MW_RIDE_(W_, KEYED_, LEAN_)                                                                                \
-    hipLaunchKernelGGL((k_expand_index_plan_next<W_, KEYED_, LEAN_>), grid, block, lds, s,                          \
+#define MW_RIDE(W_, KEYED_)                                                                                        \
+    hipLaunchKernelGGL((k_expand_index_plan_next<W_, KEYED_>), grid, block, lds, s,                          \
                        rider_rows, rider_rows + n_pack_rows, ctx->d_recs, ctx->d_row_base, P, xc, pa.perm, pa.stats, sc, ctx->hit_slots, ctx->d_base, ctx->d_hits,     \
                        (u32x4 *)out_rows, (u32x4 *)out_scales, cap32, out_src_peer, out_src_token, a, pl, pa)
-#define MW_RIDE(W_, KEYED_) do { if (lean) MW_RIDE_(W_, KEYED_, true); else MW_RIDE_(W_, KEYED_, false); } while (0)
         if (keyed) MW_RIDE(4, true);
         else if (W == 1) MW_RIDE(1, false);
         else if (W == 2) MW_RIDE(2, false);
         else if (W == 3) MW_RIDE(3, false);
         else MW_RIDE(4, false);
 #undef MW_RIDE
-#undef MW_RIDE_
     }
     MW_HIP_CHECK(hipGetLastError());
     return MW_OK;
@@ -1465,12 +1521,7 @@ int32_t mw_launch_combine(mw_ctx *ctx, int32_t P, const void *y, int64_t cap, vo
     if (c.max_recv_rows > 0 && ret_cap > 0) {
         const int n = (int)(ctx->x_row_bytes / 16);
         const mw_row_shape shape = mw_row_shape_of(n);
-        int64_t rows = c.max_recv_rows;                     // grid sized like the expander's
-        if (ctx->recv_rows_hint > 0) {
-            const int64_t want = ctx->recv_rows_hint + ctx->recv_rows_hint / 64 + 64;
-            if (want < rows) rows = want;
-        }
-        const uint32_t gy = (uint32_t)(rows < kRowGridMax ? rows : kRowGridMax);
+        const uint32_t gy = expand_grid_rows(ctx, P);
         mw_timed tm(ctx, MW_KERNEL_COMBINE, s);
         hipLaunchKernelGGL(k_combine, dim3(shape.nseg, gy), dim3(shape.bs), 0, s, ctx->d_recs, ctx->d_hits, ctx->d_base,
                            ctx->d_row_base, P, ctx->hit_slots, n, (const u32x4 *)y,

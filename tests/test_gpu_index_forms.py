@@ -102,3 +102,55 @@ def test_index_forms(which):
         assert int(gu.stats["error_flags"]) == B.MW_FLAG_DUPLICATE_DROPPED
         gu.stats["error_flags"] = 0
         H.check_unpack(gu, want, "repeats dropped")
+
+
+@pytest.mark.parametrize("hidden,forced", [(8, False), (8, True), (1024, False), (4096, True)])
+@pytest.mark.parametrize("R,E,T", [(8, 256, 1100), (4, 16, 2600), (130, 260, 300)])
+def test_stream_steps_with_riders_and_without(R, E, T, hidden, forced):
+    """mw_stream_step where index and plan ride and where they get launches of their own (movers too short),
+    and with a plan that is made to ride; rows of a peer spread over several workgroups."""
+    print("stream step", R, E, T, hidden, forced, flush=True)
+    K, my_rank, n_peers = 8, R // 2, min(R, 8)
+    rng = np.random.default_rng(R + T + hidden)
+    e2r = (np.arange(E) * R // E).astype(np.int32)
+    ctxs = [B.Context(R, E, K, my_rank, hidden, B.MW_ROW_BF16, T, n_peers * T, e2r, device=H.DEV) for _ in range(2)]
+    if forced:
+        for c in ctxs:
+            c.mw_ctx_set_ride_wait_limit((1 << 21) - 1)
+    batches = []
+    for c in ctxs:
+        toks = [_tokens(rng, R, E, K, T, hidden) for _ in range(n_peers)]
+        recs = [H.shrink(H.GpuSend(c, tk, x, None).deliver(my_rank)) for tk, x in toks]
+        cap = sum(r["n_rows"] for r in recs) * min(K, c.n_local) + 1
+        tk, x = _tokens(rng, R, E, K, T, hidden)
+        batches.append(dict(toks=[(a, b, None) for a, b in toks], recs=recs, cap=cap, table=B.peers_table(recs, H.DEV), tk=tk, x=x,
+                            tk_d=H.dev(tk), x_d=H.dev(x), send=B.SendBuffers(c, T), recv=B.RecvBuffers(c, cap)))
+    b0 = batches[0]
+    ctxs[0].mw_unpack_index(b0["table"], n_peers, b0["cap"], b0["recv"].expert_offsets, b0["recv"].stats)
+    ctxs[0].mw_get_recv_stats(b0["recv"].stats)
+    s = b0["send"]
+    ctxs[0].mw_plan(b0["tk_d"], s.mask, s.perm, s.desc, s.stats)
+    for i in range(4):
+        cur, nxt, b, n = ctxs[i % 2], ctxs[(i + 1) % 2], batches[i % 2], batches[(i + 1) % 2]
+        s, r, ns, nr = b["send"], b["recv"], n["send"], n["recv"]
+        if i > 1:
+            ns.perm.fill_(-1)
+        cur.mw_stream_step(b["x_d"], None, b["tk_d"], s.perm, s.stats, s.packed, s.row_src_token, s.row_topk, n_peers,
+                           r.out_rows, None, b["cap"], r.out_src_peer, r.out_src_token, nxt, n["table"], n_peers, n["cap"],
+                           nr.expert_offsets, nr.stats, n["tk_d"], ns.mask, ns.perm, ns.desc, ns.stats)
+        if i == 0:
+            nxt.mw_get_recv_stats(nr.stats)
+    for c, b in zip(ctxs, batches):
+        gu = H.GpuUnpack.__new__(H.GpuUnpack)
+        gu.ctx, gu.buf, gu.stats = c, b["recv"], c.mw_get_recv_stats(b["recv"].stats)
+        gu.Q = int(gu.stats["n_out_rows"])
+        H.check_unpack(gu, ref.dispatch_plain(b["toks"], e2r, my_rank, b["cap"]), "step")
+        mask, perm, desc, want = ref.plan(b["tk"], e2r, R, 2 * hidden)
+        st = c.mw_get_send_stats(b["send"].stats)
+        assert (int(st["n_rows"]), int(st["n_groups"]), int(st["error_flags"])) == (len(perm), len(desc), 0)
+        H.assert_same_bytes(st["rows_per_dest"], want["rows_per_dest"], "rows_per_dest")
+        H.assert_same_bytes(H.host(b["send"].perm)[: len(perm)], perm, "perm")
+        H.assert_same_bytes(H.host(b["send"].mask).view(np.uint64)[:T], mask, "mask")
+        H.assert_same_bytes(H.host(b["send"].desc).reshape(-1).view(B.DESC_DTYPE)[: len(desc)].view(np.uint8), desc.view(np.uint8), "desc")
+        packed, src, rtk = ref.pack(b["x"], None, b["tk"], perm)
+        H.assert_same_bytes(H.host(b["send"].packed)[: len(perm)], packed, "packed")
