@@ -106,6 +106,10 @@ struct mw_index_args {
 
 constexpr uint32_t kNotLocal = 0xffu;     // table entry of an expert that lives elsewhere; local slots are below 255
 
+// What the index may assume: at most eight ids a token, at most 64 local experts and the table in LDS; the
+// same with any number of ids; nothing.
+constexpr int kFormFew = 0, kFormMany = 1, kFormAny = 2;
+
 // LDS words of an index workgroup that handles Lc experts at a time.
 static inline size_t mw_index_lds_words(uint32_t wpl, uint32_t Lc, uint32_t tab_words, bool dedup)
 {
@@ -128,14 +132,14 @@ static inline size_t mw_index_lds_words(uint32_t wpl, uint32_t Lc, uint32_t tab_
 // kB: rows a lane requests together.  kKeep: what the lane's first kB rows parsed to stays in registers
 // for the second pass (top_k <= 8); else the rows are requested again, which the launches that
 // run the index beside the row movers do to stay small in registers.
-template <bool kPackets, bool kGeneral, int kB, bool kKeep>
+template <bool kPackets, int kForm, int kB, bool kKeep>
 __device__ __forceinline__ void recv_index_body(const mw_index_args &a, const uint32_t p, const uint32_t part, const uint32_t row_part = 0)
 {
     extern __shared__ uint32_t lds[];
     const uint32_t tid = threadIdx.x, nthr = blockDim.x;
     const uint32_t wpl = a.wpl, K = (uint32_t)a.K, Kd = (uint32_t)a.Kd, E = (uint32_t)a.E, L = (uint32_t)a.L, Lc = (uint32_t)a.Lc;
     const uint32_t P = (uint32_t)a.P, my_rank = (uint32_t)a.my_rank, max_tokens = a.max_tokens, dedup = a.dedup;
-    const bool use_tab = !kGeneral || a.tab_words != 0;
+    const bool use_tab = kForm < kFormAny || a.tab_words != 0;
     uint32_t *addr = lds;                                       // [wpl]      bit i: row i's group names this rank
     unsigned char *tab = (unsigned char *)(addr + wpl);         // [E + 1]    local slot of expert e or kNotLocal
     uint32_t *bits = addr + wpl + a.tab_words;                  // [Lc][wpl]  bit s of expert l: a row with source token s
@@ -342,7 +346,7 @@ __device__ __forceinline__ void recv_index_body(const mw_index_args &a, const ui
             local &= local - 1u;
             const uint32_t le = use_tab ? (uint32_t)(slots >> (8u * u)) & 0xffu
                                         : (uint32_t)a.eslot[ids_of(i)[j0 + u]] & 0xffffu;
-            if (!kGeneral || L <= 64) {
+            if (kForm < kFormAny || L <= 64) {
                 const uint64_t bit = 1ull << le;
                 if (named & bit) continue;
                 named |= bit;
@@ -360,15 +364,16 @@ __device__ __forceinline__ void recv_index_body(const mw_index_args &a, const ui
     auto walk_row = [&](uint32_t i, uint32_t local, uint64_t slots, auto act) __attribute__((always_inline)) -> uint32_t {
         uint32_t nk = 0;
         uint64_t named = 0;
-        walk(i, 0, local, slots, nk, named, act);
-        if constexpr (kGeneral)
-        for (uint32_t j0 = 8; j0 < K; j0 += 8) {
+        for (uint32_t j0 = 0;;) {
+            walk(i, j0, local, slots, nk, named, act);
+            if constexpr (kForm == kFormFew) break;
+            j0 += 8;
+            if (j0 >= K) break;
             int32_t e[8];
             const int32_t *tk = ids_of(i);
 #pragma unroll
             for (int u = 0; u < 8; ++u) e[u] = (j0 + u < K) ? tk[j0 + u] : -1;
             classify(e, j0, local, slots);
-            walk(i, j0, local, slots, nk, named, act);
         }
         return nk;
     };
@@ -518,17 +523,18 @@ __device__ __forceinline__ void recv_index_body(const mw_index_args &a, const ui
 
 // Workgroup w of the index of a batch that rides in a launch of row movers: a row a lane at a time,
 // nothing kept between the passes, which fits 58 vector registers without scratch (see k_expand_index_next).
+template <int kForm>
 __device__ __forceinline__ void recv_index_rider(const mw_index_args &a, const uint32_t w)
 {
     const uint32_t q = w / (uint32_t)a.P, part = q / a.row_parts;
-    recv_index_body<false, false, 1, false>(a, w - q * (uint32_t)a.P, part, q - part * a.row_parts);
+    recv_index_body<false, kForm, 1, false>(a, w - q * (uint32_t)a.P, part, q - part * a.row_parts);
 }
 __device__ __forceinline__ uint32_t index_riders(const mw_index_args &a) { return (uint32_t)a.P * a.parts * a.row_parts; }
 
-template <bool kPackets, bool kGeneral, int kB>
+template <bool kPackets, int kForm, int kB>
 __global__ __launch_bounds__(kIndexBlock) void k_recv_index(const mw_index_args a)
 {
-    recv_index_body<kPackets, kGeneral, kB, !kGeneral>(a, blockIdx.x, blockIdx.y);
+    recv_index_body<kPackets, kForm, kB, kForm == kFormFew>(a, blockIdx.x, blockIdx.y);
 }
 
 // ---- the index of a SMALL batch in one workgroup ------------------------------------------------
@@ -918,7 +924,10 @@ __global__ __launch_bounds__(1024) void k_expand(
 // SPI_RA_VGPR_SIMD_FULL_CSN and SPI_RA_TMP_STALL_CSN appear, occupancy 7 % down; fp8 step 94.9
 // against 87.4 us with the riders compiled out).  The riders therefore come in a lean form that fits
 // 58 registers without spilling (a row a lane at a time in the index, eight counters in flight in the
-// plan's second half); batches too small to hide them give them launches of their own.
+// plan's second half); batches too small to hide them give them launches of their own.  kFormMany (top_k
+// above eight) spills five: beside 61 us of movers 65 us against 72 with the index in front, beside 22
+// us 22.6 against 34.4.
+template <int kForm>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_expand_index_next(
     const uint32_t first_expand_row, const uint32_t unused0, const mw_row_rec *__restrict__ recs,
     const uint32_t *__restrict__ row_base, const uint32_t *__restrict__ base, const mw_hit *__restrict__ hits,
@@ -932,7 +941,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
         return;
     }
     const uint32_t w = blockIdx.y * gridDim.x + blockIdx.x;
-    if (w < index_riders(next)) recv_index_rider(next, w);
+    if (w < index_riders(next)) recv_index_rider<kForm>(next, w);
 }
 
 // The same launch with the PLAN of the next batch riding along as well (Section 5.1, send
@@ -944,7 +953,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
 // on a second stream and one event wait per batch (171 us); fp8 rows of half the size 101
 // against 105 us.  The riding plan is not free: its device-scope atomics and loads take
 // about 4 us of memory-channel time from the expander.
-template <int W, bool kKeyed>
+template <int W, bool kKeyed, int kForm>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_expand_index_plan_next(
     const uint32_t first_pack_row, const uint32_t first_expand_row, const mw_row_rec *__restrict__ recs,
     const uint32_t *__restrict__ row_base, int P, int xc, const int32_t *__restrict__ pack_perm,
@@ -975,7 +984,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
     }
     const uint32_t w = blockIdx.y * gridDim.x + blockIdx.x, n_index = index_riders(next);
     if (w < n_index) {
-        recv_index_rider(next, w);
+        recv_index_rider<kForm>(next, w);
         return;
     }
     extern __shared__ uint64_t plan_lds[];
@@ -1171,8 +1180,11 @@ static bool make_index_args(mw_ctx *ctx, const void *peers, bool packets, int32_
 
 // Id lists of at most eight, at most 64 local experts and a table of their slots in LDS: a row's ids are
 // one request and its distinct experts a 64-bit set, all in registers.  Anything beyond takes
-// the general form, a row a lane at a time.
-static bool index_is_general(const mw_index_args &a) { return a.K > 8 || a.L > 64 || a.tab_words == 0; }
+// the general forms, a row a lane at a time.
+static int index_form(const mw_index_args &a)
+{
+    return a.L > 64 || a.tab_words == 0 ? kFormAny : a.K > 8 ? kFormMany : kFormFew;
+}
 
 // LDS words a workgroup of `bs` lanes may reserve in a launch whose row movers should keep every wave
 // slot: its share of a CU's 160 KiB when 2048 lanes are resident.
@@ -1190,28 +1202,30 @@ static double movers_us(const mw_ctx *ctx, int32_t P, int32_t pack_tokens)
 }
 
 // Whether the next batch's index rides beside movers of `mover_us` in workgroups of `bs` lanes, and over how many
-// workgroups its rows are then spread.  A rider takes about 1.4 us for every row a lane of each pass; a launch of its own
+// workgroups its rows are then spread.  A rider takes about 1.4 us for every row and eight ids a lane of each pass; a launch of its own
 // about 12 us.  Measured (us for expander and index; rows of a peer / lanes): 42 rows a lane, expander 80 us: 85.6 riding
 // (110 with the rows not spread), 17 rows a lane, expander 11 us: 44 riding, 23.6 apart.
 static bool index_rides(const mw_ctx *next, double mover_us, int bs, mw_index_args *a)
 {
-    if (index_is_general(*a)) return false;
+    if (index_form(*a) == kFormAny) return false;                   // (spills 25 of the riders' 64 registers)
     const int64_t rows = (expected_rows(next, a->P) + a->P - 1) / a->P;
     const int64_t per_lane = (rows + bs - 1) / bs;
     a->row_parts = a->dedup ? 1u : per_lane >= 8 ? 4u : per_lane >= 4 ? 2u : 1u;
-    return 6.0 + 1.4 * (double)per_lane * (1.0 + 1.0 / a->row_parts) < mover_us + 12.0;
+    const double row_us = 1.4 * (double)((a->K + 7) / 8);
+    return 6.0 + row_us * (double)per_lane * (1.0 + 1.0 / a->row_parts) < mover_us + 12.0;
 }
 
 // Whether the next batch's plan rides.  It ranks tokens all-pairs over workgroups that talk through
 // memory: 40 us for 700 tokens, 48 for 1000 and more, a dozen more with keys of several words, free beside movers
-// that take longer; a launch of its own takes 8 (up to 2048 tokens), 13 (4096), 21 us (8192).  Measured (us a
+// that take longer; a launch of its own takes 8 (up to 2048 tokens), 13 (4096), 21 us (8192), 18 with more
+// than eight ids and bitmaps of several words.  Measured (us a
 // step, riding / apart): 1024 tokens beside 26 us of movers 49 / 31; 2000 tokens of 256 ranks beside 34 us 63 / 46;
 // 2048 tokens beside 44 us 48 / 53; 4096 tokens beside 161 us 163 / 174.  A context whose wait limit the caller has set keeps its plans riding.
 static bool plan_rides(const mw_ctx *next, double mover_us, int32_t T, bool keyed)
 {
     if (T == 0 || next->ride_wait_limit != kRideWaitDefault) return true;
     const double rider_us = 13.0 + 34.0 * (T < 1024 ? T : 1024) / 1024.0 + (keyed ? 12.0 : 0.0);
-    const double apart_us = T <= 2048 ? 8.0 : T <= 4096 ? 13.0 : 21.0;
+    const double apart_us = !keyed && next->mask_words > 1 ? 18.0 : T <= 2048 ? 8.0 : T <= 4096 ? 13.0 : 21.0;
     return rider_us < mover_us + apart_us;
 }
 
@@ -1271,9 +1285,10 @@ int32_t mw_launch_unpack_index(mw_ctx *ctx, const void *peers, bool packets, int
         if (packets) hipLaunchKernelGGL((k_recv_index<true, GENERAL_, ROWS_>), dim3(P, a.parts), dim3(ib), lds_index, s, a);   \
         else hipLaunchKernelGGL((k_recv_index<false, GENERAL_, ROWS_>), dim3(P, a.parts), dim3(ib), lds_index, s, a);          \
     } while (0)
-            if (index_is_general(a)) MW_INDEX(true, 1);
-            else if (rows_of_peer <= ib) MW_INDEX(false, 1);
-            else MW_INDEX(false, 3);
+            if (index_form(a) == kFormAny) MW_INDEX(kFormAny, 1);
+            else if (index_form(a) == kFormMany) MW_INDEX(kFormMany, 1);
+            else if (rows_of_peer <= ib) MW_INDEX(kFormFew, 1);
+            else MW_INDEX(kFormFew, 3);
 #undef MW_INDEX
         }
     }
@@ -1409,9 +1424,12 @@ int32_t mw_launch_unpack_expand_index_next(mw_ctx *ctx, int32_t P, void *out_row
     {
         mw_timed tm(ctx, MW_KERNEL_EXPAND, s);
         const uint32_t cap32 = (uint32_t)(cap < 0x7fffffffLL ? cap : 0x7fffffffLL);
-        hipLaunchKernelGGL(k_expand_index_next, dim3(shape.nseg, gy + index_rows), dim3(shape.bs), lds_index, s, index_rows, 0u,
-                           ctx->d_recs, ctx->d_row_base, ctx->d_base, ctx->d_hits, P, ctx->hit_slots, xc, sc,
-                           (u32x4 *)out_rows, (u32x4 *)out_scales, cap32, out_src_peer, out_src_token, a);
+        auto launch = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3(shape.nseg, gy + index_rows), dim3(shape.bs), lds_index, s, index_rows, 0u,
+                               ctx->d_recs, ctx->d_row_base, ctx->d_base, ctx->d_hits, P, ctx->hit_slots, xc, sc,
+                               (u32x4 *)out_rows, (u32x4 *)out_scales, cap32, out_src_peer, out_src_token, a);
+        };
+        if (index_form(a) == kFormMany) launch(k_expand_index_next<kFormMany>); else launch(k_expand_index_next<kFormFew>);
     }
     MW_HIP_CHECK(hipGetLastError());
     return MW_OK;
@@ -1500,10 +1518,16 @@ int32_t mw_launch_unpack_expand_index_plan_next(mw_ctx *ctx, int32_t P, void *ou
         const uint32_t gy_fit = gy < 65535u - riders ? gy : 65535u - riders;
         const dim3 grid(shape.nseg, gy_fit + riders), block(shape.bs);
         const uint32_t cap32 = (uint32_t)(cap < 0x7fffffffLL ? cap : 0x7fffffffLL);
+        auto launch = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, grid, block, lds, s, rider_rows, rider_rows + n_pack_rows, ctx->d_recs,
+                               ctx->d_row_base, P, xc, pa.perm, pa.stats, sc, ctx->hit_slots, ctx->d_base, ctx->d_hits,
+                               (u32x4 *)out_rows, (u32x4 *)out_scales, cap32, out_src_peer, out_src_token, a, pl, pa);
+        };
 #define MW_RIDE(W_, KEYED_)                                                                                        \
-    hipLaunchKernelGGL((k_expand_index_plan_next<W_, KEYED_>), grid, block, lds, s,                          \
-                       rider_rows, rider_rows + n_pack_rows, ctx->d_recs, ctx->d_row_base, P, xc, pa.perm, pa.stats, sc, ctx->hit_slots, ctx->d_base, ctx->d_hits,     \
-                       (u32x4 *)out_rows, (u32x4 *)out_scales, cap32, out_src_peer, out_src_token, a, pl, pa)
+    do {                                                                                                           \
+        if (index_form(a) == kFormMany) launch(k_expand_index_plan_next<W_, false, kFormMany>);   /* (not keyed) */ \
+        else launch(k_expand_index_plan_next<W_, KEYED_, kFormFew>);                                                   \
+    } while (0)
         if (keyed) MW_RIDE(4, true);
         else if (W == 1) MW_RIDE(1, false);
         else if (W == 2) MW_RIDE(2, false);

@@ -105,12 +105,13 @@ def test_index_forms(which):
 
 
 @pytest.mark.parametrize("hidden,forced", [(8, False), (8, True), (1024, False), (4096, True)])
-@pytest.mark.parametrize("R,E,T", [(8, 256, 1100), (4, 16, 2600), (130, 260, 300)])
-def test_stream_steps_with_riders_and_without(R, E, T, hidden, forced):
+@pytest.mark.parametrize("R,E,T,K", [(8, 256, 1100, 8), (4, 16, 2600, 8), (130, 260, 300, 8), (8, 256, 1100, 20), (4, 16, 2600, 9),
+                                     (130, 260, 300, 16)])
+def test_stream_steps_with_riders_and_without(R, E, T, K, hidden, forced):
     """mw_stream_step where index and plan ride and where they get launches of their own (movers too short),
     and with a plan that is made to ride; rows of a peer spread over several workgroups."""
-    print("stream step", R, E, T, hidden, forced, flush=True)
-    K, my_rank, n_peers = 8, R // 2, min(R, 8)
+    print("stream step", R, E, T, K, hidden, forced, flush=True)
+    my_rank, n_peers = R // 2, min(R, 8)
     rng = np.random.default_rng(R + T + hidden)
     e2r = (np.arange(E) * R // E).astype(np.int32)
     ctxs = [B.Context(R, E, K, my_rank, hidden, B.MW_ROW_BF16, T, n_peers * T, e2r, device=H.DEV) for _ in range(2)]
