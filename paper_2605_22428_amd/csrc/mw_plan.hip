@@ -701,51 +701,66 @@ __global__ __launch_bounds__(256) void k_plan_allgather_split(int R, uint64_t sh
 }
 
 // Plan and pack of a decode-sized batch (at most kFusedMax tokens) in one launch.  The results
-// are those of k_rank + k_groups + the packer; what changes is the latency: three dependent
-// launches and two rounds of global atomics become one launch without any global scratch.
-// Workgroup b moves packed row b.  To find that row's token every workgroup builds all
-// bitmaps in LDS and ranks all tokens itself (one token per lane): for so few tokens that is
-// cheaper than waiting for another workgroup's result.  The first workgroup also writes the
-// bitmaps, perm and the descriptors, the last one the statistics.
+// are those of mw_plan and the packer; what changes is the latency: dependent launches become one
+// without any global scratch.  Workgroup 0 makes the plan.  Workgroup 1 + b moves token b's row
+// and does not wait for it: the row is requested first, and beside it the workgroup builds all
+// bitmaps itself, one token per lane, and counts those in front of its own, which is the packed
+// row.  (A workgroup per packed row has to rank all tokens before it knows what to load.)
+// Measured (us, 14336-byte rows, workgroup per packed row / this): 16 tokens 8.0 / 4.2, 64 of 64 ranks 10.0 / 4.3,
+// 128 11.5 / 5.4, 256 14.7 / 8.3, 64 of 256 ranks 17.9 / 6.1; the plan alone is most of it.
 constexpr int kFusedMax = MW_FUSED_MAX_TOKENS;
-static_assert(kFusedMax == kBlock, "one token per lane");
 
-// kKeyed (bitmaps of more than one word, top_k <= 8): the all-pairs walk compares short keys.
+// kKeyed (bitmaps of more than one word, top_k <= 8): the plan's all-pairs walk compares short keys.
 template <int W, bool kKeyed>
-__global__ __launch_bounds__(kBlock) void k_plan_pack(const int32_t *__restrict__ topk, int T, int K,
-                                                      const int32_t *__restrict__ eslot, int E,
-                                                      const u32x4 *__restrict__ x, const u32x4 *__restrict__ scales,
-                                                      int xc, int sc, int ns, uint64_t row_bytes,
-                                                      uint64_t *__restrict__ mask_out, int32_t *__restrict__ perm,
-                                                      mw_group_desc *__restrict__ desc, mw_send_stats *__restrict__ stats,
-                                                      u32x4 *__restrict__ packed, int32_t *__restrict__ row_src_token,
-                                                      int32_t *__restrict__ row_topk)
+__global__ __launch_bounds__(kSmallPlanLanes) void k_plan_pack(
+    const int32_t *__restrict__ topk, int T, int K, const int32_t *__restrict__ eslot, int E,
+    const u32x4 *__restrict__ x, const u32x4 *__restrict__ scales, int xc, int sc, int ns, uint64_t row_bytes,
+    uint64_t *__restrict__ mask_out, int32_t *__restrict__ perm, mw_group_desc *__restrict__ desc,
+    mw_send_stats *__restrict__ stats, u32x4 *__restrict__ packed, int32_t *__restrict__ row_src_token,
+    int32_t *__restrict__ row_topk)
 {
-    __shared__ uint64_t smask[kFusedMax * W];
-    __shared__ int32_t tok[kFusedMax];
-    __shared__ uint32_t gstart[kFusedMax + 1];
-    __shared__ uint32_t hist[MW_MAX_RANKS];
-    __shared__ uint32_t scratch[18];
-    __shared__ mw_short_key skey[kKeyed ? kFusedMax : 1];
-    const mw_small_plan_lds lds = {smask, tok, gstart, hist, scratch, skey};
-    const int t = threadIdx.x;
-    const mw_small_plan_rank r = mw_small_plan_ranks<W, kKeyed>(topk, T, K, eslot, E, lds);
-
-    const uint32_t i = blockIdx.x;
-    if (i < r.N) {
-        const int32_t tt = tok[i];
-        const int n = xc + sc;
-        for (int ch = t; ch < n; ch += kBlock) {
-            const u32x4 v = (ch < xc) ? mw_ld16(x + (size_t)tt * xc + ch)
-                                      : mw_ld16(scales + (size_t)tt * sc + (ch - xc));
-            mw_st16(packed + (size_t)i * ns + ch, v);
-        }
-        if (t == 0) row_src_token[i] = tt;
-        for (int j = t; j < K; j += kBlock) row_topk[(size_t)i * K + j] = topk[(size_t)tt * K + j];
+    constexpr int kPlanWords = mw_small_plan_words<W, kKeyed>();
+    __shared__ uint64_t lds[kPlanWords];
+    if (blockIdx.x == 0) {
+        mw_small_plan<W, kKeyed>(topk, T, K, eslot, E, row_bytes, mask_out, perm, desc, stats, lds);
+        return;
     }
-    const bool writes_plan = blockIdx.x == 0, writes_stats = blockIdx.x == gridDim.x - 1;
-    if (!writes_plan && !writes_stats) return;
-    mw_small_plan_finish<W>(r, T, row_bytes, mask_out, perm, desc, stats, lds, writes_plan, writes_stats);
+    const int b = (int)blockIdx.x - 1, t = threadIdx.x, n = xc + sc;
+    int32_t *tab = (int32_t *)lds;                                      // [kSmallTab]
+    uint64_t *own = (uint64_t *)(tab + kSmallTab);                      // [MW_MASK_WORDS] token b's bitmap
+    uint32_t *before = (uint32_t *)(own + MW_MASK_WORDS);               // [kSmallPlanLanes / 64]
+    static_assert(kSmallTab / 2 + MW_MASK_WORDS + kSmallPlanLanes / 128 <= kPlanWords, "LDS of a mover");
+    auto chunk = [&](int ch) {
+        return ch < xc ? mw_ld16(x + (size_t)b * xc + ch) : mw_ld16(scales + (size_t)b * sc + (ch - xc));
+    };
+    u32x4 v0 = {0u, 0u, 0u, 0u};
+    if (t < n) v0 = chunk(t);
+    uint64_t m[MW_MASK_WORDS];
+    bool bad = false;
+    small_token_mask(topk, T, K, eslot, E, tab, m, bad);
+    if (t == b)
+#pragma unroll
+        for (int w = 0; w < MW_MASK_WORDS; ++w) own[w] = m[w];
+    mw_lds_barrier();
+    uint64_t mine[W], any = 0;
+#pragma unroll
+    for (int w = 0; w < W; ++w) { mine[w] = own[w]; any |= mine[w]; }
+    if (any == 0) return;                                               // (the whole workgroup) no destination
+    // kept tokens with (bitmap, token) < (mine, b); lanes from T on hold an empty bitmap and are not kept
+    uint64_t mine_any = 0;
+#pragma unroll
+    for (int w = 0; w < W; ++w) mine_any |= m[w];
+    const bool less = mine_any != 0 && (mask_less<W>(m, mine) || (t < b && !mask_less<W>(mine, m)));
+    const uint32_t c = (uint32_t)__popcll(__ballot(less));
+    if ((t & 63) == 0) before[t >> 6] = c;
+    mw_lds_barrier();
+    uint32_t i = 0;
+#pragma unroll
+    for (int w = 0; w < kFusedMax / 64; ++w) i += before[w];            // (tokens live in the first waves)
+    if (t < n) mw_st16(packed + (size_t)i * ns + t, v0);
+    for (int ch = t + kSmallPlanLanes; ch < n; ch += kSmallPlanLanes) mw_st16(packed + (size_t)i * ns + ch, chunk(ch));
+    if (t == 0) row_src_token[i] = b;
+    for (int j = t; j < K; j += kSmallPlanLanes) row_topk[(size_t)i * K + j] = topk[(size_t)b * K + j];
 }
 
 // ---- ordering of large batches: sorted chunks, then ranks by binary search ------------------
@@ -1039,9 +1054,8 @@ int32_t mw_launch_plan_pack(mw_ctx *ctx, const int32_t *topk, int32_t T, const v
                             uint64_t *mask, int32_t *perm, mw_group_desc *desc, mw_send_stats *stats, void *packed,
                             int32_t *row_src_token, int32_t *row_topk, hipStream_t s)
 {
-    static_assert(MW_MAX_RANKS == kBlock, "one lane per rank in the statistics");
     const int xc = (int)(ctx->x_row_bytes / 16), sc = (int)(ctx->s_row_bytes / 16);
-    const dim3 grid(T > 0 ? T : 1), block(kBlock);
+    const dim3 grid(1 + T), block(kSmallPlanLanes);
     const int K = ctx->cfg.top_k, E = ctx->cfg.n_experts;
     const uint64_t rb = (uint64_t)ctx->row_bytes;
     mw_timed tm(ctx, MW_KERNEL_PLAN_PACK, s);

@@ -79,169 +79,237 @@ __device__ __forceinline__ bool mask_less(const uint64_t *a, const uint64_t *b)
     return lt;
 }
 
-// ---- the whole plan of a small batch inside ONE workgroup of MW_FUSED_MAX_TOKENS lanes, one token
-// per lane (Section 5.1, send module: task decomposition): bitmaps, the packed order, groups and
-// statistics without any global scratch or any other workgroup.  Two halves, so that a caller can
-// put work between them that needs only the order (mw_plan_pack moves its row there).
-// LDS of the caller: smask [MW_FUSED_MAX_TOKENS * W] bitmaps, tok [..] token of packed row i,
-// gstart [.. + 1] first packed row of group g, hist [MW_MAX_RANKS], scratch [18] (17 of the scan,
-// one flag word), skey [MW_FUSED_MAX_TOKENS] short keys (kKeyed only).
-struct mw_small_plan_lds {
-    uint64_t *smask; int32_t *tok; uint32_t *gstart; uint32_t *hist; uint32_t *scratch; mw_short_key *skey;
-};
-struct mw_small_plan_rank {
-    uint64_t m[MW_MASK_WORDS];     // this lane's token's bitmap
-    uint32_t p, N;                 // its packed row (if kept), kept tokens
-    bool any;                      // the token has a destination
-};
+// ---- small batches (at most MW_FUSED_MAX_TOKENS tokens), one workgroup of kSmallPlanLanes lanes.
+constexpr int kSmallPlanLanes = 512;
+constexpr int kSmallTab = 1024;        // experts whose ranks the workgroup keeps in LDS
 
-// Bitmaps and the packed order: fills smask and tok; every barrier of the workgroup is inside.
-// kKeyed (bitmaps of more than one word, top_k <= 8): the all-pairs walk compares short keys.
-template <int W, bool kKeyed>
-__device__ __forceinline__ mw_small_plan_rank mw_small_plan_ranks(const int32_t *__restrict__ topk, int T, int K,
-                                                                  const int32_t *__restrict__ eslot, int E,
-                                                                  const mw_small_plan_lds &l)
+// Bitmap of token threadIdx.x (< T; zero for further lanes).  What bounds a small plan is its chain
+// of memory round trips, so the ids and the whole expert table are requested side by side and
+// the lookup goes to LDS (a second trip costs 0.7 us); beyond kSmallTab experts it goes to memory.
+// `tab`: kSmallTab words of LDS.  One barrier of the workgroup inside.
+__device__ __forceinline__ void small_token_mask(const int32_t *__restrict__ topk, int T, int K,
+                                                 const int32_t *__restrict__ eslot, int E, int32_t *tab,
+                                                 uint64_t m[MW_MASK_WORDS], bool &bad)
 {
     const int t = threadIdx.x;
-    const bool slot = t < MW_FUSED_MAX_TOKENS;      // (a wider workgroup's further lanes only take part in scans and barriers)
-    mw_small_plan_rank r;
-    bool bad = false;
+    const int32_t *row = topk + (size_t)t * K;
+    int32_t e[8];
 #pragma unroll
-    for (int w = 0; w < MW_MASK_WORDS; ++w) r.m[w] = 0;
-    if (t < T) token_mask(topk + (size_t)t * K, K, eslot, E, r.m, bad);
-    mw_short_key mk = {0ull, 0u, 0u};
+    for (int u = 0; u < 8; ++u) e[u] = (t < T && u < K) ? row[u] : -1;
+    const bool in_lds = E <= kSmallTab;
+    if (in_lds)
+#pragma unroll
+        for (int j = 0; j < kSmallTab / kSmallPlanLanes; ++j) {
+            const int x = t + j * kSmallPlanLanes;
+            if (x < E) tab[x] = eslot[x];
+        }
+#pragma unroll
+    for (int q = 0; q < MW_MASK_WORDS; ++q) m[q] = 0;
+    mw_lds_barrier();
+    if (t >= T) return;
+    for (int j0 = 0;;) {
+        int32_t s[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const bool ok = (uint32_t)e[u] < (uint32_t)E;
+            bad |= (e[u] != -1 && !ok);
+            s[u] = ok ? (in_lds ? tab[e[u]] : eslot[e[u]]) : -1;
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            if (s[u] < 0) continue;
+            const int r = s[u] >> 16;
+            const uint64_t bit = 1ull << (r & 63);
+            const int w = r >> 6;
+#pragma unroll
+            for (int q = 0; q < MW_MASK_WORDS; ++q) m[q] |= (w == q) ? bit : 0ull;
+        }
+        j0 += 8;
+        if (j0 >= K) break;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) e[u] = (j0 + u < K) ? row[j0 + u] : -1;
+    }
+}
+
+// The whole plan (Section 5.1, send module: task decomposition): bitmaps, the packed order, groups
+// and statistics without any global scratch or any other workgroup.
+// The order is an all-pairs walk with its lanes spread over (token, part of the other tokens): a
+// lane a token alone walked 128 others in 3.6 us (16 LDS round trips), four parts walk 32 each.
+// (mw_plan_pack of 256 tokens 14.7 -> 8.3 us, of 64 tokens of 256 ranks, four words, 17.9 -> 6.1.)
+// LDS of the caller, in 64-bit words: mw_small_plan_words.  kKeyed (bitmaps of more than one word,
+// top_k <= 8): the walk compares short keys.
+template <int W, bool kKeyed>
+constexpr int mw_small_plan_words()
+{
+    return MW_FUSED_MAX_TOKENS * W + (kKeyed ? MW_FUSED_MAX_TOKENS * (int)sizeof(mw_short_key) / 8 : 0) +
+           (MW_FUSED_MAX_TOKENS * 3 + MW_FUSED_MAX_TOKENS + 2 + kSmallTab + 24) / 2;
+}
+
+template <int W, bool kKeyed>
+__device__ __forceinline__ void mw_small_plan(const int32_t *__restrict__ topk, int T, int K,
+                                              const int32_t *__restrict__ eslot, int E, uint64_t row_bytes,
+                                              uint64_t *__restrict__ mask_out, int32_t *__restrict__ perm,
+                                              mw_group_desc *__restrict__ desc, mw_send_stats *__restrict__ stats,
+                                              uint64_t *lds)
+{
+    constexpr int kN = MW_FUSED_MAX_TOKENS;
+    uint64_t *smask = lds;                                          // [kN * W] bitmaps
+    mw_short_key *skey = (mw_short_key *)(smask + kN * W);          // [kN] short keys (kKeyed)
+    int32_t *tok = (int32_t *)(skey + (kKeyed ? kN : 0));           // [kN] token of packed row i
+    uint32_t *pos = (uint32_t *)(tok + kN);                         // [kN] packed row of token t
+    uint32_t *hist = pos + kN;                                      // [MW_MAX_RANKS] rows per destination
+    uint32_t *gstart = hist + kN;                                   // [kN + 1] first packed row of group g
+    int32_t *tab = (int32_t *)(gstart + kN + 2);                    // [kSmallTab]
+    uint32_t *scratch = (uint32_t *)(tab + kSmallTab);              // [17] of the scan, [17] flag word, [18..21] kept tokens
+    static_assert(MW_MAX_RANKS <= kN && kN == 256, "LDS layout");
+
+    const int t = threadIdx.x, lane = t & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const bool slot = t < kN;
+    if (t == 0) scratch[17] = 0;
+    uint64_t m[MW_MASK_WORDS];
+    bool bad = false;
+    small_token_mask(topk, T, K, eslot, E, tab, m, bad);            // (its barrier publishes scratch[17])
+    const bool any = (m[0] | m[1] | m[2] | m[3]) != 0;
+    if (bad) atomicOr(&scratch[17], 1u);
     if (slot) {
 #pragma unroll
-        for (int w = 0; w < W; ++w) l.smask[t * W + w] = r.m[w];
-        if constexpr (kKeyed) { mk = short_key(r.m); l.skey[t] = mk; }
-        l.hist[t] = 0;
+        for (int w = 0; w < W; ++w) smask[t * W + w] = m[w];
+        if constexpr (kKeyed) skey[t] = short_key(m);
+        hist[t] = 0;
+        pos[t] = 0;
+        const uint32_t kept = (uint32_t)__popcll(__ballot(any));
+        if (lane == 0) scratch[18 + wave] = kept;
     }
-    if (t == 0) l.scratch[17] = 0;
-    r.any = (r.m[0] | r.m[1] | r.m[2] | r.m[3]) != 0;
-    mw_block_exscan(r.any ? 1u : 0u, l.scratch, &r.N);          // its barriers also publish smask
-    if (bad) atomicOr(&l.scratch[17], 1u);
+    mw_lds_barrier();
+    const uint32_t N = scratch[18] + scratch[19] + scratch[20] + scratch[21];
 
-    // Packed row of token t = number of kept tokens u with (bitmap, u) < (bitmap, t).  The
+    // Packed row of token v = number of kept tokens u with (bitmap, u) < (bitmap, v).  The
     // walk takes eight tokens at a time -- eight LDS reads in flight, then eight compares --
-    // because a compare is a few cycles and an LDS round trip about a hundred.  Whether u < t
+    // because a compare is a few cycles and an LDS round trip about a hundred.  Whether u < v
     // is the same for the whole wavefront except among its own 64 tokens: "bitmap <= mine"
     // before them, the full test among them, "bitmap < mine" after them.  Slots from T up to
     // the next multiple of eight hold empty bitmaps (their lanes wrote zeros); an empty bitmap is
     // below every kept one: all of them are counted and taken off again.
-    const int T8 = slot ? (T + 7) & ~7 : 0;
-    const int w0 = t & ~63, w1 = w0 + 64;
-    uint32_t c = 0;
-    for (int u0 = 0; u0 < T8; u0 += 8) {
-        bool lt[8], eq[8];
-        if constexpr (kKeyed) {
-            mw_short_key q[8];
+    const int T8 = (T + 7) & ~7;
+    {
+        const int S = T <= 64 ? 64 : T <= 128 ? 128 : kN, parts = kSmallPlanLanes / S;       // tokens of a part's lanes
+        const int v = t & (S - 1), part = __builtin_amdgcn_readfirstlane(t / S);
+        const int per = (T8 / 8 + parts - 1) / parts * 8;
+        const int u_end = min(T8, (part + 1) * per);
+        const int w0 = __builtin_amdgcn_readfirstlane(v & ~63), w1 = w0 + 64;
+        mw_short_key mk = {0ull, 0u, 0u};
+        uint64_t mv[MW_MASK_WORDS] = {0, 0, 0, 0};
+        if constexpr (kKeyed) mk = skey[v];
+        else
 #pragma unroll
-            for (int k = 0; k < 8; ++k) q[k] = l.skey[u0 + k];
+            for (int w = 0; w < W; ++w) mv[w] = smask[v * W + w];
+        uint32_t c = 0;
+        for (int u0 = part * per; u0 < u_end; u0 += 8) {
+            bool lt[8], eq[8];
+            if constexpr (kKeyed) {
+                mw_short_key q[8];
 #pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const bool keq = q[k].key == mk.key;
-                lt[k] = q[k].key < mk.key || (keq && q[k].flag < mk.flag);
-                eq[k] = keq && q[k].flag == mk.flag;
+                for (int k = 0; k < 8; ++k) q[k] = skey[u0 + k];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    const bool keq = q[k].key == mk.key;
+                    lt[k] = q[k].key < mk.key || (keq && q[k].flag < mk.flag);
+                    eq[k] = keq && q[k].flag == mk.flag;
+                }
+            } else {
+                uint64_t q[8][W];
+#pragma unroll
+                for (int k = 0; k < 8; ++k)
+#pragma unroll
+                    for (int w = 0; w < W; ++w) q[k][w] = smask[(u0 + k) * W + w];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    lt[k] = mask_less<W>(q[k], mv);
+                    eq[k] = !lt[k] && !mask_less<W>(mv, q[k]);
+                }
             }
-        } else {
-            uint64_t q[8][W];
+            if (u0 + 8 <= w0) {                         // wave-uniform: all eight before this wave's tokens
 #pragma unroll
-            for (int k = 0; k < 8; ++k)
+                for (int k = 0; k < 8; ++k) c += (lt[k] || eq[k]) ? 1u : 0u;
+            } else if (u0 >= w1) {                      // all eight after them
 #pragma unroll
-                for (int w = 0; w < W; ++w) q[k][w] = l.smask[(u0 + k) * W + w];
+                for (int k = 0; k < 8; ++k) c += lt[k] ? 1u : 0u;
+            } else {
 #pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                lt[k] = mask_less<W>(q[k], r.m);
-                eq[k] = !lt[k] && !mask_less<W>(r.m, q[k]);
+                for (int k = 0; k < 8; ++k) c += (lt[k] || (eq[k] && u0 + k < v)) ? 1u : 0u;
             }
         }
-        if (u0 + 8 <= w0) {                         // wave-uniform: all eight before this wave's tokens
+        if (c) atomicAdd(&pos[v], c);
+        // rows per destination: a wavefront ballot of bit b over 64 tokens, popcounted, is the
+        // number of those tokens that name rank 64 q + b.  A wave counts an eighth of the bits over
+        // all tokens (one wave's tokens over all bits, as before, took 1.3 us a word)
+        constexpr int kBits = 64 / (kSmallPlanLanes / 64);
 #pragma unroll
-            for (int k = 0; k < 8; ++k) c += (lt[k] || eq[k]) ? 1u : 0u;
-        } else if (u0 >= w1) {                      // all eight after them
+        for (int q = 0; q < W; ++q) {
+            uint32_t mine = 0;
+            for (int u0 = 0; u0 < T; u0 += 64) {
+                const uint64_t x = smask[(u0 + lane) * W + q] >> (wave * kBits);
 #pragma unroll
-            for (int k = 0; k < 8; ++k) c += lt[k] ? 1u : 0u;
-        } else {
-#pragma unroll
-            for (int k = 0; k < 8; ++k) c += (lt[k] || (eq[k] && u0 + k < t)) ? 1u : 0u;
+                for (int b = 0; b < kBits; ++b) {
+                    const uint32_t n_b = (uint32_t)__popcll(__ballot(((uint32_t)x >> b) & 1u));
+                    mine += lane == b ? n_b : 0u;
+                }
+            }
+            if (lane < kBits) hist[q * 64 + wave * kBits + lane] = mine;
         }
     }
-    r.p = c - ((uint32_t)T8 - r.N);
-    if (r.any) l.tok[r.p] = t;                      // (any: t < T <= MW_FUSED_MAX_TOKENS)
     mw_lds_barrier();
-    return r;
-}
+    const uint32_t p = slot ? pos[t] - ((uint32_t)T8 - N) : 0u;
+    if (any) tok[p] = t;                                // (any: t < T <= kN)
+    mw_lds_barrier();
 
-// Groups, descriptors, bitmaps and perm (writes_plan) and the statistics (writes_stats).
-template <int W>
-__device__ __forceinline__ void mw_small_plan_finish(const mw_small_plan_rank &r, int T, uint64_t row_bytes,
-                                                     uint64_t *__restrict__ mask_out, int32_t *__restrict__ perm,
-                                                     mw_group_desc *__restrict__ desc, mw_send_stats *__restrict__ stats,
-                                                     const mw_small_plan_lds &l, bool writes_plan, bool writes_stats)
-{
-    const int t = threadIdx.x, lane = t & 63;
-    const uint32_t N = r.N;
     // groups: lane i looks at packed row i; a group starts where the bitmap differs from the
     // row before
     bool start = false;
+    uint64_t mi[W];
     if ((uint32_t)t < N) {
-        const uint64_t *q = l.smask + l.tok[t] * W;
-        start = t == 0 || mask_less<W>(l.smask + l.tok[t - 1] * W, q);
+        const uint64_t *q = smask + tok[t] * W, *qb = smask + tok[t > 0 ? t - 1 : 0] * W;
+        bool diff = t == 0;
+#pragma unroll
+        for (int w = 0; w < W; ++w) { mi[w] = q[w]; diff |= mi[w] != qb[w]; }
+        start = diff;
     }
     uint32_t G;
-    const uint32_t g = mw_block_exscan(start ? 1u : 0u, l.scratch, &G);
-    if (writes_plan) {
-        if (start) l.gstart[g] = (uint32_t)t;
-        if (t == 0) l.gstart[G] = N;
-        if (t < T) {
-            uint64_t *o = mask_out + (size_t)t * MW_MASK_WORDS;
+    const uint32_t g = mw_block_exscan(start ? 1u : 0u, scratch, &G);
+    if (start) gstart[g] = (uint32_t)t;
+    if (t == 0) gstart[G] = N;
+    if (t < T) {
+        uint64_t *o = mask_out + (size_t)t * MW_MASK_WORDS;
 #pragma unroll
-            for (int q = 0; q < MW_MASK_WORDS; ++q) o[q] = r.m[q];
-        }
-        if (r.any) perm[r.p] = t;
-        mw_lds_barrier();
-        if (start) {
-            const uint64_t *q = l.smask + l.tok[t] * W;
-            mw_group_desc d;
-            uint32_t nd = 0;
-#pragma unroll
-            for (int w = 0; w < MW_MASK_WORDS; ++w) {
-                d.mask[w] = (w < W) ? q[w < W ? w : 0] : 0ull;
-                nd += (uint32_t)__popcll(d.mask[w]);
-            }
-            d.row_offset = (uint32_t)t;
-            d.row_count = l.gstart[g + 1] - (uint32_t)t;
-            d.n_dest = nd;
-            d.reserved0 = 0;
-            desc[g] = d;
-        }
+        for (int q = 0; q < MW_MASK_WORDS; ++q) o[q] = m[q];
     }
-    if (writes_stats) {
-        // rows per destination: a wavefront ballot of bit b over 64 tokens, popcounted, is the
-        // number of those tokens that name rank 64 q + b; lane b keeps it
+    if (any) perm[p] = t;
+    const uint32_t h = t < MW_MAX_RANKS ? hist[t] : 0u;
+    if (t < MW_MAX_RANKS) stats->rows_per_dest[t] = h;
+    uint32_t D;
+    mw_block_exscan(h, scratch, &D);                    // (its barriers publish gstart)
+    if (start) {
+        mw_group_desc d;
+        uint32_t nd = 0;
 #pragma unroll
-        for (int q = 0; q < W; ++q) {
-            if (__ballot(r.m[q] != 0) == 0) continue;      // wave-uniform
-            uint32_t mine = 0;
-            for (int b = 0; b < 64; ++b) {
-                const uint32_t n_b = (uint32_t)__popcll(__ballot((r.m[q] >> b) & 1ull));
-                if (lane == b) mine = n_b;
-            }
-            if (mine) atomicAdd(&l.hist[q * 64 + lane], mine);
+        for (int w = 0; w < MW_MASK_WORDS; ++w) {
+            d.mask[w] = (w < W) ? mi[w < W ? w : 0] : 0ull;
+            nd += (uint32_t)__popcll(d.mask[w]);
         }
-        mw_lds_barrier();
-        const uint32_t h = t < MW_MAX_RANKS ? l.hist[t] : 0u;
-        if (t < MW_MAX_RANKS) stats->rows_per_dest[t] = h;
-        uint32_t D;
-        mw_block_exscan(h, l.scratch, &D);
-        if (t == 0) {
-            stats->n_rows = N;
-            stats->n_groups = G;
-            stats->multicast_bytes = (uint64_t)N * row_bytes;
-            stats->unicast_bytes = (uint64_t)D * row_bytes;
-            stats->error_flags = l.scratch[17] ? MW_FLAG_BAD_EXPERT : 0u;
-            stats->reserved0 = 0;
-        }
+        d.row_offset = (uint32_t)t;
+        d.row_count = gstart[g + 1] - (uint32_t)t;
+        d.n_dest = nd;
+        d.reserved0 = 0;
+        desc[g] = d;
+    }
+    if (t == 0) {
+        stats->n_rows = N;
+        stats->n_groups = G;
+        stats->multicast_bytes = (uint64_t)N * row_bytes;
+        stats->unicast_bytes = (uint64_t)D * row_bytes;
+        stats->error_flags = scratch[17] ? MW_FLAG_BAD_EXPERT : 0u;
+        stats->reserved0 = 0;
     }
 }
 

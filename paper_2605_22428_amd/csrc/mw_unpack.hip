@@ -548,14 +548,15 @@ __global__ __launch_bounds__(kIndexBlock) void k_recv_index(const mw_index_args 
 // Same outputs and flags as recv_index_body + mw_finish_counts (records, not packets; no
 // de-duplication); cnt and addr_cnt, which only those two exchange, are not written.
 // LDS words: see mw_small_index_lds_words.  P <= blockDim.x.
-constexpr int kSmallBlock = MW_FUSED_MAX_TOKENS;      // token slots of the one-workgroup plan
-constexpr int kSmallLanes = 512;                      // lanes of the small launches' workgroups (index: one or two rows a lane up to 1024 rows)
+constexpr int kSmallPeers = 256;                      // peers of the one-workgroup index (their records are scanned by four waves)
+constexpr int kSmallIndexLds = 40960;                 // LDS bytes of the one-workgroup index
+constexpr int kSmallLanes = kSmallPlanLanes;          // lanes of the small launches' workgroups (index: one or two rows a lane up to 1024 rows)
 
-static inline size_t mw_small_index_lds_words(int P, int L, uint32_t wpl, uint32_t max_tokens, uint32_t cap_rows)
+static inline size_t mw_small_index_lds_words(int P, int L, int tab, uint32_t wpl, uint32_t max_tokens, uint32_t cap_rows)
 {
     const uint64_t m_max = (uint64_t)P * max_tokens < cap_rows ? (uint64_t)P * max_tokens : cap_rows;
     const size_t wa = (size_t)((m_max + 31) / 32), n_w = (size_t)L * (size_t)P * wpl;
-    return 10 * (size_t)P + 3 * ((size_t)P + 1) + wa + 2 * n_w + 1 + 24;
+    return 10 * (size_t)P + 3 * ((size_t)P + 1) + wa + 2 * n_w + 1 + 24 + (size_t)tab;
 }
 
 // kSmallRows: rows (and descriptors) a lane keeps in registers; further ones go through memory.
@@ -575,10 +576,19 @@ __device__ __forceinline__ void recv_index_small(const mw_index_args &a, uint32_
     uint32_t *bits = addr + wa;                         // [n_w]    (expert, peer, source token) in output order
     uint32_t *pre = bits + n_w;                         // [n_w + 1] running popcount in front of each word
     uint32_t *scratch = pre + n_w + 1;                  // [17] scan scratch, [17] flags, [18] addressed rows
+    int32_t *tab = (int32_t *)(scratch + 24);           // [tab_words] the experts' ranks and slots, if there is room
+    const bool in_lds = a.tab_words != 0;
     const mw_recv_peer *peers = (const mw_recv_peer *)a.peers;
     uint32_t err = 0;
 
-    // ---- round trip 1: the records
+    // ---- round trip 1: the records, and beside them the expert table (the ids' lookup was a third
+    // round trip: 64 peers x 7 rows 9.5 -> 8.6 us, 8 x 86 11.0 -> 8.2, 8 x 3 7.1 -> 5.9)
+    int32_t tab_r[kSmallTab / kSmallLanes];
+#pragma unroll
+    for (int j = 0; j < kSmallTab / kSmallLanes; ++j) {
+        const uint32_t e = tid + (uint32_t)j * nthr;
+        tab_r[j] = in_lds && e < E ? a.eslot[e] : -1;
+    }
     uint32_t nq = 0, dq = 0;
     if (tid < P) {
         const mw_recv_peer pr = peers[tid];
@@ -590,10 +600,18 @@ __device__ __forceinline__ void recv_index_small(const mw_index_args &a, uint32_
     for (uint32_t w = tid; w < wa; w += nthr) addr[w] = 0;
     for (uint32_t w = tid; w < n_w; w += nthr) bits[w] = 0;
     if (tid < 2) scratch[17 + tid] = 0;
-    uint32_t tot;
-    const uint32_t before = mw_block_exscan(nq, scratch, &tot);
-    const uint32_t dbefore = mw_block_exscan(dq, scratch, &tot);
+    // exclusive scans over the peers: at most four waves hold one
+    const uint32_t n_inc = mw_wave_incl_scan(nq), d_inc = mw_wave_incl_scan(dq);
+    if ((tid & 63u) == 63u && tid < kSmallPeers) { scratch[tid >> 6] = n_inc; scratch[4 + (tid >> 6)] = d_inc; }
+#pragma unroll
+    for (int j = 0; j < kSmallTab / kSmallLanes; ++j) {
+        const uint32_t e = tid + (uint32_t)j * nthr;
+        if (in_lds && e < E) tab[e] = tab_r[j];
+    }
+    mw_lds_barrier();
     if (tid < P) {
+        uint32_t before = n_inc - nq, dbefore = d_inc - dq;
+        for (uint32_t w = 0; w < (tid >> 6); ++w) { before += scratch[w]; dbefore += scratch[4 + w]; }
         if (before + nq > cap_rows) err |= MW_FLAG_RECV_CAPACITY;
         const uint32_t rb = min(before, cap_rows), nr = min(before + nq, cap_rows) - rb;
         rbase[tid] = rb; nrow[tid] = nr; dbase[tid] = dbefore;
@@ -665,7 +683,7 @@ __device__ __forceinline__ void recv_index_small(const mw_index_args &a, uint32_
         for (int u = 0; u < 8; ++u) {
             const bool ok = (uint32_t)e_r[j][u] < E;
             bad_r[j] |= (e_r[j][u] != -1 && !ok);
-            t_r[j][u] = ok ? a.eslot[e_r[j][u]] : -1;
+            t_r[j][u] = ok ? (in_lds ? tab[e_r[j][u]] : a.eslot[e_r[j][u]]) : -1;
         }
     }
     // addressed rows: the row ranges of the groups whose bitmap has this rank's bit
@@ -729,7 +747,7 @@ __device__ __forceinline__ void recv_index_small(const mw_index_args &a, uint32_
                 for (int u = 0; u < 8; ++u) {
                     const bool ok = (uint32_t)e8[u] < E;
                     if (e8[u] != -1 && !ok) err |= MW_FLAG_BAD_EXPERT;
-                    t8[u] = ok ? a.eslot[e8[u]] : -1;
+                    t8[u] = ok ? (in_lds ? tab[e8[u]] : a.eslot[e8[u]]) : -1;
                 }
             }
 #pragma unroll
@@ -791,7 +809,7 @@ __device__ __forceinline__ void recv_index_small(const mw_index_args &a, uint32_
         const uint32_t w0 = min(n_w, tid * per), w1 = min(n_w, w0 + per);
         uint32_t sum = 0;
         for (uint32_t w = w0; w < w1; ++w) sum += __popc(bits[w]);
-        uint32_t run = mw_block_exscan(sum, scratch, &tot);
+        uint32_t tot, run = mw_block_exscan(sum, scratch, &tot);
         for (uint32_t w = w0; w < w1; ++w) { pre[w] = run; run += __popc(bits[w]); }
         if (tid == 0) pre[n_w] = tot;
     }
@@ -995,7 +1013,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
 // dispatch experiment, 64 and 128 tokens a rank): what k_expand_index_plan_next does, with the
 // riders in their one-workgroup forms -- grid row 0 indexes the next received batch
 // (recv_index_small), row 1, if there is a plan to make, plans the next batch to send
-// (mw_small_plan_ranks / mw_small_plan_finish, the plan of mw_plan_pack) -- then the packer's rows
+// (mw_small_plan, the plan of mw_plan_pack) -- then the packer's rows
 // and the expander's.  At these sizes the step is the riders' chain of memory round trips, and the
 // forms that spread a batch over workgroups spend half of theirs on talking to one another.
 template <int W, bool kKeyed, int kRows>
@@ -1025,16 +1043,8 @@ __global__ __launch_bounds__(kSmallLanes) void k_small_step(
         recv_index_small<kRows>(next, (uint32_t *)small_lds);
         return;
     }
-    // LDS of the plan: bitmaps, short keys, then the 32-bit arrays
-    uint64_t *smask = small_lds;
-    mw_short_key *skey = (mw_short_key *)(smask + kSmallBlock * W);
-    int32_t *tok = (int32_t *)(skey + (kKeyed ? kSmallBlock : 0));
-    uint32_t *gstart = (uint32_t *)(tok + kSmallBlock);
-    uint32_t *hist = gstart + kSmallBlock + 1;
-    uint32_t *scratch = hist + MW_MAX_RANKS;
-    const mw_small_plan_lds l = {smask, tok, gstart, hist, scratch, skey};
-    const mw_small_plan_rank r = mw_small_plan_ranks<W, kKeyed>(plan.topk, plan.T, plan.K, plan.eslot, plan.E, l);
-    mw_small_plan_finish<W>(r, plan.T, plan.row_bytes, plan.mask_out, plan.perm, plan.desc, plan.stats, l, true, true);
+    mw_small_plan<W, kKeyed>(plan.topk, plan.T, plan.K, plan.eslot, plan.E, plan.row_bytes, plan.mask_out, plan.perm,
+                             plan.desc, plan.stats, small_lds);
 }
 
 // The one-workgroup index as a launch of its own (mw_unpack_index, mw_unpack of a small batch).
@@ -1232,13 +1242,23 @@ static bool plan_rides(const mw_ctx *next, double mover_us, int32_t T, bool keye
 // the index of `P` peers' regions on `ctx` fits the one-workgroup form
 static bool small_index_fits(const mw_ctx *ctx, int32_t P)
 {
-    static_assert(kSmallBlock == MW_MAX_RANKS, "one lane per peer record, one lane per rank in the statistics");
     if (ctx->options & MW_OPT_RECV_DEDUP) return false;
-    if (P > kSmallBlock || ctx->n_local > 64) return false;
+    if (P > kSmallPeers || ctx->n_local > 64) return false;
     if ((int64_t)P * ctx->cfg.max_tokens > 16384) return false;
     const uint32_t wpl = ((uint32_t)ctx->cfg.max_tokens + 31u) / 32u;
-    return mw_small_index_lds_words(P, ctx->n_local, wpl, (uint32_t)ctx->cfg.max_tokens,
-                                    (uint32_t)ctx->cfg.max_recv_rows) * 4 <= 40960;
+    return mw_small_index_lds_words(P, ctx->n_local, 0, wpl, (uint32_t)ctx->cfg.max_tokens,
+                                    (uint32_t)ctx->cfg.max_recv_rows) * 4 <= kSmallIndexLds;
+}
+
+// LDS bytes of the one-workgroup index; a->tab_words: with the expert table where it has room
+static size_t small_index_lds(const mw_ctx *ctx, int32_t P, mw_index_args *a)
+{
+    const uint32_t wpl = ((uint32_t)ctx->cfg.max_tokens + 31u) / 32u;
+    const size_t words = mw_small_index_lds_words(P, ctx->n_local, 0, wpl, (uint32_t)ctx->cfg.max_tokens,
+                                                  (uint32_t)ctx->cfg.max_recv_rows);
+    const int E = ctx->cfg.n_experts;
+    a->tab_words = E <= kSmallTab && 4 * (words + (size_t)E) <= kSmallIndexLds ? (uint32_t)E : 0;
+    return 4 * (words + a->tab_words) + 16;
 }
 
 // rows a lane of the one-workgroup index keeps in registers: two for up to 1024 received rows (as many
@@ -1273,9 +1293,7 @@ int32_t mw_launch_unpack_index(mw_ctx *ctx, const void *peers, bool packets, int
         if (!packets && expected <= kSmallLanes && small_index_fits(ctx, P)) {
             // a row a lane at most: one workgroup for all peers, nothing to exchange between workgroups
             // (9.6 against 10.9 us at 443 rows; with two rows a lane the workgroup-per-peer form is ahead)
-            const uint32_t wpl = ((uint32_t)ctx->cfg.max_tokens + 31u) / 32u;
-            const size_t lds = 4 * mw_small_index_lds_words(P, ctx->n_local, wpl, (uint32_t)ctx->cfg.max_tokens,
-                                                            (uint32_t)ctx->cfg.max_recv_rows) + 16;
+            const size_t lds = small_index_lds(ctx, P, &a);
             if (small_index_few_rows(ctx, P)) hipLaunchKernelGGL(k_recv_index_small<2>, dim3(1), dim3(kSmallLanes), lds, s, a);
             else hipLaunchKernelGGL(k_recv_index_small<4>, dim3(1), dim3(kSmallLanes), lds, s, a);
         } else
@@ -1361,13 +1379,14 @@ static int32_t launch_small_step(mw_ctx *ctx, int32_t P, void *out_rows, float *
         pa.packed = (u32x4 *)pk->packed; pa.row_src_token = pk->row_src_token; pa.row_topk = pk->row_topk;
         n_pack_rows = (uint32_t)pk->n_tokens;
     }
-    const uint32_t wpl = ((uint32_t)next->cfg.max_tokens + 31u) / 32u;
-    const size_t lds_index = 4 * mw_small_index_lds_words(a.P, next->n_local, wpl, (uint32_t)next->cfg.max_tokens,
-                                                          (uint32_t)next->cfg.max_recv_rows);
-    const int Wk = keyed ? 4 : W;
-    const size_t lds_plan = (size_t)kSmallBlock * Wk * 8 + (keyed ? (size_t)kSmallBlock * sizeof(mw_short_key) : 0) +
-                            4 * ((size_t)kSmallBlock + kSmallBlock + 1 + MW_MAX_RANKS + 18);
-    const size_t lds = (with_plan && lds_plan > lds_index ? lds_plan : lds_index) + 16;
+    mw_index_args ai = a;
+    const size_t lds_index = small_index_lds(next, a.P, &ai);
+    const size_t lds_plan = 8 * (size_t)(keyed    ? mw_small_plan_words<4, true>()
+                                         : W == 1 ? mw_small_plan_words<1, false>()
+                                         : W == 2 ? mw_small_plan_words<2, false>()
+                                         : W == 3 ? mw_small_plan_words<3, false>()
+                                                  : mw_small_plan_words<4, false>());
+    const size_t lds = with_plan && lds_plan > lds_index ? lds_plan : lds_index;
     const uint32_t riders = with_plan ? 2u : 1u;
     const dim3 grid(nseg, riders + n_pack_rows + gy), block(kSmallLanes);
     const uint32_t cap32 = (uint32_t)(cap < 0x7fffffffLL ? cap : 0x7fffffffLL);
@@ -1377,7 +1396,7 @@ static int32_t launch_small_step(mw_ctx *ctx, int32_t P, void *out_rows, float *
 #define MW_SMALL_(W_, KEYED_, ROWS_)                                                                                   \
     hipLaunchKernelGGL((k_small_step<W_, KEYED_, ROWS_>), grid, block, lds, s, riders, riders + n_pack_rows, ctx->d_recs, \
                        ctx->d_row_base, P, xc, pa.perm, pa.stats, sc, ctx->hit_slots, ctx->d_base, ctx->d_hits,         \
-                       (u32x4 *)out_rows, (u32x4 *)out_scales, cap32, out_src_peer, out_src_token, a, pl, pa)
+                       (u32x4 *)out_rows, (u32x4 *)out_scales, cap32, out_src_peer, out_src_token, ai, pl, pa)
 #define MW_SMALL(W_, KEYED_) do { if (few) MW_SMALL_(W_, KEYED_, 2); else MW_SMALL_(W_, KEYED_, 4); } while (0)
         if (keyed) MW_SMALL(4, true);
         else if (W == 1) MW_SMALL(1, false);
