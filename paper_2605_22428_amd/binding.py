@@ -8,6 +8,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+from types import SimpleNamespace
 from typing import List, Optional, Sequence
 
 import numpy as np
@@ -123,6 +124,52 @@ def load():
     return _lib
 
 
+# Argument types of the calls of the path: p pointer, i int32, l int64.  With them ctypes converts addresses
+# by itself; an object made per pointer and a torch.cuda.Stream made per call were half of a small
+# call's time on the host (mw_plan_pack 8.6 us a call, now 5.8; mw_unpack 10.8, now 8.3).
+_SIGNATURES = {
+    "mw_plan": "ppippppp",
+    "mw_pack": "ppppppipppp",
+    "mw_pack_quantize": "pppppipppp",
+    "mw_plan_pack": "ppppipppppppp",
+    "mw_pack_packets": "pppppppipp",
+    "mw_unpack_packets": "ppipplppppp",
+    "mw_plan_allgather": "plppp",
+    "mw_pack_allgather": "pplpp",
+    "mw_plan_allgather_split": "pllppp",
+    "mw_unpack_allgather_split": "pppllpp",
+    "mw_unpack": "ppipplppppp",
+    "mw_unpack_index": "ppilppp",
+    "mw_unpack_expand": "pipplppp",
+    "mw_combine_gather": "piplplp",
+    "mw_unpack_allgather": "pplpp",
+    "mw_allgather_step": "pplpppppp",
+    "mw_relay": "ppplpp",
+    "mw_relay_index": "ppplpp",
+    "mw_relay_copy": "ppppp",
+    "mw_relay_copy_index_next": "ppppppplpp",
+    "mw_relay_packets": "ppplpp",
+    "mw_relay_packets_index": "pplpp",
+    "mw_relay_packets_copy": "ppppp",
+    "mw_relay_packets_copy_index_next": "pppppplpp",
+    "mw_stream_step": "ppppp",
+}
+_native_fns = None
+
+
+def _native():
+    """The path's functions with their argument types set; load()'s own stay without."""
+    global _native_fns
+    if _native_fns is None:
+        lib, kinds, fns = load(), {"p": C.c_void_p, "i": C.c_int32, "l": C.c_int64}, SimpleNamespace()
+        for name, sig in _SIGNATURES.items():
+            f = lib[name]                     # a function object of its own
+            f.argtypes, f.restype = [kinds[k] for k in sig], C.c_int32
+            setattr(fns, name, f)
+        _native_fns = fns
+    return _native_fns
+
+
 def status_string(status: int) -> str:
     return load().mw_status_string(C.c_int32(status)).decode()
 
@@ -136,8 +183,17 @@ def _ptr(t: Optional[torch.Tensor]) -> C.c_void_p:
     return C.c_void_p(0 if t is None else t.data_ptr())
 
 
+def _addr(t: Optional[torch.Tensor]) -> int:
+    return 0 if t is None else t.data_ptr()
+
+
+def _stream_handle() -> int:
+    """Raw handle of the current device's current stream (no torch.cuda.Stream object is made)."""
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+
+
 def _stream() -> C.c_void_p:
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return C.c_void_p(_stream_handle())
 
 
 def mw_copy_bytes(dst: torch.Tensor, src: torch.Tensor, n_bytes: int):
@@ -164,10 +220,6 @@ def mw_plan_static(n_ranks: int, n_experts: int, top_k: int, hidden: int, row_fo
     cfg = MwConfig(n_ranks, n_experts, top_k, 0, hidden, row_format, row_bytes, 0, 0, 0, 0, 0)
     _check(load().mw_plan_static(C.byref(cfg), _ptr(expert_to_rank), _ptr(topk_ids), C.c_int32(topk_ids.shape[0]),
                                  _ptr(mask), _ptr(perm), _ptr(desc), _ptr(stats), _stream()), "mw_plan_static")
-
-
-def _addr(t: Optional[torch.Tensor]) -> int:
-    return 0 if t is None else t.data_ptr()
 
 
 def send_batch(x, scales, topk_ids, perm, stats, packed, row_src_token, row_topk) -> MwSendBatch:
@@ -252,82 +304,85 @@ class Context:
     def mw_plan(self, topk_ids: torch.Tensor, mask: torch.Tensor, perm: torch.Tensor,
                 desc: torch.Tensor, stats: torch.Tensor):
         n_tokens = topk_ids.shape[0]
-        _check(load().mw_plan(self._h, _ptr(topk_ids), C.c_int32(n_tokens), _ptr(mask), _ptr(perm),
-                              _ptr(desc), _ptr(stats), _stream()), "mw_plan")
+        _check(_native().mw_plan(self._h, _addr(topk_ids), C.c_int32(n_tokens), _addr(mask), _addr(perm), _addr(desc),
+                                 _addr(stats), _stream_handle()), "mw_plan")
 
     def mw_pack(self, x: torch.Tensor, scales: Optional[torch.Tensor], topk_ids: torch.Tensor,
                 perm: torch.Tensor, stats: torch.Tensor, packed: torch.Tensor,
                 row_src_token: torch.Tensor, row_topk: torch.Tensor):
         n_tokens = topk_ids.shape[0]
-        _check(load().mw_pack(self._h, _ptr(x), _ptr(scales), _ptr(topk_ids), _ptr(perm), _ptr(stats),
-                              C.c_int32(n_tokens), _ptr(packed), _ptr(row_src_token), _ptr(row_topk),
-                              _stream()), "mw_pack")
+        _check(_native().mw_pack(self._h, _addr(x), _addr(scales), _addr(topk_ids), _addr(perm), _addr(stats),
+                                 C.c_int32(n_tokens), _addr(packed), _addr(row_src_token), _addr(row_topk),
+                                 _stream_handle()), "mw_pack")
 
     def mw_pack_quantize(self, x_bf16: torch.Tensor, topk_ids: torch.Tensor, perm: torch.Tensor,
                          stats: torch.Tensor, packed: torch.Tensor, row_src_token: torch.Tensor,
                          row_topk: torch.Tensor):
         n_tokens = topk_ids.shape[0]
-        _check(load().mw_pack_quantize(self._h, _ptr(x_bf16), _ptr(topk_ids), _ptr(perm), _ptr(stats),
-                                       C.c_int32(n_tokens), _ptr(packed), _ptr(row_src_token), _ptr(row_topk),
-                                       _stream()), "mw_pack_quantize")
+        _check(_native().mw_pack_quantize(self._h, _addr(x_bf16), _addr(topk_ids), _addr(perm), _addr(stats),
+                                          C.c_int32(n_tokens), _addr(packed), _addr(row_src_token), _addr(row_topk),
+                                          _stream_handle()), "mw_pack_quantize")
 
     def mw_plan_pack(self, topk_ids: torch.Tensor, x: torch.Tensor, scales: Optional[torch.Tensor],
                      mask: torch.Tensor, perm: torch.Tensor, desc: torch.Tensor, stats: torch.Tensor,
                      packed: torch.Tensor, row_src_token: torch.Tensor, row_topk: torch.Tensor):
         n_tokens = topk_ids.shape[0]
-        _check(load().mw_plan_pack(self._h, _ptr(topk_ids), _ptr(x), _ptr(scales), C.c_int32(n_tokens), _ptr(mask),
-                                   _ptr(perm), _ptr(desc), _ptr(stats), _ptr(packed), _ptr(row_src_token),
-                                   _ptr(row_topk), _stream()), "mw_plan_pack")
+        _check(_native().mw_plan_pack(self._h, _addr(topk_ids), _addr(x), _addr(scales), C.c_int32(n_tokens),
+                                      _addr(mask), _addr(perm), _addr(desc), _addr(stats), _addr(packed),
+                                      _addr(row_src_token), _addr(row_topk), _stream_handle()), "mw_plan_pack")
 
     def mw_pack_packets(self, x: torch.Tensor, scales: Optional[torch.Tensor], topk_ids: torch.Tensor,
                         mask: torch.Tensor, perm: torch.Tensor, stats: torch.Tensor, packets: torch.Tensor):
         n_tokens = topk_ids.shape[0]
-        _check(load().mw_pack_packets(self._h, _ptr(x), _ptr(scales), _ptr(topk_ids), _ptr(mask), _ptr(perm),
-                                      _ptr(stats), C.c_int32(n_tokens), _ptr(packets), _stream()), "mw_pack_packets")
+        _check(_native().mw_pack_packets(self._h, _addr(x), _addr(scales), _addr(topk_ids), _addr(mask), _addr(perm),
+                                         _addr(stats), C.c_int32(n_tokens), _addr(packets), _stream_handle()),
+               "mw_pack_packets")
 
     def mw_unpack_packets(self, peers: torch.Tensor, n_peers: int, out_rows: torch.Tensor,
                           out_scales: Optional[torch.Tensor], out_capacity_rows: int, out_src_peer: torch.Tensor,
                           out_src_token: torch.Tensor, expert_offsets: torch.Tensor, recv_stats: torch.Tensor):
-        _check(load().mw_unpack_packets(self._h, _ptr(peers), C.c_int32(n_peers), _ptr(out_rows), _ptr(out_scales),
-                                        C.c_int64(out_capacity_rows), _ptr(out_src_peer), _ptr(out_src_token),
-                                        _ptr(expert_offsets), _ptr(recv_stats), _stream()), "mw_unpack_packets")
+        _check(_native().mw_unpack_packets(self._h, _addr(peers), C.c_int32(n_peers), _addr(out_rows),
+                                           _addr(out_scales), C.c_int64(out_capacity_rows), _addr(out_src_peer),
+                                           _addr(out_src_token), _addr(expert_offsets), _addr(recv_stats),
+                                           _stream_handle()), "mw_unpack_packets")
 
     def mw_plan_allgather(self, shard_bytes: int, desc: torch.Tensor, stats: torch.Tensor):
-        _check(load().mw_plan_allgather(self._h, C.c_int64(shard_bytes), _ptr(desc), _ptr(stats),
-                                        _stream()), "mw_plan_allgather")
+        _check(_native().mw_plan_allgather(self._h, C.c_int64(shard_bytes), _addr(desc), _addr(stats),
+                                           _stream_handle()), "mw_plan_allgather")
 
     def mw_pack_allgather(self, shard: torch.Tensor, shard_bytes: int, send_buf: torch.Tensor):
-        _check(load().mw_pack_allgather(self._h, _ptr(shard), C.c_int64(shard_bytes), _ptr(send_buf),
-                                        _stream()), "mw_pack_allgather")
+        _check(_native().mw_pack_allgather(self._h, _addr(shard), C.c_int64(shard_bytes), _addr(send_buf),
+                                           _stream_handle()), "mw_pack_allgather")
 
     def mw_plan_allgather_split(self, shard_bytes: int, direct_bytes: int, desc: torch.Tensor, stats: torch.Tensor):
-        _check(load().mw_plan_allgather_split(self._h, C.c_int64(shard_bytes), C.c_int64(direct_bytes), _ptr(desc),
-                                              _ptr(stats), _stream()), "mw_plan_allgather_split")
+        _check(_native().mw_plan_allgather_split(self._h, C.c_int64(shard_bytes), C.c_int64(direct_bytes),
+                                                 _addr(desc), _addr(stats), _stream_handle()),
+               "mw_plan_allgather_split")
 
     def mw_unpack_allgather_split(self, direct: torch.Tensor, relayed: torch.Tensor, shard_bytes: int,
                                   direct_bytes: int, out: torch.Tensor):
-        _check(load().mw_unpack_allgather_split(self._h, _ptr(direct), _ptr(relayed), C.c_int64(shard_bytes),
-                                                C.c_int64(direct_bytes), _ptr(out), _stream()),
+        _check(_native().mw_unpack_allgather_split(self._h, _addr(direct), _addr(relayed), C.c_int64(shard_bytes),
+                                                   C.c_int64(direct_bytes), _addr(out), _stream_handle()),
                "mw_unpack_allgather_split")
 
     # ---- receive side --------------------------------------------------------------------
     def mw_unpack(self, peers: torch.Tensor, n_peers: int, out_rows: torch.Tensor,
                   out_scales: Optional[torch.Tensor], out_capacity_rows: int, out_src_peer: torch.Tensor,
                   out_src_token: torch.Tensor, expert_offsets: torch.Tensor, recv_stats: torch.Tensor):
-        _check(load().mw_unpack(self._h, _ptr(peers), C.c_int32(n_peers), _ptr(out_rows), _ptr(out_scales),
-                                C.c_int64(out_capacity_rows), _ptr(out_src_peer), _ptr(out_src_token),
-                                _ptr(expert_offsets), _ptr(recv_stats), _stream()), "mw_unpack")
+        _check(_native().mw_unpack(self._h, _addr(peers), C.c_int32(n_peers), _addr(out_rows), _addr(out_scales),
+                                   C.c_int64(out_capacity_rows), _addr(out_src_peer), _addr(out_src_token),
+                                   _addr(expert_offsets), _addr(recv_stats), _stream_handle()), "mw_unpack")
 
     def mw_unpack_index(self, peers: torch.Tensor, n_peers: int, out_capacity_rows: int,
                         expert_offsets: torch.Tensor, recv_stats: torch.Tensor):
-        _check(load().mw_unpack_index(self._h, _ptr(peers), C.c_int32(n_peers), C.c_int64(out_capacity_rows),
-                                      _ptr(expert_offsets), _ptr(recv_stats), _stream()), "mw_unpack_index")
+        _check(_native().mw_unpack_index(self._h, _addr(peers), C.c_int32(n_peers), C.c_int64(out_capacity_rows),
+                                         _addr(expert_offsets), _addr(recv_stats), _stream_handle()), "mw_unpack_index")
 
     def mw_unpack_expand(self, n_peers: int, out_rows: torch.Tensor, out_scales: Optional[torch.Tensor],
                          out_capacity_rows: int, out_src_peer: torch.Tensor, out_src_token: torch.Tensor):
-        _check(load().mw_unpack_expand(self._h, C.c_int32(n_peers), _ptr(out_rows), _ptr(out_scales),
-                                       C.c_int64(out_capacity_rows), _ptr(out_src_peer), _ptr(out_src_token),
-                                       _stream()), "mw_unpack_expand")
+        _check(_native().mw_unpack_expand(self._h, C.c_int32(n_peers), _addr(out_rows), _addr(out_scales),
+                                          C.c_int64(out_capacity_rows), _addr(out_src_peer), _addr(out_src_token),
+                                          _stream_handle()), "mw_unpack_expand")
 
     def mw_unpack_expand_index_next(self, n_peers: int, out_rows: torch.Tensor, out_scales: Optional[torch.Tensor],
                                     out_capacity_rows: int, out_src_peer: torch.Tensor, out_src_token: torch.Tensor,
@@ -366,7 +421,7 @@ class Context:
         recv = recv_batch(n_peers, out_rows, out_scales, out_capacity_rows, out_src_peer, out_src_token)
         nxt = next_batch(next_ctx, next_peers, next_n_peers, next_out_capacity_rows, next_expert_offsets,
                          next_recv_stats, next_topk_ids, next_mask, next_perm, next_desc, next_send_stats)
-        _check(load().mw_stream_step(self._h, C.byref(send), C.byref(recv), C.byref(nxt), _stream()),
+        _check(_native().mw_stream_step(self._h, C.byref(send), C.byref(recv), C.byref(nxt), _stream_handle()),
                "mw_stream_step")
 
     def mw_stream_step_records(self, send: MwSendBatch, recv: MwRecvBatch, nxt: MwNextBatch,
@@ -374,8 +429,8 @@ class Context:
         """mw_stream_step on records the caller built once (send_batch, recv_batch, next_batch) and keeps,
         together with the tensors they point to: a loop over the same buffers then marshals nothing.
         stream_handle: a stream's raw handle (torch.cuda.Stream.cuda_stream); default: the current stream."""
-        st = _stream() if stream_handle is None else C.c_void_p(stream_handle)
-        _check(load().mw_stream_step(self._h, C.byref(send), C.byref(recv), C.byref(nxt), st), "mw_stream_step")
+        st = _stream_handle() if stream_handle is None else C.c_void_p(stream_handle)
+        _check(_native().mw_stream_step(self._h, C.byref(send), C.byref(recv), C.byref(nxt), st), "mw_stream_step")
 
     def mw_ctx_set_options(self, options: int):
         _check(load().mw_ctx_set_options(self._h, C.c_uint32(options)), "mw_ctx_set_options")
@@ -385,17 +440,19 @@ class Context:
 
     def mw_combine_gather(self, n_peers: int, y: torch.Tensor, out_capacity_rows: int, ret_rows: torch.Tensor,
                           ret_capacity_rows: int):
-        _check(load().mw_combine_gather(self._h, C.c_int32(n_peers), _ptr(y), C.c_int64(out_capacity_rows),
-                                        _ptr(ret_rows), C.c_int64(ret_capacity_rows), _stream()), "mw_combine_gather")
+        _check(_native().mw_combine_gather(self._h, C.c_int32(n_peers), _addr(y), C.c_int64(out_capacity_rows),
+                                           _addr(ret_rows), C.c_int64(ret_capacity_rows), _stream_handle()),
+               "mw_combine_gather")
 
     def mw_unpack_allgather(self, peer_shards: torch.Tensor, shard_bytes: int, out: torch.Tensor):
-        _check(load().mw_unpack_allgather(self._h, _ptr(peer_shards), C.c_int64(shard_bytes), _ptr(out),
-                                          _stream()), "mw_unpack_allgather")
+        _check(_native().mw_unpack_allgather(self._h, _addr(peer_shards), C.c_int64(shard_bytes), _addr(out),
+                                             _stream_handle()), "mw_unpack_allgather")
 
     def mw_allgather_step(self, shard: torch.Tensor, shard_bytes: int, send_buf: torch.Tensor, desc: torch.Tensor,
                           stats: torch.Tensor, peer_shards: torch.Tensor, out: torch.Tensor):
-        _check(load().mw_allgather_step(self._h, _ptr(shard), C.c_int64(shard_bytes), _ptr(send_buf), _ptr(desc),
-                                        _ptr(stats), _ptr(peer_shards), _ptr(out), _stream()), "mw_allgather_step")
+        _check(_native().mw_allgather_step(self._h, _addr(shard), C.c_int64(shard_bytes), _addr(send_buf),
+                                           _addr(desc), _addr(stats), _addr(peer_shards), _addr(out),
+                                           _stream_handle()), "mw_allgather_step")
 
     # ---- relay ---------------------------------------------------------------------------
     def mw_set_forwarding(self, next_hop: np.ndarray, n_hops: int):
@@ -404,46 +461,46 @@ class Context:
 
     def mw_relay(self, in_record: torch.Tensor, children: torch.Tensor, child_capacity_rows: int,
                  stats: torch.Tensor):
-        _check(load().mw_relay(self._h, _ptr(in_record), _ptr(children), C.c_int64(child_capacity_rows),
-                               _ptr(stats), _stream()), "mw_relay")
+        _check(_native().mw_relay(self._h, _addr(in_record), _addr(children), C.c_int64(child_capacity_rows),
+                                  _addr(stats), _stream_handle()), "mw_relay")
 
     def mw_relay_index(self, in_record: torch.Tensor, children: torch.Tensor, child_capacity_rows: int,
                        stats: torch.Tensor):
-        _check(load().mw_relay_index(self._h, _ptr(in_record), _ptr(children), C.c_int64(child_capacity_rows),
-                                     _ptr(stats), _stream()), "mw_relay_index")
+        _check(_native().mw_relay_index(self._h, _addr(in_record), _addr(children), C.c_int64(child_capacity_rows),
+                                        _addr(stats), _stream_handle()), "mw_relay_index")
 
     def mw_relay_copy(self, in_record: torch.Tensor, children: torch.Tensor, stats: torch.Tensor):
-        _check(load().mw_relay_copy(self._h, _ptr(in_record), _ptr(children), _ptr(stats), _stream()),
+        _check(_native().mw_relay_copy(self._h, _addr(in_record), _addr(children), _addr(stats), _stream_handle()),
                "mw_relay_copy")
 
     def mw_relay_copy_index_next(self, in_record: torch.Tensor, children: torch.Tensor, stats: torch.Tensor,
                                  next_ctx: "Context", next_in_record: torch.Tensor, next_children: torch.Tensor,
                                  next_child_capacity_rows: int, next_stats: torch.Tensor):
-        _check(load().mw_relay_copy_index_next(self._h, _ptr(in_record), _ptr(children), _ptr(stats), next_ctx._h,
-                                               _ptr(next_in_record), _ptr(next_children),
-                                               C.c_int64(next_child_capacity_rows), _ptr(next_stats), _stream()),
-               "mw_relay_copy_index_next")
+        _check(_native().mw_relay_copy_index_next(self._h, _addr(in_record), _addr(children), _addr(stats),
+                                                  next_ctx._h, _addr(next_in_record), _addr(next_children),
+                                                  C.c_int64(next_child_capacity_rows), _addr(next_stats),
+                                                  _stream_handle()), "mw_relay_copy_index_next")
 
     def mw_relay_packets(self, in_record: torch.Tensor, children: torch.Tensor, child_capacity_rows: int,
                          stats: torch.Tensor):
-        _check(load().mw_relay_packets(self._h, _ptr(in_record), _ptr(children), C.c_int64(child_capacity_rows),
-                                       _ptr(stats), _stream()), "mw_relay_packets")
+        _check(_native().mw_relay_packets(self._h, _addr(in_record), _addr(children), C.c_int64(child_capacity_rows),
+                                          _addr(stats), _stream_handle()), "mw_relay_packets")
 
     def mw_relay_packets_index(self, in_record: torch.Tensor, child_capacity_rows: int, stats: torch.Tensor):
-        _check(load().mw_relay_packets_index(self._h, _ptr(in_record), C.c_int64(child_capacity_rows), _ptr(stats),
-                                             _stream()), "mw_relay_packets_index")
+        _check(_native().mw_relay_packets_index(self._h, _addr(in_record), C.c_int64(child_capacity_rows),
+                                                _addr(stats), _stream_handle()), "mw_relay_packets_index")
 
     def mw_relay_packets_copy(self, in_record: torch.Tensor, children: torch.Tensor, stats: torch.Tensor):
-        _check(load().mw_relay_packets_copy(self._h, _ptr(in_record), _ptr(children), _ptr(stats), _stream()),
-               "mw_relay_packets_copy")
+        _check(_native().mw_relay_packets_copy(self._h, _addr(in_record), _addr(children), _addr(stats),
+                                               _stream_handle()), "mw_relay_packets_copy")
 
     def mw_relay_packets_copy_index_next(self, in_record: torch.Tensor, children: torch.Tensor, stats: torch.Tensor,
                                          next_ctx: "Context", next_in_record: torch.Tensor,
                                          next_child_capacity_rows: int, next_stats: torch.Tensor):
-        _check(load().mw_relay_packets_copy_index_next(self._h, _ptr(in_record), _ptr(children), _ptr(stats),
-                                                       next_ctx._h, _ptr(next_in_record),
-                                                       C.c_int64(next_child_capacity_rows), _ptr(next_stats),
-                                                       _stream()), "mw_relay_packets_copy_index_next")
+        _check(_native().mw_relay_packets_copy_index_next(self._h, _addr(in_record), _addr(children), _addr(stats),
+                                                          next_ctx._h, _addr(next_in_record),
+                                                          C.c_int64(next_child_capacity_rows), _addr(next_stats),
+                                                          _stream_handle()), "mw_relay_packets_copy_index_next")
 
     def mw_get_relay_stats(self, stats: torch.Tensor) -> np.ndarray:
         host = np.zeros(1, dtype=RELAY_STATS_DTYPE)
