@@ -720,7 +720,8 @@ __device__ __forceinline__ void recv_index_small(const mw_index_args &a, uint32_
 
     // ---- per row: its distinct local experts in top-k order (duplicate ids count once; at most 64
     // local experts here, so "seen before" is one bit test); one bit per (expert, peer, source token).
-    // Slot k of the row's hit slots receives expert k; the first eight also stay in `les`, a byte each.
+    // The first eight stay in `les`, a byte each; slot k of the row's hit slots receives expert k here if it is a later
+    // one or the row is not cached, else with its rank.
     // `cached`: the row's token and the rank-table entries of its first eight ids are in registers.
     auto parse_mark = [&](uint32_t r, uint32_t q, uint32_t i, uint32_t s, bool cached, const int32_t (&tc)[8], bool badc,
                           mw_row_rec &rec, uint64_t &les) {
@@ -750,32 +751,27 @@ __device__ __forceinline__ void recv_index_small(const mw_index_args &a, uint32_
                     t8[u] = ok ? (in_lds ? tab[e8[u]] : a.eslot[e8[u]]) : -1;
                 }
             }
+            // the local ones as a bit set that is walked (most rows have one or two), their slots a byte each
+            // (L <= 64); a walk over all eight ids: 64 peers x 7 rows 8.6 -> 8.3 us, 256 x 1 8.9 -> 8.2
+            uint32_t local = 0;
+            uint64_t slots = 0;
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
-                if (t8[u] < 0 || (uint32_t)(t8[u] >> 16) != my_rank) continue;
-                const uint32_t le = (uint32_t)t8[u] & 63u;             // (L <= 64)
+                local |= (uint32_t)t8[u] >> 16 == my_rank ? 1u << u : 0u;       // (-1: no rank)
+                slots |= (uint64_t)((uint32_t)t8[u] & 63u) << (8 * u);
+            }
+            while (local) {
+                const uint32_t u = (uint32_t)__ffs((int)local) - 1u;
+                local &= local - 1u;
+                const uint32_t le = (uint32_t)(slots >> (8u * u)) & 63u;
                 if ((seen >> le) & 1ull) continue;
                 seen |= 1ull << le;
                 if (nk < 8) les |= (uint64_t)le << (8 * nk);
-                h[nk++] = mw_hit{(int32_t)le, 0};
+                if (!cached || nk >= 8) h[nk] = mw_hit{(int32_t)le, 0};
+                ++nk;
+                if ((atomicOr(&bits[(le * P + q) * wpl + (s >> 5)], 1u << (s & 31u)) >> (s & 31u)) & 1u)
+                    err |= MW_FLAG_DUP_SRC_TOKEN;
             }
-        }
-        // the row's bits: every atomic issued before the first result is looked at
-        {
-            uint32_t was[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                was[k] = 0;
-                if (k < nk) {
-                    const uint32_t le = (uint32_t)(les >> (8 * k)) & 0xffu;
-                    was[k] = atomicOr(&bits[(le * P + q) * wpl + (s >> 5)], 1u << (s & 31u));
-                }
-            }
-            uint32_t any_was = 0;
-#pragma unroll
-            for (int k = 0; k < 8; ++k) any_was |= was[k];
-            for (int k = 8; k < nk; ++k) any_was |= atomicOr(&bits[((uint32_t)h[k].le * P + q) * wpl + (s >> 5)], 1u << (s & 31u));
-            if ((any_was >> (s & 31u)) & 1u) err |= MW_FLAG_DUP_SRC_TOKEN;
         }
         if (nk == 0) err |= MW_FLAG_NO_LOCAL_EXPERT;
         rec.src = (const char *)pr.rows + (size_t)i * a.row_bytes;
@@ -834,7 +830,9 @@ __device__ __forceinline__ void recv_index_small(const mw_index_args &a, uint32_
         for (int k = 0; k < nk; ++k) {
             const int le = k < 8 ? (int)((les_r[j] >> (8 * k)) & 0xffu) : h[k].le;
             const int32_t rk = rank_of(q_r[j], s_r[j], le);
-            if (k == 0) rec_r[j].rank0 = rk; else h[k].rank = rk;
+            if (k == 0) rec_r[j].rank0 = rk;
+            else if (k < 8) h[k] = mw_hit{le, rk};
+            else h[k].rank = rk;
         }
         a.recs[r] = rec_r[j];
     }
@@ -1261,12 +1259,13 @@ static size_t small_index_lds(const mw_ctx *ctx, int32_t P, mw_index_args *a)
     return 4 * (words + a->tab_words) + 16;
 }
 
-// rows a lane of the one-workgroup index keeps in registers: two for up to 1024 received rows (as many
-// as the context saw last time, if the caller has asked for the statistics), else four
-static bool small_index_few_rows(const mw_ctx *ctx, int32_t P)
+// rows a lane of the one-workgroup index keeps in registers: one, two or four, for as many received rows
+// as the context saw last time, if the caller has asked for the statistics, else for all there can be.  (448
+// rows: with two 8.3 us, with one 7.6.)  More rows than that go through memory.
+static int small_index_rows(const mw_ctx *ctx, int32_t P)
 {
-    return ctx->recv_rows_hint > 0 ? ctx->recv_rows_hint <= 2 * kSmallLanes
-                                   : (int64_t)P * ctx->cfg.max_tokens <= 2 * kSmallLanes;
+    const int64_t rows = ctx->recv_rows_hint > 0 ? ctx->recv_rows_hint : (int64_t)P * ctx->cfg.max_tokens;
+    return rows <= kSmallLanes ? 1 : rows <= 2 * kSmallLanes ? 2 : 4;
 }
 
 int32_t mw_launch_unpack_index(mw_ctx *ctx, const void *peers, bool packets, int32_t P, int64_t cap,
@@ -1294,8 +1293,11 @@ int32_t mw_launch_unpack_index(mw_ctx *ctx, const void *peers, bool packets, int
             // a row a lane at most: one workgroup for all peers, nothing to exchange between workgroups
             // (9.6 against 10.9 us at 443 rows; with two rows a lane the workgroup-per-peer form is ahead)
             const size_t lds = small_index_lds(ctx, P, &a);
-            if (small_index_few_rows(ctx, P)) hipLaunchKernelGGL(k_recv_index_small<2>, dim3(1), dim3(kSmallLanes), lds, s, a);
-            else hipLaunchKernelGGL(k_recv_index_small<4>, dim3(1), dim3(kSmallLanes), lds, s, a);
+            auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(1), dim3(kSmallLanes), lds, s, a); };
+            const int rows = small_index_rows(ctx, P);
+            if (rows == 1) launch(k_recv_index_small<1>);
+            else if (rows == 2) launch(k_recv_index_small<2>);
+            else launch(k_recv_index_small<4>);
         } else
         {
 #define MW_INDEX(GENERAL_, ROWS_)                                                                                              \
@@ -1392,12 +1394,17 @@ static int32_t launch_small_step(mw_ctx *ctx, int32_t P, void *out_rows, float *
     const uint32_t cap32 = (uint32_t)(cap < 0x7fffffffLL ? cap : 0x7fffffffLL);
     {
         mw_timed tm(ctx, MW_KERNEL_EXPAND, s);
-        const bool few = small_index_few_rows(next, a.P);
+        const int rows = small_index_rows(next, a.P);
 #define MW_SMALL_(W_, KEYED_, ROWS_)                                                                                   \
     hipLaunchKernelGGL((k_small_step<W_, KEYED_, ROWS_>), grid, block, lds, s, riders, riders + n_pack_rows, ctx->d_recs, \
                        ctx->d_row_base, P, xc, pa.perm, pa.stats, sc, ctx->hit_slots, ctx->d_base, ctx->d_hits,         \
                        (u32x4 *)out_rows, (u32x4 *)out_scales, cap32, out_src_peer, out_src_token, ai, pl, pa)
-#define MW_SMALL(W_, KEYED_) do { if (few) MW_SMALL_(W_, KEYED_, 2); else MW_SMALL_(W_, KEYED_, 4); } while (0)
+#define MW_SMALL(W_, KEYED_)                                                                                           \
+    do {                                                                                                               \
+        if (rows == 1) MW_SMALL_(W_, KEYED_, 1);                                                                       \
+        else if (rows == 2) MW_SMALL_(W_, KEYED_, 2);                                                                  \
+        else MW_SMALL_(W_, KEYED_, 4);                                                                                 \
+    } while (0)
         if (keyed) MW_SMALL(4, true);
         else if (W == 1) MW_SMALL(1, false);
         else if (W == 2) MW_SMALL(2, false);
