@@ -176,18 +176,21 @@ __device__ __forceinline__ uint32_t relay_index_hop(
 
 // What the accounting workgroups of one index found, added up in the workspace; the one that reports last
 // writes the statistics (publication rules in mw_internal.h) and leaves the sums zero.  `groups`, `rows` and
-// `dests`: this lane's.
-__device__ __forceinline__ void relay_account_finish(uint32_t groups, uint32_t rows, uint32_t dests, uint32_t chunks,
+// `dests`: this lane's.  Rows times destinations need 64 bits: a descriptor is checked against the one in front of it
+// only, so in a damaged table any number of valid ranges may cover the same rows (a sound one stays below 2^25).  A lane
+// takes at most 1024 groups of 2^24, so its 20 low bits and the rest are summed over at most 1024 lanes in 32 bits each.
+__device__ __forceinline__ void relay_account_finish(uint32_t groups, uint32_t rows, unsigned long long dests, uint32_t chunks,
                                                      uint64_t row_bytes, mw_relay_acc *acc, mw_relay_stats *__restrict__ stats,
                                                      uint32_t *scratch)
 {
     groups = relay_block_sum(groups, scratch);
     rows = relay_block_sum(rows, scratch);
-    dests = relay_block_sum(dests, scratch);
+    const uint32_t dests_lo = relay_block_sum((uint32_t)dests & 0xfffffu, scratch);
+    const uint32_t dests_hi = relay_block_sum((uint32_t)(dests >> 20), scratch);
     if (threadIdx.x == 0) {
         __hip_atomic_fetch_add(&acc->groups, groups, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __hip_atomic_fetch_add(&acc->rows, (unsigned long long)rows, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_fetch_add(&acc->dest_rows, (unsigned long long)dests, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_fetch_add(&acc->dest_rows, dests_lo + ((unsigned long long)dests_hi << 20), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     mw_publish_barrier();
     if (threadIdx.x != 0 || mw_report(&acc->done) != chunks - 1u) return;
@@ -229,7 +232,8 @@ __device__ __forceinline__ void relay_index_body(const mw_relay_index_args &a, c
         // the array held: the copy kernel checks every entry against the descriptors.
         const uint32_t per = ((G + chunks - 1) / chunks + bs - 1) / bs * bs;
         const uint32_t g_first = min(G, c * per), g_end = min(G, g_first + per);
-        uint32_t groups = 0, rows = 0, dests = 0;
+        uint32_t groups = 0, rows = 0;
+        unsigned long long dests = 0;
         for (uint32_t g0 = g_first; g0 < g_end; g0 += bs) {
             const uint32_t g = g0 + tid, gl = min(g, g_end - 1u);
             const mw_group_desc *d = src.desc + gl;
@@ -250,7 +254,7 @@ __device__ __forceinline__ void relay_index_body(const mw_relay_index_args &a, c
                     if (m[w] & ~ok) err |= MW_FLAG_BAD_RANK;
                     nd += (uint32_t)__popcll(m[w] & ok);
                 }
-                ++groups; rows += cnt; dests += cnt * nd;
+                ++groups; rows += cnt; dests += (unsigned long long)cnt * nd;
                 if (cnt <= kLongGroup) for (uint32_t r = 0; r < cnt; ++r) a.group_of_row[off + r] = (int32_t)g;
             }
             uint64_t longs = __ballot(valid && cnt > kLongGroup);

@@ -505,3 +505,36 @@ def test_index_over_several_workgroups_a_hop(R, n_hops, T, cap_rows):
             w = ref.relay_packets_child(pk, hop, n_hops, h)[0][:cap_rows]
             assert int(st["rows_per_hop"][h]) == len(w)
             H.assert_same_bytes(H.host(o[h])[: len(w)], w, "packets of hop %d" % h)
+
+
+@pytest.mark.parametrize("R,n_hops,pairs", [(256, 3, 300), (256, 64, 1100), (64, 1, 30000)])
+def test_accounting_of_a_damaged_table_over_several_chunks(R, n_hops, pairs):
+    """A range that covers the whole buffer again and again, an empty descriptor in front of each: every full range starts
+    at or after the end of the empty one before it, so all of them count, and rows times destinations pass 2^32 inside one
+    workgroup.  No child has room for a whole range: nothing is copied, and the statistics say so exactly."""
+    T, hidden = 65536, 8
+    e2r = np.arange(R, dtype=np.int32)
+    hop = (np.arange(R) % n_hops).astype(np.int32)
+    desc = np.zeros(2 * pairs, dtype=B.DESC_DTYPE)
+    desc["mask"][:, : R // 64] = np.uint64(0xffffffffffffffff)
+    desc["n_dest"] = R
+    desc["row_count"][1::2] = T                                   # (0, 0), (0, T), (0, 0), (0, T), ...
+    rec = dict(desc=H.dev(desc.view(np.uint8)), rows=torch.zeros((T, 2 * hidden), dtype=torch.uint8, device=H.DEV),
+               row_src_token=torch.arange(T, dtype=torch.int32, device=H.DEV),
+               row_topk=torch.zeros((T, 1), dtype=torch.int32, device=H.DEV), n_desc=2 * pairs, n_rows=T)
+    table = B.peers_table([rec], H.DEV)
+    ctxs = [B.Context(R, R, 1, 0, hidden, B.MW_ROW_BF16, T, 1, e2r, device=H.DEV, max_hops=n_hops) for _ in range(2)]
+    kids = [B.RelayChildren(c, n_hops, 16) for c in ctxs]
+    for c in ctxs:
+        c.mw_set_forwarding(hop, n_hops)
+    ctxs[0].mw_relay_index(table, kids[0].table, 16, kids[0].stats)
+    ctxs[0].mw_relay_copy_index_next(table, kids[0].table, kids[0].stats, ctxs[1], table, kids[1].table, 16, kids[1].stats)
+    ctxs[1].mw_relay_copy(table, kids[1].table, kids[1].stats)
+    assert pairs * T * R > 1 << 32
+    for c, k in zip(ctxs, kids):
+        st = c.mw_get_relay_stats(k.stats)
+        assert int(st["error_flags"]) == B.MW_FLAG_BAD_DESC | B.MW_FLAG_OUT_CAPACITY
+        assert (int(st["n_groups_in"]), int(st["n_rows_in"])) == (pairs, pairs * T)
+        assert int(st["unicast_bytes"]) == pairs * T * R * 2 * hidden
+        assert int(st["forward_bytes"]) == 0 and not np.asarray(st["rows_per_hop"]).any() and not np.asarray(st["groups_per_hop"]).any()
+        c.close()
