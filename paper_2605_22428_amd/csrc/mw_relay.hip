@@ -400,8 +400,10 @@ struct mw_relay_packets_index_args {
 };
 
 // Positions of the packets of chunk c that next hop h keeps: what the hop keeps of the chunks before is counted
-// first, four headers a lane in flight, then a packet a lane (as relay_index_hop).  Of a header: the NW
-// bitmap words that can name a rank and the id count.
+// first, several headers a lane in flight, then a packet a lane (as relay_index_hop).  Of a header: the NW
+// bitmap words that can name a rank and the id count.  Four headers of four words took the riding form to 64 vector
+// registers and scratch, which its movers paid for: 4096 packets of 14464 bytes over 15 hops 59.1 us a step, with
+// one 56.2 (38 registers).
 template <int NW>
 __device__ __forceinline__ uint32_t relay_packets_index_hop(
     const char *__restrict__ packets, const uint64_t packet_bytes, const uint32_t n_rows, const uint32_t K, const int h,
@@ -432,14 +434,15 @@ __device__ __forceinline__ uint32_t relay_packets_index_hop(
     uint32_t nid = 0;
     if (first < end) load(min(first + tid, end - 1u), m, nid);
     uint32_t carry = 0;
-    for (uint32_t i0 = 0; i0 < first; i0 += 4u * bs) {
-        uint64_t mm[4][NW];
-        uint32_t nn[4];
+    constexpr int kFly = NW == 1 ? 4 : NW == 2 ? 3 : 1;
+    for (uint32_t i0 = 0; i0 < first; i0 += (uint32_t)kFly * bs) {
+        uint64_t mm[kFly][NW];
+        uint32_t nn[kFly];
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
+        for (int k = 0; k < kFly; ++k)
             if (i0 + (uint32_t)k * bs < first) load(min(i0 + (uint32_t)k * bs + tid, first - 1u), mm[k], nn[k]);
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
+        for (int k = 0; k < kFly; ++k)
             if (i0 + (uint32_t)k * bs + tid < first && kept(mm[k], nn[k])) ++carry;
     }
     if (first > 0) carry = relay_block_sum(carry, scratch);
@@ -608,16 +611,19 @@ static uint32_t relay_index_rows(const mw_ctx *next, uint32_t chunks, int nseg)
 }
 
 // Whether the next buffer's index rides in a copy of `ctx` with `bs`-lane workgroups or gets a launch of its own
-// in front.  A riding workgroup takes about 1.6 us for four groups a lane of those it counts and for every group a lane
-// it places, and narrow workgroups have few lanes; the copy takes at least its rows once in and, say,
-// twice out at 6 TB/s; a launch of its own about 10 us.  (16384 rows of 2048 bytes, 128 lanes: riding 64.5 us a step,
+// in front.  A riding workgroup takes about 1.6 us for four groups a lane of those it counts (the last
+// chunk's: all in front of it) and for every group a lane it places, and narrow workgroups have few lanes; the copy takes at
+// least its rows once in and, say, twice out at 6 TB/s; a launch of its own about 10 us.  (16384 rows of 2048 bytes, 128 lanes: riding 64.5 us a step,
 // apart 48.8; 4096 rows of 14336 bytes, 320 lanes: 55.9 and 60.5.)
+static double relay_rider_us(const mw_ctx *next, int bs, uint32_t chunks)
+{
+    const double groups = (double)next->cfg.max_tokens;
+    return 1.6 * ((chunks > 1 ? groups / (4.0 * bs) : 0.0) + groups / ((double)chunks * bs));
+}
+static double relay_copy_us(const mw_ctx *ctx, int64_t row_bytes) { return 3.0 * (double)ctx->cfg.max_tokens * (double)row_bytes / 6e6; }
 static bool relay_index_rides(const mw_ctx *ctx, const mw_ctx *next, int bs, int64_t row_bytes)
 {
-    const double groups = (double)next->cfg.max_tokens, chunks = (double)relay_chunks(next, bs);
-    const double rider_us = 1.6 * (groups / (4.0 * bs) + groups / (chunks * bs));
-    const double copy_us = 3.0 * (double)ctx->cfg.max_tokens * (double)row_bytes / 6e6;
-    return rider_us < copy_us + 10.0;
+    return relay_rider_us(next, bs, relay_chunks(next, bs)) < relay_copy_us(ctx, row_bytes) + 10.0;
 }
 
 static mw_relay_index_args relay_index_args(mw_ctx *ctx, const mw_recv_peer *in, const mw_relay_child *children,
@@ -786,9 +792,12 @@ int32_t mw_launch_relay_packets_copy(mw_ctx *ctx, const mw_recv_packets *in, voi
         } else {
             mw_relay_packets_index_args a = relay_packets_index_args(next, next_in, next_cap, next_stats, shape.bs);
             // A chunk reads the header, a cache line, of every packet in front of it: thirteen chunks are seven times
-            // the headers, which the copy pays for (4096 packets, 15 hops: 61.7 us a step, one chunk 58.8).  So
-            // one chunk as long as the copy hides it.
-            if (1.6 * (double)next->cfg.max_tokens / shape.bs < 3.0 * (double)c.max_tokens * (double)pb / 6e6) a.chunks = 1;
+            // the headers, which the copy pays for.  So as few chunks as the copy hides.  (us a step with 1, 3, 13 chunks: 4096
+            // packets of 14464 bytes, 15 hops 56.2, 56.8, 60.1; 256 ranks, 39 hops 55.9, 58.0, 65.0; 4224 bytes,
+            // 23 hops 31.5, 31.3, 34.5.)
+            const double copy_us = relay_copy_us(ctx, (int64_t)pb);
+            for (uint32_t n = 1; n < a.chunks; ++n)
+                if (relay_rider_us(next, shape.bs, n) < copy_us + 10.0) a.chunks = n;
             const uint32_t riders = relay_index_rows(next, a.chunks, shape.nseg);
             hipLaunchKernelGGL(k_relay_packets_copy_index_next, dim3(shape.nseg, gy + riders), dim3(shape.bs), 0, s, riders, 0u, in, children, ctx->n_hops, n_chunks, (uint32_t)c.max_tokens, pb,
                                ctx->d_hop_bits, ctx->d_child_pos, ctx->d_relay_flags, stats, keep, a);
