@@ -626,6 +626,18 @@ static bool relay_index_rides(const mw_ctx *ctx, const mw_ctx *next, int bs, int
     return relay_rider_us(next, bs, relay_chunks(next, bs)) < relay_copy_us(ctx, row_bytes) + 10.0;
 }
 
+// Chunks a hop of an index that rides beside copies of `copy_us`: as few as they hide, since every chunk of every hop reads
+// the descriptors in front of it again (a rider takes about 5 us before its first group).  4096 rows of 14336 bytes, us a
+// buffer with 1, 3, 13 chunks: 15 hops 55.0, 55.1, 55.4, 39 hops of 256 ranks 54.3, 54.5, 56.1, two buffers a
+// launch 54.2, 55.5, 58.0; 8192 rows of 4096 bytes, two buffers a launch, with 1, 3, 16 chunks 36.3, 31.2, 39.5.
+static uint32_t relay_riding_chunks(const mw_ctx *next, int bs, double copy_us)
+{
+    const uint32_t most = relay_chunks(next, bs);
+    uint32_t n = 1;
+    while (n < most && 5.0 + relay_rider_us(next, bs, n) >= copy_us) ++n;
+    return n;
+}
+
 static mw_relay_index_args relay_index_args(mw_ctx *ctx, const mw_recv_peer *in, const mw_relay_child *children,
                                             int64_t cap, mw_relay_stats *stats, int bs)
 {
@@ -679,7 +691,8 @@ int32_t mw_launch_relay_copy(mw_ctx *ctx, const mw_recv_peer *in, const mw_relay
                                c.top_k, n_chunks, (int)(ctx->row_stride / 16), (uint32_t)c.max_tokens,
                                (uint64_t)ctx->row_bytes, ctx->d_group_of_row, ctx->d_child_pos, ctx->d_relay_flags, stats);
         } else {
-            const mw_relay_index_args a = relay_index_args(next, next_in, next_children, next_cap, next_stats, shape.bs);
+            mw_relay_index_args a = relay_index_args(next, next_in, next_children, next_cap, next_stats, shape.bs);
+            a.chunks = relay_riding_chunks(next, shape.bs, relay_copy_us(ctx, ctx->row_bytes));
             const uint32_t riders = relay_index_rows(next, a.chunks, shape.nseg);
             hipLaunchKernelGGL(k_relay_copy_index_next, dim3(shape.nseg, gy + riders), dim3(shape.bs), 0, s, riders, 0u, in, children, ctx->n_hops, c.top_k, n_chunks,
                                (int)(ctx->row_stride / 16), (uint32_t)c.max_tokens, (uint64_t)ctx->row_bytes,
@@ -713,6 +726,7 @@ int32_t mw_launch_relay_batch(const mw_relay_job *copy, int32_t n_copy, const mw
         if (k < n_index) {
             b.index[k] = relay_index_args(index[k].ctx, index[k].in_dev, index[k].children_dev,
                                           index[k].child_capacity_rows, index[k].stats_dev, shape.bs);
+            b.index[k].chunks = relay_riding_chunks(index[k].ctx, shape.bs, n_copy * relay_copy_us(ctx, ctx->row_bytes));
             first += relay_index_rows(index[k].ctx, b.index[k].chunks, shape.nseg);
         }
     }
