@@ -1316,14 +1316,30 @@ int32_t mw_launch_unpack_index(mw_ctx *ctx, const void *peers, bool packets, int
     return MW_OK;
 }
 
-// Grid rows of the expander: about as many as the peers will hold, not the capacity -- workgroups are
+// Grid rows of the expander and of the combine: about as many as the peers will hold, not the capacity -- workgroups are
 // dispatched at a finite rate, empty ones included (16 ranks, 1000 tokens, capacity 16000 rows, 6750 there: mw_plan,
 // mw_pack and mw_unpack 34.3 us for the capacity, 32.0 for the rows).  More rows than that are reached by striding.
+// Where nobody has said how many there are, at least what fills every CU's wave slots, and no second filling of a few
+// workgroups: a rank that the routing favours gets many times its share.  (256 ranks, one
+// expert each, 64 tokens, all 16384 of them here, us for a grid of the expected 129 rows / one filling / two / the capacity:
+// mw_unpack of 14336-byte rows 150 / 86 / 86 / 81, of 4096-byte 116 / 33 / 33 / 33, of 1024-byte 67 / 18 / 19 / 21; 32000 fp8
+// rows where 1089 grid rows were expected, 1.06 fillings, 107 / - / 90 / 92.)  What is left: 114688 rows where 4036 were
+// expected stride 27 times, 620 us against 569 for 32768 grid rows, the combine 605 against 511; evenly spread batches are
+// several times faster than with the capacity (64 ranks, 512 tokens: 134 us and 27).
 static uint32_t expand_grid_rows(const mw_ctx *ctx, int32_t P)
 {
     int64_t rows = expected_rows(ctx, P);
     rows += rows / 64 + 64;
+    if (ctx->recv_rows_hint == 0) {
+        const mw_row_shape shape = mw_row_shape_of((int)(ctx->row_bytes / 16));
+        const int64_t filling = (int64_t)ctx->n_cu * 2048 / ((int64_t)shape.bs * shape.nseg);
+        if (rows < filling) rows = filling;
+        else if (rows < 2 * filling) rows = 2 * filling;
+        const int64_t most = (int64_t)P * ctx->cfg.max_tokens;
+        if (rows > most) rows = most;
+    }
     if (rows > ctx->cfg.max_recv_rows) rows = ctx->cfg.max_recv_rows;
+    if (rows < 1) rows = 1;
     return (uint32_t)(rows < kRowGridMax ? rows : kRowGridMax);
 }
 
