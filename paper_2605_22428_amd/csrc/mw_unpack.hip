@@ -102,6 +102,7 @@ struct mw_index_args {
     uint32_t parts;     // workgroups per peer: part j takes the expert chunks j, j + parts, ... of Lc experts each
     uint32_t row_parts; // ... times this many: all of them mark every row, each ranks and writes its share of the rows
     uint32_t tab_words; // LDS words of the table of local slots (0: the rank table in memory is looked up)
+    uint32_t row_limit; // more received rows than this are left to the other form of k_small_step's index (0: there is none)
 };
 
 constexpr uint32_t kNotLocal = 0xffu;     // table entry of an expert that lives elsewhere; local slots are below 255
@@ -529,7 +530,7 @@ __device__ __forceinline__ void recv_index_rider(const mw_index_args &a, const u
     const uint32_t q = w / (uint32_t)a.P, part = q / a.row_parts;
     recv_index_body<false, kForm, 1, false>(a, w - q * (uint32_t)a.P, part, q - part * a.row_parts);
 }
-__device__ __forceinline__ uint32_t index_riders(const mw_index_args &a) { return (uint32_t)a.P * a.parts * a.row_parts; }
+__host__ __device__ __forceinline__ uint32_t index_riders(const mw_index_args &a) { return (uint32_t)a.P * a.parts * a.row_parts; }
 
 template <bool kPackets, int kForm, int kB>
 __global__ __launch_bounds__(kIndexBlock) void k_recv_index(const mw_index_args a)
@@ -609,6 +610,7 @@ __device__ __forceinline__ void recv_index_small(const mw_index_args &a, uint32_
         if (in_lds && e < E) tab[e] = tab_r[j];
     }
     mw_lds_barrier();
+    if (a.row_limit != 0 && scratch[0] + scratch[1] + scratch[2] + scratch[3] > a.row_limit) return;
     if (tid < P) {
         uint32_t before = n_inc - nq, dbefore = d_inc - dq;
         for (uint32_t w = 0; w < (tid >> 6); ++w) { before += scratch[w]; dbefore += scratch[4 + w]; }
@@ -1014,7 +1016,11 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
 // (mw_small_plan, the plan of mw_plan_pack) -- then the packer's rows
 // and the expander's.  At these sizes the step is the riders' chain of memory round trips, and the
 // forms that spread a batch over workgroups spend half of theirs on talking to one another.
-template <int W, bool kKeyed, int kRows>
+// kEither: nobody has said how many rows the peers hold.  One workgroup takes 9.5 us for every 1024 of them, so the
+// launch has the riders of recv_index_body too (grid rows from general_row on), and whoever is not needed
+// leaves: the choice is made here, from the peers' own counts (64 ranks, rows of 7168, us a step without / with: 64 tokens
+// that all come here 43.2 / 28.4, fp8 38.1 / 16.9; 200 of 256 tokens, fp8 124 / 44; an even share of 64 tokens 10.4 / 9.1.)
+template <int W, bool kKeyed, int kRows, bool kEither>
 __global__ __launch_bounds__(kSmallLanes) void k_small_step(
     const uint32_t first_pack_row, const uint32_t first_expand_row, const mw_row_rec *__restrict__ recs,
     const uint32_t *__restrict__ row_base, int P, int xc, const int32_t *__restrict__ pack_perm,
@@ -1022,7 +1028,8 @@ __global__ __launch_bounds__(kSmallLanes) void k_small_step(
     const uint32_t *__restrict__ base, const mw_hit *__restrict__ hits,
     u32x4 *__restrict__ out_rows, u32x4 *__restrict__ out_scales, uint32_t cap,
     int32_t *__restrict__ out_src_peer, int32_t *__restrict__ out_src_token,
-    const mw_index_args next, const mw_plan_args plan, const mw_pack_args pack)
+    const mw_index_args next, const mw_plan_args plan, const mw_pack_args pack, const mw_index_args general,
+    const uint32_t general_row)
 {
     if (blockIdx.y >= first_expand_row) {
         expand_body(recs, hits, base, row_base, P, Kd, xc, sc, out_rows, out_scales, cap, out_src_peer, out_src_token,
@@ -1035,8 +1042,25 @@ __global__ __launch_bounds__(kSmallLanes) void k_small_step(
                      first_expand_row - first_pack_row);
         return;
     }
-    if (blockIdx.x != 0) return;
     extern __shared__ uint64_t small_lds[];
+    if constexpr (kEither) {
+        if (blockIdx.y >= general_row) {
+            const uint32_t w = (blockIdx.y - general_row) * gridDim.x + blockIdx.x;
+            if (w >= index_riders(general)) return;
+            uint32_t *wave_n = (uint32_t *)small_lds;
+            const uint32_t q = threadIdx.x;
+            const uint32_t n = mw_wave_sum(q < (uint32_t)general.P ? min(((const mw_recv_peer *)general.peers)[q].n_rows, general.max_tokens) : 0u);
+            if ((q & 63u) == 0) wave_n[q >> 6] = n;
+            mw_lds_barrier();
+            uint32_t rows = 0;
+#pragma unroll
+            for (int v = 0; v < kSmallLanes / 64; ++v) rows += wave_n[v];
+            mw_lds_barrier();                                  // (the index uses the same words)
+            if (rows > next.row_limit) recv_index_rider<kFormMany>(general, w);
+            return;
+        }
+    }
+    if (blockIdx.x != 0) return;
     if (blockIdx.y == 0) {
         recv_index_small<kRows>(next, (uint32_t *)small_lds);
         return;
@@ -1182,7 +1206,7 @@ static bool make_index_args(mw_ctx *ctx, const void *peers, bool packets, int32_
                        (uint32_t)c.max_tokens, wpl, (uint32_t)c.max_recv_rows,
                        (uint64_t)(packets ? hb + ctx->row_bytes : ctx->row_stride), hb, cap,
                        ctx->d_cnt, ctx->d_row_base, ctx->d_addr_cnt, ctx->d_recs, ctx->d_hits, ctx->d_base,
-                       expert_offsets, stats, ctx->d_flags, dedup, n_chunks < max_parts ? n_chunks : max_parts, 1u, tab_words};
+                       expert_offsets, stats, ctx->d_flags, dedup, n_chunks < max_parts ? n_chunks : max_parts, 1u, tab_words, 0u};
     return true;
 }
 
@@ -1360,17 +1384,41 @@ int32_t mw_launch_unpack_expand(mw_ctx *ctx, int32_t P, void *out_rows, float *o
     return MW_OK;
 }
 
+// Rows up to which the one-workgroup index is used where nobody has said how many there will be: two a lane.
+// (940 rows: 13.0 us against 10.9 of a workgroup a peer, but nothing has to be cleared, counted or waited for.)
+constexpr int kEitherRows = 2 * kSmallLanes;
+
+// The riders of k_small_step beside its one-workgroup index (false: they are not needed).  *fits: both forms can be had.
+static bool small_step_riders(mw_ctx *next, const void *peers, int32_t P, int64_t cap, int64_t *expert_offsets,
+                              mw_recv_stats *stats, mw_index_args *general, size_t *lds, bool *fits)
+{
+    *fits = true;
+    if (next->recv_rows_hint > 0 || (int64_t)P * next->cfg.max_tokens <= kEitherRows) return false;
+    const uint32_t words = kSmallIndexLds / 4;
+    *fits = make_index_args(next, peers, false, P, cap, expert_offsets, stats, words, words, 1, kMaxIndexParts, general, lds) &&
+            index_form(*general) != kFormAny;
+    if (!*fits) return false;
+    const int per_lane = (next->cfg.max_tokens + kSmallLanes - 1) / kSmallLanes;
+    general->row_parts = per_lane >= 8 ? 4u : per_lane >= 4 ? 2u : 1u;
+    return true;
+}
+
 // Whether a step is small enough for k_small_step -- this batch's rows (received and to pack) under
 // 24 MiB, so that the riders and not the movers are the step; the next batch's index in one
 // workgroup's LDS and at most MW_FUSED_MAX_TOKENS tokens to plan -- and, if so, its launch.
 // with_plan: the launch plans next_T tokens (possibly none); pk: rows to pack, or null.
-static bool small_step_fits(const mw_ctx *ctx, const mw_ctx *next, int32_t next_P, int32_t next_T, const mw_pack_call *pk,
+static bool small_step_fits(const mw_ctx *ctx, mw_ctx *next, int32_t next_P, int32_t next_T, const mw_pack_call *pk,
                             uint32_t gy)
 {
     const int64_t rows = (int64_t)gy + (pk ? pk->n_tokens : 0);
     if (rows * ctx->row_bytes > (24LL << 20)) return false;
     if (next_T > MW_FUSED_MAX_TOKENS) return false;
-    return small_index_fits(next, next_P);
+    if (!small_index_fits(next, next_P)) return false;
+    mw_index_args general;
+    size_t lds;
+    bool fits;
+    small_step_riders(next, nullptr, next_P, 0, nullptr, nullptr, &general, &lds, &fits);
+    return fits;
 }
 
 static int32_t launch_small_step(mw_ctx *ctx, int32_t P, void *out_rows, float *out_scales, int64_t cap,
@@ -1404,22 +1452,32 @@ static int32_t launch_small_step(mw_ctx *ctx, int32_t P, void *out_rows, float *
                                          : W == 2 ? mw_small_plan_words<2, false>()
                                          : W == 3 ? mw_small_plan_words<3, false>()
                                                   : mw_small_plan_words<4, false>());
-    const size_t lds = with_plan && lds_plan > lds_index ? lds_plan : lds_index;
-    const uint32_t riders = with_plan ? 2u : 1u;
+    size_t lds = with_plan && lds_plan > lds_index ? lds_plan : lds_index;
+    const uint32_t general_row = with_plan ? 2u : 1u;
+    mw_index_args general = {};
+    size_t lds_general = 0;
+    bool fits;
+    const bool either = small_step_riders(next, a.peers, a.P, a.out_cap, a.expert_offsets, a.stats, &general, &lds_general, &fits);
+    if (either) {
+        ai.row_limit = kEitherRows;
+        if (lds < lds_general) lds = lds_general;
+    }
+    const uint32_t riders = general_row + (either ? (index_riders(general) + (uint32_t)nseg - 1) / (uint32_t)nseg : 0u);
     const dim3 grid(nseg, riders + n_pack_rows + gy), block(kSmallLanes);
     const uint32_t cap32 = (uint32_t)(cap < 0x7fffffffLL ? cap : 0x7fffffffLL);
     {
         mw_timed tm(ctx, MW_KERNEL_EXPAND, s);
         const int rows = small_index_rows(next, a.P);
-#define MW_SMALL_(W_, KEYED_, ROWS_)                                                                                   \
-    hipLaunchKernelGGL((k_small_step<W_, KEYED_, ROWS_>), grid, block, lds, s, riders, riders + n_pack_rows, ctx->d_recs, \
+#define MW_SMALL_(W_, KEYED_, ROWS_, EITHER_)                                                                          \
+    hipLaunchKernelGGL((k_small_step<W_, KEYED_, ROWS_, EITHER_>), grid, block, lds, s, riders, riders + n_pack_rows, ctx->d_recs, \
                        ctx->d_row_base, P, xc, pa.perm, pa.stats, sc, ctx->hit_slots, ctx->d_base, ctx->d_hits,         \
-                       (u32x4 *)out_rows, (u32x4 *)out_scales, cap32, out_src_peer, out_src_token, ai, pl, pa)
+                       (u32x4 *)out_rows, (u32x4 *)out_scales, cap32, out_src_peer, out_src_token, ai, pl, pa, general, general_row)
 #define MW_SMALL(W_, KEYED_)                                                                                           \
     do {                                                                                                               \
-        if (rows == 1) MW_SMALL_(W_, KEYED_, 1);                                                                       \
-        else if (rows == 2) MW_SMALL_(W_, KEYED_, 2);                                                                  \
-        else MW_SMALL_(W_, KEYED_, 4);                                                                                 \
+        if (either) MW_SMALL_(W_, KEYED_, 2, true);                                                                    \
+        else if (rows == 1) MW_SMALL_(W_, KEYED_, 1, false);                                                           \
+        else if (rows == 2) MW_SMALL_(W_, KEYED_, 2, false);                                                           \
+        else MW_SMALL_(W_, KEYED_, 4, false);                                                                          \
     } while (0)
         if (keyed) MW_SMALL(4, true);
         else if (W == 1) MW_SMALL(1, false);
