@@ -1247,16 +1247,26 @@ static bool index_rides(const mw_ctx *next, double mover_us, int bs, mw_index_ar
     return 6.0 + row_us * (double)per_lane * (1.0 + 1.0 / a->row_parts) < mover_us + 12.0;
 }
 
-// Whether the next batch's plan rides.  It ranks tokens all-pairs over workgroups that talk through
-// memory: 40 us for 700 tokens, 48 for 1000 and more, a dozen more with keys of several words, free beside movers
-// that take longer; a launch of its own takes 8 (up to 2048 tokens), 13 (4096), 21 us (8192), 18 with more
-// than eight ids and bitmaps of several words.  Measured (us a
-// step, riding / apart): 1024 tokens beside 26 us of movers 49 / 31; 2000 tokens of 256 ranks beside 34 us 63 / 46;
-// 2048 tokens beside 44 us 48 / 53; 4096 tokens beside 161 us 163 / 174.  A context whose wait limit the caller has set keeps its plans riding.
-static bool plan_rides(const mw_ctx *next, double mover_us, int32_t T, bool keyed)
+// Whether the next batch's plan rides beside movers of `mover_us` in workgroups of `bs` lanes.  It ranks tokens all-pairs over
+// workgroups that talk through memory; the finishing ones walk every token's counters, T * T / bs of them, which
+// is what grows beyond a thousand tokens.  Beside movers that are shorter it takes 48 us for 1000 tokens in wide workgroups, 6
+// more with keys of several words, 56 in workgroups of two waves, and there 64 (4096 tokens), 72 (6144), 90 (8192).  A launch of its
+// own takes 8 (up to 2048 tokens), 13 (4096), 21 us (8192), 18 with more than eight ids and bitmaps of several words.  Measured,
+// us a step riding / apart, rows of 7168 from 16 and from 64 peers:
+//   bf16, 256 ranks   1024 tokens 56 / 18, 60 / 23   4096 66 / 43, 68 / 67   6144 72 / 61, 93 / 98   8192 90 / 78, 130 / 128
+//   fp8, 256 ranks    1024 tokens 54 / 15, 55 / 19   4096 57 / 35, 57 / 49   6144 58 / 50, 62 / 72   8192 59 / 63, 83 / 93
+//   bf16, 64 ranks    1024 tokens 56 / 22, 64 / 47   4096 69 / 67, 161 / 172 6144 91 / 100, 256 / 264 8192 122 / 130, 348 / 355
+//   fp8, 64 ranks     1024 tokens 48 / 27, 50 / 31   4096 51 / 49, 95 / 108  6144 58 / 72, 148 / 162 8192 79 / 93, 203 / 218
+// Beside movers of any length it still takes memory time from them, beyond 7168 tokens in two-wave workgroups with keys of
+// several words more than a launch of its own (130 / 128 above; skewed ids, 20673 rows, 156 / 153).
+// A context whose wait limit the caller has set keeps its plans riding.
+static bool plan_rides(const mw_ctx *next, double mover_us, int32_t T, bool keyed, int bs)
 {
     if (T == 0 || next->ride_wait_limit != kRideWaitDefault) return true;
-    const double rider_us = 13.0 + 34.0 * (T < 1024 ? T : 1024) / 1024.0 + (keyed ? 12.0 : 0.0);
+    if (keyed && bs < 256 && T > 7168) return false;
+    const double t = T / 8192.0;
+    const double rider_us = 13.0 + 35.0 * (T < 1024 ? T : 1024) / 1024.0 + (bs < 256 ? 8.0 : keyed ? 6.0 : 0.0) +
+                            32.0 * t * t * 128.0 / bs;
     const double apart_us = !keyed && next->mask_words > 1 ? 18.0 : T <= 2048 ? 8.0 : T <= 4096 ? 13.0 : 21.0;
     return rider_us < mover_us + apart_us;
 }
@@ -1567,7 +1577,7 @@ int32_t mw_launch_unpack_expand_index_plan_next(mw_ctx *ctx, int32_t P, void *ou
         if (rc != MW_OK) return rc;
         a.parts = 0;
     }
-    const bool with_plan = plan_rides(next, mover_us, next_T, keyed);
+    const bool with_plan = plan_rides(next, mover_us, next_T, keyed, shape.bs);
     if (!with_plan) {
         const int32_t rc = mw_launch_plan(next, next_topk, next_T, next_mask, next_perm, next_desc, next_send_stats, s);
         if (rc != MW_OK) return rc;
