@@ -104,14 +104,16 @@ ws_layout layout(const mw_config &c, int32_t L)
     }
     // keys of the plan's two-launch form (batches up to 8192 tokens), a flag word per workgroup that makes them behind
     w.plan_keys = o;
-    o += mw_align_up(8LL * (ntok < 8192 ? ntok : 8192), A) + A;
-    // sorted chunks for the plan of large batches (only contexts that can see such batches)
+    o += mw_align_up(8LL * (ntok < kPlanOrderMax ? ntok : kPlanOrderMax), A) + A;
+    // sorted chunks and row-indexed arrays for the plan of large batches (only contexts that can see such batches)
     w.sort_key = w.sort_sec = w.chunk_kept = w.row_cnt = w.row_start = -1;
-    if (c.max_tokens > 4096) {
-        const int64_t padded = mw_align_up(ntok, 1024);
+    const int64_t padded = mw_align_up(ntok, 1024);
+    if (c.max_tokens > kPlanOrderMax) {
         w.sort_key = o;   o += mw_align_up(8LL * padded, A);
         w.sort_sec = o;   o += mw_align_up(4LL * padded, A);
         w.chunk_kept = o; o += mw_align_up(4LL * 64, A);
+    }
+    if (c.max_tokens >= kPlanRowsFrom) {
         w.row_cnt = o;    o += mw_align_up(8LL * padded, A);
         w.row_start = o;  o += mw_align_up(padded, A);
     }
@@ -164,7 +166,7 @@ MW_API int32_t mw_ctx_create(const mw_config *cfg, void *workspace_dev, int64_t 
     ctx->d_plan_cnt = (uint64_t *)(b + w.plan_cnt);
     ctx->d_plan_state = (uint32_t *)(b + w.plan_state);
     ctx->d_plan_keys = (uint64_t *)(b + w.plan_keys);
-    ctx->d_plan_bad = (uint32_t *)(b + w.plan_keys + mw_align_up(8LL * (cfg->max_tokens < 1 ? 1 : cfg->max_tokens < 8192 ? cfg->max_tokens : 8192), 256));
+    ctx->d_plan_bad = (uint32_t *)(b + w.plan_keys + mw_align_up(8LL * (cfg->max_tokens < 1 ? 1 : cfg->max_tokens < kPlanOrderMax ? cfg->max_tokens : kPlanOrderMax), 256));
     ctx->d_sort_key = w.sort_key >= 0 ? (uint64_t *)(b + w.sort_key) : nullptr;
     ctx->d_sort_sec = w.sort_sec >= 0 ? (uint32_t *)(b + w.sort_sec) : nullptr;
     ctx->d_chunk_kept = w.chunk_kept >= 0 ? (uint32_t *)(b + w.chunk_kept) : nullptr;

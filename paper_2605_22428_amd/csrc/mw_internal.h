@@ -53,6 +53,9 @@ static inline mw_row_shape mw_row_shape_of(int chunks)
     return mw_row_shape{b, (chunks + b - 1) / b};
 }
 
+// Tokens up to which k_plan_order makes the plan (beyond: sorted chunks), and from which k_groups works on
+// row-indexed arrays; the workspace has the arrays of either only where a batch can need them.
+constexpr int kPlanOrderMax = 8192, kPlanRowsFrom = 24576;
 constexpr uint32_t kRideWaitDefault = 1u << 21;      // polls a riding plan's second half waits for its first
 
 // Host-side context.  Every d_* pointer is a slice of the caller's workspace.

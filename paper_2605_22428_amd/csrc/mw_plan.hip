@@ -208,7 +208,7 @@ __global__ __launch_bounds__(kBlock) void k_groups(const uint64_t *__restrict__ 
 // is, the others plus one (they are at most 254, since a higher one precedes them), zero for "no further
 // rank".  Comparing keys is comparing the bitmaps as numbers, and different bitmaps have different
 // keys.  The key of a one-word bitmap is the word.
-constexpr int kOrderBlock = 1024, kOrderMaxTokens = 8192;
+constexpr int kOrderBlock = 1024, kOrderMaxTokens = kPlanOrderMax;
 constexpr int kOwnMax = 4, kOwnBuckets = 64;      // a workgroup's tokens, without and with buckets, at most
 
 template <bool kBytes> struct mw_order_key {
@@ -782,7 +782,6 @@ __global__ __launch_bounds__(kSmallPlanLanes) void k_plan_pack(
 // tokens without a destination and the padding of the last chunk carry the largest key and a
 // second word above every kept token's, so they sort behind all kept tokens of the chunk.
 constexpr int kChunk = 1024;
-constexpr int kRowsFrom = 24576;       // from here k_groups works on row-indexed arrays
 constexpr uint32_t kSecEmpty = 0x40000000u, kSecPad = 0x7fffffffu;
 
 template <int W>
@@ -1022,6 +1021,7 @@ int32_t mw_launch_plan(mw_ctx *ctx, const int32_t *topk, int32_t T, uint64_t *ma
                                ctx->d_sort_key, ctx->d_sort_sec, ctx->d_chunk_kept, cnt);
         }
     } else if (T > 0) {
+        if (ctx->mask_words == 1) return MW_ERR_UNSUPPORTED;       // (k_rank has no one-word form: every such batch has a key)
         // Bitmaps of more than one word and more than eight ids: no 64-bit key.  Split the predecessor walk into
         // slices so that about 4 workgroups land on every CU; a slice's bitmaps must fit in LDS.
         int ns = (4 * ctx->n_cu + tb - 1) / tb;
@@ -1043,7 +1043,7 @@ int32_t mw_launch_plan(mw_ctx *ctx, const int32_t *topk, int32_t T, uint64_t *ma
     }
     {
         mw_timed tm(ctx, MW_KERNEL_PLAN_GROUPS, s);
-        if (T >= kRowsFrom && ctx->d_row_cnt) {
+        if (T >= kPlanRowsFrom && ctx->d_row_cnt) {
             hipLaunchKernelGGL(k_rows_from_counters, dim3(tb), dim3(kBlock), 0, s, T, cnt, pstate, perm,
                                (unsigned long long *)ctx->d_row_cnt, ctx->d_row_start);
             hipLaunchKernelGGL(k_groups<true>, dim3(tb), dim3(kBlock), 0, s, mask, T, (uint64_t)ctx->row_bytes, cnt,
