@@ -1069,12 +1069,11 @@ __global__ __launch_bounds__(kSmallLanes) void k_small_step(
                              plan.desc, plan.stats, small_lds);
 }
 
-// The one-workgroup index as a launch of its own (mw_unpack_index, mw_unpack of a small batch).
-template <int kRows>
+// The one-workgroup index as a launch of its own (mw_unpack_index, mw_unpack of at most a row a lane).
 __global__ __launch_bounds__(kSmallLanes) void k_recv_index_small(const mw_index_args a)
 {
     extern __shared__ uint64_t small_index_lds[];
-    recv_index_small<kRows>(a, (uint32_t *)small_index_lds);
+    recv_index_small<1>(a, (uint32_t *)small_index_lds);
 }
 
 // The way back (Section 2.1, combine-style AlltoAll; Section 2.3.2: the combine phase reduces
@@ -1327,11 +1326,7 @@ int32_t mw_launch_unpack_index(mw_ctx *ctx, const void *peers, bool packets, int
             // a row a lane at most: one workgroup for all peers, nothing to exchange between workgroups
             // (9.6 against 10.9 us at 443 rows; with two rows a lane the workgroup-per-peer form is ahead)
             const size_t lds = small_index_lds(ctx, P, &a);
-            auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(1), dim3(kSmallLanes), lds, s, a); };
-            const int rows = small_index_rows(ctx, P);
-            if (rows == 1) launch(k_recv_index_small<1>);
-            else if (rows == 2) launch(k_recv_index_small<2>);
-            else launch(k_recv_index_small<4>);
+            hipLaunchKernelGGL(k_recv_index_small, dim3(1), dim3(kSmallLanes), lds, s, a);
         } else
         {
 #define MW_INDEX(GENERAL_, ROWS_)                                                                                              \
