@@ -187,9 +187,15 @@ def _addr(t: Optional[torch.Tensor]) -> int:
     return 0 if t is None else t.data_ptr()
 
 
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)      # not part of torch's public interface
+
+
 def _stream_handle() -> int:
-    """Raw handle of the current device's current stream (no torch.cuda.Stream object is made)."""
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    """Raw handle of the current device's current stream; no torch.cuda.Stream object is made where torch can say it
+    without one."""
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _stream() -> C.c_void_p:
