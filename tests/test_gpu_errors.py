@@ -235,8 +235,9 @@ def test_riding_plan_gives_up_and_the_context_plans_again():
     tk2 = W.topk_ids(w, 3, 1)[:5000]
     st = _ride(ctxs, w, n_peers, cap, table, bufs, H.dev(tk2), sb)
     assert int(st["error_flags"]) == B.MW_FLAG_PLAN_TIMEOUT and int(st["n_rows"]) == 0
-    # ... and rides with the default limit
-    ctxs[1].mw_ctx_set_ride_wait_limit(1 << 21)
+    # ... and rides with a limit that is as good as the default (with the default itself it would not ride
+    # beside movers as short as these)
+    ctxs[1].mw_ctx_set_ride_wait_limit((1 << 21) - 1)
     sb2 = B.SendBuffers(ctxs[1], w.n_tokens)
     st = _ride(ctxs, w, n_peers, cap, table, bufs, tk_d, sb2)
     _check_plan(w, sb2, st, tk_me)
@@ -247,12 +248,14 @@ def test_riding_plan_gives_up_and_the_context_plans_again():
 
 
 def test_riding_plan_with_the_default_limit_is_the_oracles():
-    """The same launch with the default wait limit, batch after batch on one pair of contexts
+    """The same launch with the default wait limit (but for one poll: beside movers as short as these a plan
+    rides only where the caller has set the limit), batch after batch on one pair of contexts
     (sizes going down and up again, so a finishing workgroup count that changes from launch to
     launch finds clean state): every plan complete and exact, never a time-out flag."""
     w = W.DispatchWorkload("ride", 42, 64, 256, 8, 4096, 256, "bf16", "uniform")
     n_peers, peer_tokens = 5, 200
     ctxs, toks, cap, table, bufs = _ride_setup(w, n_peers, peer_tokens)
+    ctxs[1].mw_ctx_set_ride_wait_limit((1 << 21) - 1)
     for i, n in enumerate((4096, 700, 1, 0, 2049)):
         tk = W.topk_ids(w, 10 + i, 1)[:n]
         sb = B.SendBuffers(ctxs[1], max(n, 1))

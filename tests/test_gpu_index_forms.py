@@ -1,7 +1,8 @@
 """GPU parity of the receive index where its form changes: experts spread over several workgroups a
 peer and over several passes of one, id lists that are not whole 16-byte units or do not start on
 one, more than eight ids, more than 64 local experts, more experts than the table in LDS holds, the
-largest batch; on its own, riding beside the expander, from packets, and dropping repeated rows.
+largest batch; on its own, in front of or (small batches) beside the expander, from packets, and dropping repeated
+rows.  (Riding beside long movers: test_gpu_riding_index.py.)
 Against the oracle's plain definition, bit-exact."""
 import numpy as np
 import pytest
@@ -17,13 +18,13 @@ pytestmark = pytest.mark.gpu
 #          ranks, experts, top_k, tokens, my_rank
 SHAPES = {
     "four_parts": (8, 256, 8, 1500, 3),            # 32 experts here, more rows of a peer than lanes
-    "parts_and_passes": (2, 128, 8, 8192, 1),      # riding: more chunks of experts than workgroups a peer
+    "parts_and_passes": (2, 128, 8, 8192, 1),      # several experts, long bitmaps
     "sixty_four_local": (4, 256, 8, 300, 2),
     "sixty_five_local": (1, 65, 8, 400, 0),        # no 64-bit set of experts
     "nine_ids": (8, 64, 9, 700, 7),
     "six_ids": (8, 64, 6, 700, 0),                 # ids word by word
     "one_id": (16, 64, 1, 333, 5),
-    "table_in_memory": (100, 3000, 4, 300, 99),    # riding: no room for the table of slots in LDS
+    "table_in_memory": (100, 3000, 4, 300, 99),    # more experts than a small workgroup's table of slots
     "many_local": (2, 2000, 4, 500, 1),            # slots do not fit a byte
     "largest": (1, 1, 1, 65536, 0),                # every row to one expert: the count is 2^16
 }
@@ -78,7 +79,7 @@ def test_index_forms(which):
         gu = H.GpuUnpack.__new__(H.GpuUnpack)
         gu.ctx, gu.buf, gu.stats = nxt, b, nxt.mw_get_recv_stats(b.stats)
         gu.Q = int(gu.stats["n_out_rows"])
-        H.check_unpack(gu, want, "riding")
+        H.check_unpack(gu, want, "with an expander")
 
     ptable = B.packets_table(packets, [int(t.shape[0]) for t in packets], H.DEV)
     nxt.mw_unpack_packets(ptable, n_peers, b.out_rows, None, cap, b.out_src_peer, b.out_src_token, b.expert_offsets, b.stats)

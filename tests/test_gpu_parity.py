@@ -468,6 +468,8 @@ def test_plan_of_the_next_batch_rides_with_the_expander(which):
     _say("riding plan", w.name)
     e2r = W.expert_to_rank(w)
     ctxs = [H.make_ctx(w, my_rank, max_tokens=1200), H.make_ctx(w, my_rank, max_tokens=1200)]
+    for c in ctxs:                    # not the default: plans ride also beside movers as short as these
+        c.mw_ctx_set_ride_wait_limit((1 << 21) - 1)
     R = w.n_ranks
     batches = []
     for seed in (1, 2, 3, 4, 5):
