@@ -208,8 +208,7 @@ __global__ __launch_bounds__(kBlock) void k_groups(const uint64_t *__restrict__ 
 // is, the others plus one (they are at most 254, since a higher one precedes them), zero for "no further
 // rank".  Comparing keys is comparing the bitmaps as numbers, and different bitmaps have different
 // keys.  The key of a one-word bitmap is the word.
-constexpr int kOrderBlock = 1024, kOrderMaxTokens = kPlanOrderMax;
-constexpr int kOwnMax = 4, kOwnBuckets = 64;      // a workgroup's tokens, without and with buckets, at most
+constexpr int kOrderBlock = 1024, kOrderMaxTokens = kPlanOrderMax, kOwnMax = 32;
 
 template <bool kBytes> struct mw_order_key {
     // a value no kept token's key has: marks free slots of the hash table.  (One word: 0 is the empty
@@ -388,10 +387,9 @@ __global__ __launch_bounds__(kOrderBlock) void k_plan_order(
     extern __shared__ __align__(16) uint64_t order_lds[];
     unsigned long long *slot = (unsigned long long *)order_lds;       // [1 << slots_log] hash table of keys
     const uint32_t n_slots = 1u << slots_log;
-    constexpr int kOwn = kByBucket ? kOwnBuckets : kOwnMax, kParts = kByBucket ? 1 : 16;
-    uint64_t *own = order_lds + n_slots;                              // [kOwn]             keys of this workgroup's tokens
-    uint2 *part = (uint2 *)(own + kOwn);                              // [kParts][kOwn]     the waves' counts for them
-    uint32_t *wave_n = (uint32_t *)(part + kParts * kOwn);            // [16][4]            kept, distinct, destinations, bad
+    uint64_t *own = order_lds + n_slots;                              // [kOwnMax]          keys of this workgroup's tokens
+    uint2 *part = (uint2 *)(own + kOwnMax);                           // [16][kOwnMax]      the waves' counts for them
+    uint32_t *wave_n = (uint32_t *)(part + 16 * kOwnMax);             // [16][4]            kept, distinct, destinations, bad
     uint32_t *wave_r = wave_n + 64;                                   // [16][4]            tokens that name rank r
     uint32_t *bins = wave_r + 64;                                     // [kBuckets]         (by bucket) tokens and representatives
     uint16_t *tab = kFromKeys || E > kTableExperts ? nullptr : (uint16_t *)(bins + (kByBucket ? kBuckets : 0));
@@ -947,13 +945,11 @@ static void launch_plan_order(mw_ctx *ctx, const int32_t *topk, int32_t T, uint6
     const int K = ctx->cfg.top_k, E = ctx->cfg.n_experts, R = ctx->cfg.n_ranks;
     const bool from_keys = T >= kKeysFrom;
     const int bs = T <= 256 ? 256 : T <= 512 ? 512 : kOrderBlock;
-    // About a workgroup per CU, and enough of them that each counts at most four ranks.  Above 4096 tokens only every other
-    // CU: a workgroup takes 146 KiB of LDS for 20 us, and the launch it runs beside keeps the rest (a step of 8192 tokens of
-    // 256 ranks whose plan runs on a second stream: 148 us with 256 of them, 142 with 160, 140.5 with 128; mw_plan alone
-    // 23.4, 24.9, 25.4).  Up to 4096 tokens it makes no difference to a neighbour (4096 fp8 tokens 100.0 and 99.7 us a step).
-    const int most_wg = T > 4096 ? 128 : 256;
-    static_assert(kOrderMaxTokens / 128 <= kOwnBuckets && 4096 / 256 <= kOwnBuckets && kOrderBlock / 256 <= kOwnMax, "tokens a workgroup");
-    int n_own = (T + most_wg - 1) / most_wg;
+    // About a workgroup per CU, and enough of them that each counts at most four ranks.  Each takes 146 KiB of LDS from 2049
+    // tokens on, so a launch beside the plan waits for its CUs: a step of 8192 tokens of 256 ranks whose plan runs on a second
+    // stream takes 148 us, with 128 workgroups 140.5 -- and the plan alone 25.4 instead of 23.4, with skewed ids 37 instead of
+    // 31 us.  (Up to 4096 tokens a neighbour loses nothing: 4096 fp8 tokens 100.0 and 99.7 us a step.)
+    int n_own = (T + 255) / 256;
     if (n_own < 1) n_own = 1;
     int n_wg = (T + n_own - 1) / n_own;
     if (n_wg < (R + 3) / 4) n_wg = (R + 3) / 4;
@@ -963,8 +959,7 @@ static void launch_plan_order(mw_ctx *ctx, const int32_t *topk, int32_t T, uint6
     while ((1 << slots_log) < 2 * T || ((1 << slots_log) < 4 * T && slots_log < 14)) ++slots_log;
     const size_t tab = E <= kTableExperts ? ((size_t)E + 4) / 4 * 8 : 0;
     const bool by_bucket = T >= kBucketsFrom;
-    const size_t lds_own = by_bucket ? 8 * kOwnBuckets + 8 * kOwnBuckets : 8 * kOwnMax + 8 * 16 * kOwnMax;
-    const size_t lds = ((size_t)8 << slots_log) + lds_own + 4 * 128 + (by_bucket ? 4 * kBuckets : 0) +
+    const size_t lds = ((size_t)8 << slots_log) + 8 * kOwnMax + 8 * 16 * kOwnMax + 4 * 128 + (by_bucket ? 4 * kBuckets : 0) +
                        (from_keys ? 0 : tab);
     const int n_key_wg = (T + kKeysBlock - 1) / kKeysBlock;
     if (from_keys) {
