@@ -166,8 +166,9 @@ def bench_dispatch(args, name: str, brief: bool = False) -> dict:
     sched0 = args.schedule
     if sched0 == "auto":
         # the plan of the next batch rides in the step's one launch where it stays in the row
-        # movers' shadow (up to 4096 tokens); beyond that it runs on a second stream
-        sched0 = "one_launch" if w.n_tokens <= 4096 else "launch_and_plan"
+        # movers' shadow (up to 4096 tokens); beyond that send and receive side take a stream each (8192 tokens
+        # over 256 ranks: "aligned" 142.6 us a step, "launch_and_plan" 148, "one_launch" 153)
+        sched0 = "one_launch" if w.n_tokens <= 4096 else "aligned"
     describe = {
         "c0": "C0 tiny dispatch: 8 simulated ranks, 16 experts, top-2 uniform, 128 tokens x 256 bf16, 8 peer "
               "receive regions (launch-latency bound, cache resident: its % of peak is not meaningful)",
@@ -311,7 +312,7 @@ def bench_dispatch(args, name: str, brief: bool = False) -> dict:
     #            made during the step before, and the plan waits until the step that last packed
     #            from its output buffers (the same buffer set, N_SETS - 1 steps ago) has finished.
     #  "one_launch" (what "auto", the default, takes for batches of up to 4096 tokens; larger
-    #            ones get "launch_and_plan")  mw_stream_step: the packer joins that launch too -- one
+    #            ones get "aligned")  mw_stream_step: the packer joins that launch too -- one
     #            launch per batch, the two bandwidth-bound parts with no launch boundary between
     #            them.  The launch's algorithmic bytes are then the packer's plus the expander's.
     ev_unpack_done = [DeviceEvent(torch) for _ in range(2)]

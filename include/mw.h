@@ -444,10 +444,9 @@ MW_API int32_t mw_unpack_expand_index_next(mw_ctx *ctx, const mw_recv_batch *rec
  * (with mw_stream_step, and the packer) is too short to hide the index or the plan, the library gives them
  * launches of their own in front, with the same results; a plan always rides on a next context whose
  * wait limit was set to something else than the default.  The riding
- * plan ranks tokens all-pairs (as mw_plan does up to about 8000 tokens): it stays in the
+ * plan ranks tokens all-pairs, which mw_plan does not: it stays in the
  * expander's shadow while that takes less time than the expander -- 4096 tokens beside 30000
- * received rows of 14 KiB do, 8192 tokens over 256 ranks beside 20000 such rows do not (use
- * mw_plan on a second stream there).
+ * received rows of 14 KiB do, 8192 tokens over 256 ranks beside 20000 such rows do not and are planned in front.
  * Inside the launch the plan's second half waits for its first half (workgroups that come
  * earlier in the same launch and wait for nothing themselves); the wait is bounded (about a
  * second by default, mw_ctx_set_ride_wait_limit).  Past the bound -- not observed, and not

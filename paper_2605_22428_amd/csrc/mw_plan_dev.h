@@ -1,6 +1,7 @@
 // Device code of the plan that more than one translation unit uses: the bitmap builder, the
-// short keys, the all-pairs ranking of one workgroup (k_rank, and the plan that rides along
-// with the expander), and the second half of that riding plan.
+// short keys, the plan of a small batch in one workgroup, the all-pairs ranking of one workgroup (the plan that rides along
+// with the expander, and k_rank, which mw_plan takes only for bitmaps of several words with more than eight ids),
+// and the second half of that riding plan.
 #ifndef MW_PLAN_DEV_H_
 #define MW_PLAN_DEV_H_
 
@@ -315,7 +316,7 @@ __device__ __forceinline__ void mw_small_plan(const int32_t *__restrict__ topk, 
 
 // cnt[t] += (#smaller | #equal before << 21 | #equal at-or-after << 42) over this slice, where
 // "smaller" means (bitmap, index) < (bitmap[t], t).  Empty bitmaps compare below every kept
-// token; k_groups subtracts their number.  A kept token always has a non-zero third field.
+// token; whoever reads the counters (mw_plan_finish_ride, k_groups) subtracts their number.  A kept token always has a non-zero third field.
 // kKeyed (bitmaps of more than one word, top_k <= 8): the slice holds short keys instead of bitmaps.
 // Workgroup (bx, by) of `bs` lanes: tokens [bx bs, bx bs + bs) against slice by.  kAgentMask:
 // the bitmaps are written through to device scope, for a reader in the same launch.
@@ -531,7 +532,7 @@ __device__ __forceinline__ void mw_plan_finish_ride(const mw_plan_args &a, uint3
         for (uint32_t k = tid; k < rpw; k += bs) { tok[k] = 0; tokc[k] = 0; }   // (a row no token claims -- corrupted counters only -- reads token 0)
         mw_lds_barrier();
         // all tokens' counters: which land in this workgroup's rows, how many groups start before
-        // its first row, how many groups there are (sixteen counters per lane in flight)
+        // its first row, how many groups there are (eight counters per lane in flight)
         uint32_t starts_before = 0, starts_total = 0;
         for (uint32_t t0 = 0; t0 < T; t0 += kInFlight * bs) {
             unsigned long long cc[kInFlight];

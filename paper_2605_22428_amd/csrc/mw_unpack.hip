@@ -523,7 +523,7 @@ __device__ __forceinline__ void recv_index_body(const mw_index_args &a, const ui
 }
 
 // Workgroup w of the index of a batch that rides in a launch of row movers: a row a lane at a time,
-// nothing kept between the passes, which fits 58 vector registers without scratch (see k_expand_index_next).
+// nothing kept between the passes, which fits 57 vector registers without scratch (see k_expand_index_next).
 template <int kForm>
 __device__ __forceinline__ void recv_index_rider(const mw_index_args &a, const uint32_t w)
 {
@@ -941,7 +941,7 @@ __global__ __launch_bounds__(1024) void k_expand(
 // with any scratch at all, the dispatcher refills the movers' wave slots more slowly (rocprofv3:
 // SPI_RA_VGPR_SIMD_FULL_CSN and SPI_RA_TMP_STALL_CSN appear, occupancy 7 % down; fp8 step 94.9
 // against 87.4 us with the riders compiled out).  The riders therefore come in a lean form that fits
-// 58 registers without spilling (a row a lane at a time in the index, eight counters in flight in the
+// 57 registers without spilling (a row a lane at a time in the index, eight counters in flight in the
 // plan's second half); batches too small to hide them give them launches of their own.  kFormMany (top_k
 // above eight) spills five: beside 61 us of movers 65 us against 72 with the index in front, beside 22
 // us 22.6 against 34.4.
