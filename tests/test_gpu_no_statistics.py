@@ -4,6 +4,7 @@ expected.  Row movers then stride over a grid sized for the expectation, and the
 its form on the GPU from the peers' counts.  Against the oracle's plain definition, bit-exact."""
 import numpy as np
 import pytest
+import torch
 
 from oracle import ref
 from paper_2605_22428_amd import binding as B
@@ -106,3 +107,38 @@ def test_unpack_and_combine_of_a_favoured_rank(hidden, R, max_tokens, rows):
     H.check_unpack(_received(ctx, buf), want)
     back = np.concatenate([H.host(r["rows"])[: r["n_rows"]] for r in recs])
     H.assert_same_bytes(H.host(ret)[: len(back)], back, "returned rows")
+
+
+def test_replayed_small_steps_choose_by_the_counts_of_each_replay():
+    """One captured launch, replayed with the peers' records rewritten in between: few rows, more than the one-workgroup
+    index takes, few again."""
+    R, E, K, max_tokens, my_rank, hidden = 8, 32, 4, 2000, 3, 64
+    print("captured step without statistics", flush=True)
+    rng = np.random.default_rng(77)
+    e2r = (np.arange(E) * R // E).astype(np.int32)
+    cur, nxt, maker = (B.Context(R, E, K, my_rank, hidden, B.MW_ROW_BF16, max_tokens, R * max_tokens, e2r, device=H.DEV) for _ in range(3))
+    batches = [_batch(rng, maker, R, E, K, my_rank, hidden, c) for c in ([5] * R, [1500] * R, [128] * R, [900, 0, 0, 125, 0, 0, 0, 0], [2] * R)]
+    tables = [B.peers_table(b[0], H.DEV) for b in batches]
+    cap = max(b[1] for b in batches)
+    a, b, table = B.RecvBuffers(cur, cap), B.RecvBuffers(nxt, cap), tables[0].clone()
+    cur.mw_unpack_index(tables[0], R, cap, a.expert_offsets, a.stats)
+
+    def step():
+        cur.mw_unpack_expand_index_next(R, a.out_rows, None, cap, a.out_src_peer, a.out_src_token, nxt, table, R, cap, b.expert_offsets,
+                                        b.stats)
+        nxt.mw_unpack_expand(R, b.out_rows, None, cap, b.out_src_peer, b.out_src_token)
+
+    step()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        step()
+    for i in (0, 1, 2, 3, 1, 4):
+        table.copy_(tables[i])
+        b.out_rows.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        stats = np.frombuffer(H.host(b.stats).tobytes(), dtype=B.RECV_STATS_DTYPE)[0]     # (mw_get_recv_stats would be the hint)
+        gu = H.GpuUnpack.__new__(H.GpuUnpack)
+        gu.ctx, gu.buf, gu.stats, gu.Q = nxt, b, stats, int(stats["n_out_rows"])
+        H.check_unpack(gu, batches[i][2], "replay of batch %d" % i)
