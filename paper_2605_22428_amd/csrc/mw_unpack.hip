@@ -102,7 +102,6 @@ struct mw_index_args {
     uint32_t parts;     // workgroups per peer: part j takes the expert chunks j, j + parts, ... of Lc experts each
     uint32_t row_parts; // ... times this many: all of them mark every row, each ranks and writes its share of the rows
     uint32_t tab_words; // LDS words of the table of local slots (0: the rank table in memory is looked up)
-    uint32_t row_limit; // more received rows than this are left to the other form of k_small_step's index (0: there is none)
 };
 
 constexpr uint32_t kNotLocal = 0xffu;     // table entry of an expert that lives elsewhere; local slots are below 255
@@ -552,6 +551,9 @@ __global__ __launch_bounds__(kIndexBlock) void k_recv_index(const mw_index_args 
 constexpr int kSmallPeers = 256;                      // peers of the one-workgroup index (their records are scanned by four waves)
 constexpr int kSmallIndexLds = 40960;                 // LDS bytes of the one-workgroup index
 constexpr int kSmallLanes = kSmallPlanLanes;          // lanes of the small launches' workgroups (index: one or two rows a lane up to 1024 rows)
+// Rows up to which a small step's index is one workgroup's: two a lane.  Where there were more, or may be more because nobody
+// has said how many, the launch has both forms.
+constexpr uint32_t kEitherRows = 2 * kSmallLanes;
 
 static inline size_t mw_small_index_lds_words(int P, int L, int tab, uint32_t wpl, uint32_t max_tokens, uint32_t cap_rows)
 {
@@ -561,7 +563,8 @@ static inline size_t mw_small_index_lds_words(int P, int L, int tab, uint32_t wp
 }
 
 // kSmallRows: rows (and descriptors) a lane keeps in registers; further ones go through memory.
-template <int kSmallRows>
+// kLimit: more received rows than this (0: any number) are left to the launch's other form.
+template <int kSmallRows, uint32_t kLimit = 0>
 __device__ __forceinline__ void recv_index_small(const mw_index_args &a, uint32_t *lds)
 {
     const uint32_t tid = threadIdx.x, nthr = blockDim.x;
@@ -610,7 +613,7 @@ __device__ __forceinline__ void recv_index_small(const mw_index_args &a, uint32_
         if (in_lds && e < E) tab[e] = tab_r[j];
     }
     mw_lds_barrier();
-    if (a.row_limit != 0 && scratch[0] + scratch[1] + scratch[2] + scratch[3] > a.row_limit) return;
+    if (kLimit != 0 && scratch[0] + scratch[1] + scratch[2] + scratch[3] > kLimit) return;
     if (tid < P) {
         uint32_t before = n_inc - nq, dbefore = d_inc - dq;
         for (uint32_t w = 0; w < (tid >> 6); ++w) { before += scratch[w]; dbefore += scratch[4 + w]; }
@@ -1016,7 +1019,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
 // (mw_small_plan, the plan of mw_plan_pack) -- then the packer's rows
 // and the expander's.  At these sizes the step is the riders' chain of memory round trips, and the
 // forms that spread a batch over workgroups spend half of theirs on talking to one another.
-// kEither: nobody has said how many rows the peers hold.  One workgroup takes 9.5 us for every 1024 of them, so the
+// kEither: the peers hold more than 1024 rows, or may, since nobody has said.  One workgroup takes 9.5 us for every 1024, so the
 // launch has the riders of recv_index_body too (grid rows from general_row on), and whoever is not needed
 // leaves: the choice is made here, from the peers' own counts (64 ranks, rows of 7168, us a step without / with: 64 tokens
 // that all come here 43.2 / 28.4, fp8 38.1 / 16.9; 200 of 256 tokens, fp8 124 / 44; an even share of 64 tokens 10.4 / 9.1.)
@@ -1056,13 +1059,13 @@ __global__ __launch_bounds__(kSmallLanes) void k_small_step(
 #pragma unroll
             for (int v = 0; v < kSmallLanes / 64; ++v) rows += wave_n[v];
             mw_lds_barrier();                                  // (the index uses the same words)
-            if (rows > next.row_limit) recv_index_rider<kFormMany>(general, w);
+            if (rows > kEitherRows) recv_index_rider<kFormMany>(general, w);
             return;
         }
     }
     if (blockIdx.x != 0) return;
     if (blockIdx.y == 0) {
-        recv_index_small<kRows>(next, (uint32_t *)small_lds);
+        recv_index_small<kRows, kEither ? kEitherRows : 0>(next, (uint32_t *)small_lds);
         return;
     }
     mw_small_plan<W, kKeyed>(plan.topk, plan.T, plan.K, plan.eslot, plan.E, plan.row_bytes, plan.mask_out, plan.perm,
@@ -1205,7 +1208,7 @@ static bool make_index_args(mw_ctx *ctx, const void *peers, bool packets, int32_
                        (uint32_t)c.max_tokens, wpl, (uint32_t)c.max_recv_rows,
                        (uint64_t)(packets ? hb + ctx->row_bytes : ctx->row_stride), hb, cap,
                        ctx->d_cnt, ctx->d_row_base, ctx->d_addr_cnt, ctx->d_recs, ctx->d_hits, ctx->d_base,
-                       expert_offsets, stats, ctx->d_flags, dedup, n_chunks < max_parts ? n_chunks : max_parts, 1u, tab_words, 0u};
+                       expert_offsets, stats, ctx->d_flags, dedup, n_chunks < max_parts ? n_chunks : max_parts, 1u, tab_words};
     return true;
 }
 
@@ -1292,13 +1295,12 @@ static size_t small_index_lds(const mw_ctx *ctx, int32_t P, mw_index_args *a)
     return 4 * (words + a->tab_words) + 16;
 }
 
-// rows a lane of the one-workgroup index keeps in registers: one, two or four, for as many received rows
-// as the context saw last time, if the caller has asked for the statistics, else for all there can be.  (448
-// rows: with two 8.3 us, with one 7.6.)  More rows than that go through memory.
-static int small_index_rows(const mw_ctx *ctx, int32_t P)
+// Rows that a small step's index has to reckon with: as many as the context saw last time, if the caller has asked
+// for the statistics, else all there can be.  The one-workgroup index keeps one or two of them a lane in registers (448 rows: with
+// two 8.3 us, with one 7.6); more go through memory.
+static int64_t small_index_rows(const mw_ctx *ctx, int32_t P)
 {
-    const int64_t rows = ctx->recv_rows_hint > 0 ? ctx->recv_rows_hint : (int64_t)P * ctx->cfg.max_tokens;
-    return rows <= kSmallLanes ? 1 : rows <= 2 * kSmallLanes ? 2 : 4;
+    return ctx->recv_rows_hint > 0 ? ctx->recv_rows_hint : (int64_t)P * ctx->cfg.max_tokens;
 }
 
 int32_t mw_launch_unpack_index(mw_ctx *ctx, const void *peers, bool packets, int32_t P, int64_t cap,
@@ -1389,16 +1391,12 @@ int32_t mw_launch_unpack_expand(mw_ctx *ctx, int32_t P, void *out_rows, float *o
     return MW_OK;
 }
 
-// Rows up to which the one-workgroup index is used where nobody has said how many there will be: two a lane.
-// (940 rows: 13.0 us against 10.9 of a workgroup a peer, but nothing has to be cleared, counted or waited for.)
-constexpr int kEitherRows = 2 * kSmallLanes;
-
 // The riders of k_small_step beside its one-workgroup index (false: they are not needed).  *fits: both forms can be had.
 static bool small_step_riders(mw_ctx *next, const void *peers, int32_t P, int64_t cap, int64_t *expert_offsets,
                               mw_recv_stats *stats, mw_index_args *general, size_t *lds, bool *fits)
 {
     *fits = true;
-    if (next->recv_rows_hint > 0 || (int64_t)P * next->cfg.max_tokens <= kEitherRows) return false;
+    if (small_index_rows(next, P) <= (int64_t)kEitherRows) return false;
     const uint32_t words = kSmallIndexLds / 4;
     *fits = make_index_args(next, peers, false, P, cap, expert_offsets, stats, words, words, 1, kMaxIndexParts, general, lds) &&
             index_form(*general) != kFormAny;
@@ -1463,16 +1461,13 @@ static int32_t launch_small_step(mw_ctx *ctx, int32_t P, void *out_rows, float *
     size_t lds_general = 0;
     bool fits;
     const bool either = small_step_riders(next, a.peers, a.P, a.out_cap, a.expert_offsets, a.stats, &general, &lds_general, &fits);
-    if (either) {
-        ai.row_limit = kEitherRows;
-        if (lds < lds_general) lds = lds_general;
-    }
+    if (either && lds < lds_general) lds = lds_general;
     const uint32_t riders = general_row + (either ? (index_riders(general) + (uint32_t)nseg - 1) / (uint32_t)nseg : 0u);
     const dim3 grid(nseg, riders + n_pack_rows + gy), block(kSmallLanes);
     const uint32_t cap32 = (uint32_t)(cap < 0x7fffffffLL ? cap : 0x7fffffffLL);
     {
         mw_timed tm(ctx, MW_KERNEL_EXPAND, s);
-        const int rows = small_index_rows(next, a.P);
+        const bool one_row = small_index_rows(next, a.P) <= kSmallLanes;
 #define MW_SMALL_(W_, KEYED_, ROWS_, EITHER_)                                                                          \
     hipLaunchKernelGGL((k_small_step<W_, KEYED_, ROWS_, EITHER_>), grid, block, lds, s, riders, riders + n_pack_rows, ctx->d_recs, \
                        ctx->d_row_base, P, xc, pa.perm, pa.stats, sc, ctx->hit_slots, ctx->d_base, ctx->d_hits,         \
@@ -1480,9 +1475,8 @@ static int32_t launch_small_step(mw_ctx *ctx, int32_t P, void *out_rows, float *
 #define MW_SMALL(W_, KEYED_)                                                                                           \
     do {                                                                                                               \
         if (either) MW_SMALL_(W_, KEYED_, 2, true);                                                                    \
-        else if (rows == 1) MW_SMALL_(W_, KEYED_, 1, false);                                                           \
-        else if (rows == 2) MW_SMALL_(W_, KEYED_, 2, false);                                                           \
-        else MW_SMALL_(W_, KEYED_, 4, false);                                                                          \
+        else if (one_row) MW_SMALL_(W_, KEYED_, 1, false);                                                             \
+        else MW_SMALL_(W_, KEYED_, 2, false);                                                                          \
     } while (0)
         if (keyed) MW_SMALL(4, true);
         else if (W == 1) MW_SMALL(1, false);
