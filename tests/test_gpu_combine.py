@@ -153,3 +153,49 @@ def test_refused_for_other_row_formats_and_bounded_by_capacity():
     H.assert_same_bytes(got[:short], want[:short], "rows below the return capacity")
     assert np.all(got[short:] == 0x1234)
     ctx.close()
+
+
+@pytest.mark.parametrize("K", [1, 2, 3, 4, 5, 8])
+@pytest.mark.parametrize("part", [1.0, 0.5, 0.0])
+def test_hits_in_threes_and_outputs_dropped_for_capacity(K, part):
+    """Rows of one to K local experts (hit slots are taken two at a time behind the first), with the expert outputs from
+    `part` of the rows on beyond y's capacity: those add nothing, whichever of a row's hits they are.  The sums are
+    float32 additions in hit order with one rounding at the end, so the comparison is of bits."""
+    w = W.DispatchWorkload("threes", 75, 2, 2 * K + 2, K, 90, 136, "bf16", "uniform")
+    e2r, my_rank = W.expert_to_rank(w), 0
+    ctx = H.make_ctx(w, my_rank)
+    recs, toks, ids = [], [], []
+    for p in range(w.n_ranks):
+        tk = W.topk_ids(w, 5, p); x, _ = W.payload_rows(w, 5, p)
+        recs.append(H.shrink(H.GpuSend(ctx, tk, x, None).deliver(my_rank)))
+        toks.append((tk, x, None))
+    m = sum(r["n_rows"] for r in recs)
+    full = max(1, m * K)
+    plain = ref.dispatch_plain(toks, e2r, my_rank, full)
+    gu = H.GpuUnpack(ctx, recs, full)
+    H.check_unpack(gu, plain, "dispatch before the way back")
+    y = W.f32_to_bf16_bits(np.random.default_rng(K).standard_normal((gu.Q, w.hidden), dtype=np.float32))
+    cap = int(gu.Q * part)
+    mine = np.nonzero(e2r == my_rank)[0]
+    at = {}
+    for l, e in enumerate(mine):
+        for q in range(int(plain[4][l]), int(plain[4][l + 1])):
+            at[int(e), int(plain[2][q]), int(plain[3][q])] = q
+    want = np.full((m, w.hidden), 0x1234, dtype=np.uint16)
+    i = 0
+    for p, r in enumerate(recs):
+        for s in H.host(r["row_src_token"])[: r["n_rows"]]:
+            pos = [at[int(e), p, int(s)] for e in toks[p][0][int(s)] if e2r[e] == my_rank]
+            acc = None
+            for q in pos:
+                if q < cap:
+                    v = bf16_value(y[q])
+                    acc = v if acc is None else acc + v
+            if acc is not None:
+                want[i] = W.f32_to_bf16_bits(acc)
+            i += 1
+    ret = torch.full((max(m, 1), w.hidden), 0x1234, dtype=torch.int16, device=H.DEV)
+    ctx.mw_combine_gather(len(recs), H.dev(y), cap, ret, m)
+    torch.cuda.synchronize()
+    H.assert_same_bytes(H.host(ret).view(np.uint16)[:m], want, "returned rows")
+    ctx.close()
