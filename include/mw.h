@@ -250,7 +250,7 @@ MW_API int32_t mw_plan(mw_ctx *ctx, const int32_t *topk_ids_dev, int32_t n_token
  * mw_plan_static: mw_plan for callers that cannot allocate device memory or keep a workspace
  * around -- code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.
  * No context and no workspace: the plan's scratch memory (per-token counters, plan state, the
- * expert table, sort keys; 136704 bytes) is one array inside the library's device image, which every GPU the
+ * expert table, sort keys; 144896 bytes) is one array inside the library's device image, which every GPU the
  * library runs on holds until the process ends.  The call allocates and frees nothing, on the
  * host or on the device, and enqueues kernels only (one small one that clears the scratch and
  * builds the expert table, then mw_plan's own).

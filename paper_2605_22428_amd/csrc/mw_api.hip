@@ -18,7 +18,7 @@ namespace {
 
 struct ws_layout {
     int64_t eslot, plan_cnt, plan_state, flags, cnt, base, row_base, addr_cnt, recs, hits, row_map,
-        hop_bits, group_of_row, child_pos, plan_keys, sort_key, sort_sec, chunk_kept, row_cnt, row_start, total;
+        hop_bits, group_of_row, child_pos, plan_keys, plan_idx, sort_key, sort_sec, chunk_kept, row_cnt, row_start, total;
 };
 
 }  // namespace
@@ -102,9 +102,12 @@ ws_layout layout(const mw_config &c, int32_t L)
         w.group_of_row = o; o += mw_align_up(4LL * ntok, A);
         w.child_pos = o;    o += mw_align_up(4LL * MW_MAX_HOPS * ntok, A);
     }
-    // keys of the plan's two-launch form (batches up to 8192 tokens), a flag word per workgroup that makes them behind
+    // keys of the plan's two-launch form (batches up to 8192 tokens), a flag word per workgroup that makes them behind; their
+    // tokens, a byte each
     w.plan_keys = o;
     o += mw_align_up(8LL * (ntok < kPlanOrderMax ? ntok : kPlanOrderMax), A) + A;
+    w.plan_idx = o;
+    o += mw_align_up(ntok < kPlanOrderMax ? ntok : kPlanOrderMax, A);
     // sorted chunks and row-indexed arrays for the plan of large batches (only contexts that can see such batches)
     w.sort_key = w.sort_sec = w.chunk_kept = w.row_cnt = w.row_start = -1;
     const int64_t padded = mw_align_up(ntok, 1024);
@@ -166,6 +169,7 @@ MW_API int32_t mw_ctx_create(const mw_config *cfg, void *workspace_dev, int64_t 
     ctx->d_plan_cnt = (uint64_t *)(b + w.plan_cnt);
     ctx->d_plan_state = (uint32_t *)(b + w.plan_state);
     ctx->d_plan_keys = (uint64_t *)(b + w.plan_keys);
+    ctx->d_plan_idx = (uint8_t *)(b + w.plan_idx);
     ctx->d_plan_bad = (uint32_t *)(b + w.plan_keys + mw_align_up(8LL * (cfg->max_tokens < 1 ? 1 : cfg->max_tokens < kPlanOrderMax ? cfg->max_tokens : kPlanOrderMax), 256));
     ctx->d_sort_key = w.sort_key >= 0 ? (uint64_t *)(b + w.sort_key) : nullptr;
     ctx->d_sort_sec = w.sort_sec >= 0 ? (uint32_t *)(b + w.sort_sec) : nullptr;

@@ -75,6 +75,7 @@ struct mw_ctx {
     uint64_t *d_plan_cnt;       // [max_tokens] packed per-token counters; zero between plans
     uint32_t *d_plan_state;     // [MW_PLAN_STATE_WORDS] rows per destination, kept tokens, flags, workgroups done; zero between plans
     uint64_t *d_plan_keys;      // [min(max_tokens, 8192)] keys of the plan's two-launch form
+    uint8_t *d_plan_idx;        // [min(max_tokens, 8192)] their tokens
     uint32_t *d_plan_bad;       // [64] its workgroups that saw an id outside the range
     uint64_t *d_sort_key;       // [max_tokens rounded up to 1024] sorted chunks of the large-batch plan (or null)
     uint32_t *d_sort_sec;       // same count: second sort word

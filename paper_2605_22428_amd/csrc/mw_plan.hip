@@ -10,7 +10,7 @@
 // No host synchronisation, launches on the caller's stream only:
 //   k_plan_order  batches of up to 8192 tokens whose bitmaps have a 64-bit key (one word, or at most
 //                 eight ids a token): every workgroup holds all keys and finishes a few tokens, nothing is
-//                 exchanged between workgroups.  Above 2048 tokens k_plan_keys makes the keys first.
+//                 exchanged between workgroups.  Above 2048 tokens k_plan_keys makes and sorts the keys first.
 //   k_rank        otherwise (several words, more than eight ids): a workgroup owns 256 tokens and a
 //                 slice of all tokens.  It builds the bitmaps of both from the top-k ids (one lane per
 //                 token; the slice goes to LDS), then every lane counts, over the slice, the tokens whose
@@ -191,24 +191,27 @@ __global__ __launch_bounds__(kBlock) void k_groups(const uint64_t *__restrict__ 
 
 // ---- the plan of a batch whose bitmaps have a 64-bit order-preserving key, at most 8192 tokens -------
 // (bitmaps of one word, or of up to eight ranks anywhere: top_k <= 8.)  Every workgroup holds the keys of ALL
-// tokens, a few a lane in registers, and finishes the tokens [wg n_own, wg n_own + n_own) by itself:
+// tokens, a few a lane in registers, and finishes n_own of them by itself:
 //   packed row   the number of tokens with (key, index) below: one 64-bit compare per 64 tokens, whose
-//                result mask is counted by scalar instructions;
-//   group index  the number of DISTINCT keys below: a hash table in LDS makes one token of every key its
-//                representative, and the same compare masks are counted under the representatives' mask.
+//                result mask is counted by scalar instructions, or searches in sorted chunks of keys;
+//   group index  the number of DISTINCT keys below: one token of every key is made its representative, and
+//                the same compares or searches count the representatives.
 // So no workgroup waits for another, nothing is summed up in global memory, nothing has to be cleared and
 // one launch does it all; what it costs is that the keys are made once per workgroup.  Up to kKeysFrom
-// tokens each workgroup makes them from the ids; beyond, a first launch makes them once
+// tokens each workgroup makes them from the ids; beyond, a first launch makes them once and sorts them in chunks
 // (k_plan_keys) and the workgroups only load them: 8 instead of 4 top_k bytes a token, no look-ups.
-// Bound by latency (a dependent instruction 3.4 ns, a block barrier with its LDS traffic about 0.1 us).
+// Bound by latency and, from 4096 tokens on, by the instructions that all workgroups repeat (a dependent instruction 3.4
+// ns, a block barrier with its LDS traffic about 0.1 us): of 15 us for 8192 tokens 3.4 are the first launch, 2 load and
+// clear, 5 find the representatives and count ranks, 2 write the chunks, 2 search them.
 // Before, with per-slice counts joined by global atomics and a second launch that inverted them (mw_plan
-// alone, us): 1000 tokens 15.0 -> 7.4, 2048 15.8 -> 8.8, 4096 19.2 -> 12.3, 8192 33.9 -> 21.3 (256 ranks 37.3 -> 21.8).
+// alone, us): 1000 tokens 15.0 -> 5.4, 2048 15.8 -> 8.7, 4096 19.2 -> 10.8, 8192 33.9 -> 15.1 (256 ranks 37.3 -> 16.0).
 //
 // The key of a multi-word bitmap: its rank positions, highest first, a byte each; the highest as it
 // is, the others plus one (they are at most 254, since a higher one precedes them), zero for "no further
 // rank".  Comparing keys is comparing the bitmaps as numbers, and different bitmaps have different
 // keys.  The key of a one-word bitmap is the word.
 constexpr int kOrderBlock = 1024, kOrderMaxTokens = kPlanOrderMax, kOwnMax = 32;
+constexpr int kOrderChunks = 64, kFilterBits = 32;       // (sorted) chunks of 8192 tokens; bits of each of the hash table's bitmaps for one slot
 
 template <bool kBytes> struct mw_order_key {
     // a value no kept token's key has: marks free slots of the hash table.  (One word: 0 is the empty
@@ -321,21 +324,6 @@ __device__ __forceinline__ void keys_of_ids(int32_t (&e)[kN][8], const int32_t *
     for (int n = 0; n < kN; ++n) if (t + n * stride >= T) key[n] = mw_order_key<kBytes>::kNone;
 }
 
-// Bucket of a key among kBuckets, never decreasing with the key, fine where keys are dense: up to twelve ranks
-// the bitmap itself, up to 24 the highest rank and the six bits below it, beyond (few of many ranks
-// named) the two highest ranks; of a byte key the highest rank and the upper half of the second's byte.
-constexpr int kBuckets = 4096;
-template <bool kBytes>
-__device__ __forceinline__ uint32_t bucket_of(uint64_t key, int R)
-{
-    if constexpr (kBytes) return (uint32_t)(key >> 52);
-    if (R <= 12) return (uint32_t)key & (kBuckets - 1u);
-    const int h = 63 - __clzll((long long)(key | 1ull));
-    const uint64_t rest = key & ~(1ull << h);
-    if (R <= 24) return (uint32_t)h * 64u + (uint32_t)((h >= 6 ? rest >> (h - 6) : rest << (6 - h)) & 63ull);
-    return (uint32_t)h * 64u + (rest ? 64u - (uint32_t)__clzll((long long)rest) : 0u);
-}
-
 // LDS table of rank + 1 per expert: needs (E + 1) halfwords; entry E is 0.
 __device__ __forceinline__ void fill_rank_table(uint16_t *tab, const int32_t *__restrict__ eslot, int E)
 {
@@ -346,123 +334,243 @@ __device__ __forceinline__ void fill_rank_table(uint16_t *tab, const int32_t *__
 }
 constexpr int kTableExperts = 4095;        // experts of the LDS table (8 KiB); more: look-ups in memory
 
-// First launch of the two-launch form: a token a lane.  bad[wg]: one of its ids was outside [0, E).
-constexpr int kKeysBlock = 128;
+// First launch of the two-launch form: the keys of kChunkTokens tokens in (key, token) order, one below its value where a key
+// is a bitmap (tokens without a destination then have ~0 in both kinds and come last), idx[i] the token of place i
+// inside the chunk.  A chunk is ordered by counting: four lanes a token, each comparing it with 32 keys that all lanes read at
+// once.  bad[wg]: one of the workgroup's ids was outside [0, E).
+constexpr int kChunkTokens = 128, kKeysBlock = 4 * kChunkTokens;
 template <bool kBytes>
 __global__ __launch_bounds__(kKeysBlock) void k_plan_keys(const int32_t *__restrict__ topk, int T, int K,
                                                           const int32_t *__restrict__ eslot, int E,
-                                                          uint64_t *__restrict__ keys, uint32_t *__restrict__ bad_out)
+                                                          uint64_t *__restrict__ keys, uint8_t *__restrict__ idx,
+                                                          uint32_t *__restrict__ bad_out)
 {
     extern __shared__ uint64_t keys_lds[];
     uint16_t *tab = E <= kTableExperts ? (uint16_t *)keys_lds : nullptr;
+    __shared__ __align__(16) uint64_t val[kChunkTokens];
+    __shared__ uint32_t below[4][kChunkTokens];
     __shared__ uint32_t any_bad;
     if (threadIdx.x == 0) any_bad = 0;
-    const int t = blockIdx.x * kKeysBlock + threadIdx.x;
+    const int i = threadIdx.x & (kChunkTokens - 1);
+    const int part = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kChunkTokens);
+    const int t = blockIdx.x * kChunkTokens + i;
     int32_t e[1][8];
-    load_ids<1>(topk, T, K, 0, t, 0, e);
+    if (part == 0) load_ids<1>(topk, T, K, 0, t, 0, e);
     if (tab) fill_rank_table(tab, eslot, E);
     mw_lds_barrier();
-    uint64_t key[1];
-    bool bad = false;
-    keys_of_ids<kBytes, 1>(e, topk, T, K, eslot, E, tab, t, 0, key, bad);
-    if (t < T) keys[t] = key[0];
-    if (bad) any_bad = 1;
+    uint64_t v = 0;
+    if (part == 0) {
+        uint64_t key[1];
+        bool bad = false;
+        keys_of_ids<kBytes, 1>(e, topk, T, K, eslot, E, tab, t, 0, key, bad);
+        v = kBytes ? key[0] : key[0] - 1u;
+        val[i] = v;
+        if (bad) any_bad = 1;
+    }
     mw_lds_barrier();
+    if (part != 0) v = val[i];
+    {
+        const ulonglong2 *q = (const ulonglong2 *)(val + part * 32);
+        const int half = __builtin_amdgcn_readfirstlane(i >> 6);             // the wave's tokens are one half of the chunk
+        uint32_t n = 0;
+        if ((part >> 1) < half) {                                            // keys of earlier tokens: equal ones count
+#pragma unroll
+            for (int u = 0; u < 16; ++u) { const ulonglong2 x = q[u]; n += (x.x <= v ? 1u : 0u) + (x.y <= v ? 1u : 0u); }
+        } else if ((part >> 1) > half) {
+#pragma unroll
+            for (int u = 0; u < 16; ++u) { const ulonglong2 x = q[u]; n += (x.x < v ? 1u : 0u) + (x.y < v ? 1u : 0u); }
+        } else {
+#pragma unroll
+            for (int u = 0; u < 16; ++u) {
+                const ulonglong2 x = q[u];
+                const int j = part * 32 + 2 * u;
+                n += (x.x < v || (x.x == v && j < i) ? 1u : 0u) + (x.y < v || (x.y == v && j + 1 < i) ? 1u : 0u);
+            }
+        }
+        below[part][i] = n;
+    }
+    mw_lds_barrier();
+    if (part == 0 && t < T) {
+        const uint32_t at = blockIdx.x * kChunkTokens + below[0][i] + below[1][i] + below[2][i] + below[3][i];
+        keys[at] = v;
+        idx[at] = (uint8_t)i;
+    }
     if (threadIdx.x == 0) bad_out[blockIdx.x] = any_bad;
 }
 
-// kU: tokens a lane holds (T <= kU blockDim.x).  kFromKeys: keys and bad[n_bad] come from k_plan_keys.
+// kU: tokens a lane holds (T <= kU blockDim.x).
+// kSorted: keys, idx and bad[n_bad] come from k_plan_keys, and what counts the keys below a token's is a binary search in every
+// chunk, a lane a chunk: 64 chunks of 8192 tokens cost a wave eight LDS reads a lane, however the keys are spread.  A wave holds
+// whole chunks, so a running count of the representatives inside a chunk turns the same searches into the group index.
+// (With the keys counted into 4096 buckets and a token compared with its bucket, 8192 tokens of 256 ranks with skewed ids
+// spent 7 us in the buckets' atomics, 2 in their scan and 6 in the compares of 24; the searches take 2.)
 // pstate: only its flag word is looked at (mw_plan_static reports bad table entries there).
-// kByBucket: keys are first counted into buckets (LDS), the bucket's start gives most of a token's packed row and group
-// index, and only the keys of its own bucket are compared with it -- where a workgroup's tokens times all
-// tokens would be the time (8192 tokens: 34 us of compares).
-template <bool kBytes, int kU, bool kFromKeys, bool kByBucket>
+template <bool kBytes, int kU, bool kSorted>
 __global__ __launch_bounds__(kOrderBlock) void k_plan_order(
     const int32_t *__restrict__ topk, int T, int K, const int32_t *__restrict__ eslot, int E, int R, int n_own, int slots_log,
-    const uint64_t *__restrict__ keys, const uint32_t *__restrict__ bad_in, int n_bad, const uint32_t *__restrict__ pstate,
+    const uint64_t *__restrict__ keys, const uint8_t *__restrict__ idx, const uint32_t *__restrict__ bad_in, int n_bad,
+    const uint32_t *__restrict__ pstate,
     uint64_t row_bytes, uint64_t *__restrict__ mask_out, int32_t *__restrict__ perm, mw_group_desc *__restrict__ desc,
     mw_send_stats *__restrict__ stats)
 {
     constexpr uint64_t kNone = mw_order_key<kBytes>::kNone;
     extern __shared__ __align__(16) uint64_t order_lds[];
-    unsigned long long *slot = (unsigned long long *)order_lds;       // [1 << slots_log] hash table of keys
     const uint32_t n_slots = 1u << slots_log;
-    uint64_t *own = order_lds + n_slots;                              // [kOwnMax]          keys of this workgroup's tokens
+    // [1 << slots_log] hash table of keys, (sorted) two bitmaps of kFilterBits bits a slot in front of it
+    const uint32_t filter_words = kSorted ? n_slots * kFilterBits / 32 : 0;
+    uint32_t *taken = (uint32_t *)order_lds, *shared = taken + filter_words;
+    unsigned long long *slot = (unsigned long long *)(shared + filter_words);
+    uint64_t *own = (uint64_t *)(slot + n_slots);                     // [kOwnMax]          keys of this workgroup's tokens
     uint2 *part = (uint2 *)(own + kOwnMax);                           // [16][kOwnMax]      the waves' counts for them
     uint32_t *wave_n = (uint32_t *)(part + 16 * kOwnMax);             // [16][4]            kept, distinct, destinations, bad
     uint32_t *wave_r = wave_n + 64;                                   // [16][4]            tokens that name rank r
-    uint32_t *bins = wave_r + 64;                                     // [kBuckets]         (by bucket) tokens and representatives
-    uint16_t *tab = kFromKeys || E > kTableExperts ? nullptr : (uint16_t *)(bins + (kByBucket ? kBuckets : 0));
+    uint32_t *in_chunk = wave_r + 64;                                 // [kOrderChunks]     (sorted) a chunk's kept tokens
+    uint16_t *tab = kSorted || E > kTableExperts ? nullptr : (uint16_t *)(wave_r + 64);
     const int tid = threadIdx.x, bs = blockDim.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), n_wave = bs >> 6;
+    // This workgroup's tokens: t0 .. t0 + n_own - 1, or (sorted) those in these places of the chunks.
     const int wg = blockIdx.x, n_wg = gridDim.x, t0 = wg * n_own;
-    __shared__ uint32_t scan[kByBucket ? 17 : 1];
+    // token or place of the lane's key j (sorted: chunk wave + 16 (j / 2), its first or second half)
+    auto at_of = [&](int j) __attribute__((always_inline)) {
+        return kSorted ? (wave + 16 * (j >> 1)) * kChunkTokens + (j & 1) * 64 + lane : tid + j * bs;
+    };
 
     uint64_t key[kU];
-    int32_t e[kFromKeys ? 1 : kU][8];
+    int32_t e[kSorted ? 1 : kU][8];
     bool bad = false;
-    if constexpr (kFromKeys) {
+    uint32_t own_idx = 0;
+    if constexpr (kSorted) {
 #pragma unroll
-        for (int j = 0; j < kU; ++j) key[j] = tid + j * bs < T ? keys[tid + j * bs] : kNone;
+        for (int j = 0; j < kU; ++j) key[j] = keys[min(at_of(j), T - 1)];
+        if (tid < n_own && t0 + tid < T) own_idx = idx[t0 + tid];
         bad = wg == 0 && tid < n_bad && bad_in[tid] != 0;
     } else if (T > 0) {
         load_ids<kU>(topk, T, K, 0, tid, bs, e);
     }
     if (tab) fill_rank_table(tab, eslot, E);
-    for (uint32_t s = tid; s < n_slots / 2; s += bs) ((ulonglong2 *)slot)[s] = make_ulonglong2(kNone, kNone);
-    if constexpr (kByBucket) for (uint32_t b = tid; b < kBuckets / 4; b += bs) ((uint4 *)bins)[b] = make_uint4(0, 0, 0, 0);
+    const bool own_bit = kSorted && !kBytes && R <= 5 + slots_log;    // (a bitmap of R ranks is below 32 << slots_log)
+    if (!own_bit) for (uint32_t s = tid; s < n_slots / 2; s += bs) ((ulonglong2 *)slot)[s] = make_ulonglong2(kNone, kNone);
+    for (uint32_t w = tid; w < filter_words / (own_bit ? 4 : 2); w += bs) ((uint4 *)taken)[w] = make_uint4(0, 0, 0, 0);
     mw_lds_barrier();
-    if constexpr (!kFromKeys) {
+    if constexpr (!kSorted) {
         if (T > 0) {
             keys_of_ids<kBytes, kU>(e, topk, T, K, eslot, E, tab, tid, bs, key, bad);
         } else {                                                      // an empty batch has no ids to read
 #pragma unroll
             for (int j = 0; j < kU; ++j) key[j] = kNone;
         }
+    } else {
+#pragma unroll
+        for (int j = 0; j < kU; ++j) key[j] = at_of(j) >= T ? kNone : kBytes ? key[j] : key[j] + 1u;
     }
 #pragma unroll
     for (int j = 0; j < kU; ++j) {
-        const int o = tid + j * bs - t0;
+        const int o = at_of(j) - t0;
         if (o >= 0 && o < n_own) own[o] = key[j];
     }
 
-    // ---- one representative per distinct key: the token whose key takes the slot.  A lane's probes go out together,
-    // round after round until the longest chain has ended (at least half of the slots stay free).  A wave whose
-    // tokens all have one key sends one lane: thousands of compare-and-swaps on one address would queue.
+    // ---- one representative per distinct key.
+    // Sorted: equal keys of a wave are neighbours, and the first of them stands for all.  Most keys are nobody else's, and a
+    // bit tells: 32 a token, and who finds his taken marks it as shared.  Only tokens of shared bits go on to a hash table, whose
+    // slots belong to the token that fills them: a wave seldom has one, and the table is nearly empty.  (All tokens in a
+    // table of two slots a token: every wave waits for the longest probe chain, 6 to 9 us of a plan of 8192.)  The table has a slot for
+    // every token, so a chain ends whatever the keys are.  Bitmaps of few ranks have a bit each: who finds it free is the
+    // representative.
+    // Not sorted: all tokens go to the table, of four slots a token; a wave whose tokens all have one key sends one lane
+    // (thousands of compare-and-swaps on one address would queue).
     uint64_t kept[kU], rep[kU];                                       // wave masks
-    uint64_t hit[kU];                                                 // what the token's slot held: kNone for a representative
-    uint32_t at[kU], stride[kU];
-    bool same[kU];                                                    // (uniform) the wave's kept tokens have one key
-#pragma unroll
-    for (int j = 0; j < kU; ++j) {
-        const bool k = key[j] != kNone;
-        kept[j] = __ballot(k);
-        const int first = kept[j] ? (int)__builtin_ctzll(kept[j]) : 0;
-        const uint64_t fk = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)key[j], first) |
-                            (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(key[j] >> 32), first) << 32;
-        same[j] = __ballot(key[j] == fk) == kept[j];
-        const uint32_t h = ((uint32_t)key[j] ^ ((uint32_t)(key[j] >> 32) * 0x9E3779B1u)) * 0x85EBCA6Bu;
-        at[j] = h >> (32 - slots_log);
-        stride[j] = (h >> 3) | 1u;                                    // odd: visits every slot
-        hit[j] = key[j];
-        if (k && (!same[j] || lane == first))
-            hit[j] = atomicCAS(&slot[at[j]], (unsigned long long)kNone, (unsigned long long)key[j]);
-    }
-    while (true) {
-        bool more = false;
-#pragma unroll
-        for (int j = 0; j < kU; ++j) more |= hit[j] != kNone && hit[j] != key[j];
-        if (!__any(more)) break;
+    if constexpr (kSorted) {
+        uint32_t hash[kU], word[kU], bit[kU], old[kU];
+        bool first[kU], sent[kU];                                     // sent: the table decides
 #pragma unroll
         for (int j = 0; j < kU; ++j) {
-            if (hit[j] != kNone && hit[j] != key[j]) {                // taken by another key
-                at[j] = (at[j] + stride[j]) & (n_slots - 1u);
+            const uint32_t lo = (uint32_t)key[j], hi = (uint32_t)(key[j] >> 32);
+            // (the lane before: wave_shr:1; lane 0 gets kNone)
+            const uint32_t plo = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)kNone, (int)lo, 0x138, 0xf, 0xf, false);
+            const uint32_t phi = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)(kNone >> 32), (int)hi, 0x138, 0xf, 0xf, false);
+            kept[j] = __ballot(key[j] != kNone);
+            first[j] = key[j] != kNone && ((lo ^ plo) | (hi ^ phi)) != 0;
+            hash[j] = (lo ^ (hi << 15 | hi >> 17)) * 0x9E3779B1u;
+            word[j] = own_bit ? lo >> 5 : hash[j] >> (32 - slots_log);           // (kFilterBits == 32: a word a slot)
+            bit[j] = 1u << ((own_bit ? lo : hash[j] >> 12) & 31u);
+            old[j] = 0;
+            if (first[j]) old[j] = atomicOr(&taken[word[j]], bit[j]);
+        }
+        if (own_bit) {
+#pragma unroll
+            for (int j = 0; j < kU; ++j) rep[j] = __ballot(first[j] && !(old[j] & bit[j]));
+        } else {
+#pragma unroll
+            for (int j = 0; j < kU; ++j) if (old[j] & bit[j]) atomicOr(&shared[word[j]], bit[j]);
+            mw_lds_barrier();
+            bool any = false;
+#pragma unroll
+            for (int j = 0; j < kU; ++j) {
+                sent[j] = first[j] && (shared[word[j]] & bit[j]) != 0;
+                any |= sent[j];
+            }
+            if (__any(any)) {
+                bool going[kU];
+#pragma unroll
+                for (int j = 0; j < kU; ++j) {
+                    hash[j] = (hash[j] ^ hash[j] >> 15) * 0x2C1B3C6Du;
+                    word[j] = hash[j] >> (32 - slots_log);
+                    going[j] = sent[j];
+                }
+                while (true) {
+                    bool more = false;
+                    unsigned long long held[kU];
+#pragma unroll
+                    for (int j = 0; j < kU; ++j)
+                        if (going[j]) held[j] = atomicCAS(&slot[word[j]], (unsigned long long)kNone, (unsigned long long)key[j]);
+#pragma unroll
+                    for (int j = 0; j < kU; ++j) {
+                        if (!going[j]) continue;
+                        if (held[j] == kNone) sent[j] = false;        // the slot is this token's
+                        going[j] = held[j] != kNone && held[j] != key[j];
+                        word[j] = (word[j] + (hash[j] << 1 | 1u)) & (n_slots - 1u);          // (odd: visits every slot)
+                        more |= going[j];
+                    }
+                    if (!__any(more)) break;
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < kU; ++j) rep[j] = __ballot(first[j] && !sent[j]);
+        }
+    } else {
+        uint64_t hit[kU];                                             // what the token's slot held: kNone for a representative
+        uint32_t at[kU], stride[kU];
+#pragma unroll
+        for (int j = 0; j < kU; ++j) {
+            const bool k = key[j] != kNone;
+            kept[j] = __ballot(k);
+            const int first = kept[j] ? (int)__builtin_ctzll(kept[j]) : 0;
+            const uint64_t fk = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)key[j], first) |
+                                (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(key[j] >> 32), first) << 32;
+            const bool same = __ballot(key[j] == fk) == kept[j];      // (uniform) the wave's kept tokens have one key
+            const uint32_t h = ((uint32_t)key[j] ^ ((uint32_t)(key[j] >> 32) * 0x9E3779B1u)) * 0x85EBCA6Bu;
+            at[j] = h >> (32 - slots_log);
+            stride[j] = (h >> 3) | 1u;                                // odd: visits every slot
+            hit[j] = key[j];
+            if (k && (!same || lane == first))
                 hit[j] = atomicCAS(&slot[at[j]], (unsigned long long)kNone, (unsigned long long)key[j]);
+        }
+        while (true) {                                                // a lane's probes go out together
+            bool more = false;
+#pragma unroll
+            for (int j = 0; j < kU; ++j) more |= hit[j] != kNone && hit[j] != key[j];
+            if (!__any(more)) break;
+#pragma unroll
+            for (int j = 0; j < kU; ++j) {
+                if (hit[j] != kNone && hit[j] != key[j]) {            // taken by another key
+                    at[j] = (at[j] + stride[j]) & (n_slots - 1u);
+                    hit[j] = atomicCAS(&slot[at[j]], (unsigned long long)kNone, (unsigned long long)key[j]);
+                }
             }
         }
-    }
 #pragma unroll
-    for (int j = 0; j < kU; ++j) rep[j] = __ballot(hit[j] == kNone) & kept[j];   // (a lane without a key: hit == key == kNone)
+        for (int j = 0; j < kU; ++j) rep[j] = __ballot(hit[j] == kNone) & kept[j];   // (a lane without a key: hit == key == kNone)
+    }
 
     // ---- totals (workgroup 0) and rows per destination (rank r: workgroup r modulo the grid)
     if (lane == 0) {
@@ -496,99 +604,82 @@ __global__ __launch_bounds__(kOrderBlock) void k_plan_order(
             if constexpr (!kBytes) {
                 names = (key[j] >> r) & 1ull;
             } else {
-                const uint64_t x = (key[j] | 0xff00000000000000ull) ^ (0x0001010101010101ull * (uint64_t)((r + 1) & 0xff));
-                const bool low = (((x - 0x0001010101010101ull) & ~x & 0x0080808080808080ull) != 0) && r < 255;
-                names = key[j] != kNone && (low || (uint32_t)(key[j] >> 56) == (uint32_t)r);
+                // a byte of the key is this rank's: a zero byte after the exclusive or (the last rank is never a lower byte)
+                const uint32_t b = 0x01010101u * (uint32_t)(r + 1);
+                const uint32_t lo = (uint32_t)key[j] ^ b, hi = (uint32_t)(key[j] >> 32) ^ ((b & 0xffffffu) | (uint32_t)r << 24);
+                names = r < 255 ? ((((lo - 0x01010101u) & ~lo) | ((hi - 0x01010101u) & ~hi)) & 0x80808080u) != 0 : hi >> 24 == 0;
             }
-            n += (uint32_t)__popcll(__ballot(names));
+            n += (uint32_t)__popcll(__ballot(names) & kept[j]);
         }
         if (lane == 0) wave_r[wave * 4 + q] = n;
     }
-    uint32_t bucket[kU], pos[kU];
-    if constexpr (kByBucket) {
-#pragma unroll
-        for (int j = 0; j < kU; ++j) {
-            bucket[j] = bucket_of<kBytes>(key[j], R);
-            if (same[j]) {                                            // one add for the wave's tokens
-                const int first = kept[j] ? (int)__builtin_ctzll(kept[j]) : 0;
-                uint32_t p = 0;
-                if (kept[j] && lane == first)
-                    p = atomicAdd(&bins[bucket[j]], (uint32_t)__popcll(kept[j]) | (uint32_t)__popcll(rep[j]) << 16);
-                pos[j] = ((uint32_t)__builtin_amdgcn_readlane((int)p, first) & 0xffffu) +
-                         (uint32_t)__popcll(kept[j] & ((1ull << lane) - 1ull));
-            } else if (key[j] != kNone) {
-                pos[j] = atomicAdd(&bins[bucket[j]], 1u | (hit[j] == kNone ? 0x10000u : 0u)) & 0xffffu;
-            }
-        }
-    }
     mw_lds_barrier();
 
-    if constexpr (kByBucket) {
-        // ---- bucket starts (both counts at once, halves stay below 2^16), then the keys bucket by bucket in the hash
-        // table's place; the order inside a bucket does not matter
-        unsigned long long *lkey = slot;                              // [T]
-        uint16_t *lidx = (uint16_t *)(lkey + T);                      // [T]    token, bit 15: representative
-        static_assert(kBuckets == 4 * kOrderBlock, "four buckets a lane");
-        {
-            uint4 c = ((uint4 *)bins)[tid];
-            uint32_t total;
-            uint32_t run = mw_block_exscan(c.x + c.y + c.z + c.w, scan, &total);
-            const uint4 st = make_uint4(run, run + c.x, run + c.x + c.y, run + c.x + c.y + c.z);
-            ((uint4 *)bins)[tid] = st;
+    if constexpr (kSorted) {
+        // ---- the chunks in the hash table's place, an entry apart so that a place is in another bank in every chunk
+        constexpr int kStride = kChunkTokens + 1, kRepStride = kChunkTokens + 4, kChunks = 8 * kU;      // (16 waves of kU / 2)
+        uint64_t *chunk = order_lds;                                  // [kChunks][kStride]
+        uint8_t *reps = (uint8_t *)(chunk + kChunks * kStride);       // [kChunks][kRepStride] representatives in front of a place
+        static_assert(kChunkTokens == 1 << 7 && kStride * 8 + kRepStride <= kChunkTokens * (8 + kFilterBits / 4), "room of the table and its bitmaps");
+#pragma unroll
+        for (int j = 0; j < kU; j += 2) {
+            const int c = wave + 16 * (j >> 1);
+            const uint64_t lower = (1ull << lane) - 1ull;
+            const uint32_t first = (uint32_t)__popcll(rep[j]);
+            chunk[c * kStride + lane] = key[j];
+            chunk[c * kStride + 64 + lane] = key[j + 1];
+            reps[c * kRepStride + lane] = (uint8_t)__popcll(rep[j] & lower);
+            reps[c * kRepStride + 64 + lane] = (uint8_t)(first + (uint32_t)__popcll(rep[j + 1] & lower));
+            if (lane == 0) {
+                reps[c * kRepStride + kChunkTokens] = (uint8_t)(first + (uint32_t)__popcll(rep[j + 1]));
+                in_chunk[c] = (uint32_t)__popcll(kept[j]) + (uint32_t)__popcll(kept[j + 1]);
+            }
         }
         mw_lds_barrier();
+        // ---- a wave per own token (two side by side beyond 4096 tokens), a lane per chunk
+        constexpr int kN = (kU + 3) / 4;
+        const bool mine = lane < kChunks;
+        const uint32_t n = mine ? in_chunk[lane] : 0u;
+        const uint64_t *c = chunk + (mine ? lane : 0) * kStride;
+        uint64_t k[kN];
+        uint32_t lb[kN], ub[kN], place[kN];
+        int own_c[kN];
+        bool more = false;
 #pragma unroll
-        for (int j = 0; j < kU; ++j) {
-            if (key[j] == kNone) continue;
-            const uint32_t i = (bins[bucket[j]] & 0xffffu) + pos[j];
-            lkey[i] = key[j];
-            lidx[i] = (uint16_t)((uint32_t)(tid + j * bs) | (hit[j] == kNone ? 0x8000u : 0u));
+        for (int q = 0; q < kN; ++q) {
+            const int o = wave + 16 * q;
+            k[q] = o < n_own && t0 + o < T ? own[o] : kNone;
+            own_c[q] = (t0 + o) / kChunkTokens;
+            place[q] = (uint32_t)(t0 + o) % kChunkTokens;
+            lb[q] = 0;                                                // keys below k
         }
-        mw_lds_barrier();
-        // ---- a wave per own token
-        uint32_t n_kept = 0, n_distinct = 0;
-        for (int w = 0; w < n_wave; ++w) { n_kept += wave_n[w * 4]; n_distinct += wave_n[w * 4 + 1]; }
-        for (int o = wave; o < n_own && t0 + o < T; o += n_wave) {
-            const uint64_t k = own[o];
-            if (k == kNone) continue;
-            const uint32_t b = bucket_of<kBytes>(k, R), st = bins[b];
-            const uint32_t end = b + 1 < kBuckets ? bins[b + 1] : n_kept | n_distinct << 16;
-            const uint32_t from = st & 0xffffu, to = end & 0xffffu;
-            uint32_t below = from, distinct = st >> 16, before = 0, after = 0;
-            uint32_t i0 = from;
-            if ((end >> 16) - distinct == 1) {                        // one key in the bucket: only the tokens' order counts
-                for (; i0 + 256 <= to; i0 += 256) {
-                    uint32_t id[4];
 #pragma unroll
-                    for (int c = 0; c < 4; ++c) id[c] = lidx[i0 + 64u * c + lane];
+        for (int b = 7; b >= 0; --b)
 #pragma unroll
-                    for (int c = 0; c < 4; ++c) before += (uint32_t)__popcll(__ballot((int)(id[c] & 0x7fffu) < t0 + o));
-                }
-                after = i0 - from - before;
-            }
-            auto count = [&](uint64_t q, uint32_t id, uint64_t in) __attribute__((always_inline)) {
-                const uint64_t lt = __ballot(q < k) & in, eq = __ballot(q == k) & in;
-                below += (uint32_t)__popcll(lt);
-                distinct += (uint32_t)__popcll(lt & __ballot(id > 0x7fffu));
-                if (eq) {
-                    const uint64_t ahead = __ballot((int)(id & 0x7fffu) < t0 + o);
-                    before += (uint32_t)__popcll(eq & ahead);
-                    after += (uint32_t)__popcll(eq & ~ahead);
-                }
-            };
-            for (; i0 + 256 <= to; i0 += 256) {                       // a crowded bucket: four reads in flight
-                uint64_t q[4];
-                uint32_t id[4];
+            for (int q = 0; q < kN; ++q) { const uint32_t at_ = lb[q] + (1u << b); if (at_ <= n && c[at_ - 1] < k[q]) lb[q] = at_; }
+        // tokens of the same key: the own one, seldom others
 #pragma unroll
-                for (int c = 0; c < 4; ++c) { q[c] = lkey[i0 + 64u * c + lane]; id[c] = lidx[i0 + 64u * c + lane]; }
+        for (int q = 0; q < kN; ++q) {
+            const uint32_t look = lane == own_c[q] ? place[q] + 1u : lb[q];
+            more |= look < n && c[look] == k[q];
+            ub[q] = lb[q];
+        }
+        if (__any(more)) {
 #pragma unroll
-                for (int c = 0; c < 4; ++c) count(q[c], id[c], ~0ull);
-            }
-            for (; i0 < to; i0 += 64) {
-                const uint32_t i = min(i0 + (uint32_t)lane, to - 1u), left = to - i0;
-                count(lkey[i], lidx[i], left >= 64 ? ~0ull : (1ull << left) - 1ull);
-            }
-            if (lane == 0) part[o] = make_uint2(below | distinct << 16, before | after << 16);
+            for (int b = 7; b >= 0; --b)
+#pragma unroll
+                for (int q = 0; q < kN; ++q) { const uint32_t at_ = ub[q] + (1u << b); if (at_ <= n && c[at_ - 1] <= k[q]) ub[q] = at_; }
+        } else {
+#pragma unroll
+            for (int q = 0; q < kN; ++q) if (lane == own_c[q]) ub[q] = place[q] + 1u;
+        }
+#pragma unroll
+        for (int q = 0; q < kN; ++q) {
+            if (k[q] == kNone) continue;                              // (the whole wave)
+            const uint32_t distinct = mine ? reps[lane * kRepStride + lb[q]] : 0u;
+            const uint32_t before = lane < own_c[q] ? ub[q] - lb[q] : lane == own_c[q] ? place[q] - lb[q] : 0u;
+            const uint32_t s0 = mw_wave_sum(lb[q] | distinct << 16), s1 = mw_wave_sum(before | (ub[q] - lb[q] - before) << 16);
+            if (lane == 0) part[wave + 16 * q] = make_uint2(s0, s1);
         }
     } else
     // ---- counts for the workgroup's own tokens
@@ -609,10 +700,16 @@ __global__ __launch_bounds__(kOrderBlock) void k_plan_order(
                 distinct += (uint32_t)__popcll(lt & rep[j]);
                 const uint64_t eq = __ballot(key[j] == k) & kept[j];
                 if (eq) {
-                    const int ahead = t0 + o - (j * bs + wave * 64);  // tokens of this wave's 64 that come before
-                    const uint64_t m = ahead <= 0 ? 0ull : ahead >= 64 ? ~0ull : (1ull << ahead) - 1ull;
-                    before += (uint32_t)__popcll(eq & m);
-                    after += (uint32_t)__popcll(eq & ~m);
+                    const int first = j * bs + wave * 64, ahead = t0 + o - first;        // of the wave's 64 tokens, how many come before
+                    if (first >= t0 + n) {                            // (the same for all own tokens)
+                        after += (uint32_t)__popcll(eq);
+                    } else if (first + 64 <= t0) {
+                        before += (uint32_t)__popcll(eq);
+                    } else {
+                        const uint64_t m = ahead <= 0 ? 0ull : ahead >= 64 ? ~0ull : (1ull << ahead) - 1ull;
+                        before += (uint32_t)__popcll(eq & m);
+                        after += (uint32_t)__popcll(eq & ~m);
+                    }
                 }
             }
             if (lane == o) { c0 = below | distinct << 16; c1 = before | after << 16; }
@@ -621,9 +718,9 @@ __global__ __launch_bounds__(kOrderBlock) void k_plan_order(
     }
     mw_lds_barrier();
     if (tid < n_own && t0 + tid < T) {
-        const int t = t0 + tid;
+        const int t = kSorted ? (t0 + tid) / kChunkTokens * kChunkTokens + (int)own_idx : t0 + tid;
         uint32_t c0 = 0, c1 = 0;
-        for (int w = 0; w < (kByBucket ? 1 : n_wave); ++w) { const uint2 c = part[w * kOwnMax + tid]; c0 += c.x; c1 += c.y; }     // (halves stay below 2^16)
+        for (int w = 0; w < (kSorted ? 1 : n_wave); ++w) { const uint2 c = part[w * kOwnMax + tid]; c0 += c.x; c1 += c.y; }     // (halves stay below 2^16)
         uint64_t m[MW_MASK_WORDS];
         const uint64_t k = own[tid];
         mask_of_key<kBytes>(k, m);
@@ -931,52 +1028,50 @@ int32_t mw_launch_plan_allgather_split(mw_ctx *ctx, int64_t shard_bytes, int64_t
     return MW_OK;
 }
 
-// Tokens from which the keys get a launch of their own, and from which a token is compared with its bucket only
-// (mw_plan alone, us).  Keys: 64 ranks, 2048 tokens 8.8 in one launch, 9.9 in two; 3000 tokens 13.3 / 10.9, 8192
-// tokens 37.6 / 21.3 (256 ranks 41.2 / 21.8).  Buckets: up to one token a lane the buckets' two scans cost what the
-// compares do, with 4096 tokens 18 us without them and 12.3 with, with 8192 36 and 21.3.
+// Tokens from which the keys get a launch of their own, in sorted chunks (mw_plan alone, us: 64 ranks uniform / 256 ranks
+// skewed / 8 ranks).  1025 tokens 7.5 / 9.7 / 7.3 in one launch, 2048 8.7 / 10.7 / 8.2; sorted, 2049 10.1 / 11.8 / 9.9, 4096
+// 10.8 / 11.9 / 10.4, 6000 12.9 / 15.1 / 12.7, 8192 15.1 / 16.1 / 14.1.  (One launch that compared a token with a bucket of keys instead
+// of with all: 1025 8.1 / 10.3 / 7.7, 2048 8.8 / 11.4 / 7.9; keys not sorted, buckets behind them: 4096 12.8 / 14.6 / 10.8, 6000 18.7 /
+// 22.4 / 13.5, 8192 21.8 / 28.0 / 14.6.)
 constexpr int kKeysFrom = 2049;
-constexpr int kBucketsFrom = 1025;
 
 template <bool kBytes>
 static void launch_plan_order(mw_ctx *ctx, const int32_t *topk, int32_t T, uint64_t *mask, int32_t *perm, mw_group_desc *desc,
                               mw_send_stats *stats, hipStream_t s)
 {
     const int K = ctx->cfg.top_k, E = ctx->cfg.n_experts, R = ctx->cfg.n_ranks;
-    const bool from_keys = T >= kKeysFrom;
+    const bool sorted = T >= kKeysFrom;
     const int bs = T <= 256 ? 256 : T <= 512 ? 512 : kOrderBlock;
-    // About a workgroup per CU, and enough of them that each counts at most four ranks.  Each takes 146 KiB of LDS from 2049
-    // tokens on, so a launch beside the plan waits for its CUs: a step of 8192 tokens of 256 ranks whose plan runs on a second
-    // stream takes 148 us, with 128 workgroups 140.5 -- and the plan alone 25.4 instead of 23.4, with skewed ids 37 instead of
-    // 31 us.  (Up to 4096 tokens a neighbour loses nothing: 4096 fp8 tokens 100.0 and 99.7 us a step.)
+    // About a workgroup per CU, and enough of them that each counts at most four ranks.  (Half as many: the plan alone 2 us
+    // slower at 8192 tokens.)
     int n_own = (T + 255) / 256;
     if (n_own < 1) n_own = 1;
     int n_wg = (T + n_own - 1) / n_own;
     if (n_wg < (R + 3) / 4) n_wg = (R + 3) / 4;
-    // four slots a token up to 4096 tokens, then the two that LDS has room for: half the slots taken means probe
-    // chains of up to ten, and every wave waits for the longest
+    // four slots a token: half the slots taken means probe chains of up to ten, and every wave waits for the longest.  Sorted:
+    // one for each of the lanes' tokens
     int slots_log = 6;
-    while ((1 << slots_log) < 2 * T || ((1 << slots_log) < 4 * T && slots_log < 14)) ++slots_log;
+    while ((1 << slots_log) < 4 * T) ++slots_log;
+    if (sorted) slots_log = T <= 4 * kOrderBlock ? 12 : 13;
     const size_t tab = E <= kTableExperts ? ((size_t)E + 4) / 4 * 8 : 0;
-    const bool by_bucket = T >= kBucketsFrom;
-    const size_t lds = ((size_t)8 << slots_log) + 8 * kOwnMax + 8 * 16 * kOwnMax + 4 * 128 + (by_bucket ? 4 * kBuckets : 0) +
-                       (from_keys ? 0 : tab);
-    const int n_key_wg = (T + kKeysBlock - 1) / kKeysBlock;
-    if (from_keys) {
+    const size_t lds = ((size_t)(sorted ? 8 + kFilterBits / 4 : 8) << slots_log) + 8 * kOwnMax + 8 * 16 * kOwnMax + 4 * 128 + (sorted ? 4 * kOrderChunks : tab);
+    const int n_key_wg = (T + kChunkTokens - 1) / kChunkTokens;
+    if (sorted) {
         mw_timed tm(ctx, MW_KERNEL_PLAN_RANK, s);
         hipLaunchKernelGGL(k_plan_keys<kBytes>, dim3(n_key_wg), dim3(kKeysBlock), tab, s, topk, T, K, ctx->d_eslot, E,
-                           ctx->d_plan_keys, ctx->d_plan_bad);
+                           ctx->d_plan_keys, ctx->d_plan_idx, ctx->d_plan_bad);
     }
-    mw_timed tm(ctx, from_keys ? MW_KERNEL_PLAN_GROUPS : MW_KERNEL_PLAN_RANK, s);
-#define MW_ORDER(U_, KEYS_, BUCKET_)                                                                                    \
-    hipLaunchKernelGGL((k_plan_order<kBytes, U_, KEYS_, BUCKET_>), dim3(n_wg), dim3(bs), lds, s, topk, T, K, ctx->d_eslot, E, R, \
-                       n_own, slots_log, ctx->d_plan_keys, ctx->d_plan_bad, n_key_wg, ctx->d_plan_state,                      \
+    mw_timed tm(ctx, sorted ? MW_KERNEL_PLAN_GROUPS : MW_KERNEL_PLAN_RANK, s);
+#define MW_ORDER(U_, SORTED_)                                                                                           \
+    hipLaunchKernelGGL((k_plan_order<kBytes, U_, SORTED_>), dim3(n_wg), dim3(bs), lds, s, topk, T, K, ctx->d_eslot, E, R,  \
+                       n_own, slots_log, ctx->d_plan_keys, ctx->d_plan_idx, ctx->d_plan_bad, n_key_wg, ctx->d_plan_state,     \
                        (uint64_t)ctx->row_bytes, mask, perm, desc, stats)
-    static_assert(kBucketsFrom == kOrderBlock + 1 && kKeysFrom == 2 * kOrderBlock + 1, "tokens a lane of each form");
-    if (!by_bucket) MW_ORDER(1, false, false);
-    else if (!from_keys) MW_ORDER(2, false, true);
-    else if (T <= 4 * kOrderBlock) MW_ORDER(4, true, true);
-    else MW_ORDER(8, true, true);
+    static_assert(kKeysFrom == 2 * kOrderBlock + 1, "tokens a lane of each form");
+    if (T <= kOrderBlock) MW_ORDER(1, false);
+    else if (!sorted) MW_ORDER(2, false);
+    else if (T <= 4 * kOrderBlock) MW_ORDER(4, true);
+    else if (T <= 6 * kOrderBlock) MW_ORDER(6, true);
+    else MW_ORDER(8, true);
 #undef MW_ORDER
 }
 

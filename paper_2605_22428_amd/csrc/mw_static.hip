@@ -19,7 +19,7 @@ constexpr int64_t kCntBytes = 8LL * MW_STATIC_MAX_TOKENS;            // packed p
 constexpr int64_t kStateBytes = (4LL * MW_PLAN_STATE_WORDS + 255) / 256 * 256;
 constexpr int64_t kSlotBytes = 4LL * MW_STATIC_MAX_EXPERTS;          // (rank << 16) | slot per expert
 constexpr int64_t kKeyBytes = 8LL * MW_STATIC_MAX_TOKENS + 256;      // keys, a flag word per workgroup that makes them
-constexpr int64_t kScratchBytes = kCntBytes + kStateBytes + kSlotBytes + kKeyBytes;   // 136704 bytes
+constexpr int64_t kScratchBytes = kCntBytes + kStateBytes + kSlotBytes + kKeyBytes + MW_STATIC_MAX_TOKENS;   // (and their tokens) 144896 bytes
 
 static __device__ __align__(256) __attribute__((used)) unsigned char scratch[kScratchBytes];
 
@@ -118,6 +118,7 @@ extern "C" MW_API int32_t mw_plan_static(const mw_config *cfg, const int32_t *ex
     tmp.d_eslot = (int32_t *)(slot.ptr + kCntBytes + kStateBytes);
     tmp.d_plan_keys = (uint64_t *)(slot.ptr + kCntBytes + kStateBytes + kSlotBytes);
     tmp.d_plan_bad = (uint32_t *)(tmp.d_plan_keys + MW_STATIC_MAX_TOKENS);
+    tmp.d_plan_idx = slot.ptr + kScratchBytes - MW_STATIC_MAX_TOKENS;
 
     const hipStream_t s = (hipStream_t)stream;
     hipLaunchKernelGGL(k_static_prepare, dim3(1), dim3(kPrepBlock), 0, s, expert_to_rank_dev, cfg->n_experts,

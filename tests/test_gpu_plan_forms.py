@@ -70,3 +70,34 @@ def test_plan_forms(shape, T):
         H.assert_same_bytes(got[:N], perm, kind + " perm")
         assert (got[N:] == -7).all(), kind + ": perm behind the last packed row was written"
         H.assert_same_bytes(H.host(buf.desc).reshape(-1).view(B.DESC_DTYPE)[:G].view(np.uint8), desc.view(np.uint8), kind + " desc")
+
+
+@pytest.mark.parametrize("T", [2049, 2176, 4095, 6144, 6145, 8065, 8192])
+@pytest.mark.parametrize("R,E,K", [(64, 64, 64), (256, 256, 8), (17, 34, 4), (18, 36, 4), (19, 38, 4)])
+def test_plan_of_sorted_chunks(R, E, K, T):
+    """Chunks of 128 tokens, a lane's four, six or eight tokens, the last chunk partly filled; keys that appear exactly twice,
+    anywhere; every rank named (the largest one-word key) among tokens without a destination; most tokens of two keys.  The
+    ranks up to which a bitmap has a bit of its own are 17 (up to 4096 tokens) and 18."""
+    print("sorted chunks", R, E, K, T, flush=True)
+    e2r = (np.arange(E) * R // E).astype(np.int32)
+    ctx = B.Context(R, E, K, 0, 8, B.MW_ROW_BF16, T, 1, e2r, device=H.DEV)
+    buf = B.SendBuffers(ctx, T)
+    rng = np.random.default_rng(T + R)
+    half = np.argsort(rng.random(((T + 1) // 2, E)), axis=1)[:, :K].astype(np.int32)
+    twice = np.concatenate([half, half])[rng.permutation(2 * len(half))[:T]]
+    if K == E:
+        twice[rng.random((T, K)) < 0.5] = -1
+    ends = np.tile(np.arange(K, dtype=np.int32) if K == E else np.arange(E - K, E, dtype=np.int32), (T, 1))
+    ends[rng.random(T) < 0.4] = -1
+    two = np.argsort(rng.random((T, E)), axis=1)[:, :K].astype(np.int32)
+    two[rng.random(T) < 0.6] = two[0]
+    two[rng.random(T) < 0.3] = two[1]
+    for tk in (twice, ends, two):
+        ctx.mw_plan(H.dev(tk), buf.mask, buf.perm, buf.desc, buf.stats)
+        st = ctx.mw_get_send_stats(buf.stats)
+        mask, perm, desc, want = ref.plan(tk, e2r, R, 16)
+        assert (int(st["n_rows"]), int(st["n_groups"]), int(st["error_flags"])) == (len(perm), len(desc), 0)
+        H.assert_same_bytes(st["rows_per_dest"], want["rows_per_dest"], "rows_per_dest")
+        H.assert_same_bytes(H.host(buf.mask).view(np.uint64)[:T], mask, "mask")
+        H.assert_same_bytes(H.host(buf.perm)[: len(perm)], perm, "perm")
+        H.assert_same_bytes(H.host(buf.desc).reshape(-1).view(B.DESC_DTYPE)[: len(desc)].view(np.uint8), desc.view(np.uint8), "desc")
