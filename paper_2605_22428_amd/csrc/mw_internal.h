@@ -195,6 +195,16 @@ __device__ __forceinline__ void mw_publish_barrier()
 #endif
     __syncthreads();
 }
+// The same where one wave wrote all there is to publish: its lanes' accesses are acknowledged, then one of them reports.
+__device__ __forceinline__ void mw_publish_wave()
+{
+#if MW_PUBLISH_FENCES
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    __builtin_amdgcn_wave_barrier();
+#else
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#endif
+}
 __device__ __forceinline__ uint32_t mw_report(uint32_t *counter)
 {
 #if MW_PUBLISH_FENCES

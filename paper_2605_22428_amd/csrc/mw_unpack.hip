@@ -29,6 +29,8 @@
 // Further entry points share these bodies: k_recv_index<true> reads per-row headers (packets),
 // k_expand_index_next runs the expander with the next batch's index in the same launch, and
 // k_combine is the expander's mirror image for the way back.
+#include <cmath>
+
 #include "mw_internal.h"
 #include "mw_plan_dev.h"
 #include "mw_pack_dev.h"
@@ -45,6 +47,8 @@ __device__ __forceinline__ void st_agent(uint32_t *p, uint32_t v)
 {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+
+constexpr uint32_t kWaveCounts = 8;       // counts a lane of mw_finish_counts_wave
 
 // One workgroup: exclusive scan of the (expert, peer) counts in output order, expert
 // offsets, totals and flags.  `scratch` is LDS scan scratch of 17 words.  Every device-scope
@@ -82,6 +86,44 @@ __device__ __forceinline__ void mw_finish_counts(const uint32_t *cnt, const uint
         stats->n_out_rows = Q;
         stats->error_flags = err | (((int64_t)Q > out_cap) ? MW_FLAG_OUT_CAPACITY : 0u);
         stats->n_rows_seen = row_base_total;
+        st_agent(&flags[1], 0u);           // ready for the next unpack
+        st_agent(&flags[2], 0u);
+    }
+}
+
+// The same by one wave, without a barrier, for at most 64 kWaveCounts counts, all requested together.  (The workgroup's two
+// scans and their barriers: 1.5 us after the last report, this 1.0.)
+__device__ __forceinline__ void mw_finish_counts_wave(const uint32_t *cnt, const uint32_t *addr_cnt, uint32_t *flags,
+                                                      const uint32_t *row_base, uint32_t L, uint32_t P, int64_t out_cap,
+                                                      uint32_t *base, int64_t *expert_offsets, mw_recv_stats *stats)
+{
+    const uint32_t lane = threadIdx.x & 63u, n_lp = L * P;
+    uint32_t v[kWaveCounts], w[4];                   // (P <= 256)
+#pragma unroll
+    for (uint32_t j = 0; j < kWaveCounts; ++j) v[j] = lane + 64u * j < n_lp ? ld_agent(&cnt[lane + 64u * j]) : 0u;
+#pragma unroll
+    for (uint32_t j = 0; j < 4; ++j) w[j] = lane + 64u * j < P ? ld_agent(&addr_cnt[lane + 64u * j]) : 0u;
+    const uint32_t err = ld_agent(&flags[1]), seen = ld_agent(&row_base[P]);
+    const float per = 1.0f / (float)P;               // (f + 1/2) / P is at least 1/512 away from a whole number: f below 2^9 is exact
+    uint32_t Q = 0;
+#pragma unroll
+    for (uint32_t j = 0; j < kWaveCounts; ++j) {
+        const uint32_t f = lane + 64u * j;
+        if (64u * j >= n_lp) break;
+        const uint32_t inc = mw_wave_incl_scan(v[j]), at = Q + inc - v[j], l = (uint32_t)(((float)f + 0.5f) * per);
+        if (f < n_lp) {
+            base[f] = at;
+            if (l * P == f) expert_offsets[l] = (int64_t)at;
+        }
+        Q += (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+    }
+    const uint32_t m = mw_wave_sum(w[0] + w[1] + w[2] + w[3]);
+    if (lane == 0) {
+        expert_offsets[L] = Q;
+        stats->n_recv_rows = m;
+        stats->n_out_rows = Q;
+        stats->error_flags = err | (((int64_t)Q > out_cap) ? MW_FLAG_OUT_CAPACITY : 0u);
+        stats->n_rows_seen = seen;
         st_agent(&flags[1], 0u);           // ready for the next unpack
         st_agent(&flags[2], 0u);
     }
@@ -128,7 +170,9 @@ static inline size_t mw_index_lds_words(uint32_t wpl, uint32_t Lc, uint32_t tab_
 // over all eight ids with the hits in an array of registers took several hundred.  Measured, with that walk and
 // with this: 16 peers of 429 rows 16.9 -> 8.3 us, 64 peers of 481 rows 14.0 -> 9.4, 8 peers of 681 rows and
 // 32 experts 23.8 -> 8.6, of 2720 rows 34.6 -> 13.6; riding beside the expander with two waves a peer (8 peers of
-// 1360 rows, 32 experts) the step 170 -> 83 us, because the index no longer outlasts the movers.
+// 1360 rows, 32 experts) the step 170 -> 83 us, because the index no longer outlasts the movers.  With the experts' words scanned by a
+// wave each, the report sent before the ranks are written and the counts finished by one wave: 16 peers of 429 rows 8.8 -> 7.8,
+// 64 of 478 10.5 -> 8.7, 8 of 1360 and 32 experts 11.3 -> 10.3.
 // kB: rows a lane requests together.  kKeep: what the lane's first kB rows parsed to stays in registers
 // for the second pass (top_k <= 8); else the rows are requested again, which the launches that
 // run the index beside the row movers do to stay small in registers.
@@ -145,7 +189,7 @@ __device__ __forceinline__ void recv_index_body(const mw_index_args &a, const ui
     uint32_t *bits = addr + wpl + a.tab_words;                  // [Lc][wpl]  bit s of expert l: a row with source token s
     uint16_t *pre = (uint16_t *)(bits + (size_t)Lc * wpl);      // [Lc][wpl]  running popcount before each word (modulo 2^16)
     uint32_t *scratch = bits + (size_t)Lc * wpl + ((size_t)Lc * wpl + 1) / 2;  // [17] scans, [17] "I am last", [18] addressed
-                                                                // rows, [19] repeats dropped, [20..35] waves' sums
+                                                                // rows, [19] repeats dropped, [20..35] waves' sums, [36] flags
     uint32_t *seen_tok = scratch + 64;                          // [wpl]      (dedup only) bit s: a row with source token s was taken
 
     // ---- everything that depends on the peer record alone is requested before the first wait:
@@ -232,6 +276,7 @@ __device__ __forceinline__ void recv_index_body(const mw_index_args &a, const ui
     if (dedup) for (uint32_t w = tid; w < wpl; w += nthr) seen_tok[w] = 0;
     for (uint32_t w = tid; w < lc * wpl; w += nthr) bits[w] = 0;
     if (tid < 2) scratch[18 + tid] = 0;
+    if (tid == 0) scratch[36] = 0;
     if (use_tab) {
         for (uint32_t e = tid; e <= E; e += nthr) {
             const int32_t q = e < nthr ? slot0 : (e < E ? a.eslot[e] : 0);
@@ -247,7 +292,8 @@ __device__ __forceinline__ void recv_index_body(const mw_index_args &a, const ui
     if (pr.n_rows > max_tokens || before + mine > a.cap_rows) err |= MW_FLAG_RECV_CAPACITY;
     const uint32_t rb = min(before, a.cap_rows);
     const uint32_t n_rows = min(before + mine, a.cap_rows) - rb;
-    if (tid == 0 && part == 0 && row_part == 0) {
+    const bool speaker = tid == nthr - 64u;           // first lane of the wave that reports (the last: it has the fewest rows)
+    if (speaker && part == 0 && row_part == 0) {
         a.row_base[p] = rb;
         if (p == P - 1u) st_agent(&a.row_base[P], rb + n_rows);    // (also read by the last workgroup)
     }
@@ -309,6 +355,7 @@ __device__ __forceinline__ void recv_index_body(const mw_index_args &a, const ui
 
     // ---- per row: its distinct local experts in the order of its id list (repeated ids count once).
     // classify: which of ids j0 .. j0 + 7 are local (bit u), and -- with the LDS table -- their slots, a byte each.
+    // (flags are pass 1's; what pass 2 finds again, or in rows that are not addressed, is not reported)
     auto classify = [&](const int32_t (&e)[8], uint32_t j0, uint32_t &local, uint64_t &slots) __attribute__((always_inline)) {
         local = 0; slots = 0;
         uint32_t top = 0;                            // E: some id is outside [0, E)
@@ -429,28 +476,43 @@ __device__ __forceinline__ void recv_index_body(const mw_index_args &a, const ui
     bool first_chunk = true;
     mark_from(step, true);
     while (true) {
+        if (err) { atomicOr(&scratch[36], err); err = 0; }
         mw_lds_barrier();
 
-        // ---- running popcounts over the chunk's words (expert-major): consecutive words per lane, one scan
-        // of the lanes' sums.  Only differences inside one expert's words are used, and those are below
-        // 65536, so sixteen bits hold them.
-        {
-            const uint32_t n_words = lc * wpl, per = (n_words + nthr - 1u) / nthr;
-            const uint32_t w0 = min(n_words, tid * per), w1 = min(n_words, w0 + per);
-            uint32_t sum = 0, tot;
-            for (uint32_t w = w0; w < w1; ++w) sum += __popc(bits[w]);
-            uint32_t run = mw_block_exscan(sum, scratch, &tot);
-            for (uint32_t w = w0; w < w1; ++w) { pre[w] = (uint16_t)run; run += __popc(bits[w]); }
+        // ---- running popcounts over each expert's words, a wave an expert at a time: no scan over the waves, no barrier
+        // inside.  A count in front of a word is below 65536.
+        uint32_t lane = tid;
+        asm volatile("" : "+v"(lane));               // (made here, not kept in registers through the passes: the riders have none to spare)
+        const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(lane >> 6));
+        lane &= 63u;
+        const uint32_t per = (wpl + 63u) / 64u, w0 = min(wpl, lane * per), w1 = min(wpl, w0 + per);
+        for (uint32_t l = wave; l < lc; l += nthr >> 6) {
+            const uint32_t *b = bits + l * wpl;
+            const uint32_t c = w0 < w1 ? (uint32_t)__popc(b[w0]) : 0u;
+            uint32_t sum = c;
+            for (uint32_t w = w0 + 1u; w < w1; ++w) sum += (uint32_t)__popc(b[w]);
+            uint32_t run = mw_wave_incl_scan(sum) - sum;
+            if (w0 < w1) pre[l * wpl + w0] = (uint16_t)run;
+            run += c;
+            for (uint32_t w = w0 + 1u; w < w1; ++w) { pre[l * wpl + w] = (uint16_t)run; run += (uint32_t)__popc(b[w]); }
         }
         mw_lds_barrier();
-        if (row_part == 0)
-        for (uint32_t l = tid; l < lc; l += nthr) {
-            uint32_t n = 0;
-            if (wpl) {
-                const uint32_t w = (l + 1u) * wpl - 1u;
-                n = (uint32_t)(uint16_t)(pre[w] - pre[l * wpl]) + __popc(bits[w]);
+        // ---- the counts, and after the last chunk's the report that they are there: now, so that its way to memory and back
+        // goes by while the other waves write ranks and records (which only the next kernel reads)
+        if (wave == (nthr >> 6) - 1u) {
+            if (row_part == 0)
+                for (uint32_t l = lane; l < lc; l += 64u) {
+                    const uint32_t w = (l + 1u) * wpl - 1u;
+                    st_agent(&a.cnt[(size_t)(le0 + l) * P + p], wpl ? pre[w] + (uint32_t)__popc(bits[w]) : 0u);
+                }
+            if (le0 + a.parts * Lc >= L) {
+                if (lane == 0) {
+                    if (scratch[36]) __hip_atomic_fetch_or(&a.flags[1], scratch[36], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if (part == 0 && row_part == 0) st_agent(&a.addr_cnt[p], scratch[18] - scratch[19]);
+                }
+                mw_publish_wave();
+                if (lane == 0) scratch[17] = mw_report(&a.flags[2]) == P * a.parts * a.row_parts - 1u ? 1u : 0u;
             }
-            st_agent(&a.cnt[(size_t)(le0 + l) * P + p], n);
         }
 
         // ---- pass 2: stable rank of every row among the peer's rows for each of its experts in the chunk;
@@ -469,8 +531,7 @@ __device__ __forceinline__ void recv_index_body(const mw_index_args &a, const ui
                         const uint32_t l = le - le0;
                         if (l >= lc) return;
                         const uint32_t w = l * wpl + (s >> 5);
-                        const int32_t rk = (int32_t)((uint32_t)(uint16_t)(pre[w] - pre[l * wpl]) +
-                                                     __popc(bits[w] & ((1u << (s & 31u)) - 1u)));
+                        const int32_t rk = (int32_t)(pre[w] + (uint32_t)__popc(bits[w] & ((1u << (s & 31u)) - 1u)));
                         if (k > 0) h[k] = mw_hit{(int32_t)le, rk};
                         else { first_le = (int32_t)le; first_rank = rk; }
                     });
@@ -503,21 +564,23 @@ __device__ __forceinline__ void recv_index_body(const mw_index_args &a, const ui
         mw_lds_barrier();                            // this chunk's ranks have been read
         for (uint32_t w = tid; w < lc * wpl; w += nthr) bits[w] = 0;
         mw_lds_barrier();
+        err = 0;
         mark_from(0, false);
     }
-    if (err) __hip_atomic_fetch_or(&a.flags[1], err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (tid == 0 && part == 0 && row_part == 0) st_agent(&a.addr_cnt[p], scratch[18] - scratch[19]);    // (both complete: barriers in between)
-
-    // ---- the workgroup that finishes last turns the counts into output bases ----------
-    // Everything the last workgroup reads (counts, addressed-row counts, flags) is written and
-    // read with device-scope atomics, and every workgroup reports through one counter when all
-    // its lanes are done (publication rules in mw_internal.h); the workgroup whose report is the
-    // last has thereby acquired what all the others released.  The row records and hit slots,
-    // written with ordinary stores, are read by the next kernel only.
-    mw_publish_barrier();
-    if (tid == 0) scratch[17] = mw_report(&a.flags[2]) == P * a.parts * a.row_parts - 1u ? 1u : 0u;
-    __syncthreads();
+    // ---- the workgroup that reported last turns the counts into output bases ----------
+    // Everything it reads (counts, addressed-row counts, flags) is written and read with device-scope
+    // atomics, and every workgroup reports through one counter when the wave that wrote them has them acknowledged
+    // (publication rules in mw_internal.h); the workgroup whose report is the last has thereby acquired
+    // what all the others released.  The row records and hit slots, written with ordinary stores, are
+    // read by the next kernel only.
+    if (L * P <= 64u * kWaveCounts) {
+        if (tid >= nthr - 64u && scratch[17])        // (the wave that reported)
+            mw_finish_counts_wave(a.cnt, a.addr_cnt, a.flags, a.row_base, L, P, a.out_cap, a.base, a.expert_offsets, a.stats);
+        return;
+    }
+    mw_lds_barrier();
     if (!scratch[17]) return;
+    mw_lds_barrier();                                // (scratch is used again)
     mw_finish_counts(a.cnt, a.addr_cnt, a.flags, a.row_base, L, P, a.out_cap, a.base, a.expert_offsets, a.stats, scratch);
 }
 
@@ -1328,11 +1391,14 @@ int32_t mw_launch_unpack_index(mw_ctx *ctx, const void *peers, bool packets, int
                          kMaxIndexParts, &a, &lds_index))
         return MW_ERR_UNSUPPORTED;
     // A lane per row as long as a workgroup has that many (a peer seldom sends more than a fraction of its
-    // tokens to one rank): fewer lanes have shorter barriers and scans, more of them fewer rows each.  With
+    // tokens to one rank): fewer lanes have shorter barriers and scans, more of them fewer rows each.  The rows of one
+    // peer spread about their mean, and the peer with one row more than lanes is the one all wait for: three roots more than
+    // the mean (64 peers of 478 +- 21 rows: 10.0 us with 512 lanes, 8.7 with 1024).  With
     // more rows than lanes three a lane are requested together (8 peers of 2720 rows: 13.6 us, one at a time
     // 14.5), with fewer one (16 peers of 429 rows: 8.3 us, with room for three 8.7).
     const int64_t rows_of_peer = (expected_rows(ctx, P) + P - 1) / P;
-    const int ib = rows_of_peer <= 256 ? 256 : rows_of_peer <= 512 ? 512 : kIndexBlock;
+    const double most = (double)rows_of_peer + 3.0 * std::sqrt((double)rows_of_peer);
+    const int ib = most <= 256.0 ? 256 : most <= 512.0 ? 512 : kIndexBlock;
     {
         mw_timed tm(ctx, MW_KERNEL_RECV_INDEX, s);
         const int64_t expected = ctx->recv_rows_hint > 0 ? ctx->recv_rows_hint : (int64_t)P * ctx->cfg.max_tokens;

@@ -156,3 +156,35 @@ def test_stream_steps_with_riders_and_without(R, E, T, K, hidden, forced):
         H.assert_same_bytes(H.host(b["send"].desc).reshape(-1).view(B.DESC_DTYPE)[: len(desc)].view(np.uint8), desc.view(np.uint8), "desc")
         packed, src, rtk = ref.pack(b["x"], None, b["tk"], perm)
         H.assert_same_bytes(H.host(b["send"].packed)[: len(perm)], packed, "packed")
+
+
+@pytest.mark.parametrize("R,L,n_peers", [(73, 7, 73), (128, 4, 128), (171, 3, 171), (256, 2, 256), (256, 2, 255), (256, 3, 170), (40, 13, 40),
+                                         (97, 1, 97), (60, 16, 32), (60, 16, 33)])
+def test_counts_finished_by_a_wave_or_a_workgroup(R, L, n_peers):
+    """Up to 512 (expert, peer) counts are scanned by the wave that reported last, more by its workgroup; peers of no row, of
+    one, and of more rows than lanes; a flag raised by one batch is gone in the next."""
+    print("counts", R, L, n_peers, flush=True)
+    E, K, T, my_rank, hidden = R * L, 4, 500, R - 1, 8
+    rng = np.random.default_rng(R * L + n_peers)
+    e2r = (np.arange(E) * R // E).astype(np.int32)
+    mine = np.nonzero(e2r == my_rank)[0]
+    ctx = B.Context(R, E, K, my_rank, hidden, B.MW_ROW_BF16, T, n_peers * T, e2r, device=H.DEV)
+    toks, recs = [], []
+    for p in range(n_peers):
+        n = T if p == n_peers // 2 else p % 4
+        tk = np.argsort(rng.random((n, E)), axis=1)[:, :K].astype(np.int32) if n else np.zeros((0, K), np.int32)
+        tk[np.arange(n), rng.integers(0, K, n)] = rng.choice(mine, n)
+        x = rng.integers(0, 1 << 16, size=(n, hidden), dtype=np.uint16)
+        toks.append((tk, x, None))
+        recs.append(H.shrink(H.GpuSend(ctx, tk, x, None).deliver(my_rank)))
+    cap = sum(r["n_rows"] for r in recs) * min(K, L)
+    want = ref.dispatch_plain(toks, e2r, my_rank, cap)
+    H.check_unpack(H.GpuUnpack(ctx, recs, cap), want, "first")
+    bad = dict(recs[n_peers // 2], row_topk=recs[n_peers // 2]["row_topk"].clone())
+    ids = bad["row_topk"][7]
+    ids[~torch.isin(ids, H.dev(mine.astype(np.int32)))] = E
+    broken = recs[: n_peers // 2] + [bad] + recs[n_peers // 2 + 1:]
+    flagged = bool((ids == E).any())
+    for _ in range(2):
+        assert int(H.GpuUnpack(ctx, broken, cap).stats["error_flags"]) == (B.MW_FLAG_BAD_EXPERT if flagged else 0)
+    H.check_unpack(H.GpuUnpack(ctx, recs, cap), want, "after a flagged batch")
