@@ -383,11 +383,8 @@ MW_API int32_t mw_unpack(mw_ctx *ctx, const mw_recv_peer *peers_dev, int32_t n_p
         rc = check_unpack_expand(ctx, n_peers, out_rows_dev, out_scales_dev, out_capacity_rows, out_src_peer_dev,
                                  out_src_token_dev);
     if (rc != MW_OK) return rc;
-    rc = mw_launch_unpack_index(ctx, peers_dev, false, n_peers, out_capacity_rows, expert_offsets_dev, recv_stats_dev,
-                                (hipStream_t)stream);
-    if (rc != MW_OK) return rc;
-    return mw_launch_unpack_expand(ctx, n_peers, out_rows_dev, out_scales_dev, out_capacity_rows, out_src_peer_dev,
-                                   out_src_token_dev, (hipStream_t)stream);
+    return mw_launch_unpack(ctx, peers_dev, n_peers, out_rows_dev, out_scales_dev, out_capacity_rows, out_src_peer_dev,
+                            out_src_token_dev, expert_offsets_dev, recv_stats_dev, (hipStream_t)stream);
 }
 
 MW_API int32_t mw_packet_header_bytes(int32_t top_k, int64_t *header_bytes)

@@ -625,26 +625,53 @@ static inline size_t mw_small_index_lds_words(int P, int L, int tab, uint32_t wp
     return 10 * (size_t)P + 3 * ((size_t)P + 1) + wa + 2 * n_w + 1 + 24 + (size_t)tab;
 }
 
+struct mw_small_lds {
+    mw_recv_peer *pinfo;    // [P]      the peers' records
+    uint32_t *rbase;        // [P + 1]  first row (over all peers) of peer q
+    uint32_t *nrow;         // [P + 1]  rows taken from peer q
+    uint32_t *dbase;        // [P + 1]  first descriptor (over all peers) of peer q
+    uint32_t *addr;         // [wa]     bit r: row r's group names this rank
+    uint32_t *bits;         // [n_w]    (expert, peer, source token) in output order
+    uint32_t *pre;          // [n_w + 1] running popcount in front of each word
+    uint32_t *scratch;      // [17] scan scratch, [17] flags, [18] addressed rows
+    int32_t *tab;           // [tab_words] the experts' ranks and slots, if there is room
+    uint32_t wa, n_w;
+};
+__device__ __forceinline__ mw_small_lds small_lds_at(const mw_index_args &a, uint32_t *lds)
+{
+    const uint32_t P = (uint32_t)a.P;
+    const uint64_t m_max = (uint64_t)P * a.max_tokens < a.cap_rows ? (uint64_t)P * a.max_tokens : a.cap_rows;
+    mw_small_lds m;
+    m.wa = (uint32_t)((m_max + 31) / 32);
+    m.n_w = (uint32_t)a.L * P * a.wpl;
+    m.pinfo = (mw_recv_peer *)lds;
+    m.rbase = lds + 10 * P;
+    m.nrow = m.rbase + P + 1;
+    m.dbase = m.nrow + P + 1;
+    m.addr = m.dbase + P + 1;
+    m.bits = m.addr + m.wa;
+    m.pre = m.bits + m.n_w;
+    m.scratch = m.pre + m.n_w + 1;
+    m.tab = (int32_t *)(m.scratch + 24);
+    return m;
+}
+
 // kSmallRows: rows (and descriptors) a lane keeps in registers; further ones go through memory.
 // kLimit: more received rows than this (0: any number) are left to the launch's other form.
-template <int kSmallRows, uint32_t kLimit = 0>
+// kAll: every workgroup of the launch makes the index for itself, in LDS (expand_small goes on from there); the first one writes what
+// is written once, records and hits are left to expand_small.
+template <int kSmallRows, uint32_t kLimit = 0, bool kAll = false>
 __device__ __forceinline__ void recv_index_small(const mw_index_args &a, uint32_t *lds)
 {
     const uint32_t tid = threadIdx.x, nthr = blockDim.x;
     const uint32_t P = (uint32_t)a.P, L = (uint32_t)a.L, wpl = a.wpl, K = (uint32_t)a.K, Kd = (uint32_t)a.Kd;
     const uint32_t E = (uint32_t)a.E, my_rank = (uint32_t)a.my_rank, max_tokens = a.max_tokens, cap_rows = a.cap_rows;
-    const uint64_t m_max = (uint64_t)P * max_tokens < cap_rows ? (uint64_t)P * max_tokens : cap_rows;
-    const uint32_t wa = (uint32_t)((m_max + 31) / 32), n_w = L * P * wpl;
-    mw_recv_peer *pinfo = (mw_recv_peer *)lds;          // [P]      the peers' records
-    uint32_t *rbase = lds + 10 * P;                     // [P + 1]  first row (over all peers) of peer q
-    uint32_t *nrow = rbase + P + 1;                     // [P + 1]  rows taken from peer q
-    uint32_t *dbase = nrow + P + 1;                     // [P + 1]  first descriptor (over all peers) of peer q
-    uint32_t *addr = dbase + P + 1;                     // [wa]     bit r: row r's group names this rank
-    uint32_t *bits = addr + wa;                         // [n_w]    (expert, peer, source token) in output order
-    uint32_t *pre = bits + n_w;                         // [n_w + 1] running popcount in front of each word
-    uint32_t *scratch = pre + n_w + 1;                  // [17] scan scratch, [17] flags, [18] addressed rows
-    int32_t *tab = (int32_t *)(scratch + 24);           // [tab_words] the experts' ranks and slots, if there is room
-    const bool in_lds = a.tab_words != 0;
+    const mw_small_lds at = small_lds_at(a, lds);
+    const uint32_t wa = at.wa, n_w = at.n_w;
+    mw_recv_peer *pinfo = at.pinfo;
+    uint32_t *rbase = at.rbase, *nrow = at.nrow, *dbase = at.dbase, *addr = at.addr, *bits = at.bits, *pre = at.pre, *scratch = at.scratch;
+    int32_t *tab = at.tab;
+    const bool in_lds = a.tab_words != 0, writer = !kAll || blockIdx.x == 0;
     const mw_recv_peer *peers = (const mw_recv_peer *)a.peers;
     uint32_t err = 0;
 
@@ -683,8 +710,8 @@ __device__ __forceinline__ void recv_index_small(const mw_index_args &a, uint32_
         if (before + nq > cap_rows) err |= MW_FLAG_RECV_CAPACITY;
         const uint32_t rb = min(before, cap_rows), nr = min(before + nq, cap_rows) - rb;
         rbase[tid] = rb; nrow[tid] = nr; dbase[tid] = dbefore;
-        a.row_base[tid] = rb;
-        if (tid == P - 1) { rbase[P] = rb + nr; dbase[P] = dbefore + dq; a.row_base[P] = rb + nr; }
+        if (writer) a.row_base[tid] = rb;
+        if (tid == P - 1) { rbase[P] = rb + nr; dbase[P] = dbefore + dq; if (writer) a.row_base[P] = rb + nr; }
     }
     mw_lds_barrier();
     const uint32_t M = rbase[P], D = dbase[P];
@@ -835,7 +862,7 @@ __device__ __forceinline__ void recv_index_small(const mw_index_args &a, uint32_
                 if ((seen >> le) & 1ull) continue;
                 seen |= 1ull << le;
                 if (nk < 8) les |= (uint64_t)le << (8 * nk);
-                if (!cached || nk >= 8) h[nk] = mw_hit{(int32_t)le, 0};
+                if (!kAll && (!cached || nk >= 8)) h[nk] = mw_hit{(int32_t)le, 0};
                 ++nk;
                 if ((atomicOr(&bits[(le * P + q) * wpl + (s >> 5)], 1u << (s & 31u)) >> (s & 31u)) & 1u)
                     err |= MW_FLAG_DUP_SRC_TOKEN;
@@ -863,7 +890,7 @@ __device__ __forceinline__ void recv_index_small(const mw_index_args &a, uint32_
         mw_row_rec rec;
         uint64_t les;
         parse_mark(r, q, i, s, false, none, false, rec, les);
-        a.recs[r] = rec;
+        if (!kAll) a.recs[r] = rec;
     }
     mw_lds_barrier();
 
@@ -879,11 +906,13 @@ __device__ __forceinline__ void recv_index_small(const mw_index_args &a, uint32_
     }
     mw_lds_barrier();
     const uint32_t Q = pre[n_w];
+    if (writer)
     for (uint32_t f = tid; f < L * P; f += nthr) {
         const uint32_t b = pre[f * wpl];
         a.base[f] = b;
         if (f % P == 0) a.expert_offsets[f / P] = (int64_t)b;
     }
+    if constexpr (!kAll) {
     // ---- ranks: output row of (row, expert) minus the base of its (expert, peer)
     auto rank_of = [&](uint32_t q, uint32_t s, int le) -> int32_t {
         const uint32_t w0 = ((uint32_t)le * P + q) * wpl, wi = w0 + (s >> 5);
@@ -914,6 +943,8 @@ __device__ __forceinline__ void recv_index_small(const mw_index_args &a, uint32_
             if (k == 0) rc->rank0 = rk; else h[k].rank = rk;
         }
     }
+    }
+    if (!writer) return;                                // (the whole workgroup)
     if (err) atomicOr(&scratch[17], err);
     mw_lds_barrier();
     if (tid == 0) {
@@ -1140,6 +1171,74 @@ __global__ __launch_bounds__(kSmallLanes) void k_recv_index_small(const mw_index
 {
     extern __shared__ uint64_t small_index_lds[];
     recv_index_small<1>(a, (uint32_t *)small_index_lds);
+}
+
+// Index and expander of a small batch in one launch (mw_unpack).  At a few hundred rows both are latency: the index's chain, a
+// launch, and the expander's own chain from the record to the row.  Here every workgroup makes the whole index for itself in
+// LDS -- a few dozen bytes a row, from L2 -- and then moves its share of the rows, a wave a segment of 64 chunks at a time: the row's
+// ids, its token and its payload are requested together, and its places are read off the bitmaps.  Records and hit slots are
+// still written (the way back and a second expander read them), each by the wave that has the row's first segment.
+// Measured beside the rule in mw_launch_unpack.
+__device__ __forceinline__ void expand_small(const mw_index_args &a, uint32_t *lds, int xc, int sc, u32x4 *__restrict__ out_rows,
+                                             u32x4 *__restrict__ out_scales, uint32_t cap, int32_t *__restrict__ out_src_peer,
+                                             int32_t *__restrict__ out_src_token)
+{
+    const mw_small_lds at = small_lds_at(a, lds);
+    const uint32_t P = (uint32_t)a.P, K = (uint32_t)a.K, E = (uint32_t)a.E, wpl = a.wpl, lane = threadIdx.x & 63u;
+    const uint32_t n = (uint32_t)(xc + sc), nseg = (n + 63u) / 64u;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const uint32_t n_wave = gridDim.x * (blockDim.x >> 6), M = at.rbase[P], items = M * nseg;
+    for (uint32_t item = blockIdx.x * (blockDim.x >> 6) + wave; item < items; item += n_wave) {
+        const uint32_t r = item / nseg, seg = item - r * nseg;            // (rows of at most 64 KiB: items stay below 2^20)
+        // the peer whose rows reach over r: the last one that begins at or before it
+        uint32_t q = 0;
+        for (uint32_t b = 0; b < P; b += 64u) q += (uint32_t)__popcll(__ballot(b + lane < P && at.rbase[b + lane] <= r));
+        --q;
+        const mw_recv_peer &pr = at.pinfo[q];
+        const uint32_t i = r - at.rbase[q], c = seg * 64u + lane;
+        const char *src = (const char *)pr.rows + (size_t)i * a.row_bytes;
+        u32x4 v = {0u, 0u, 0u, 0u};
+        if (c < n) v = mw_ld16_global(src, (int)c);
+        const uint32_t s_ = (uint32_t)pr.row_src_token[i];
+        const uint32_t e = lane < K ? (uint32_t)pr.row_topk[(size_t)i * K + lane] : 0xffffffffu;
+        const uint32_t s = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_);
+        const int32_t t = e < E ? (a.tab_words ? at.tab[e] : a.eslot[e]) : -1;
+        uint64_t local = __ballot((uint32_t)t >> 16 == (uint32_t)a.my_rank);                   // (-1: no rank)
+        if (!((at.addr[r >> 5] >> (r & 31u)) & 1u) || s >= a.max_tokens) local = 0;
+        mw_row_rec rec = {nullptr, 0, (int32_t)q, 0, 0, 0, 0};
+        if (local) { rec.src = src; rec.src_token = (int32_t)s; }
+        uint64_t named = 0;
+        int32_t nk = 0;
+        while (local) {
+            const int b = (int)__builtin_ctzll(local);
+            local &= local - 1ull;
+            const uint32_t le = (uint32_t)__builtin_amdgcn_readlane(t, b) & 63u;
+            if ((named >> le) & 1ull) continue;
+            named |= 1ull << le;
+            const uint32_t w0 = (le * P + q) * wpl, w = w0 + (s >> 5);
+            const uint32_t dst = at.pre[w] + (uint32_t)__popc(at.bits[w] & ((1u << (s & 31u)) - 1u));
+            const int32_t rank = (int32_t)(dst - at.pre[w0]);
+            if (dst < cap) {
+                if (c < (uint32_t)xc) mw_st16(out_rows + (size_t)dst * xc + c, v);
+                else if (c < n) out_scales[(size_t)dst * sc + (c - (uint32_t)xc)] = v;
+                if (c == 0) { out_src_peer[dst] = (int32_t)q; out_src_token[dst] = (int32_t)s; }
+            }
+            if (nk == 0) { rec.le0 = (int32_t)le; rec.rank0 = rank; }
+            else if (c == 0) a.hits[(size_t)r * a.Kd + nk] = mw_hit{(int32_t)le, rank};
+            ++nk;
+        }
+        rec.n_hits = nk;
+        if (c == 0) a.recs[r] = rec;
+    }
+}
+
+__global__ __launch_bounds__(kSmallLanes) void k_unpack_small(const mw_index_args a, int xc, int sc, u32x4 *__restrict__ out_rows,
+                                                              u32x4 *__restrict__ out_scales, uint32_t cap,
+                                                              int32_t *__restrict__ out_src_peer, int32_t *__restrict__ out_src_token)
+{
+    extern __shared__ uint64_t small_unpack_lds[];
+    recv_index_small<1, 0, true>(a, (uint32_t *)small_unpack_lds);
+    expand_small(a, (uint32_t *)small_unpack_lds, xc, sc, out_rows, out_scales, cap, out_src_peer, out_src_token);
 }
 
 // The way back (Section 2.1, combine-style AlltoAll; Section 2.3.2: the combine phase reduces
@@ -1467,6 +1566,36 @@ int32_t mw_launch_unpack_expand(mw_ctx *ctx, int32_t P, void *out_rows, float *o
     }
     MW_HIP_CHECK(hipGetLastError());
     return MW_OK;
+}
+
+int32_t mw_launch_unpack(mw_ctx *ctx, const mw_recv_peer *peers, int32_t P, void *out_rows, float *out_scales, int64_t cap,
+                         int32_t *out_src_peer, int32_t *out_src_token, int64_t *expert_offsets, mw_recv_stats *stats, hipStream_t s)
+{
+    // Index and expander in one launch as long as a row is at most a lane's and the payload is short (us in two launches / in
+    // one: 244 rows of 512 bytes 9.6 / 6.7, 355 of 14336 12.9 / 10.6, 506 of 14336 12.4 / 11.7 but 14.0 / 14.2 for a call among
+    // idle ones, 244 of 65536 12.5 / 16.1; 812 rows of 2048 12.9 / 11.7, 646 of 14336 15.4 / 16.2, 1007 of 14336 15.5 / 21.0).
+    // More rows than expected are moved all the same.
+    constexpr int64_t kSmallUnpackBytes = 6 << 20;
+    const int64_t expected = ctx->recv_rows_hint > 0 ? ctx->recv_rows_hint : (int64_t)P * ctx->cfg.max_tokens;
+    mw_index_args a;
+    size_t lds_index;
+    if (expected <= kSmallLanes && small_index_fits(ctx, P) && expected * ctx->row_bytes <= kSmallUnpackBytes &&
+        ctx->row_bytes <= 65536 && ctx->cfg.max_recv_rows > 0 &&
+        make_index_args(ctx, peers, false, P, cap, expert_offsets, stats, kIndexAcceptWords, 16384, 1, kMaxIndexParts, &a, &lds_index)) {
+        { mw_timed tm(ctx, MW_KERNEL_RECV_INDEX, s); }       // (its event pair, where a caller has set one, brackets nothing)
+        mw_timed tm(ctx, MW_KERNEL_EXPAND, s);
+        const int xc = (int)(ctx->x_row_bytes / 16), sc = (int)(ctx->s_row_bytes / 16);
+        const int64_t waves = expected * ((xc + sc + 63) / 64), wgs = (waves + kSmallLanes / 64 - 1) / (kSmallLanes / 64);
+        const int grid = wgs < 1 ? 1 : wgs < ctx->n_cu ? (int)wgs : ctx->n_cu;
+        const size_t lds = small_index_lds(ctx, P, &a);
+        hipLaunchKernelGGL(k_unpack_small, dim3(grid), dim3(kSmallLanes), lds, s, a, xc, sc, (u32x4 *)out_rows, (u32x4 *)out_scales,
+                           (uint32_t)(cap < 0x7fffffffLL ? cap : 0x7fffffffLL), out_src_peer, out_src_token);
+        MW_HIP_CHECK(hipGetLastError());
+        return MW_OK;
+    }
+    const int32_t rc = mw_launch_unpack_index(ctx, peers, false, P, cap, expert_offsets, stats, s);
+    if (rc != MW_OK) return rc;
+    return mw_launch_unpack_expand(ctx, P, out_rows, out_scales, cap, out_src_peer, out_src_token, s);
 }
 
 // The riders of k_small_step beside its one-workgroup index (false: they are not needed).  *fits: both forms can be had.
