@@ -17,14 +17,15 @@
 namespace {
 
 // blockIdx.x = segment of blockDim.x chunks, blockIdx.y walks packed rows.
+template <bool kFold>
 __global__ __launch_bounds__(1024) void k_pack(const int32_t *__restrict__ perm, const mw_send_stats *__restrict__ stats,
                                                const u32x4 *__restrict__ x, const u32x4 *__restrict__ scales,
                                                int xc, int sc, int ns, int K,      // (in registers when a wave starts)
                                                const int32_t *__restrict__ topk, u32x4 *__restrict__ packed,
                                                int32_t *__restrict__ row_src_token, int32_t *__restrict__ row_topk)
 {
-    mw_pack_body(x, scales, xc, sc, ns, topk, K, perm, stats, packed, row_src_token, row_topk, blockIdx.x, blockIdx.y,
-                 gridDim.y);
+    mw_pack_body<kFold>(x, scales, xc, sc, ns, topk, K, perm, stats, packed, row_src_token, row_topk, blockIdx.x, blockIdx.y,
+                        gridDim.y);
 }
 
 // The packer for packets (Section 6.4: the bitmap embedded in front of the payload): packet i =
@@ -218,12 +219,12 @@ int32_t mw_launch_pack(mw_ctx *ctx, const void *x, const float *scales, const in
 {
     if (T == 0) return MW_OK;
     const int xc = (int)(ctx->x_row_bytes / 16), sc = (int)(ctx->s_row_bytes / 16);
-    const mw_row_shape shape = mw_row_shape_of(xc + sc);
+    const mw_row_shape shape = mw_row_shape_folded(xc + sc);
     const uint32_t gy = (uint32_t)T < kRowGridMax ? (uint32_t)T : kRowGridMax;
     {
         mw_timed tm(ctx, MW_KERNEL_PACK, s);
-        hipLaunchKernelGGL(k_pack, dim3(shape.nseg, gy), dim3(shape.bs), 0, s, perm, stats, (const u32x4 *)x,
-                           (const u32x4 *)scales, xc, sc, (int)(ctx->row_stride / 16), ctx->cfg.top_k, topk,
+        hipLaunchKernelGGL(mw_is_folded(shape, xc + sc) ? k_pack<true> : k_pack<false>, dim3(shape.nseg, gy), dim3(shape.bs), 0, s,
+                           perm, stats, (const u32x4 *)x, (const u32x4 *)scales, xc, sc, (int)(ctx->row_stride / 16), ctx->cfg.top_k, topk,
                            (u32x4 *)packed, row_src_token, row_topk);
     }
     MW_HIP_CHECK(hipGetLastError());

@@ -18,6 +18,8 @@ struct mw_pack_args {
     u32x4 *packed; int32_t *row_src_token, *row_topk;
 };
 
+// kFold: a row is one workgroup, and its lane c takes chunk c + blockDim.x as well where there is one (mw_row_shape_folded).
+template <bool kFold>
 __device__ __forceinline__ void mw_pack_body(const u32x4 *__restrict__ x, const u32x4 *__restrict__ scales,
                                              int xc, int sc, int ns, const int32_t *__restrict__ topk, int K,
                                              const int32_t *__restrict__ perm,
@@ -37,10 +39,14 @@ __device__ __forceinline__ void mw_pack_body(const u32x4 *__restrict__ x, const 
     MW_PIN_S(t); MW_PIN_S(n_rows);
     const int n = xc + sc;
     const int c = seg * bdim + threadIdx.x;
+    const int c2 = c + (int)bdim;
     while (i < n_rows) {
         if (c < n) {
+            u32x4 v2;
+            if (kFold && c2 < n) v2 = (c2 < xc) ? mw_ld16(x + (size_t)t * xc + c2) : mw_ld16(scales + (size_t)t * sc + (c2 - xc));
             const u32x4 v = (c < xc) ? mw_ld16(x + (size_t)t * xc + c) : mw_ld16(scales + (size_t)t * sc + (c - xc));
             mw_st16(packed + (size_t)i * ns + c, v);
+            if (kFold && c2 < n) mw_st16(packed + (size_t)i * ns + c2, v2);
         }
         if (seg == 0) {
             if (threadIdx.x == 0) row_src_token[i] = t;

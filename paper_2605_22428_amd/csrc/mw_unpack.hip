@@ -486,7 +486,19 @@ __device__ __forceinline__ void recv_index_body(const mw_index_args &a, const ui
         const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(lane >> 6));
         lane &= 63u;
         const uint32_t per = (wpl + 63u) / 64u, w0 = min(wpl, lane * per), w1 = min(wpl, w0 + per);
-        for (uint32_t l = wave; l < lc; l += nthr >> 6) {
+        const uint32_t n_wave = nthr >> 6;
+        uint32_t l = wave;
+        if (per == 1)                                // a word a lane: four experts side by side
+            for (; l + 3u * n_wave < lc; l += 4u * n_wave) {
+                uint32_t c[4], inc[4];
+#pragma unroll
+                for (uint32_t j = 0; j < 4; ++j) c[j] = lane < wpl ? (uint32_t)__popc(bits[(l + j * n_wave) * wpl + lane]) : 0u;
+#pragma unroll
+                for (uint32_t j = 0; j < 4; ++j) inc[j] = mw_wave_incl_scan(c[j]);
+#pragma unroll
+                for (uint32_t j = 0; j < 4; ++j) if (lane < wpl) pre[(l + j * n_wave) * wpl + lane] = (uint16_t)(inc[j] - c[j]);
+            }
+        for (; l < lc; l += n_wave) {
             const uint32_t *b = bits + l * wpl;
             const uint32_t c = w0 < w1 ? (uint32_t)__popc(b[w0]) : 0u;
             uint32_t sum = c;
@@ -963,6 +975,8 @@ __device__ __forceinline__ void recv_index_small(const mw_index_args &a, uint32_
 // the first output position are issued together; the position is there long before the
 // payload is.
 // g_first / g_stride: the first row of this workgroup and the distance to its next one.
+// kFold: a row is one workgroup, and its lane c takes chunk c + blockDim.x as well where there is one (mw_row_shape_folded).
+template <bool kFold = false>
 __device__ __forceinline__ void expand_body(
     const mw_row_rec *__restrict__ recs, const mw_hit *__restrict__ hits, const uint32_t *__restrict__ base,
     const uint32_t *__restrict__ row_base, int P, int Kd, int xc, int sc,
@@ -985,18 +999,24 @@ __device__ __forceinline__ void expand_body(
     MW_PIN_S4(r0); MW_PIN_S4(r1); MW_PIN_S(m_total);
     const int n = xc + sc;
     const int c = blockIdx.x * bdim + threadIdx.x;
+    const int c2 = c + (int)bdim;
     while (g < m_total) {
         const int n_hits = (int)r1.x;
         if (n_hits > 0) {
             const int peer = (int)r0.w;
             const void *src = (const void *)(((uint64_t)r0.y << 32) | r0.x);
             uint32_t b0 = base[r1.y * (uint32_t)P + (uint32_t)peer];
-            u32x4 v = {0u, 0u, 0u, 0u};
+            u32x4 v = {0u, 0u, 0u, 0u}, v2 = v;
             if (c < n) v = mw_ld16_global(src, c);
+            if (kFold && c2 < n) v2 = mw_ld16_global(src, c2);
             MW_PIN_S(b0);                                  // position lookup in flight with the payload
             uint32_t dst = b0 + r1.z;                      // below 2^30: 2^24 rows, 64 experts each
             for (int k = 1;; ++k) {
                 if (dst < cap) {
+                    if (kFold && c2 < n) {
+                        if (c2 < xc) mw_st16(out_rows + (size_t)dst * xc + c2, v2);
+                        else out_scales[(size_t)dst * sc + (c2 - xc)] = v2;
+                    }
                     if (c < xc) mw_st16(out_rows + (size_t)dst * xc + c, v);
                     // a row's scales are a fraction of a cache line (224 bytes of fp8 rows): an
                     // ordinary store lets L2 put neighbouring rows' pieces together before the
@@ -1015,14 +1035,15 @@ __device__ __forceinline__ void expand_body(
     }
 }
 
+template <bool kFold>
 __global__ __launch_bounds__(1024) void k_expand(
     const mw_row_rec *__restrict__ recs, const uint32_t *__restrict__ row_base, const uint32_t *__restrict__ base,
     const mw_hit *__restrict__ hits, int P, int Kd, int xc, int sc,     // (in registers when a wave starts)
     u32x4 *__restrict__ out_rows, u32x4 *__restrict__ out_scales, uint32_t cap,
     int32_t *__restrict__ out_src_peer, int32_t *__restrict__ out_src_token)
 {
-    expand_body(recs, hits, base, row_base, P, Kd, xc, sc, out_rows, out_scales, cap, out_src_peer, out_src_token,
-                blockIdx.y, gridDim.y);
+    expand_body<kFold>(recs, hits, base, row_base, P, Kd, xc, sc, out_rows, out_scales, cap, out_src_peer, out_src_token,
+                       blockIdx.y, gridDim.y);
 }
 
 // One launch for a steady stream of batches: the expander of the current batch and, in the
@@ -1042,7 +1063,7 @@ __global__ __launch_bounds__(1024) void k_expand(
 // plan's second half); batches too small to hide them give them launches of their own.  kFormMany (top_k
 // above eight) spills five: beside 61 us of movers 65 us against 72 with the index in front, beside 22
 // us 22.6 against 34.4.
-template <int kForm>
+template <int kForm, bool kFold>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_expand_index_next(
     const uint32_t first_expand_row, const uint32_t unused0, const mw_row_rec *__restrict__ recs,
     const uint32_t *__restrict__ row_base, const uint32_t *__restrict__ base, const mw_hit *__restrict__ hits,
@@ -1051,8 +1072,8 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
     int32_t *__restrict__ out_src_peer, int32_t *__restrict__ out_src_token, const mw_index_args next)
 {
     if (blockIdx.y >= first_expand_row) {
-        expand_body(recs, hits, base, row_base, P, Kd, xc, sc, out_rows, out_scales, cap, out_src_peer, out_src_token,
-                    blockIdx.y - first_expand_row, gridDim.y - first_expand_row);
+        expand_body<kFold>(recs, hits, base, row_base, P, Kd, xc, sc, out_rows, out_scales, cap, out_src_peer, out_src_token,
+                           blockIdx.y - first_expand_row, gridDim.y - first_expand_row);
         return;
     }
     const uint32_t w = blockIdx.y * gridDim.x + blockIdx.x;
@@ -1068,7 +1089,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
 // on a second stream and one event wait per batch (171 us); fp8 rows of half the size 101
 // against 105 us.  The riding plan is not free: its device-scope atomics and loads take
 // about 4 us of memory-channel time from the expander.
-template <int W, bool kKeyed, int kForm>
+template <int W, bool kKeyed, int kForm, bool kFold>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_expand_index_plan_next(
     const uint32_t first_pack_row, const uint32_t first_expand_row, const mw_row_rec *__restrict__ recs,
     const uint32_t *__restrict__ row_base, int P, int xc, const int32_t *__restrict__ pack_perm,
@@ -1088,13 +1109,13 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
     // where decoding the roles one by one took five.
     const uint32_t y_pack = first_pack_row, y_expand = first_expand_row;
     if (blockIdx.y >= y_expand) {
-        expand_body(recs, hits, base, row_base, P, Kd, xc, sc, out_rows, out_scales, cap, out_src_peer, out_src_token,
-                    blockIdx.y - y_expand, gridDim.y - y_expand);
+        expand_body<kFold>(recs, hits, base, row_base, P, Kd, xc, sc, out_rows, out_scales, cap, out_src_peer, out_src_token,
+                           blockIdx.y - y_expand, gridDim.y - y_expand);
         return;
     }
     if (blockIdx.y >= y_pack) {         // (mw_stream_step: the packer of a batch planned by an earlier launch)
-        mw_pack_body(pack.x, pack.scales, pack.xc, pack.sc, pack.ns, pack.topk, pack.K, pack_perm, pack_stats, pack.packed,
-                     pack.row_src_token, pack.row_topk, blockIdx.x, blockIdx.y - y_pack, y_expand - y_pack);
+        mw_pack_body<kFold>(pack.x, pack.scales, pack.xc, pack.sc, pack.ns, pack.topk, pack.K, pack_perm, pack_stats, pack.packed,
+                            pack.row_src_token, pack.row_topk, blockIdx.x, blockIdx.y - y_pack, y_expand - y_pack);
         return;
     }
     const uint32_t w = blockIdx.y * gridDim.x + blockIdx.x, n_index = index_riders(next);
@@ -1134,9 +1155,9 @@ __global__ __launch_bounds__(kSmallLanes) void k_small_step(
         return;
     }
     if (blockIdx.y >= first_pack_row) {
-        mw_pack_body(pack.x, pack.scales, pack.xc, pack.sc, pack.ns, pack.topk, pack.K, pack_perm, pack_stats, pack.packed,
-                     pack.row_src_token, pack.row_topk, blockIdx.x, blockIdx.y - first_pack_row,
-                     first_expand_row - first_pack_row);
+        mw_pack_body<false>(pack.x, pack.scales, pack.xc, pack.sc, pack.ns, pack.topk, pack.K, pack_perm, pack_stats, pack.packed,
+                            pack.row_src_token, pack.row_topk, blockIdx.x, blockIdx.y - first_pack_row,
+                            first_expand_row - first_pack_row);
         return;
     }
     extern __shared__ uint64_t small_lds[];
@@ -1399,7 +1420,6 @@ static int index_form(const mw_index_args &a)
 static uint32_t rider_lds_words(int bs) { return (uint32_t)bs * 20u; }
 constexpr uint32_t kRiderAcceptWords = 1280, kIndexAcceptWords = 12288;   // limits on max_tokens the entry points state
 constexpr uint32_t kMaxIndexParts = 16;
-
 // What the row movers of a launch will take, in microseconds: `pack_tokens` rows packed and the received rows
 // read once and written once per local expert, at 5.6 TB/s.
 static double movers_us(const mw_ctx *ctx, int32_t P, int32_t pack_tokens)
@@ -1409,6 +1429,33 @@ static double movers_us(const mw_ctx *ctx, int32_t P, int32_t pack_tokens)
     return ((double)expected_rows(ctx, P) * (1.0 + copies) + 2.0 * pack_tokens) * (double)ctx->row_bytes / 5.6e6;
 }
 
+// Workgroups over which the rows of a peer are spread, and what a rider then takes.
+static int64_t rows_a_lane(const mw_ctx *next, int32_t P, int bs)
+{
+    const int64_t rows = (expected_rows(next, P) + P - 1) / P;
+    return (rows + bs - 1) / bs;
+}
+static uint32_t index_row_parts(const mw_ctx *next, int32_t P, int bs)
+{
+    const int64_t per_lane = rows_a_lane(next, P, bs);
+    return per_lane >= 8 ? 4u : per_lane >= 4 ? 2u : 1u;
+}
+static double rider_us(const mw_ctx *next, int32_t P, int bs, uint32_t row_parts)
+{
+    const double row_us = 1.4 * (double)((next->cfg.top_k + 7) / 8);
+    return 6.0 + row_us * (double)rows_a_lane(next, P, bs) * (1.0 + 1.0 / row_parts);
+}
+
+// Row movers beside riders: folded where the narrower riders stay well below the movers (2048 fp8 tokens of 264 chunks, us a step not
+// folded / folded: 16 ranks, 860 rows a peer, 39.3 / 36.4; 8 ranks, 1344 rows a peer and 32 experts, 37.2 / 38.6).
+static mw_row_shape rider_row_shape(const mw_ctx *ctx, const mw_ctx *next, int32_t P, int32_t next_P, int32_t pack_tokens, int chunks)
+{
+    const mw_row_shape s = mw_row_shape_folded(chunks);
+    if (mw_is_folded(s, chunks) && rider_us(next, next_P, s.bs, index_row_parts(next, next_P, s.bs)) > 0.7 * movers_us(ctx, P, pack_tokens))
+        return mw_row_shape_of(chunks);
+    return s;
+}
+
 // Whether the next batch's index rides beside movers of `mover_us` in workgroups of `bs` lanes, and over how many
 // workgroups its rows are then spread.  A rider takes about 1.4 us for every row and eight ids a lane of each pass; a launch of its own
 // about 12 us.  Measured (us for expander and index; rows of a peer / lanes): 42 rows a lane, expander 80 us: 85.6 riding
@@ -1416,11 +1463,8 @@ static double movers_us(const mw_ctx *ctx, int32_t P, int32_t pack_tokens)
 static bool index_rides(const mw_ctx *next, double mover_us, int bs, mw_index_args *a)
 {
     if (index_form(*a) == kFormAny) return false;                   // (spills 25 of the riders' 64 registers)
-    const int64_t rows = (expected_rows(next, a->P) + a->P - 1) / a->P;
-    const int64_t per_lane = (rows + bs - 1) / bs;
-    a->row_parts = a->dedup ? 1u : per_lane >= 8 ? 4u : per_lane >= 4 ? 2u : 1u;
-    const double row_us = 1.4 * (double)((a->K + 7) / 8);
-    return 6.0 + row_us * (double)per_lane * (1.0 + 1.0 / a->row_parts) < mover_us + 12.0;
+    a->row_parts = a->dedup ? 1u : index_row_parts(next, a->P, bs);
+    return rider_us(next, a->P, bs, a->row_parts) < mover_us + 12.0;
 }
 
 // Whether the next batch's plan rides beside movers of `mover_us` in workgroups of `bs` lanes.  It ranks tokens all-pairs over
@@ -1539,7 +1583,7 @@ static uint32_t expand_grid_rows(const mw_ctx *ctx, int32_t P)
     int64_t rows = expected_rows(ctx, P);
     rows += rows / 64 + 64;
     if (ctx->recv_rows_hint == 0) {
-        const mw_row_shape shape = mw_row_shape_of((int)(ctx->row_bytes / 16));
+        const mw_row_shape shape = mw_row_shape_folded((int)(ctx->row_bytes / 16));
         const int64_t filling = (int64_t)ctx->n_cu * 2048 / ((int64_t)shape.bs * shape.nseg);
         if (rows < filling) rows = filling;
         else if (rows < 2 * filling) rows = 2 * filling;
@@ -1557,12 +1601,12 @@ int32_t mw_launch_unpack_expand(mw_ctx *ctx, int32_t P, void *out_rows, float *o
     const mw_config &c = ctx->cfg;
     if (c.max_recv_rows > 0) {
         const int xc = (int)(ctx->x_row_bytes / 16), sc = (int)(ctx->s_row_bytes / 16);
-        const mw_row_shape shape = mw_row_shape_of(xc + sc);
+        const mw_row_shape shape = mw_row_shape_folded(xc + sc);
         const uint32_t gy = expand_grid_rows(ctx, P);
         mw_timed tm(ctx, MW_KERNEL_EXPAND, s);
-        hipLaunchKernelGGL(k_expand, dim3(shape.nseg, gy), dim3(shape.bs), 0, s, ctx->d_recs, ctx->d_row_base, ctx->d_base,
-                           ctx->d_hits, P, ctx->hit_slots, xc, sc, (u32x4 *)out_rows, (u32x4 *)out_scales,
-                           (uint32_t)(cap < 0x7fffffffLL ? cap : 0x7fffffffLL), out_src_peer, out_src_token);
+        hipLaunchKernelGGL(mw_is_folded(shape, xc + sc) ? k_expand<true> : k_expand<false>, dim3(shape.nseg, gy), dim3(shape.bs), 0, s,
+                           ctx->d_recs, ctx->d_row_base, ctx->d_base, ctx->d_hits, P, ctx->hit_slots, xc, sc, (u32x4 *)out_rows,
+                           (u32x4 *)out_scales, (uint32_t)(cap < 0x7fffffffLL ? cap : 0x7fffffffLL), out_src_peer, out_src_token);
     }
     MW_HIP_CHECK(hipGetLastError());
     return MW_OK;
@@ -1705,7 +1749,7 @@ int32_t mw_launch_unpack_expand_index_next(mw_ctx *ctx, int32_t P, void *out_row
     const mw_config &c = ctx->cfg;
     if (c.max_recv_rows < 1) return MW_ERR_UNSUPPORTED;       // nothing to ride on
     const int xc = (int)(ctx->x_row_bytes / 16), sc = (int)(ctx->s_row_bytes / 16);
-    mw_row_shape shape = mw_row_shape_of(xc + sc);
+    mw_row_shape shape = rider_row_shape(ctx, next, P, next_P, 0, xc + sc);
     // Rows of whole cache lines: two-wave workgroups here.  The expander runs as fast with them
     // as with single waves (138.8 against 139.4 us at 30590 rows of 14336 bytes), and the riding
     // index gets two waves per peer: with one it outlasts the expander (142 against 139 us).
@@ -1735,7 +1779,9 @@ int32_t mw_launch_unpack_expand_index_next(mw_ctx *ctx, int32_t P, void *out_row
                                ctx->d_recs, ctx->d_row_base, ctx->d_base, ctx->d_hits, P, ctx->hit_slots, xc, sc,
                                (u32x4 *)out_rows, (u32x4 *)out_scales, cap32, out_src_peer, out_src_token, a);
         };
-        if (index_form(a) == kFormMany) launch(k_expand_index_next<kFormMany>); else launch(k_expand_index_next<kFormFew>);
+        const bool fold = mw_is_folded(shape, xc + sc);
+        if (index_form(a) == kFormMany) launch(fold ? k_expand_index_next<kFormMany, true> : k_expand_index_next<kFormMany, false>);
+        else launch(fold ? k_expand_index_next<kFormFew, true> : k_expand_index_next<kFormFew, false>);
     }
     MW_HIP_CHECK(hipGetLastError());
     return MW_OK;
@@ -1753,7 +1799,7 @@ int32_t mw_launch_unpack_expand_index_plan_next(mw_ctx *ctx, int32_t P, void *ou
     if (c.max_recv_rows < 1) return MW_ERR_UNSUPPORTED;       // nothing to ride on
     if (next_T > MW_RIDE_MAX_TOKENS) return MW_ERR_UNSUPPORTED;
     const int xc = (int)(ctx->x_row_bytes / 16), sc = (int)(ctx->s_row_bytes / 16);
-    mw_row_shape shape = mw_row_shape_of(xc + sc);
+    mw_row_shape shape = rider_row_shape(ctx, next, P, next_P, pk ? pk->n_tokens : 0, xc + sc);
     if (shape.bs == 64 && (xc + sc) % 16 == 0) { shape.bs = 128; shape.nseg = (xc + sc) / 128 + ((xc + sc) % 128 ? 1 : 0); }
     mw_index_args a;
     size_t lds_index;
@@ -1824,15 +1870,18 @@ int32_t mw_launch_unpack_expand_index_plan_next(mw_ctx *ctx, int32_t P, void *ou
         const uint32_t gy_fit = gy < 65535u - riders ? gy : 65535u - riders;
         const dim3 grid(shape.nseg, gy_fit + riders), block(shape.bs);
         const uint32_t cap32 = (uint32_t)(cap < 0x7fffffffLL ? cap : 0x7fffffffLL);
+        const bool fold = mw_is_folded(shape, xc + sc);
         auto launch = [&](auto kernel) {
             hipLaunchKernelGGL(kernel, grid, block, lds, s, rider_rows, rider_rows + n_pack_rows, ctx->d_recs,
                                ctx->d_row_base, P, xc, pa.perm, pa.stats, sc, ctx->hit_slots, ctx->d_base, ctx->d_hits,
                                (u32x4 *)out_rows, (u32x4 *)out_scales, cap32, out_src_peer, out_src_token, a, pl, pa);
         };
-#define MW_RIDE(W_, KEYED_)                                                                                        \
-    do {                                                                                                           \
-        if (index_form(a) == kFormMany) launch(k_expand_index_plan_next<W_, false, kFormMany>);   /* (not keyed) */ \
-        else launch(k_expand_index_plan_next<W_, KEYED_, kFormFew>);                                                   \
+#define MW_RIDE_(W_, KEYED_, FORM_)                                                                                  \
+    launch(fold ? k_expand_index_plan_next<W_, KEYED_, FORM_, true> : k_expand_index_plan_next<W_, KEYED_, FORM_, false>)
+#define MW_RIDE(W_, KEYED_)                                                                                          \
+    do {                                                                                                             \
+        if (index_form(a) == kFormMany) MW_RIDE_(W_, false, kFormMany);                            /* (not keyed) */ \
+        else MW_RIDE_(W_, KEYED_, kFormFew);                                                                         \
     } while (0)
         if (keyed) MW_RIDE(4, true);
         else if (W == 1) MW_RIDE(1, false);
@@ -1840,6 +1889,7 @@ int32_t mw_launch_unpack_expand_index_plan_next(mw_ctx *ctx, int32_t P, void *ou
         else if (W == 3) MW_RIDE(3, false);
         else MW_RIDE(4, false);
 #undef MW_RIDE
+#undef MW_RIDE_
     }
     MW_HIP_CHECK(hipGetLastError());
     return MW_OK;
