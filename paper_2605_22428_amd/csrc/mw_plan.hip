@@ -701,9 +701,10 @@ __global__ __launch_bounds__(kOrderBlock) void k_plan_order(
                 const uint64_t eq = __ballot(key[j] == k) & kept[j];
                 if (eq) {
                     const int first = j * bs + wave * 64, ahead = t0 + o - first;        // of the wave's 64 tokens, how many come before
-                    if (first >= t0 + n) {                            // (the same for all own tokens)
+                    // (kU > 1: branches that are the same for all own tokens; with one key a lane they cost what they save)
+                    if (kU > 1 && first >= t0 + n) {
                         after += (uint32_t)__popcll(eq);
-                    } else if (first + 64 <= t0) {
+                    } else if (kU > 1 && first + 64 <= t0) {
                         before += (uint32_t)__popcll(eq);
                     } else {
                         const uint64_t m = ahead <= 0 ? 0ull : ahead >= 64 ? ~0ull : (1ull << ahead) - 1ull;
