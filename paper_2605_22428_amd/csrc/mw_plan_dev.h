@@ -12,6 +12,26 @@ namespace {
 constexpr uint64_t kField = 0x1fffffull;      // 21-bit fields of the packed counter
 constexpr int kPsKept = 256, kPsFlags = 257, kPsDone = 258, kPsDone2 = 259;  // plan state words after the 256 histogram bins
 
+// Ids j0 .. j0 + 7 of one token's list (-1 past its end).  Lists of whole 16-byte units that start on one take two requests
+// instead of eight: a request of 64 lanes whose lists are 32 bytes apart touches sixteen cache lines, and a workgroup's
+// requests take turns (a 64-token stream step of 64 ranks, index and plan, 8.4 -> 7.6 us).
+__device__ __forceinline__ void load_eight_ids(const int32_t *__restrict__ row, int j0, int K, int32_t (&e)[8])
+{
+#pragma unroll
+    for (int u = 0; u < 8; ++u) e[u] = -1;
+    if ((K & 3) == 0 && ((uintptr_t)row & 15u) == 0) {
+        const u32x4 q = *(const u32x4 *)(row + j0);
+        e[0] = (int32_t)q.x; e[1] = (int32_t)q.y; e[2] = (int32_t)q.z; e[3] = (int32_t)q.w;
+        if (j0 + 4 < K) {
+            const u32x4 p = *(const u32x4 *)(row + j0 + 4);
+            e[4] = (int32_t)p.x; e[5] = (int32_t)p.y; e[6] = (int32_t)p.z; e[7] = (int32_t)p.w;
+        }
+    } else {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) if (j0 + u < K) e[u] = row[j0 + u];
+    }
+}
+
 // Destination bitmap of one token (Section 4.1): ids are fetched in independent batches.
 __device__ __forceinline__ void token_mask(const int32_t *__restrict__ row, int K,
                                            const int32_t *__restrict__ eslot, int E, uint64_t m[MW_MASK_WORDS],
@@ -21,8 +41,7 @@ __device__ __forceinline__ void token_mask(const int32_t *__restrict__ row, int 
     for (int q = 0; q < MW_MASK_WORDS; ++q) m[q] = 0;
     for (int j0 = 0; j0 < K; j0 += 8) {
         int32_t e[8], s[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) e[u] = (j0 + u < K) ? row[j0 + u] : -1;
+        load_eight_ids(row, j0, K, e);
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
             const bool ok = (uint32_t)e[u] < (uint32_t)E;
@@ -94,9 +113,8 @@ __device__ __forceinline__ void small_token_mask(const int32_t *__restrict__ top
 {
     const int t = threadIdx.x;
     const int32_t *row = topk + (size_t)t * K;
-    int32_t e[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) e[u] = (t < T && u < K) ? row[u] : -1;
+    int32_t e[8] = {-1, -1, -1, -1, -1, -1, -1, -1};
+    if (t < T) load_eight_ids(row, 0, K, e);
     const bool in_lds = E <= kSmallTab;
     if (in_lds)
 #pragma unroll
@@ -127,8 +145,7 @@ __device__ __forceinline__ void small_token_mask(const int32_t *__restrict__ top
         }
         j0 += 8;
         if (j0 >= K) break;
-#pragma unroll
-        for (int u = 0; u < 8; ++u) e[u] = (j0 + u < K) ? row[j0 + u] : -1;
+        load_eight_ids(row, j0, K, e);
     }
 }
 

@@ -771,8 +771,7 @@ __device__ __forceinline__ void recv_index_small(const mw_index_args &a, uint32_
             const mw_recv_peer &pr = pinfo[q_r[j]];
             s_r[j] = (uint32_t)pr.row_src_token[i_r[j]];
             const int32_t *tk = pr.row_topk + (size_t)i_r[j] * K;
-#pragma unroll
-            for (int u = 0; u < 8; ++u) if ((uint32_t)u < K) e_r[j][u] = tk[u];
+            load_eight_ids(tk, 0, (int)K, e_r[j]);
         }
         dm_d[j] = 0; off_d[j] = 0; cnt_d[j] = 0;
         if (r < D) {
@@ -849,8 +848,7 @@ __device__ __forceinline__ void recv_index_small(const mw_index_args &a, uint32_
                 if (badc) err |= MW_FLAG_BAD_EXPERT;
             } else {
                 int32_t e8[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) e8[u] = (j0 + u < K) ? tk[j0 + u] : -1;
+                load_eight_ids(tk, (int)j0, (int)K, e8);
 #pragma unroll
                 for (int u = 0; u < 8; ++u) {
                     const bool ok = (uint32_t)e8[u] < E;
