@@ -1628,7 +1628,9 @@ int32_t mw_launch_unpack(mw_ctx *ctx, const mw_recv_peer *peers, int32_t P, void
         { mw_timed tm(ctx, MW_KERNEL_RECV_INDEX, s); }       // (its event pair, where a caller has set one, brackets nothing)
         mw_timed tm(ctx, MW_KERNEL_EXPAND, s);
         const int xc = (int)(ctx->x_row_bytes / 16), sc = (int)(ctx->s_row_bytes / 16);
-        const int64_t waves = expected * ((xc + sc + 63) / 64), wgs = (waves + kSmallLanes / 64 - 1) / (kSmallLanes / 64);
+        // (64 rows more than the last batch had: the next one may be larger, and a wave then strides)
+        const int64_t rows = ctx->recv_rows_hint > 0 ? expected + 64 : expected;
+        const int64_t waves = rows * ((xc + sc + 63) / 64), wgs = (waves + kSmallLanes / 64 - 1) / (kSmallLanes / 64);
         const int grid = wgs < 1 ? 1 : wgs < ctx->n_cu ? (int)wgs : ctx->n_cu;
         const size_t lds = small_index_lds(ctx, P, &a);
         hipLaunchKernelGGL(k_unpack_small, dim3(grid), dim3(kSmallLanes), lds, s, a, xc, sc, (u32x4 *)out_rows, (u32x4 *)out_scales,
