@@ -7,7 +7,7 @@
 // peer.  The bitmap of a row's group is the authority on whether this rank is addressed;
 // which local experts get the row follows from the row's top-k ids and the rank table.
 //
-// Two launches on the caller's stream:
+// Two launches on the caller's stream (a batch of a few hundred rows: one, k_unpack_small):
 //   k_recv_index  one workgroup per peer (a few where a peer has many experts here).  Marks
 //                 addressed rows from the descriptor bitmaps, then for every local expert
 //                 builds an LDS bitmap over the peer's source-token indices.  A prefix of popcounts over that bitmap
@@ -15,8 +15,8 @@
 //                 whatever order the rows were packed in -- no sort, no order-dependent
 //                 atomics (LDS atomic ORs only set bits).  Emits per-(expert, peer)
 //                 counts and one record per received row: source address, source token,
-//                 peer and (expert slot, rank) pairs.  The workgroup that finishes last
-//                 (device-scope counter) scans the counts into output bases, so no
+//                 peer and (expert slot, rank) pairs.  The workgroup that reports its counts last
+//                 (device-scope counter) scans them into output bases, so no
 //                 third launch and no grid-wide barrier is needed.
 //   k_expand      small workgroups (a single wave for long cache-line-sized rows, one
 //                 workgroup per row up to 10 KiB), each moving consecutive 16-byte chunks of
