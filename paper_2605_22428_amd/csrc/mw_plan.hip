@@ -448,7 +448,8 @@ __global__ __launch_bounds__(kOrderBlock) void k_plan_order(
         load_ids<kU>(topk, T, K, 0, tid, bs, e);
     }
     if (tab) fill_rank_table(tab, eslot, E);
-    const bool own_bit = kSorted && !kBytes && R <= 5 + slots_log;    // (a bitmap of R ranks is below 32 << slots_log)
+    // keys that have a bit each: bitmaps of R ranks below 32 << slots_log, and keys of at most two ranks
+    const bool few_ranks = !kBytes && R <= 5 + slots_log, own_bit = kSorted && (few_ranks || K <= 2);
     if (!own_bit) for (uint32_t s = tid; s < n_slots / 2; s += bs) ((ulonglong2 *)slot)[s] = make_ulonglong2(kNone, kNone);
     for (uint32_t w = tid; w < filter_words / (own_bit ? 4 : 2); w += bs) ((uint4 *)taken)[w] = make_uint4(0, 0, 0, 0);
     mw_lds_barrier();
@@ -474,8 +475,8 @@ __global__ __launch_bounds__(kOrderBlock) void k_plan_order(
     // bit tells: 32 a token, and who finds his taken marks it as shared.  Only tokens of shared bits go on to a hash table, whose
     // slots belong to the token that fills them: a wave seldom has one, and the table is nearly empty.  (All tokens in a
     // table of two slots a token: every wave waits for the longest probe chain, 6 to 9 us of a plan of 8192.)  The table has a slot for
-    // every token, so a chain ends whatever the keys are.  Bitmaps of few ranks have a bit each: who finds it free is the
-    // representative.
+    // every token, so a chain ends whatever the keys are.  Bitmaps of few ranks and keys of one or two have a bit each: who finds
+    // it free is the representative (72 ranks, two ids: 2600 possible keys for 4414 tokens, 16.2 us through the table).
     // Not sorted: all tokens go to the table, of four slots a token; a wave whose tokens all have one key sends one lane
     // (thousands of compare-and-swaps on one address would queue).
     uint64_t kept[kU], rep[kU];                                       // wave masks
@@ -491,8 +492,14 @@ __global__ __launch_bounds__(kOrderBlock) void k_plan_order(
             kept[j] = __ballot(key[j] != kNone);
             first[j] = key[j] != kNone && ((lo ^ plo) | (hi ^ phi)) != 0;
             hash[j] = (lo ^ (hi << 15 | hi >> 17)) * 0x9E3779B1u;
-            word[j] = own_bit ? lo >> 5 : hash[j] >> (32 - slots_log);           // (kFilterBits == 32: a word a slot)
-            bit[j] = 1u << ((own_bit ? lo : hash[j] >> 12) & 31u);
+            uint32_t own_at = kBytes ? hi >> 16 : lo;                            // (two ranks: two bytes, or two positions)
+            if (!kBytes && own_bit && !few_ranks) {                              // (uniform)
+                const int h = 63 - __clzll((long long)(key[j] | 1ull));
+                const uint64_t rest = key[j] & ~(1ull << h);
+                own_at = (uint32_t)(h * 64 + (rest ? 63 - __clzll((long long)rest) : h));
+            }
+            word[j] = own_bit ? own_at >> 5 : hash[j] >> (32 - slots_log);       // (kFilterBits == 32: a word a slot)
+            bit[j] = 1u << ((own_bit ? own_at : hash[j] >> 12) & 31u);
             old[j] = 0;
             if (first[j]) old[j] = atomicOr(&taken[word[j]], bit[j]);
         }

@@ -73,7 +73,8 @@ def test_plan_forms(shape, T):
 
 
 @pytest.mark.parametrize("T", [2049, 2176, 4095, 6144, 6145, 8065, 8192])
-@pytest.mark.parametrize("R,E,K", [(64, 64, 64), (256, 256, 8), (17, 34, 4), (18, 36, 4), (19, 38, 4)])
+@pytest.mark.parametrize("R,E,K", [(64, 64, 64), (256, 256, 8), (17, 34, 4), (18, 36, 4), (19, 38, 4), (64, 128, 2), (256, 256, 2),
+                                   (256, 256, 1), (72, 144, 2)])
 def test_plan_of_sorted_chunks(R, E, K, T):
     """Chunks of 128 tokens, a lane's four, six or eight tokens, the last chunk partly filled; keys that appear exactly twice,
     anywhere; every rank named (the largest one-word key) among tokens without a destination; most tokens of two keys.  The
