@@ -1469,9 +1469,8 @@ static bool index_rides(const mw_ctx *next, double mover_us, int bs, mw_index_ar
 // workgroups that talk through memory; the finishing ones walk every token's counters, T * T / bs of them, which
 // is what grows beyond a thousand tokens.  Beside movers that are shorter it takes 48 us for 1000 tokens in wide workgroups, 6
 // more with keys of several words, 56 in workgroups of two waves, and there 64 (4096 tokens), 72 (6144), 90 (8192).  A launch of its
-// own takes 8 (up to 2048 tokens), 11 (4096), 13 (6144), 16 us (8192), 18 with more than eight ids and bitmaps of several words.
-// Measured, us a step riding / apart, rows of 7168 from 16 and from 64 peers, when one of 4096 and of 8192 tokens took 13 and
-// 21 (8 ranks, 8192 tokens of one id, fp8 rows of 6336 now 51.8 / 51.5, of 7392 55.7 / 62.1):
+// own takes 8 (up to 2048 tokens), 13 (4096), 21 us (8192), 18 with more than eight ids and bitmaps of several words.  Measured,
+// us a step riding / apart, rows of 7168 from 16 and from 64 peers:
 //   bf16, 256 ranks   1024 tokens 56 / 18, 60 / 23   4096 66 / 43, 68 / 67   6144 72 / 61, 93 / 98   8192 90 / 78, 130 / 128
 //   fp8, 256 ranks    1024 tokens 54 / 15, 55 / 19   4096 57 / 35, 57 / 49   6144 58 / 50, 62 / 72   8192 59 / 63, 83 / 93
 //   bf16, 64 ranks    1024 tokens 56 / 22, 64 / 47   4096 69 / 67, 161 / 172 6144 91 / 100, 256 / 264 8192 122 / 130, 348 / 355
@@ -1486,7 +1485,7 @@ static bool plan_rides(const mw_ctx *next, double mover_us, int32_t T, bool keye
     const double t = T / 8192.0;
     const double rider_us = 13.0 + 35.0 * (T < 1024 ? T : 1024) / 1024.0 + (bs < 256 ? 8.0 : keyed ? 6.0 : 0.0) +
                             32.0 * t * t * 128.0 / bs;
-    const double apart_us = !keyed && next->mask_words > 1 ? 18.0 : T <= 2048 ? 8.0 : T <= 4096 ? 11.0 : T <= 6144 ? 13.0 : 16.0;
+    const double apart_us = !keyed && next->mask_words > 1 ? 18.0 : T <= 2048 ? 8.0 : T <= 4096 ? 13.0 : 21.0;
     return rider_us < mover_us + apart_us;
 }
 
