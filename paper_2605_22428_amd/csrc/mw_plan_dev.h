@@ -41,7 +41,9 @@ __device__ __forceinline__ void token_mask(const int32_t *__restrict__ row, int 
     for (int q = 0; q < MW_MASK_WORDS; ++q) m[q] = 0;
     for (int j0 = 0; j0 < K; j0 += 8) {
         int32_t e[8], s[8];
-        load_eight_ids(row, j0, K, e);
+        // (word by word: both forms side by side cost a riding plan of 4090 tokens of nine ids 4 us a step, 110 -> 118.4 for two)
+#pragma unroll
+        for (int u = 0; u < 8; ++u) e[u] = (j0 + u < K) ? row[j0 + u] : -1;
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
             const bool ok = (uint32_t)e[u] < (uint32_t)E;
