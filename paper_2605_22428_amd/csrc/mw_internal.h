@@ -188,12 +188,18 @@ __device__ __forceinline__ void mw_lds_barrier()
 // depends on reports through a counter; the other side reads the counter and then the data.
 //   producer   every lane: its stores / atomics;  mw_publish_barrier();  one lane: mw_report(counter)
 //   consumer   one lane: reads the counter (mw_report's return value, or a poll followed by
-//              mw_acquire_after_poll());  workgroup barrier;  every lane: reads the data
+//              mw_acquire_after_poll());  mw_consume_barrier();  every lane: reads the data
+// Where ONE WAVE wrote all there is to publish its first lane reports behind mw_publish_wave(), while the other waves go on.
+// If the report was the last the same wave may go on as the consumer without a workgroup barrier: mw_consume_wave()
+// brings the counter's value from its first lane to all of them.  If its workgroup is to go on, that lane hands the value over
+// in LDS and mw_consume_barrier() stands between it and every lane's reads, as above.
 // In memory-model terms: the barrier orders every lane's accesses before the reporting lane's
 // (workgroup scope); the report is a release (and, as a read-modify-write whose value decides who
 // is last, an acquire) at agent scope; the consumer's counter read is an acquire at agent scope;
 // happens-before is transitive over the two scopes, so everything the producer's lanes did is
 // visible to every lane of the consumer after its barrier, whatever cache either side runs behind.
+// (One wave: a release fence of every lane, the wave's barrier and an acquire take the place of the workgroup barrier in
+// front of the report; behind it the wave's barrier and an agent-scope acquire fence of every lane.)
 // The data itself is additionally written and read with agent-scope atomics, which are performed
 // at the device's coherence point, so the release and acquire fences find next to nothing to
 // write back or invalidate on their own account.
@@ -211,22 +217,42 @@ __device__ __forceinline__ void mw_publish_barrier()
 #endif
     __syncthreads();
 }
-// The same where one wave wrote all there is to publish: its lanes' accesses are acknowledged, then one of them reports.
-__device__ __forceinline__ void mw_publish_wave()
-{
-#if MW_PUBLISH_FENCES
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-    __builtin_amdgcn_wave_barrier();
-#else
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-#endif
-}
 __device__ __forceinline__ uint32_t mw_report(uint32_t *counter)
 {
 #if MW_PUBLISH_FENCES
     return __hip_atomic_fetch_add(counter, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
 #else
     return __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#endif
+}
+__device__ __forceinline__ void mw_publish_wave()
+{
+#if MW_PUBLISH_FENCES
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#else
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#endif
+}
+// `value`: what mw_report returned, in the wave's first lane.  Returns it in every lane.
+__device__ __forceinline__ uint32_t mw_consume_wave(uint32_t value)
+{
+    value = (uint32_t)__builtin_amdgcn_readfirstlane((int)value);
+#if MW_PUBLISH_FENCES
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+#endif
+    return value;
+}
+// Between the lane that read the counter and the lanes that read the data.  (LDS only without the fences: the wait for the
+// counter's value is in front of the LDS write that says what it was.)
+__device__ __forceinline__ void mw_consume_barrier()
+{
+#if MW_PUBLISH_FENCES
+    __syncthreads();
+#else
+    mw_lds_barrier();
 #endif
 }
 __device__ __forceinline__ void mw_acquire_after_poll()

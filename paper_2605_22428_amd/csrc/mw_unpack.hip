@@ -188,8 +188,8 @@ __device__ __forceinline__ void recv_index_body(const mw_index_args &a, const ui
     unsigned char *tab = (unsigned char *)(addr + wpl);         // [E + 1]    local slot of expert e or kNotLocal
     uint32_t *bits = addr + wpl + a.tab_words;                  // [Lc][wpl]  bit s of expert l: a row with source token s
     uint16_t *pre = (uint16_t *)(bits + (size_t)Lc * wpl);      // [Lc][wpl]  running popcount before each word (modulo 2^16)
-    uint32_t *scratch = bits + (size_t)Lc * wpl + ((size_t)Lc * wpl + 1) / 2;  // [17] scans, [17] "I am last", [18] addressed
-                                                                // rows, [19] repeats dropped, [20..35] waves' sums, [36] flags
+    uint32_t *scratch = bits + (size_t)Lc * wpl + ((size_t)Lc * wpl + 1) / 2;  // [17] scans, [17] reports in front of this one,
+                                                                // [18] addressed rows, [19] repeats dropped, [20..35] waves' sums, [36] flags
     uint32_t *seen_tok = scratch + 64;                          // [wpl]      (dedup only) bit s: a row with source token s was taken
 
     // ---- everything that depends on the peer record alone is requested before the first wait:
@@ -523,7 +523,7 @@ __device__ __forceinline__ void recv_index_body(const mw_index_args &a, const ui
                     if (part == 0 && row_part == 0) st_agent(&a.addr_cnt[p], scratch[18] - scratch[19]);
                 }
                 mw_publish_wave();
-                if (lane == 0) scratch[17] = mw_report(&a.flags[2]) == P * a.parts * a.row_parts - 1u ? 1u : 0u;
+                if (lane == 0) scratch[17] = mw_report(&a.flags[2]);
             }
         }
 
@@ -582,17 +582,22 @@ __device__ __forceinline__ void recv_index_body(const mw_index_args &a, const ui
     // ---- the workgroup that reported last turns the counts into output bases ----------
     // Everything it reads (counts, addressed-row counts, flags) is written and read with device-scope
     // atomics, and every workgroup reports through one counter when the wave that wrote them has them acknowledged
-    // (publication rules in mw_internal.h); the workgroup whose report is the last has thereby acquired
-    // what all the others released.  The row records and hit slots, written with ordinary stores, are
-    // read by the next kernel only.
+    // (publication of one wave, mw_internal.h); the wave whose report is the last has thereby acquired
+    // what all the others released, and goes on by itself or hands its decision to the workgroup.  The row records
+    // and hit slots, written with ordinary stores, are read by the next kernel only.
     if (L * P <= 64u * kWaveCounts) {
-        if (tid >= nthr - 64u && scratch[17])        // (the wave that reported)
+        // Only the wave that reported, whose first lane reads its own word (kept in a register through pass 2 it cost the
+        // riders of more than eight ids a spill: 2048 fp8 tokens of nine ids 54.1 -> 54.7 us a step)
+        if (tid < nthr - 64u) return;
+        uint32_t n = 0;
+        if (tid == nthr - 64u) n = scratch[17];
+        if (mw_consume_wave(n) == P * a.parts * a.row_parts - 1u)
             mw_finish_counts_wave(a.cnt, a.addr_cnt, a.flags, a.row_base, L, P, a.out_cap, a.base, a.expert_offsets, a.stats);
         return;
     }
-    mw_lds_barrier();
-    if (!scratch[17]) return;
-    mw_lds_barrier();                                // (scratch is used again)
+    mw_consume_barrier();
+    if (scratch[17] != P * a.parts * a.row_parts - 1u) return;
+    mw_consume_barrier();                            // (scratch is used again)
     mw_finish_counts(a.cnt, a.addr_cnt, a.flags, a.row_base, L, P, a.out_cap, a.base, a.expert_offsets, a.stats, scratch);
 }
 
