@@ -53,18 +53,20 @@ static inline mw_row_shape mw_row_shape_of(int chunks)
     return mw_row_shape{b, (chunks + b - 1) / b};
 }
 
-// The same for movers whose first lanes can take a second chunk (expander, packer).  A row of one workgroup whose last wave would
-// have at most sixteen chunks gives them to the first lanes, where a CU's 32 wave slots then hold a third more rows.  An
-// fp8 row's scales are a thirty-second of it and make just such a wave: 264 chunks (4096 codes) in five waves are six rows a
-// CU, in four eight.  Measured, us, before / after: 6600 rows of 264 chunks expanded 13.6 / 13.0, a stream step of 2048 such tokens of
-// 16 ranks 39.3 / 36.4; of 528 chunks 43.5 / 42.8 and 57.6 / 52.7.  Where the CU holds
-// hardly more rows it only costs: 330 chunks 29.4 / 29.4, 396 chunks 33.4 / 33.5 and 49.0 / 49.2, 462 chunks (four rows a CU either
-// way) 76.0 / 76.3 and 90.0 / 94.8.  Short rows: 132 chunks (three waves) 25.2 / 24.6, but 6700 rows of 1.4 hits 10.8 / 11.2.
+// The same for movers whose first lanes can take a second chunk (expander, packer).  A row whose last wave would have at most
+// sixteen chunks gives them to its first lanes where four, eight or sixteen waves are left: a CU's 32 wave slots then hold a
+// third more rows, and no slot is left over.  An fp8 row's scales are a thirty-second of it and make just such a wave: 264
+// chunks (4096 codes) in five waves are six rows a CU, in four eight.  Measured, us, before / after: 6600 rows of 264 chunks
+// expanded 13.6 / 13.0, a stream step of 2048 such tokens of 16 ranks 39.3 / 36.4; of 528 chunks 43.5 / 42.8 and 57.6 / 52.7; of
+// 1025 chunks (two workgroups before) 77.4 / 52.6 and 189.4 / 128.0.  Elsewhere it only costs.  Ten waves, three rows a CU instead
+// of two: 644 chunks expanded 28.2 / 28.9, a step of 655 chunks 87.2 / 88.9.  Where the CU holds hardly more rows: 330 chunks
+// 29.4 / 29.4, 396 chunks 33.4 / 33.5 and 49.0 / 49.2, 462 chunks (four rows a CU either way) 76.0 / 76.3 and 90.0 / 94.8.  Short
+// rows: 132 chunks (three waves) 25.2 / 24.6, but 6700 rows of 1.4 hits 10.8 / 11.2.
 static inline mw_row_shape mw_row_shape_folded(int chunks)
 {
     mw_row_shape s = mw_row_shape_of(chunks);
     const int rest = chunks % 64, waves = chunks / 64;
-    if (s.bs > 64 && waves >= 4 && chunks <= 1040 && rest >= 1 && rest <= 16 && 3 * (32 / waves) >= 4 * (32 / (waves + 1))) s = mw_row_shape{waves * 64, 1};
+    if (s.bs > 64 && (waves == 4 || waves == 8 || waves == 16) && rest >= 1 && rest <= 16) s = mw_row_shape{waves * 64, 1};
     return s;
 }
 static inline bool mw_is_folded(const mw_row_shape &s, int chunks) { return (int64_t)s.bs * s.nseg < chunks; }
