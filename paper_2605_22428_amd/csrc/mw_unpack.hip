@@ -1221,14 +1221,15 @@ __device__ __forceinline__ void expand_small(const mw_index_args &a, uint32_t *l
         const mw_recv_peer &pr = at.pinfo[q];
         const uint32_t i = r - at.rbase[q], c = seg * 64u + lane;
         const char *src = (const char *)pr.rows + (size_t)i * a.row_bytes;
+        const bool here = (at.addr[r >> 5] >> (r & 31u)) & 1u;            // (a region may hold other ranks' rows: their payload stays unread)
         u32x4 v = {0u, 0u, 0u, 0u};
-        if (c < n) v = mw_ld16_global(src, (int)c);
+        if (here && c < n) v = mw_ld16_global(src, (int)c);
         const uint32_t s_ = (uint32_t)pr.row_src_token[i];
         const uint32_t e = lane < K ? (uint32_t)pr.row_topk[(size_t)i * K + lane] : 0xffffffffu;
         const uint32_t s = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_);
         const int32_t t = e < E ? (a.tab_words ? at.tab[e] : a.eslot[e]) : -1;
         uint64_t local = __ballot((uint32_t)t >> 16 == (uint32_t)a.my_rank);                   // (-1: no rank)
-        if (!((at.addr[r >> 5] >> (r & 31u)) & 1u) || s >= a.max_tokens) local = 0;
+        if (!here || s >= a.max_tokens) local = 0;
         mw_row_rec rec = {nullptr, 0, (int32_t)q, 0, 0, 0, 0};
         if (local) { rec.src = src; rec.src_token = (int32_t)s; }
         uint64_t named = 0;
@@ -1581,6 +1582,9 @@ int32_t mw_launch_unpack_index(mw_ctx *ctx, const void *peers, bool packets, int
 // rows where 1089 grid rows were expected, 1.06 fillings, 107 / - / 90 / 92.)  What is left: 114688 rows where 4036 were
 // expected stride 27 times, 620 us against 569 for 32768 grid rows, the combine 605 against 511; evenly spread batches are
 // several times faster than with the capacity (64 ranks, 512 tokens: 134 us and 27).
+// The filling is that of folded rows for every caller, also where the launch does not fold them (the combine, small steps, riders
+// that refuse): a few more grid rows, which are not slower (12800 rows of 264 chunks that nobody had announced, us for the
+// filling of folded / unfolded rows: combine 19.8 / 21.9, of 528 chunks 36.7 / 37.9; 1664-row small steps 9.4 / 9.4 and 11.8 / 11.8).
 static uint32_t expand_grid_rows(const mw_ctx *ctx, int32_t P)
 {
     int64_t rows = expected_rows(ctx, P);
