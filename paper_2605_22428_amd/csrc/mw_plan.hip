@@ -399,13 +399,15 @@ __global__ __launch_bounds__(kKeysBlock) void k_plan_keys(const int32_t *__restr
 }
 
 // kU: tokens a lane holds (T <= kU blockDim.x).
+// kFew: so few keys are possible that nearly every wave has one like a token's (the rule is where it is launched): equals are counted
+// without asking whether there are any.
 // kSorted: keys, idx and bad[n_bad] come from k_plan_keys, and what counts the keys below a token's is a binary search in every
 // chunk, a lane a chunk: 64 chunks of 8192 tokens cost a wave eight LDS reads a lane, however the keys are spread.  A wave holds
 // whole chunks, so a running count of the representatives inside a chunk turns the same searches into the group index.
 // (With the keys counted into 4096 buckets and a token compared with its bucket, 8192 tokens of 256 ranks with skewed ids
 // spent 7 us in the buckets' atomics, 2 in their scan and 6 in the compares of 24; the searches take 2.)
 // pstate: only its flag word is looked at (mw_plan_static reports bad table entries there).
-template <bool kBytes, int kU, bool kSorted>
+template <bool kBytes, int kU, bool kSorted, bool kFew>
 __global__ __launch_bounds__(kOrderBlock) void k_plan_order(
     const int32_t *__restrict__ topk, int T, int K, const int32_t *__restrict__ eslot, int E, int R, int n_own, int slots_log,
     const uint64_t *__restrict__ keys, const uint8_t *__restrict__ idx, const uint32_t *__restrict__ bad_in, int n_bad,
@@ -706,20 +708,23 @@ __global__ __launch_bounds__(kOrderBlock) void k_plan_order(
                 below += (uint32_t)__popcll(lt);
                 distinct += (uint32_t)__popcll(lt & rep[j]);
                 const uint64_t eq = __ballot(key[j] == k) & kept[j];
-                if (eq) {
-                    const int first = j * bs + wave * 64, ahead = t0 + o - first;        // of the wave's 64 tokens, how many come before
-                    // (kU > 1: branches that are the same for all own tokens; with one key a lane they cost what they save)
-                    if (kU > 1 && first >= t0 + n) {
-                        after += (uint32_t)__popcll(eq);
-                    } else if (kU > 1 && first + 64 <= t0) {
-                        before += (uint32_t)__popcll(eq);
-                    } else {
-                        const uint64_t m = ahead <= 0 ? 0ull : ahead >= 64 ? ~0ull : (1ull << ahead) - 1ull;
-                        before += (uint32_t)__popcll(eq & m);
-                        after += (uint32_t)__popcll(eq & ~m);
+                const int first = j * bs + wave * 64;
+                if constexpr (kFew) {
+                    uint64_t m = first + 64 <= t0 ? ~0ull : 0ull;     // the wave's tokens that come before: all or none of them ...
+                    if (first < t0 + n && first + 64 > t0) {          // ... but in the wave around the own ones (a branch: 7.9 -> 9.1 us without)
+                        const int ahead = t0 + o - first;
+                        m = ahead <= 0 ? 0ull : ahead >= 64 ? ~0ull : (1ull << ahead) - 1ull;
                     }
+                    before += (uint32_t)__popcll(eq & m);
+                    after += (uint32_t)__popcll(eq);
+                } else if (eq) {
+                    const int ahead = t0 + o - first;
+                    const uint64_t m = ahead <= 0 ? 0ull : ahead >= 64 ? ~0ull : (1ull << ahead) - 1ull;
+                    before += (uint32_t)__popcll(eq & m);
+                    after += (uint32_t)__popcll(eq & ~m);
                 }
             }
+            if (kFew) after -= before;
             if (lane == o) { c0 = below | distinct << 16; c1 = before | after << 16; }
         }
         if (lane < n) part[wave * kOwnMax + lane] = make_uint2(c0, c1);
@@ -1037,7 +1042,7 @@ int32_t mw_launch_plan_allgather_split(mw_ctx *ctx, int64_t shard_bytes, int64_t
 }
 
 // Tokens from which the keys get a launch of their own, in sorted chunks (mw_plan alone, us: 64 ranks uniform / 256 ranks
-// skewed / 8 ranks).  1025 tokens 7.5 / 9.7 / 7.3 in one launch, 2048 8.7 / 10.7 / 8.2; sorted, 2049 10.1 / 11.8 / 9.9, 4096
+// skewed / 8 ranks).  1025 tokens 7.4 / 9.6 / 7.3 in one launch, 2048 8.5 / 10.5 / 8.2; sorted, 2049 10.1 / 11.8 / 9.9, 4096
 // 10.8 / 11.9 / 10.4, 6000 12.9 / 15.1 / 12.7, 8192 15.1 / 16.1 / 14.1.  (One launch that compared a token with a bucket of keys instead
 // of with all: 1025 8.1 / 10.3 / 7.7, 2048 8.8 / 11.4 / 7.9; keys not sorted, buckets behind them: 4096 12.8 / 14.6 / 10.8, 6000 18.7 /
 // 22.4 / 13.5, 8192 21.8 / 28.0 / 14.6.)
@@ -1070,16 +1075,24 @@ static void launch_plan_order(mw_ctx *ctx, const int32_t *topk, int32_t T, uint6
                            ctx->d_plan_keys, ctx->d_plan_idx, ctx->d_plan_bad);
     }
     mw_timed tm(ctx, sorted ? MW_KERNEL_PLAN_GROUPS : MW_KERNEL_PLAN_RANK, s);
-#define MW_ORDER(U_, SORTED_)                                                                                           \
-    hipLaunchKernelGGL((k_plan_order<kBytes, U_, SORTED_>), dim3(n_wg), dim3(bs), lds, s, topk, T, K, ctx->d_eslot, E, R,  \
+    // Destination sets that K ids can name among R ranks: up to 256 of them a wave nearly always has a key like a token's.  2048
+    // tokens, us asking whether there are equals / not asking: 8 ranks, one to eight ids 8.9 / 7.8, 8.8 / 7.9, 8.0 / 7.8,
+    // 8.2 / 7.9 (8 to 255 sets), 24 ranks, one and two ids 8.9 / 7.9, 8.1 / 8.2 (300 sets), 12 ranks, four ids 7.5 / 7.8, 256 ranks,
+    // one and eight ids 9.8 / 9.5, 10.4 / 10.6.
+    int64_t sets = 1, of_size = 1;
+    for (int j = 1; j <= K && j <= R && sets <= 257; ++j) { of_size = of_size * (R - j + 1) / j; sets += of_size; }
+    const bool few = sets <= 257;                                     // (the empty set among them)
+#define MW_ORDER(U_, SORTED_, FEW_)                                                                                     \
+    hipLaunchKernelGGL((k_plan_order<kBytes, U_, SORTED_, FEW_>), dim3(n_wg), dim3(bs), lds, s, topk, T, K, ctx->d_eslot, E, R,  \
                        n_own, slots_log, ctx->d_plan_keys, ctx->d_plan_idx, ctx->d_plan_bad, n_key_wg, ctx->d_plan_state,     \
                        (uint64_t)ctx->row_bytes, mask, perm, desc, stats)
     static_assert(kKeysFrom == 2 * kOrderBlock + 1, "tokens a lane of each form");
-    if (T <= kOrderBlock) MW_ORDER(1, false);
-    else if (!sorted) MW_ORDER(2, false);
-    else if (T <= 4 * kOrderBlock) MW_ORDER(4, true);
-    else if (T <= 6 * kOrderBlock) MW_ORDER(6, true);
-    else MW_ORDER(8, true);
+    if (T <= kOrderBlock) MW_ORDER(1, false, false);
+    else if (!sorted && few) MW_ORDER(2, false, true);
+    else if (!sorted) MW_ORDER(2, false, false);
+    else if (T <= 4 * kOrderBlock) MW_ORDER(4, true, false);
+    else if (T <= 6 * kOrderBlock) MW_ORDER(6, true, false);
+    else MW_ORDER(8, true, false);
 #undef MW_ORDER
 }
 

@@ -1,5 +1,5 @@
-"""GPU parity of mw_plan where its form changes: one, two, four and eight tokens a lane, keys made in the
-same launch or in one of their own, tokens compared with all others or with their bucket, one-word and
+"""GPU parity of mw_plan where its form changes: one, two, four, six and eight tokens a lane, keys made in the
+same launch or in one of their own, tokens compared with all others or searched for in sorted chunks, one-word and
 byte keys, the batch beyond; empty tokens, one bitmap throughout, few bitmaps, every bit set; an id
 outside the range.  Every output against the oracle, bit-exact."""
 import numpy as np
@@ -13,7 +13,7 @@ import gpu_harness as H
 pytestmark = pytest.mark.gpu
 
 SIZES = [1, 64, 255, 257, 513, 1024, 1025, 2048, 2049, 4096, 4097, 8192, 8193]
-# ranks, experts, top_k: every bucket rule (up to 12 ranks, up to 24, beyond, byte keys), a byte key's first
+# ranks, experts, top_k: few and many possible destination sets, one-word and byte keys, a byte key's first
 # position at 255, one id, more than eight ids with one word, ids that are not whole 16-byte units
 SHAPES = [(8, 256, 8), (12, 60, 4), (13, 26, 6), (24, 96, 8), (25, 50, 3), (64, 256, 8), (64, 64, 64), (65, 130, 8),
           (256, 256, 8), (200, 400, 5), (7, 7, 1)]
@@ -70,6 +70,34 @@ def test_plan_forms(shape, T):
         H.assert_same_bytes(got[:N], perm, kind + " perm")
         assert (got[N:] == -7).all(), kind + ": perm behind the last packed row was written"
         H.assert_same_bytes(H.host(buf.desc).reshape(-1).view(B.DESC_DTYPE)[:G].view(np.uint8), desc.view(np.uint8), kind + " desc")
+
+
+@pytest.mark.parametrize("T", [1025, 1100, 1300, 1700, 2047])
+@pytest.mark.parametrize("R,E,K", [(1, 2, 2), (2, 64, 8), (8, 64, 8), (9, 27, 6), (22, 44, 2), (23, 46, 2), (64, 64, 1), (65, 65, 1),
+                                   (256, 512, 1)])
+def test_plan_of_few_destination_sets(R, E, K, T):
+    """1025 to 2048 tokens around the rule of 256 possible destination sets (8 ranks, eight ids: 255; 22 ranks, two ids: 253; 23:
+    276), five to eight tokens a workgroup, which then lie in one wave's 64 tokens or in two; a third of the tokens go nowhere."""
+    print("few sets", R, E, K, T, flush=True)
+    e2r = (np.arange(E) * R // E).astype(np.int32)
+    ctx = B.Context(R, E, K, 0, 8, B.MW_ROW_BF16, T, 1, e2r, device=H.DEV)
+    buf = B.SendBuffers(ctx, T)
+    rng = np.random.default_rng(T + R)
+    for kind in ("random", "some", "ends"):
+        tk = _tokens(rng, kind, T, E, K)
+        if kind == "some":
+            tk[rng.random(T) < 0.3] = -1
+        buf.perm.fill_(-7)
+        ctx.mw_plan(H.dev(tk), buf.mask, buf.perm, buf.desc, buf.stats)
+        st = ctx.mw_get_send_stats(buf.stats)
+        mask, perm, desc, want = ref.plan(tk, e2r, R, 16)
+        assert (int(st["n_rows"]), int(st["n_groups"]), int(st["error_flags"])) == (len(perm), len(desc), 0)
+        H.assert_same_bytes(st["rows_per_dest"], want["rows_per_dest"], "rows_per_dest")
+        H.assert_same_bytes(H.host(buf.mask).view(np.uint64)[:T], mask, "mask")
+        got = H.host(buf.perm)
+        H.assert_same_bytes(got[: len(perm)], perm, "perm")
+        assert (got[len(perm):] == -7).all(), "perm behind the last packed row was written"
+        H.assert_same_bytes(H.host(buf.desc).reshape(-1).view(B.DESC_DTYPE)[: len(desc)].view(np.uint8), desc.view(np.uint8), "desc")
 
 
 @pytest.mark.parametrize("T", [2049, 2176, 4095, 6144, 6145, 8065, 8192])
