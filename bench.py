@@ -483,6 +483,7 @@ def bench_dispatch(args, name: str, brief: bool = False) -> dict:
         other[sched] = round((time.perf_counter() - t0) * 1e3 / args.steps, 4)
 
     # ---------------------------------------------------------------- per-kernel breakdown (one stream, untimed)
+    # (with events set for the index, mw_unpack of a small batch is two launches; without, as timed above, it is one)
     names = {"plan_rank": B.MW_KERNEL_PLAN_RANK,
              "plan_groups": B.MW_KERNEL_PLAN_GROUPS, "pack": B.MW_KERNEL_PACK,
              "recv_index": B.MW_KERNEL_RECV_INDEX, "expand": B.MW_KERNEL_EXPAND}

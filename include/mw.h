@@ -773,6 +773,9 @@ MW_API int32_t mw_get_relay_stats(mw_ctx *ctx, const mw_relay_stats *stats_dev, 
  * this context records `ev_start` just before it and `ev_stop` just after it on the
  * call's stream, so the caller can read the kernel's own duration with
  * hipEventElapsedTime.  NULL, NULL switches the hook off (the default).
+ * mw_unpack of a few hundred rows is one launch of index and expander, recorded as
+ * MW_KERNEL_EXPAND; while a pair is set for MW_KERNEL_RECV_INDEX it is two launches, like any
+ * other mw_unpack, so that either pair brackets its own kernel.
  */
 #define MW_KERNEL_PLAN_RANK    0
 #define MW_KERNEL_PLAN_GROUPS  1

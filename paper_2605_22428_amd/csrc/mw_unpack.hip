@@ -1625,15 +1625,16 @@ int32_t mw_launch_unpack(mw_ctx *ctx, const mw_recv_peer *peers, int32_t P, void
     // Index and expander in one launch as long as a row is at most a lane's and the payload is short (us in two launches / in
     // one: 244 rows of 512 bytes 9.6 / 6.7, 355 of 14336 12.9 / 10.6, 506 of 14336 12.4 / 11.7 but 14.0 / 14.2 for a call among
     // idle ones, 244 of 65536 12.5 / 16.1; 812 rows of 2048 12.9 / 11.7, 646 of 14336 15.4 / 16.2, 1007 of 14336 15.5 / 21.0).
-    // More rows than expected are moved all the same.
+    // More rows than expected are moved all the same.  A caller who has set events for the index wants its own duration:
+    // two launches then.
     constexpr int64_t kSmallUnpackBytes = 6 << 20;
     const int64_t expected = ctx->recv_rows_hint > 0 ? ctx->recv_rows_hint : (int64_t)P * ctx->cfg.max_tokens;
     mw_index_args a;
     size_t lds_index;
-    if (expected <= kSmallLanes && small_index_fits(ctx, P) && expected * ctx->row_bytes <= kSmallUnpackBytes &&
+    const bool timed = ctx->ev_start[MW_KERNEL_RECV_INDEX] || ctx->ev_stop[MW_KERNEL_RECV_INDEX];
+    if (expected <= kSmallLanes && small_index_fits(ctx, P) && expected * ctx->row_bytes <= kSmallUnpackBytes && !timed &&
         ctx->row_bytes <= 65536 && ctx->cfg.max_recv_rows > 0 &&
         make_index_args(ctx, peers, false, P, cap, expert_offsets, stats, kIndexAcceptWords, 16384, 1, kMaxIndexParts, &a, &lds_index)) {
-        { mw_timed tm(ctx, MW_KERNEL_RECV_INDEX, s); }       // (its event pair, where a caller has set one, brackets nothing)
         mw_timed tm(ctx, MW_KERNEL_EXPAND, s);
         const int xc = (int)(ctx->x_row_bytes / 16), sc = (int)(ctx->s_row_bytes / 16);
         // (64 rows more than the last batch had: the next one may be larger, and a wave then strides)

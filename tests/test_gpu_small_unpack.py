@@ -121,3 +121,72 @@ def test_damaged_regions_match_the_two_halves(damage):
             if x is not None:
                 H.assert_same_bytes(x, y, what)
     H.check_unpack(H.GpuUnpack(ctx, recs, cap), ref.dispatch_plain(toks, e2r, my_rank, cap), "sound again")
+
+
+def test_events_bracket_the_kernels_they_name():
+    """With events set for the receive index mw_unpack of a small batch is two launches again: the index of 12800 rows where 64
+    were seen last takes one workgroup tens of microseconds, an empty bracket three."""
+    print("timing events", flush=True)
+    R, E, K, T, hidden, my_rank = 64, 256, 8, 256, 8, 5
+    rng = np.random.default_rng(11)
+    e2r = (np.arange(E) * R // E).astype(np.int32)
+    ctx = B.Context(R, E, K, my_rank, hidden, B.MW_ROW_BF16, T, R * T, e2r, device=H.DEV)
+    _, few = _regions(rng, R, E, K, [1] * R, hidden, "bf16", ctx, e2r, my_rank)
+    toks, recs = _regions(rng, R, E, K, [200] * R, hidden, "bf16", ctx, e2r, my_rank)
+    cap = sum(r["n_rows"] for r in recs) * 4
+    want = ref.dispatch_plain(toks, e2r, my_rank, cap)
+    for timed in (False, True, False):
+        H.GpuUnpack(ctx, few, cap)                           # (its statistics are read: the next batch is expected to be as small)
+        ev = [[torch.cuda.Event(enable_timing=True) for _ in range(2)] for _ in range(2)]
+        if timed:
+            for kernel, (a, b) in zip((B.MW_KERNEL_RECV_INDEX, B.MW_KERNEL_EXPAND), ev):
+                for e in (a, b):
+                    e.record()
+                ctx.mw_ctx_set_timing_events(kernel, a, b)
+        H.check_unpack(H.GpuUnpack(ctx, recs, cap), want, "timed" if timed else "not timed")
+        if timed:
+            for kernel in (B.MW_KERNEL_RECV_INDEX, B.MW_KERNEL_EXPAND):
+                ctx.mw_ctx_set_timing_events(kernel, None, None)
+            index, expand = (1e3 * a.elapsed_time(b) for a, b in ev)
+            print("index %.1f us, expander %.1f us" % (index, expand), flush=True)
+            assert index > 30.0 and expand > 0.0
+
+
+@pytest.mark.parametrize("hidden", [64, 2048])
+def test_a_captured_small_batch_replayed_on_a_larger_one(hidden):
+    """A graph captured when the context expected a few rows, replayed on region tables of none, of as many and of a hundred times
+    as many."""
+    print("captured small unpack", hidden, flush=True)
+    R, E, K, T, my_rank = 16, 64, 4, 512, 7
+    rng = np.random.default_rng(hidden)
+    e2r = (np.arange(E) * R // E).astype(np.int32)
+    ctx = B.Context(R, E, K, my_rank, hidden, B.MW_ROW_BF16, T, R * T, e2r, device=H.DEV)
+    batches = []
+    for n in (3, 0, T, 1):
+        toks, recs = _regions(rng, R, E, K, [n] * R, hidden, "bf16", ctx, e2r, my_rank)
+        cap = max(1, sum(r["n_rows"] for r in recs) * 4)
+        batches.append((recs, B.peers_table(recs, H.DEV), ref.dispatch_plain(toks, e2r, my_rank, cap)))
+    buf = B.RecvBuffers(ctx, max(1, 4 * R * T))
+    table = batches[0][1].clone()
+
+    def unpack():
+        ctx.mw_unpack(table, R, buf.out_rows, buf.out_scales, buf.capacity, buf.out_src_peer, buf.out_src_token, buf.expert_offsets, buf.stats)
+    unpack()
+    ctx.mw_get_recv_stats(buf.stats)
+    side = torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side):
+        unpack()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=side):
+        unpack()
+    for recs, other, want in batches + batches[::-1]:
+        table.copy_(other)
+        buf.out_rows.fill_(0)
+        graph.replay()
+        torch.cuda.synchronize()
+        gu = H.GpuUnpack.__new__(H.GpuUnpack)
+        gu.ctx, gu.buf = ctx, buf
+        gu.stats = H.host(buf.stats).view(B.RECV_STATS_DTYPE)[0]
+        gu.Q = int(gu.stats["n_out_rows"])
+        H.check_unpack(gu, want, "replay")
