@@ -83,7 +83,9 @@ extern "C" {
 #define MW_ROW_FP8_E4M3_BLOCK128 1 /* row = hidden e4m3 codes then hidden/128 fp32 scales */
 #define MW_ROW_BYTES            2  /* row = row_bytes opaque bytes (AllGather shards, tests) */
 
-/* device-side error flags (mw_send_stats.error_flags / mw_recv_stats.error_flags) */
+/* device-side error flags (mw_send_stats.error_flags / mw_recv_stats.error_flags).  On the receive side flags about a
+ * row (BAD_EXPERT, NO_LOCAL_EXPERT, BAD_SRC_TOKEN, DUP_SRC_TOKEN) speak of rows whose group names this rank: other
+ * ranks' rows in a region are not looked at. */
 #define MW_FLAG_BAD_EXPERT       0x01u  /* expert id outside {-1} U [0, n_experts): entry ignored */
 #define MW_FLAG_OUT_CAPACITY     0x02u  /* more output rows than out_capacity_rows: surplus rows dropped */
 #define MW_FLAG_NO_LOCAL_EXPERT  0x04u  /* row's group names this rank but none of its experts is local */

@@ -188,3 +188,46 @@ def test_counts_finished_by_a_wave_or_a_workgroup(R, L, n_peers):
     for _ in range(2):
         assert int(H.GpuUnpack(ctx, broken, cap).stats["error_flags"]) == (B.MW_FLAG_BAD_EXPERT if flagged else 0)
     H.check_unpack(H.GpuUnpack(ctx, recs, cap), want, "after a flagged batch")
+
+
+@pytest.mark.parametrize("T", [12, 60, 400, 2000, 4000])
+def test_rows_of_other_ranks_are_not_looked_at(T):
+    """Whole sender buffers as regions: rows whose group does not name this rank carry ids and source tokens outside every range, and
+    raise no flag, whichever form the index takes (one launch with the expander, one workgroup, rows a lane keeps in registers and
+    rows beyond them, rows spread over riders)."""
+    print("other ranks' rows", T, flush=True)
+    R, E, K, my_rank, hidden = 8, 32, 4, 5, 8
+    rng = np.random.default_rng(T)
+    e2r = (np.arange(E) * R // E).astype(np.int32)
+    ctx, nxt, far = (B.Context(R, E, K, my_rank, hidden, B.MW_ROW_BF16, mt, R * mt, e2r, device=H.DEV) for mt in (T, T, 65536))
+    recs, bufs = [], []
+    for _ in range(R):
+        tk = rng.integers(0, E, size=(T, K)).astype(np.int32)
+        x = rng.integers(0, 1 << 16, size=(T, hidden), dtype=np.uint16)
+        _, perm, desc, _ = ref.plan(tk, e2r, R, 2 * hidden)
+        packed, src, rtk = ref.pack(x, None, tk, perm)
+        src, rtk, other = src.copy(), rtk.copy(), 0
+        for d in desc:
+            if not (int(d["mask"][0]) >> my_rank) & 1:
+                rows = slice(int(d["row_offset"]), int(d["row_offset"]) + int(d["row_count"]))
+                rtk[rows], src[rows], other = E + 5, T + 9, other + int(d["row_count"])
+        assert other > 0
+        bufs.append((desc, packed, src, rtk))
+        recs.append(dict(desc=H.dev(desc.view(np.uint8).reshape(len(desc), -1)), rows=H.dev(packed), row_src_token=H.dev(src), row_topk=H.dev(rtk),
+                         n_desc=len(desc), n_rows=len(perm)))
+    cap = K * R * T
+    want = ref.unpack(bufs, K, e2r, my_rank, 2 * hidden, 0, cap)
+    for _ in range(2):
+        H.check_unpack(H.GpuUnpack(ctx, recs, cap), want, "unpack")
+    table = B.peers_table(recs, H.DEV)
+    a, b = B.RecvBuffers(far, cap), B.RecvBuffers(nxt, cap)
+    far.mw_unpack_index(table, R, cap, a.expert_offsets, a.stats)
+    if 3 * ((T + 31) // 32) + 64 <= 1280:
+        far.mw_unpack_expand_index_next(R, a.out_rows, None, cap, a.out_src_peer, a.out_src_token, nxt, table, R, cap, b.expert_offsets, b.stats)
+    else:
+        nxt.mw_unpack_index(table, R, cap, b.expert_offsets, b.stats)
+    nxt.mw_unpack_expand(R, b.out_rows, None, cap, b.out_src_peer, b.out_src_token)
+    gu = H.GpuUnpack.__new__(H.GpuUnpack)
+    gu.ctx, gu.buf, gu.stats = nxt, b, nxt.mw_get_recv_stats(b.stats)
+    gu.Q = int(gu.stats["n_out_rows"])
+    H.check_unpack(gu, want, "index beside an expander")
