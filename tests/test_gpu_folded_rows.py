@@ -1,6 +1,7 @@
 """GPU parity of the packer and the expander where a row's last few chunks go to the lanes of its first wave: one chunk and
-sixteen too many for whole waves, seventeen (a wave of their own), the largest row of one workgroup and the first beyond; fp8 rows,
-whose scales are those chunks; alone and in a stream's launch.  Bit-exact."""
+sixteen too many for whole waves, seventeen (a wave of their own), ten waves and a few (not folded), the largest row of one workgroup
+and the first beyond; fp8 rows, whose scales are those chunks; and the same widths in steps of a stream too short to fold them
+(folded beside riders: test_gpu_riding_index.py).  Bit-exact."""
 import numpy as np
 import pytest
 
@@ -29,7 +30,7 @@ def _dispatch(w, my_rank):
     ctx.close()
 
 
-@pytest.mark.parametrize("chunks", [64, 65, 80, 81, 128, 129, 144, 145, 257, 264, 272, 273, 330, 513, 528, 1024, 1025, 1039, 1041])
+@pytest.mark.parametrize("chunks", [64, 65, 80, 81, 128, 129, 144, 145, 257, 264, 272, 273, 330, 513, 528, 641, 655, 1024, 1025, 1039, 1041])
 def test_rows_of_whole_waves_and_a_few_chunks(chunks):
     print("folded rows", chunks, flush=True)
     _dispatch(W.DispatchWorkload("fold", 76, 4, 16, 4, 150, 8 * chunks, "bf16", "uniform"), 1)

@@ -1,6 +1,7 @@
-"""GPU parity with id lists that are read by 16-byte requests (whole units that start on one) and word by word (four bytes into an
-allocation, or not whole units): the plan of a small batch, of a batch without keys and of one beyond 8192 tokens, the small
-launches' index, the riding plan and a small stream step.  Bit-exact."""
+"""GPU parity with id lists of every alignment.  The plan of a small batch (mw_plan_pack, a small stream step) and the small
+launches' index read lists of whole 16-byte units that start on one by 16-byte requests, else word by word; here both, also
+for rows beyond one a lane.  Plans beyond 8192 tokens and riding plans read word by word whatever the alignment; they get the same
+shifted lists.  Bit-exact."""
 import numpy as np
 import pytest
 import torch
@@ -48,7 +49,39 @@ def test_id_lists(K, shifted):
         _check(ctx, buf, tk, e2r, R, 16, "%d tokens" % T)
         ctx.close()
 
-    # the small index (a batch of up to 512 rows, then one of more), and steps whose index and plan ride
+    # the one-workgroup index, rows in registers and (a batch of more than 512 rows where a few were seen last) through memory: with
+    # the expander in one launch, and by itself
+    R, E, T, hidden, my_rank = 8, 32, 700, 8, 3
+    e2r = (np.arange(E) * R // E).astype(np.int32)
+    ctx = B.Context(R, E, K, my_rank, hidden, B.MW_ROW_BF16, T, R * T, e2r, device=H.DEV)
+    sizes = []
+    for n in (9, T):
+        toks, recs = [], []
+        for p in range(R):
+            tk, x = _ids(rng, n, E, K), rng.integers(0, 1 << 16, size=(n, hidden), dtype=np.uint16)
+            toks.append((tk, x, None))
+            r = H.shrink(H.GpuSend(ctx, tk, x, None).deliver(my_rank))
+            recs.append(dict(r, row_topk=move(r["row_topk"])))
+        cap = max(1, sum(r["n_rows"] for r in recs) * min(K, 4))
+        sizes.append((recs, cap, ref.dispatch_plain(toks, e2r, my_rank, cap)))
+    (few, few_cap, few_want), (many, cap, want) = sizes
+    assert sum(r["n_rows"] for r in few) <= 512 < sum(r["n_rows"] for r in many)
+    for halves in (False, True):
+        for _ in range(2):                                   # (after the large batch the first one is indexed in the general form)
+            H.check_unpack(H.GpuUnpack(ctx, few, few_cap), few_want, "a few rows")
+        b = B.RecvBuffers(ctx, cap)
+        if halves:
+            ctx.mw_unpack_index(B.peers_table(many, H.DEV), R, cap, b.expert_offsets, b.stats)
+            ctx.mw_unpack_expand(R, b.out_rows, None, cap, b.out_src_peer, b.out_src_token)
+        else:
+            ctx.mw_unpack(B.peers_table(many, H.DEV), R, b.out_rows, None, cap, b.out_src_peer, b.out_src_token, b.expert_offsets, b.stats)
+        gu = H.GpuUnpack.__new__(H.GpuUnpack)
+        gu.ctx, gu.buf, gu.stats = ctx, b, ctx.mw_get_recv_stats(b.stats)
+        gu.Q = int(gu.stats["n_out_rows"])
+        H.check_unpack(gu, want, "more rows than lanes")
+    ctx.close()
+
+    # steps whose index and plan ride
     R, E, T, hidden, my_rank = 8, 32, 60, 64, 3
     e2r = (np.arange(E) * R // E).astype(np.int32)
     ctxs = [B.Context(R, E, K, my_rank, hidden, B.MW_ROW_BF16, T, R * T, e2r, device=H.DEV) for _ in range(2)]
@@ -89,7 +122,8 @@ def test_id_lists(K, shifted):
 @pytest.mark.parametrize("shifted", [False, True])
 @pytest.mark.parametrize("R,E,K", [(8, 64, 8), (130, 260, 12)])
 def test_riding_plan(R, E, K, shifted, monkeypatch):
-    """A plan that rides beside rows (300 tokens, several workgroups), its ids on a 16-byte unit and four bytes behind one."""
+    """A plan that rides beside rows (300 tokens, several workgroups), its ids on a 16-byte unit and four bytes behind one: read word by
+    word either way."""
     if shifted:
         monkeypatch.setattr(forms.H, "dev", lambda a, dev=H.dev: forms._shifted(dev(a)) if getattr(a, "dtype", None) == np.int32 and a.ndim == 2
                             and a.shape[1] == K else dev(a))

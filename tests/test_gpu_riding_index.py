@@ -1,6 +1,7 @@
 """GPU parity of the receive index where it really rides in the expander's launch: the experts of a peer over several
 workgroups, more chunks of experts than workgroups, a peer's rows over two and four workgroups, more than eight ids, repeated
-rows dropped, wide bitmaps, with and without a riding plan, in workgroups of two and of eight waves.  The context
+rows dropped, wide bitmaps, with and without a riding plan, in workgroups of two and of eight waves; and of movers whose
+rows are folded, packer and expander, beside index and plan.  The context
 whose batch is expanded is made for far more rows than it holds, so that movers are expected that hide any index; that
 nothing got a launch of its own is read from the events that bracket such launches.  Against the oracle, bit-exact."""
 import numpy as np
@@ -140,3 +141,81 @@ def test_riding_index_drops_repeats():
     assert int(gu.stats["error_flags"]) == B.MW_FLAG_DUPLICATE_DROPPED
     gu.stats["error_flags"] = 0
     H.check_unpack(gu, ref.dispatch_plain(toks, e2r, my_rank, cap))
+
+
+#                       row format, hidden: chunks of a row
+FOLDED = {"257": (B.MW_ROW_BF16, 2056), "264_fp8": (B.MW_ROW_FP8_E4M3_BLOCK128, 4096), "528_fp8": (B.MW_ROW_FP8_E4M3_BLOCK128, 8192),
+          "1039": (B.MW_ROW_BF16, 8312), "655_not_folded": (B.MW_ROW_BF16, 5240)}
+
+
+def _batch(rng, ctx, R, E, K, T, P, hidden, fmt, my_rank):
+    """P senders' tokens and regions and this rank's own tokens."""
+    def tokens(n):
+        tk = rng.integers(0, E, size=(n, K)).astype(np.int32)
+        tk[rng.random((n, K)) < 0.1] = -1
+        if fmt == B.MW_ROW_BF16:
+            return tk, rng.integers(0, 1 << 16, size=(n, hidden), dtype=np.uint16), None
+        return tk, rng.integers(0, 256, size=(n, hidden), dtype=np.uint8), rng.random((n, hidden // 128), dtype=np.float32)
+    toks = [tokens(T) for _ in range(P)]
+    recs = [H.shrink(H.GpuSend(ctx, *t).deliver(my_rank)) for t in toks]
+    cap = max(1, sum(r["n_rows"] for r in recs) * min(K, ctx.n_local))
+    return dict(toks=toks, recs=recs, cap=cap, table=B.peers_table(recs, H.DEV), own=tokens(T))
+
+
+@pytest.mark.parametrize("call", ["index", "index_plan", "step"])
+@pytest.mark.parametrize("R,E,K", [(8, 64, 8), (8, 64, 9), (130, 260, 8)])
+@pytest.mark.parametrize("which", sorted(FOLDED))
+def test_folded_rows_beside_riders(which, R, E, K, call):
+    """Every byte of rows whose last chunks go to their first lanes, moved by the launch that also makes the next batch's index and
+    plan.  Riders narrow the movers only where these are expected to take a good part longer: 200000 rows at several
+    kilobytes, hundreds of microseconds, beside an index of 500 rows a peer, some ten."""
+    fmt, hidden = FOLDED[which]
+    print("folded beside riders", which, R, K, call, flush=True)
+    P, T, my_rank = 8, 500, R // 2
+    rng = np.random.default_rng(hidden + R + K)
+    e2r = (np.arange(E) * R // E).astype(np.int32)
+    nxt = B.Context(R, E, K, my_rank, hidden, fmt, T, P * T, e2r, device=H.DEV)
+    cur = B.Context(R, E, K, my_rank, hidden, fmt, 65536, min(200000, R * 65536), e2r, device=H.DEV)
+    nxt.mw_ctx_set_ride_wait_limit((1 << 21) - 1)               # plans ride whatever the sizes
+    now, then = _batch(rng, nxt, R, E, K, 150, P, hidden, fmt, my_rank), _batch(rng, nxt, R, E, K, T, P, hidden, fmt, my_rank)
+    a, b = B.RecvBuffers(cur, now["cap"]), B.RecvBuffers(nxt, then["cap"])
+    a.out_rows.fill_(0x5a)
+    cur.mw_unpack_index(now["table"], P, now["cap"], a.expert_offsets, a.stats)
+    tk, x, sc = now["own"]
+    tk_d, x_d, sc_d, s = H.dev(tk), H.dev(x), H.dev(sc), B.SendBuffers(cur, len(tk))
+    cur.mw_plan(tk_d, s.mask, s.perm, s.desc, s.stats)
+    ntk, ns = H.dev(then["own"][0]), B.SendBuffers(nxt, T)
+    s.packed.fill_(0x3c)
+    checks = [(_untouched(nxt, B.MW_KERNEL_RECV_INDEX), "the index")]
+    if call != "index":
+        checks += [(_untouched(nxt, k), "the plan") for k in (B.MW_KERNEL_PLAN_RANK, B.MW_KERNEL_PLAN_GROUPS)]
+    expander = (P, a.out_rows, a.out_scales, now["cap"], a.out_src_peer, a.out_src_token)
+    index = (nxt, then["table"], P, then["cap"], b.expert_offsets, b.stats)
+    if call == "index":
+        cur.mw_unpack_expand_index_next(*expander, *index)
+    elif call == "index_plan":
+        cur.mw_unpack_expand_index_plan_next(*expander, *index, ntk, ns.mask, ns.perm, ns.desc, ns.stats)
+    else:
+        cur.mw_stream_step(x_d, sc_d, tk_d, s.perm, s.stats, s.packed, s.row_src_token, s.row_topk, *expander, *index, ntk, ns.mask,
+                           ns.perm, ns.desc, ns.stats)
+    torch.cuda.synchronize()
+    for check, what in checks:
+        check(what)
+    nxt.mw_unpack_expand(P, b.out_rows, b.out_scales, then["cap"], b.out_src_peer, b.out_src_token)
+    for ctx, buf, batch, what in ((cur, a, now, "this batch"), (nxt, b, then, "the next")):
+        gu = H.GpuUnpack.__new__(H.GpuUnpack)
+        gu.ctx, gu.buf, gu.stats = ctx, buf, ctx.mw_get_recv_stats(buf.stats)
+        gu.Q = int(gu.stats["n_out_rows"])
+        H.check_unpack(gu, ref.dispatch_plain(batch["toks"], e2r, my_rank, batch["cap"]), what)
+    if call == "step":
+        _, perm, _, _ = ref.plan(tk, e2r, R, cur.row_bytes)
+        packed, src, rtk = ref.pack(x, sc, tk, perm)
+        H.assert_same_bytes(H.host(s.packed)[: len(perm), : cur.row_bytes], packed, "packed rows")
+        assert (H.host(s.packed)[len(perm):] == 0x3c).all(), "rows behind the last packed one were written"
+        H.assert_same_bytes(H.host(s.row_src_token)[: len(perm)], src, "row_src_token")
+        H.assert_same_bytes(H.host(s.row_topk)[: len(perm)], rtk, "row_topk")
+    if call != "index":
+        _, perm, desc, _ = ref.plan(then["own"][0], e2r, R, nxt.row_bytes)
+        st = nxt.mw_get_send_stats(ns.stats)
+        assert (int(st["n_rows"]), int(st["n_groups"]), int(st["error_flags"])) == (len(perm), len(desc), 0)
+        H.assert_same_bytes(H.host(ns.perm)[: len(perm)], perm, "perm")
