@@ -1451,10 +1451,15 @@ static double rider_us(const mw_ctx *next, int32_t P, int bs, uint32_t row_parts
 }
 
 // Row movers beside riders: folded where the narrower riders stay well below the movers (2048 fp8 tokens of 264 chunks, us a step not
-// folded / folded: 16 ranks, 860 rows a peer, 39.3 / 36.4; 8 ranks, 1344 rows a peer and 32 experts, 37.2 / 38.6).
+// folded / folded: 16 ranks, 860 rows a peer, 39.3 / 36.4; 8 ranks, 1344 rows a peer and 32 experts, 37.2 / 38.6), and where they
+// have room and time for the table of experts: of four waves up to ten experts a lane (100 ranks, 160 rows a peer, 2400 experts
+// 44.5 / 41.4, 2560 44.7 / 42.5, 3200 44.9 / 44.7, 4800 48.4 / 52.8, and 5600, for whose table a rider has no LDS, 51.5 / 70.7), of eight
+// waves as long as there is LDS (528 chunks, 256 ranks, 130 rows a peer, 4800 experts 55.7 / 50.3, 10000 56.1 / 51.6).  Sixteen waves
+// are not narrower than rows in two workgroups.
 static mw_row_shape rider_row_shape(const mw_ctx *ctx, const mw_ctx *next, int32_t P, int32_t next_P, int32_t pack_tokens, int chunks)
 {
     const mw_row_shape s = mw_row_shape_folded(chunks);
+    if (mw_is_folded(s, chunks) && s.bs < 1024 && next->cfg.n_experts > (s.bs < 512 ? 10 * s.bs : 20 * s.bs - 4)) return mw_row_shape_of(chunks);
     if (mw_is_folded(s, chunks) && rider_us(next, next_P, s.bs, index_row_parts(next, next_P, s.bs)) > 0.7 * movers_us(ctx, P, pack_tokens))
         return mw_row_shape_of(chunks);
     return s;

@@ -29,7 +29,8 @@ SHAPES = {
 
 
 def _untouched(ctx, kernel):
-    """Two recorded events that a launch of `kernel` on `ctx` would record again; returns the check that none did."""
+    """Two recorded events that a launch of `kernel` on `ctx` would record again; returns the check that none did.  (Reading the same
+    two events again can give a nanosecond more or less: device ticks are converted anew each time.)"""
     a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
     a.record()
     torch.zeros(1 << 22, device=H.DEV).add_(1)
@@ -40,7 +41,7 @@ def _untouched(ctx, kernel):
 
     def check(what):
         ctx.mw_ctx_set_timing_events(kernel, None, None)
-        assert a.elapsed_time(b) == was, "%s got a launch of its own" % what
+        assert abs(a.elapsed_time(b) - was) < 1e-5, "%s got a launch of its own" % what
     return check
 
 
@@ -163,12 +164,13 @@ def _batch(rng, ctx, R, E, K, T, P, hidden, fmt, my_rank):
 
 
 @pytest.mark.parametrize("call", ["index", "index_plan", "step"])
-@pytest.mark.parametrize("R,E,K", [(8, 64, 8), (8, 64, 9), (130, 260, 8)])
-@pytest.mark.parametrize("which", sorted(FOLDED))
-def test_folded_rows_beside_riders(which, R, E, K, call):
+@pytest.mark.parametrize("R,E,K,which", [r + (w,) for w in sorted(FOLDED) for r in ((8, 64, 8), (8, 64, 9), (130, 260, 8))] +
+                         [(100, 5600, 8, "264_fp8"), (100, 5600, 8, "528_fp8"), (200, 10700, 8, "528_fp8")])
+def test_folded_rows_beside_riders(R, E, K, which, call):
     """Every byte of rows whose last chunks go to their first lanes, moved by the launch that also makes the next batch's index and
     plan.  Riders narrow the movers only where these are expected to take a good part longer: 200000 rows at several
-    kilobytes, hundreds of microseconds, beside an index of 500 rows a peer, some ten."""
+    kilobytes, hundreds of microseconds, beside an index of 500 rows a peer, some ten.  (5600 and 10700 experts: their table has no room
+    in the LDS of a rider of four and of eight waves, and the index has to ride all the same.)"""
     fmt, hidden = FOLDED[which]
     print("folded beside riders", which, R, K, call, flush=True)
     P, T, my_rank = 8, 500, R // 2
