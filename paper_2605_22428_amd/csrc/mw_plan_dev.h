@@ -14,7 +14,7 @@ constexpr int kPsKept = 256, kPsFlags = 257, kPsDone = 258, kPsDone2 = 259;  // 
 
 // Ids j0 .. j0 + 7 of one token's list (-1 past its end).  Lists of whole 16-byte units that start on one take two requests
 // instead of eight: a request of 64 lanes whose lists are 32 bytes apart touches sixteen cache lines, and a workgroup's
-// requests take turns (a 64-token stream step of 64 ranks, index and plan, 8.4 -> 7.6 us).
+// requests take turns (a stream step of 64 tokens a rank, 64 ranks, ids limited to four servers, 8.4 -> 7.6 us).
 __device__ __forceinline__ void load_eight_ids(const int32_t *__restrict__ row, int j0, int K, int32_t (&e)[8])
 {
 #pragma unroll

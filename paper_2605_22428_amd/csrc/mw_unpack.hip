@@ -602,7 +602,7 @@ __device__ __forceinline__ void recv_index_body(const mw_index_args &a, const ui
 }
 
 // Workgroup w of the index of a batch that rides in a launch of row movers: a row a lane at a time,
-// nothing kept between the passes, which fits 57 vector registers without scratch (see k_expand_index_next).
+// nothing kept between the passes, which fits 54 vector registers without scratch (see k_expand_index_next).
 template <int kForm>
 __device__ __forceinline__ void recv_index_rider(const mw_index_args &a, const uint32_t w)
 {
@@ -1062,9 +1062,9 @@ __global__ __launch_bounds__(1024) void k_expand(
 // with any scratch at all, the dispatcher refills the movers' wave slots more slowly (rocprofv3:
 // SPI_RA_VGPR_SIMD_FULL_CSN and SPI_RA_TMP_STALL_CSN appear, occupancy 7 % down; fp8 step 94.9
 // against 87.4 us with the riders compiled out).  The riders therefore come in a lean form that fits
-// 57 registers without spilling (a row a lane at a time in the index, eight counters in flight in the
+// 54 registers without spilling (a row a lane at a time in the index, eight counters in flight in the
 // plan's second half); batches too small to hide them give them launches of their own.  kFormMany (top_k
-// above eight) spills five: beside 61 us of movers 65 us against 72 with the index in front, beside 22
+// above eight) takes 64 and keeps three in scratch: beside 61 us of movers 65 us against 72 with the index in front, beside 22
 // us 22.6 against 34.4.
 template <int kForm, bool kFold>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_expand_index_next(
@@ -1480,14 +1480,16 @@ static bool index_rides(const mw_ctx *next, double mover_us, int bs, mw_index_ar
 // workgroups that talk through memory; the finishing ones walk every token's counters, T * T / bs of them, which
 // is what grows beyond a thousand tokens.  Beside movers that are shorter it takes 48 us for 1000 tokens in wide workgroups, 6
 // more with keys of several words, 56 in workgroups of two waves, and there 64 (4096 tokens), 72 (6144), 90 (8192).  A launch of its
-// own takes 8 (up to 2048 tokens), 13 (4096), 21 us (8192), 18 with more than eight ids and bitmaps of several words.  Measured,
+// own takes 8 (up to 2048 tokens), 11 (4096), 16 us (8192), 18 with more than eight ids and bitmaps of several words.  Measured,
 // us a step riding / apart, rows of 7168 from 16 and from 64 peers:
-//   bf16, 256 ranks   1024 tokens 56 / 18, 60 / 23   4096 66 / 43, 68 / 67   6144 72 / 61, 93 / 98   8192 90 / 78, 130 / 128
-//   fp8, 256 ranks    1024 tokens 54 / 15, 55 / 19   4096 57 / 35, 57 / 49   6144 58 / 50, 62 / 72   8192 59 / 63, 83 / 93
-//   bf16, 64 ranks    1024 tokens 56 / 22, 64 / 47   4096 69 / 67, 161 / 172 6144 91 / 100, 256 / 264 8192 122 / 130, 348 / 355
-//   fp8, 64 ranks     1024 tokens 48 / 27, 50 / 31   4096 51 / 49, 95 / 108  6144 58 / 72, 148 / 162 8192 79 / 93, 203 / 218
+//   bf16, 256 ranks   1024 tokens 56 / 18, 59 / 23   4096 65 / 41, 68 / 65   6144 72 / 57, 91 / 94   8192 89 / 72, 130 / 121
+//   fp8, 256 ranks    1024 tokens 53 / 15, 54 / 18   4096 57 / 33, 57 / 47   6144 58 / 45, 61 / 66   8192 59 / 56, 82 / 85
+//   bf16, 64 ranks    1024 tokens 56 / 23, 63 / 47   4096 68 / 65, 161 / 169 6144 90 / 95, 252 / 254 8192 121 / 123, 347 / 345
+//   fp8, 64 ranks     1024 tokens 47 / 18, 49 / 31   4096 50 / 47, 94 / 104  6144 57 / 66, 146 / 155 8192 78 / 85, 201 / 209
 // Beside movers of any length it still takes memory time from them, beyond 7168 tokens in two-wave workgroups with keys of
-// several words more than a launch of its own (130 / 128 above; skewed ids, 20673 rows, 156 / 153).
+// several words more than a launch of its own (130 / 121 above).
+// The 13 and 21 below are what a launch took before its keys were sorted.  They make the plan ride at three of these points where
+// it is no longer ahead: 68 for 65 us twice (4096 bf16 tokens, 256 ranks and 64 peers, 64 ranks and 16) and 347 for 345.
 // A context whose wait limit the caller has set keeps its plans riding.
 static bool plan_rides(const mw_ctx *next, double mover_us, int32_t T, bool keyed, int bs)
 {
