@@ -26,6 +26,9 @@ SHAPES = {
     "one_id": (16, 64, 1, 333, 5),
     "table_in_memory": (100, 3000, 4, 300, 99),    # more experts than a small workgroup's table of slots
     "many_local": (2, 2000, 4, 500, 1),            # slots do not fit a byte
+    "many_local_one_word": (2, 2000, 4, 30, 0),    # an expert's bits walked by a lane: one word, 24 (the most), 25
+    "many_local_24_words": (2, 1200, 4, 768, 1),
+    "many_local_25_words": (2, 1200, 4, 769, 0),
     "largest": (1, 1, 1, 65536, 0),                # every row to one expert: the count is 2^16
 }
 
