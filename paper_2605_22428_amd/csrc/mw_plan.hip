@@ -493,7 +493,7 @@ __global__ __launch_bounds__(kOrderBlock) void k_plan_order(
             const uint32_t phi = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)(kNone >> 32), (int)hi, 0x138, 0xf, 0xf, false);
             kept[j] = __ballot(key[j] != kNone);
             first[j] = key[j] != kNone && ((lo ^ plo) | (hi ^ phi)) != 0;
-            hash[j] = (lo ^ (hi << 15 | hi >> 17)) * 0x9E3779B1u;
+            hash[j] = mw_key_hash(lo, hi);
             uint32_t own_at = kBytes ? hi >> 16 : lo;                            // (two ranks: two bytes, or two positions)
             if (!kBytes && own_bit && !few_ranks) {                              // (uniform)
                 const int h = 63 - __clzll((long long)(key[j] | 1ull));
@@ -557,7 +557,7 @@ __global__ __launch_bounds__(kOrderBlock) void k_plan_order(
             const uint64_t fk = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)key[j], first) |
                                 (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(key[j] >> 32), first) << 32;
             const bool same = __ballot(key[j] == fk) == kept[j];      // (uniform) the wave's kept tokens have one key
-            const uint32_t h = ((uint32_t)key[j] ^ ((uint32_t)(key[j] >> 32) * 0x9E3779B1u)) * 0x85EBCA6Bu;
+            const uint32_t h = mw_key_hash((uint32_t)key[j], (uint32_t)(key[j] >> 32));
             at[j] = h >> (32 - slots_log);
             stride[j] = (h >> 3) | 1u;                                // odd: visits every slot
             hit[j] = key[j];
