@@ -12,23 +12,31 @@ namespace {
 constexpr uint64_t kField = 0x1fffffull;      // 21-bit fields of the packed counter
 constexpr int kPsKept = 256, kPsFlags = 257, kPsDone = 258, kPsDone2 = 259;  // plan state words after the 256 histogram bins
 
-// Ids j0 .. j0 + 7 of one token's list (-1 past its end).  Lists of whole 16-byte units that start on one take two requests
-// instead of eight: a request of 64 lanes whose lists are 32 bytes apart touches sixteen cache lines, and a workgroup's
-// requests take turns (a stream step of 64 tokens a rank, 64 ranks, ids limited to four servers, 8.4 -> 7.6 us).
+// Four ids that start on any word: one request (a load of several words needs no more than a word's alignment).
+typedef u32x4 mw_four_ids __attribute__((aligned(4)));
+
+// Ids j0 .. j0 + 7 of one token's list (-1 past its end), four to a request as long as there are four: a request of 64 lanes whose
+// lists are 32 bytes apart touches sixteen cache lines, and a workgroup's requests take turns.  Stream steps of 64 tokens over 64 ranks,
+// us with a word a request / four only where a list is whole 16-byte units that start on one / this: eight ids 8.0 / 7.0 / 7.0, nine 7.75 /
+// 8.1 / 7.35, six 6.9 / 7.1 / 6.85, one 5.6 / 5.7 / 5.6.
 __device__ __forceinline__ void load_eight_ids(const int32_t *__restrict__ row, int j0, int K, int32_t (&e)[8])
 {
 #pragma unroll
     for (int u = 0; u < 8; ++u) e[u] = -1;
-    if ((K & 3) == 0 && ((uintptr_t)row & 15u) == 0) {
-        const u32x4 q = *(const u32x4 *)(row + j0);
-        e[0] = (int32_t)q.x; e[1] = (int32_t)q.y; e[2] = (int32_t)q.z; e[3] = (int32_t)q.w;
-        if (j0 + 4 < K) {
-            const u32x4 p = *(const u32x4 *)(row + j0 + 4);
+    const int n = K - j0;
+    if (n >= 4) {
+        const u32x4 q = *(const mw_four_ids *)(row + j0);
+        if (n >= 8) {
+            const u32x4 p = *(const mw_four_ids *)(row + j0 + 4);
             e[4] = (int32_t)p.x; e[5] = (int32_t)p.y; e[6] = (int32_t)p.z; e[7] = (int32_t)p.w;
+        } else {
+#pragma unroll
+            for (int u = 4; u < 7; ++u) if (u < n) e[u] = row[j0 + u];
         }
+        e[0] = (int32_t)q.x; e[1] = (int32_t)q.y; e[2] = (int32_t)q.z; e[3] = (int32_t)q.w;
     } else {
 #pragma unroll
-        for (int u = 0; u < 8; ++u) if (j0 + u < K) e[u] = row[j0 + u];
+        for (int u = 0; u < 3; ++u) if (u < n) e[u] = row[j0 + u];
     }
 }
 
@@ -41,7 +49,7 @@ __device__ __forceinline__ void token_mask(const int32_t *__restrict__ row, int 
     for (int q = 0; q < MW_MASK_WORDS; ++q) m[q] = 0;
     for (int j0 = 0; j0 < K; j0 += 8) {
         int32_t e[8], s[8];
-        // (word by word: both forms side by side cost a riding plan of 4090 tokens of nine ids 4 us a step, 110 -> 118.4 for two)
+        // (word by word: with requests of 16 bytes beside them a riding plan of 4090 tokens of nine ids took 4 us more a step, 110 -> 118.4 for two)
 #pragma unroll
         for (int u = 0; u < 8; ++u) e[u] = (j0 + u < K) ? row[j0 + u] : -1;
 #pragma unroll

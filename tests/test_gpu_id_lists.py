@@ -1,7 +1,7 @@
-"""GPU parity with id lists of every alignment.  The plan of a small batch (mw_plan_pack, a small stream step) and the small
-launches' index read lists of whole 16-byte units that start on one by 16-byte requests, else word by word; here both, also
-for rows beyond one a lane.  Plans beyond 8192 tokens and riding plans read word by word whatever the alignment; they get the same
-shifted lists.  Bit-exact."""
+"""GPU parity with id lists of every length and alignment.  The plan of a small batch (mw_plan_pack, a small stream step) and the small
+launches' index read four ids a request, wherever they start, and what is left word by word; here lists of whole fours, of one to three
+ids more, and of fewer, on a 16-byte unit and four bytes behind one, also for rows beyond one a lane.  Plans beyond 8192 tokens and
+riding plans read word by word; they get the same lists.  Bit-exact."""
 import numpy as np
 import pytest
 import torch
@@ -30,7 +30,7 @@ def _check(ctx, buf, tk, e2r, R, row_bytes, what):
     H.assert_same_bytes(H.host(buf.desc).reshape(-1).view(B.DESC_DTYPE)[: len(desc)].view(np.uint8), desc.view(np.uint8), what + " desc")
 
 
-@pytest.mark.parametrize("K", [1, 4, 6, 8, 12])
+@pytest.mark.parametrize("K", [1, 3, 4, 5, 6, 7, 8, 9, 11, 12])
 @pytest.mark.parametrize("shifted", [False, True])
 def test_id_lists(K, shifted):
     print("id lists", K, shifted, flush=True)
