@@ -1602,8 +1602,9 @@ int32_t mw_launch_unpack_index(mw_ctx *ctx, const void *peers, bool packets, int
 // expected stride 27 times, 620 us against 569 for 32768 grid rows, the combine 605 against 511; evenly spread batches are
 // several times faster than with the capacity (64 ranks, 512 tokens: 134 us and 27).
 // The filling is that of folded rows for every caller, also where the launch does not fold them (the combine, small steps, riders
-// that refuse): a few more grid rows, which are not slower (12800 rows of 264 chunks that nobody had announced, us for the
-// filling of folded / unfolded rows: combine 19.8 / 21.9, of 528 chunks 36.7 / 37.9; 1664-row small steps 9.4 / 9.4 and 11.8 / 11.8).
+// that refuse): a few more grid rows than the launch's own shape would give.  Neither is ahead everywhere (us for the filling of
+// folded / unfolded rows, 12800 rows that nobody had announced: combine of 264 chunks 19.8 / 21.9, of 528 36.7 / 37.9; steps of 256 tokens
+// of 264 chunks 18.3 / 17.5, of 64 tokens 9.4 / 9.4, of 1025 chunks 16.9 / 17.3).
 static uint32_t expand_grid_rows(const mw_ctx *ctx, int32_t P)
 {
     int64_t rows = expected_rows(ctx, P);
