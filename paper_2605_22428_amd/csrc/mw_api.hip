@@ -420,11 +420,8 @@ MW_API int32_t mw_unpack_packets(mw_ctx *ctx, const mw_recv_packets *peers_dev, 
         rc = check_unpack_expand(ctx, n_peers, out_rows_dev, out_scales_dev, out_capacity_rows, out_src_peer_dev,
                                  out_src_token_dev);
     if (rc != MW_OK) return rc;
-    rc = mw_launch_unpack_index(ctx, peers_dev, true, n_peers, out_capacity_rows, expert_offsets_dev, recv_stats_dev,
-                                (hipStream_t)stream);
-    if (rc != MW_OK) return rc;
-    return mw_launch_unpack_expand(ctx, n_peers, out_rows_dev, out_scales_dev, out_capacity_rows, out_src_peer_dev,
-                                   out_src_token_dev, (hipStream_t)stream);
+    return mw_launch_unpack_two(ctx, peers_dev, true, n_peers, out_rows_dev, out_scales_dev, out_capacity_rows, out_src_peer_dev,
+                                out_src_token_dev, expert_offsets_dev, recv_stats_dev, (hipStream_t)stream);
 }
 
 // the members of the three batch records, as the calls they stand for check their arguments

@@ -359,6 +359,8 @@ int32_t mw_launch_unpack_expand(mw_ctx *ctx, int32_t P, void *out_rows, float *o
                                 int32_t *out_src_peer, int32_t *out_src_token, hipStream_t s);
 int32_t mw_launch_unpack(mw_ctx *ctx, const mw_recv_peer *peers, int32_t P, void *out_rows, float *out_scales, int64_t cap,
                          int32_t *out_src_peer, int32_t *out_src_token, int64_t *expert_offsets, mw_recv_stats *stats, hipStream_t s);
+int32_t mw_launch_unpack_two(mw_ctx *ctx, const void *peers, bool packets, int32_t P, void *out_rows, float *out_scales, int64_t cap,
+                             int32_t *out_src_peer, int32_t *out_src_token, int64_t *expert_offsets, mw_recv_stats *stats, hipStream_t s);
 int32_t mw_launch_unpack_expand_index_next(mw_ctx *ctx, int32_t P, void *out_rows, float *out_scales, int64_t cap,
                                            int32_t *out_src_peer, int32_t *out_src_token, mw_ctx *next,
                                            const mw_recv_peer *next_peers, int32_t next_P, int64_t next_cap,

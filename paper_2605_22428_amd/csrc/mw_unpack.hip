@@ -177,7 +177,9 @@ static inline size_t mw_index_lds_words(uint32_t wpl, uint32_t Lc, uint32_t tab_
 // kB: rows a lane requests together.  kKeep: what the lane's first kB rows parsed to stays in registers
 // for the second pass (top_k <= 8); else the rows are requested again, which the launches that
 // run the index beside the row movers do to stay small in registers.
-template <bool kPackets, int kForm, int kB, bool kKeep>
+// kDefer: a launch whose arguments name no statistics leaves the counts as they are, unreported: the expander behind it makes
+// its places of them (k_expand_counts).
+template <bool kPackets, int kForm, int kB, bool kKeep, bool kDefer = false>
 __device__ __forceinline__ void recv_index_body(const mw_index_args &a, const uint32_t p, const uint32_t part, const uint32_t row_part = 0)
 {
     extern __shared__ uint32_t lds[];
@@ -534,8 +536,10 @@ __device__ __forceinline__ void recv_index_body(const mw_index_args &a, const ui
                     if (scratch[36]) __hip_atomic_fetch_or(&a.flags[1], scratch[36], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     if (part == 0 && row_part == 0) st_agent(&a.addr_cnt[p], scratch[18] - scratch[19]);
                 }
-                mw_publish_wave();
-                if (lane == 0) scratch[17] = mw_report(&a.flags[2]);
+                if (!(kDefer && a.stats == nullptr)) {
+                    mw_publish_wave();
+                    if (lane == 0) scratch[17] = mw_report(&a.flags[2]);
+                }
             }
         }
 
@@ -591,6 +595,7 @@ __device__ __forceinline__ void recv_index_body(const mw_index_args &a, const ui
         err = 0;
         mark_from(0, false);
     }
+    if (kDefer && a.stats == nullptr) return;
     // ---- the workgroup that reported last turns the counts into output bases ----------
     // Everything it reads (counts, addressed-row counts, flags) is written and read with device-scope
     // atomics, and every workgroup reports through one counter when the wave that wrote them has them acknowledged
@@ -626,7 +631,7 @@ __host__ __device__ __forceinline__ uint32_t index_riders(const mw_index_args &a
 template <bool kPackets, int kForm, int kB>
 __global__ __launch_bounds__(kIndexBlock) void k_recv_index(const mw_index_args a)
 {
-    recv_index_body<kPackets, kForm, kB, kForm == kFormFew>(a, blockIdx.x, blockIdx.y);
+    recv_index_body<kPackets, kForm, kB, kForm == kFormFew, true>(a, blockIdx.x, blockIdx.y);
 }
 
 // ---- the index of a SMALL batch in one workgroup ------------------------------------------------
@@ -1059,6 +1064,103 @@ __global__ __launch_bounds__(1024) void k_expand(
 {
     expand_body<kFold>(recs, hits, base, row_base, P, Kd, xc, sc, out_rows, out_scales, cap, out_src_peer, out_src_token,
                        blockIdx.y, gridDim.y);
+}
+
+// The expander behind an index that has left its counts unreported (mw_unpack, mw_unpack_packets).  What an index otherwise ends
+// with -- the counts acknowledged, a report of every workgroup (256 peers to one address: 8 ns each), the last one's reads of all
+// counts -- is a chain of three round trips in front of this launch.  Here a wave of grid row 0 makes bases, expert offsets
+// and statistics, and the movers do not wait for it: a wave requests the counts in front of the payload (one
+// kilobyte that its CU's cache holds) and adds up what is in front of its place while that is on its way, a dozen vector instructions.  kCounts: counts a lane holds, 1 (at most
+// 64 in all) or 4 (at most 256).  us for mw_plan, mw_pack and mw_unpack, before / after: 1000 fp8 tokens of 16 ranks 30.6 / 28.4, 4096 of 64
+// ranks 107.3 / 106.5, 8192 bf16 tokens of 256 ranks 154.4 / 151.4; 2048 packets of 16 ranks 68.5 / 67.1.
+// Otherwise this is expand_body.  (The hits behind the first requested with the record and their rows stored without a wait
+// in between: 1000 tokens 28.2, but 8192 of 256 ranks 152.0; in the stream's launch 16000 rows of 1.5 hits 80 -> 82.)
+template <int kCounts> struct mw_counts_of { typedef uint32_t type; };
+template <> struct mw_counts_of<4> { typedef u32x4 type; };
+template <bool kFold, int kCounts>
+__device__ __forceinline__ void expand_counts_body(
+    const mw_row_rec *__restrict__ recs, const mw_hit *__restrict__ hits, const uint32_t *__restrict__ cnt,
+    const uint32_t *__restrict__ row_base, int P, int Kd, int xc, int sc, uint32_t n_counts,
+    u32x4 *__restrict__ out_rows, u32x4 *__restrict__ out_scales, uint32_t cap,
+    int32_t *__restrict__ out_src_peer, int32_t *__restrict__ out_src_token)
+{
+    using mw_counts = typename mw_counts_of<kCounts>::type;
+    uint32_t g = blockIdx.y - 1u;
+    const u32x4 *rp = (const u32x4 *)(recs + g);
+    u32x4 r0 = rp[0], r1 = rp[1];
+    uint32_t m_total = row_base[P];
+    uint32_t gdim = gridDim.y, bdim = blockDim.x;          // (less one below: here it would be waited for in front of the record's request)
+    MW_PIN_S(gdim); MW_PIN_S(bdim); MW_PIN_S(Kd); MW_PIN_S(xc); MW_PIN_S(sc); MW_PIN_S(cap);
+    MW_PIN_PTR(hits); MW_PIN_PTR(out_rows); MW_PIN_PTR(out_scales); MW_PIN_PTR(out_src_peer);
+    MW_PIN_PTR(out_src_token);
+    // (a lane without counts reads the last ones again: nobody looks at what it adds up)
+    mw_counts own = ((const mw_counts *)cnt)[min(threadIdx.x & 63u, (n_counts - 1u) / (uint32_t)kCounts)];
+    MW_PIN_S4(r0); MW_PIN_S4(r1); MW_PIN_S(m_total);
+    gdim -= 1u;
+    const int n = xc + sc;
+    const int c = blockIdx.x * bdim + threadIdx.x;
+    const int c2 = c + (int)bdim;
+    uint32_t in_front = 0;                                 // counts of the lanes before
+    bool summed = false;
+    // first output row of (expert, peer) f
+    auto base_of = [&](uint32_t f) __attribute__((always_inline)) -> uint32_t {
+        uint32_t v = in_front;
+        if constexpr (kCounts == 4) v += ((f & 3u) > 0 ? own.x : 0u) + ((f & 3u) > 1 ? own.y : 0u) + ((f & 3u) > 2 ? own.z : 0u);
+        return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)(f / kCounts));
+    };
+    while (g < m_total) {
+        const int n_hits = (int)r1.x;
+        if (n_hits > 0) {
+            const int peer = (int)r0.w;
+            const void *src = (const void *)(((uint64_t)r0.y << 32) | r0.x);
+            // (lanes beyond the row read its last chunk again: no branch, so that the wait for the counts is none for the payload)
+            u32x4 v = mw_ld16_global(src, min(c, n - 1)), v2 = {0u, 0u, 0u, 0u};
+            if (kFold) v2 = mw_ld16_global(src, min(c2, n - 1));
+            if (!summed) {
+                asm volatile("" : "+v"(own));              // (here, not in front of the payload's request)
+                uint32_t sum;
+                if constexpr (kCounts == 4) sum = own.x + own.y + own.z + own.w; else sum = own;
+                in_front = mw_wave_incl_scan(sum) - sum;
+                summed = true;
+            }
+            uint32_t dst = base_of(r1.y * (uint32_t)P + (uint32_t)peer) + r1.z;      // below 2^30: 2^24 rows, 64 experts each
+            asm volatile("" : "+v"(v));                    // waited for here, whether it is stored or not: a load that is still on its
+            if (kFold) asm volatile("" : "+v"(v2));        // way at the loop's end makes the next payload's request wait for everything
+            for (int k = 1;; ++k) {
+                if (dst < cap) {
+                    if (kFold && c2 < n) {
+                        if (c2 < xc) mw_st16(out_rows + (size_t)dst * xc + c2, v2);
+                        else out_scales[(size_t)dst * sc + (c2 - xc)] = v2;
+                    }
+                    if (c < xc) mw_st16(out_rows + (size_t)dst * xc + c, v);
+                    else if (c < n) out_scales[(size_t)dst * sc + (c - xc)] = v;
+                    if (c == 0) { out_src_peer[dst] = peer; out_src_token[dst] = (int32_t)r0.z; }
+                }
+                if (k >= n_hits) break;
+                const mw_hit hk = hits[(size_t)g * Kd + k];
+                dst = base_of((uint32_t)hk.le * P + (uint32_t)peer) + (uint32_t)hk.rank;
+            }
+        }
+        g += gdim;
+        if (g < m_total) { rp = (const u32x4 *)(recs + g); r0 = rp[0]; r1 = rp[1]; }
+    }
+}
+
+template <bool kFold, int kCounts>
+__global__ __launch_bounds__(1024) void k_expand_counts(
+    const mw_row_rec *__restrict__ recs, const uint32_t *__restrict__ row_base, const uint32_t *__restrict__ cnt,
+    const mw_hit *__restrict__ hits, int P, int Kd, int xc, int sc, uint32_t n_counts,     // (in registers when a wave starts)
+    u32x4 *__restrict__ out_rows, u32x4 *__restrict__ out_scales, uint32_t cap,
+    int32_t *__restrict__ out_src_peer, int32_t *__restrict__ out_src_token,
+    uint32_t L, int64_t out_cap, const uint32_t *addr_cnt, uint32_t *flags, uint32_t *base, int64_t *expert_offsets, mw_recv_stats *stats)
+{
+    if (blockIdx.y == 0) {
+        if (blockIdx.x == 0 && threadIdx.x < 64)
+            mw_finish_counts_wave(cnt, addr_cnt, flags, row_base, L, (uint32_t)P, out_cap, base, expert_offsets, stats);
+        return;
+    }
+    expand_counts_body<kFold, kCounts>(recs, hits, cnt, row_base, P, Kd, xc, sc, n_counts, out_rows, out_scales, cap, out_src_peer,
+                                       out_src_token);
 }
 
 // One launch for a steady stream of batches: the expander of the current batch and, in the
@@ -1544,9 +1646,12 @@ static int64_t small_index_rows(const mw_ctx *ctx, int32_t P)
     return ctx->recv_rows_hint > 0 ? ctx->recv_rows_hint : (int64_t)P * ctx->cfg.max_tokens;
 }
 
-int32_t mw_launch_unpack_index(mw_ctx *ctx, const void *peers, bool packets, int32_t P, int64_t cap,
-                               int64_t *expert_offsets, mw_recv_stats *stats, hipStream_t s)
+// defer: the caller's expander can make its places of the counts (k_expand_counts).  *deferred: it has to (the one-workgroup index
+// has them in LDS and finishes by itself).
+static int32_t launch_unpack_index(mw_ctx *ctx, const void *peers, bool packets, int32_t P, int64_t cap, int64_t *expert_offsets,
+                                   mw_recv_stats *stats, bool defer, bool *deferred, hipStream_t s)
 {
+    *deferred = false;
     mw_index_args a;
     size_t lds_index;
     // A few peers with many experts each: up to four workgroups a peer (8 peers of 2720 rows, 32 experts:
@@ -1575,6 +1680,7 @@ int32_t mw_launch_unpack_index(mw_ctx *ctx, const void *peers, bool packets, int
             hipLaunchKernelGGL(k_recv_index_small, dim3(1), dim3(kSmallLanes), lds, s, a);
         } else
         {
+            if (defer) { a.stats = nullptr; *deferred = true; }
 #define MW_INDEX(GENERAL_, ROWS_)                                                                                              \
     do {                                                                                                                       \
         if (packets) hipLaunchKernelGGL((k_recv_index<true, GENERAL_, ROWS_>), dim3(P, a.parts), dim3(ib), lds_index, s, a);   \
@@ -1589,6 +1695,13 @@ int32_t mw_launch_unpack_index(mw_ctx *ctx, const void *peers, bool packets, int
     }
     MW_HIP_CHECK(hipGetLastError());
     return MW_OK;
+}
+
+int32_t mw_launch_unpack_index(mw_ctx *ctx, const void *peers, bool packets, int32_t P, int64_t cap, int64_t *expert_offsets,
+                               mw_recv_stats *stats, hipStream_t s)
+{
+    bool deferred;
+    return launch_unpack_index(ctx, peers, packets, P, cap, expert_offsets, stats, false, &deferred, s);
 }
 
 // Grid rows of the expander and of the combine: about as many as the peers will hold, not the capacity -- workgroups are
@@ -1639,6 +1752,36 @@ int32_t mw_launch_unpack_expand(mw_ctx *ctx, int32_t P, void *out_rows, float *o
     return MW_OK;
 }
 
+// Counts that a wave of the expander adds up for itself: four a lane, one 16-byte request.  More are a second request of a kilobyte
+// in front of every kilobyte of payload; the index's last workgroup adds them up once for all.
+constexpr int64_t kCountsMax = 256;
+
+// Index and expander of one batch in two launches.
+int32_t mw_launch_unpack_two(mw_ctx *ctx, const void *peers, bool packets, int32_t P, void *out_rows, float *out_scales, int64_t cap,
+                             int32_t *out_src_peer, int32_t *out_src_token, int64_t *expert_offsets, mw_recv_stats *stats, hipStream_t s)
+{
+    const uint32_t n_counts = (uint32_t)ctx->n_local * (uint32_t)P;
+    const bool defer = (int64_t)ctx->n_local * P <= kCountsMax && ctx->cfg.max_recv_rows > 0;
+    bool deferred;
+    const int32_t rc = launch_unpack_index(ctx, peers, packets, P, cap, expert_offsets, stats, defer, &deferred, s);
+    if (rc != MW_OK) return rc;
+    if (!deferred) return mw_launch_unpack_expand(ctx, P, out_rows, out_scales, cap, out_src_peer, out_src_token, s);
+    const int xc = (int)(ctx->x_row_bytes / 16), sc = (int)(ctx->s_row_bytes / 16);
+    const mw_row_shape shape = mw_row_shape_folded(xc + sc);
+    const bool fold = mw_is_folded(shape, xc + sc), one = n_counts <= 64;
+    const uint32_t gy = expand_grid_rows(ctx, P) + 1;
+    {
+        mw_timed tm(ctx, MW_KERNEL_EXPAND, s);
+        hipLaunchKernelGGL((one ? fold ? k_expand_counts<true, 1> : k_expand_counts<false, 1> : fold ? k_expand_counts<true, 4> : k_expand_counts<false, 4>),
+                           dim3(shape.nseg, gy), dim3(shape.bs), 0, s, ctx->d_recs, ctx->d_row_base, ctx->d_cnt, ctx->d_hits, P,
+                           ctx->hit_slots, xc, sc, n_counts, (u32x4 *)out_rows, (u32x4 *)out_scales,
+                           (uint32_t)(cap < 0x7fffffffLL ? cap : 0x7fffffffLL), out_src_peer, out_src_token, (uint32_t)ctx->n_local, cap,
+                           ctx->d_addr_cnt, ctx->d_flags, ctx->d_base, expert_offsets, stats);
+    }
+    MW_HIP_CHECK(hipGetLastError());
+    return MW_OK;
+}
+
 int32_t mw_launch_unpack(mw_ctx *ctx, const mw_recv_peer *peers, int32_t P, void *out_rows, float *out_scales, int64_t cap,
                          int32_t *out_src_peer, int32_t *out_src_token, int64_t *expert_offsets, mw_recv_stats *stats, hipStream_t s)
 {
@@ -1667,9 +1810,7 @@ int32_t mw_launch_unpack(mw_ctx *ctx, const mw_recv_peer *peers, int32_t P, void
         MW_HIP_CHECK(hipGetLastError());
         return MW_OK;
     }
-    const int32_t rc = mw_launch_unpack_index(ctx, peers, false, P, cap, expert_offsets, stats, s);
-    if (rc != MW_OK) return rc;
-    return mw_launch_unpack_expand(ctx, P, out_rows, out_scales, cap, out_src_peer, out_src_token, s);
+    return mw_launch_unpack_two(ctx, peers, false, P, out_rows, out_scales, cap, out_src_peer, out_src_token, expert_offsets, stats, s);
 }
 
 // The riders of k_small_step beside its one-workgroup index (false: they are not needed).  *fits: both forms can be had.

@@ -1,0 +1,84 @@
+"""GPU parity of mw_unpack and mw_unpack_packets where the expander makes its places of the index's counts: one count, a wave of them
+and one more or less, the most a wave takes and one more, rows of one and of several workgroups, folded rows; more rows than the launch
+was made for, the first ones of every workgroup not addressed; and what is left behind for a second expander.  Bit-exact."""
+import numpy as np
+import pytest
+
+from oracle import ref
+from paper_2605_22428_amd import binding as B
+
+import gpu_harness as H
+
+pytestmark = pytest.mark.gpu
+
+
+def _filled(gu, ctx, n_peers, cap, want, what):
+    """The second expander reads the bases that the first left in the workspace."""
+    H.check_unpack(gu, want, what)
+    again = B.RecvBuffers(ctx, cap)
+    ctx.mw_unpack_expand(n_peers, again.out_rows, again.out_scales, cap, again.out_src_peer, again.out_src_token)
+    for a, b in ((again.out_rows, want[0]), (again.out_src_peer, want[2]), (again.out_src_token, want[3])):
+        H.assert_same_bytes(H.host(a)[: gu.Q], b, what + ", second expander")
+
+
+#                         local experts, ranks, tokens, chunks
+@pytest.mark.parametrize("L,R,T,chunks", [(1, 1, 700, 1), (7, 9, 300, 1), (8, 8, 300, 65), (5, 13, 200, 1), (15, 17, 100, 264),
+                                          (1, 256, 40, 1), (4, 64, 40, 648), (32, 8, 300, 3), (257, 1, 700, 1), (6, 43, 50, 1)])
+def test_counts(L, R, T, chunks):
+    print("counts", L, R, T, chunks, flush=True)
+    rng = np.random.default_rng(L * 1000 + R)
+    E, K, me, hidden = L * R, min(4, L * R), R - 1, 8 * chunks
+    e2r = (np.arange(E) // L).astype(np.int32)
+    most = 6 * T
+    ctx = B.Context(R, E, K, me, hidden, B.MW_ROW_BF16, most, R * most, e2r, device=H.DEV)
+    # The last rank's bit is the highest: in a whole sender's buffer the rows for it come last.
+    for batch, n, whole in ((0, T, False), (1, most if chunks == 1 else T, True)):
+        toks, recs, packets = [], [], []
+        for p in range(R):
+            tk = rng.integers(0, E, size=(n, K)).astype(np.int32)
+            tk[rng.random((n, K)) < 0.1] = -1
+            x = rng.integers(0, 1 << 16, size=(n, hidden), dtype=np.uint16)
+            toks.append((tk, x, None))
+            g = H.GpuSend(ctx, tk, x, None)
+            recs.append(g.full_record() if whole else H.shrink(g.deliver(me)))
+            mask, perm, _, _ = ref.plan(tk, e2r, R, 2 * hidden)
+            packets.append(H.dev(ref.deliver_packets(ref.pack_packets(x, None, tk, mask, perm), me)))
+        cap = max(1, R * n * min(K, L))
+        want = ref.dispatch_plain(toks, e2r, me, cap)
+        for r in ("", " again"):
+            _filled(H.GpuUnpack(ctx, recs, cap), ctx, R, cap, want, "batch %d%s" % (batch, r))
+        buf = B.RecvBuffers(ctx, cap)
+        ctx.mw_unpack_packets(B.packets_table(packets, [int(t.shape[0]) for t in packets], H.DEV), R, buf.out_rows, None, cap,
+                              buf.out_src_peer, buf.out_src_token, buf.expert_offsets, buf.stats)
+        gu = H.GpuUnpack.__new__(H.GpuUnpack)
+        gu.ctx, gu.buf, gu.stats = ctx, buf, ctx.mw_get_recv_stats(buf.stats)
+        gu.Q = int(gu.stats["n_out_rows"])
+        _filled(gu, ctx, R, cap, want, "packets %d" % batch)
+    ctx.close()
+
+
+def test_counts_capacity_and_flags():
+    """Fewer output rows than arrive, and an id outside the range: what is in front is written, the flags say so, once."""
+    rng = np.random.default_rng(5)
+    L, R, T, K = 4, 16, 200, 4
+    e2r = (np.arange(L * R) // L).astype(np.int32)
+    ctx = B.Context(R, L * R, K, 3, 64, B.MW_ROW_BF16, T, R * T, e2r, device=H.DEV)
+    toks, recs = [], []
+    for p in range(R):
+        tk = rng.integers(0, L * R, size=(T, K)).astype(np.int32)
+        x = rng.integers(0, 1 << 16, size=(T, 64), dtype=np.uint16)
+        toks.append((tk, x, None))
+        recs.append(H.shrink(H.GpuSend(ctx, tk, x, None).deliver(3)))
+    want = ref.dispatch_plain(toks, e2r, 3, R * T * K)
+    q = len(want[2])
+    gu = H.GpuUnpack(ctx, recs, q - 7)
+    assert int(gu.stats["error_flags"]) == B.MW_FLAG_OUT_CAPACITY and gu.Q == q
+    H.assert_same_bytes(H.host(gu.buf.out_rows)[: q - 7], want[0][: q - 7], "rows within the capacity")
+    row = int((recs[2]["row_topk"][:, 0] // L == 3).nonzero()[0])        # (a row whose first id is local keeps its place)
+    spoilt = recs[2]["row_topk"].clone()
+    others = [j for j in range(1, K) if int(spoilt[row, j]) // L != 3]
+    spoilt[row, others[0]] = L * R + 5
+    gu = H.GpuUnpack(ctx, [dict(r, row_topk=spoilt) if i == 2 else r for i, r in enumerate(recs)], q)
+    assert int(gu.stats["error_flags"]) == B.MW_FLAG_BAD_EXPERT
+    H.check_unpack(H.GpuUnpack(ctx, recs, q), want, "after an error")
+    ctx.close()
