@@ -8,7 +8,6 @@ from __future__ import annotations
 
 import ctypes as C
 import os
-from types import SimpleNamespace
 from typing import List, Optional, Sequence
 
 import numpy as np
@@ -16,6 +15,7 @@ import torch
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libmw.so")
+CALLS_PATH = os.path.join(HERE, "_mwcall.so")
 
 MW_OK = 0
 MW_ERR_INVALID_ARG, MW_ERR_CAPACITY, MW_ERR_UNSUPPORTED, MW_ERR_HIP, MW_ERR_WORKSPACE = -1, -2, -3, -4, -5
@@ -124,50 +124,19 @@ def load():
     return _lib
 
 
-# Argument types of the calls of the path: p pointer, i int32, l int64.  With them ctypes converts addresses
-# by itself; an object made per pointer and a torch.cuda.Stream made per call were half of a small
-# call's time on the host (mw_plan_pack 8.6 us a call, now 5.8; mw_unpack 10.8, now 8.3).
-_SIGNATURES = {
-    "mw_plan": "ppippppp",
-    "mw_pack": "ppppppipppp",
-    "mw_pack_quantize": "pppppipppp",
-    "mw_plan_pack": "ppppipppppppp",
-    "mw_pack_packets": "pppppppipp",
-    "mw_unpack_packets": "ppipplppppp",
-    "mw_plan_allgather": "plppp",
-    "mw_pack_allgather": "pplpp",
-    "mw_plan_allgather_split": "pllppp",
-    "mw_unpack_allgather_split": "pppllpp",
-    "mw_unpack": "ppipplppppp",
-    "mw_unpack_index": "ppilppp",
-    "mw_unpack_expand": "pipplppp",
-    "mw_combine_gather": "piplplp",
-    "mw_unpack_allgather": "pplpp",
-    "mw_allgather_step": "pplpppppp",
-    "mw_relay": "ppplpp",
-    "mw_relay_index": "ppplpp",
-    "mw_relay_copy": "ppppp",
-    "mw_relay_copy_index_next": "ppppppplpp",
-    "mw_relay_packets": "ppplpp",
-    "mw_relay_packets_index": "pplpp",
-    "mw_relay_packets_copy": "ppppp",
-    "mw_relay_packets_copy_index_next": "pppppplpp",
-    "mw_stream_step": "ppppp",
-}
-_native_fns = None
+_calls = None
 
 
 def _native():
-    """The path's functions with their argument types set; load()'s own stay without."""
-    global _native_fns
-    if _native_fns is None:
-        lib, kinds, fns = load(), {"p": C.c_void_p, "i": C.c_int32, "l": C.c_int64}, SimpleNamespace()
-        for name, sig in _SIGNATURES.items():
-            f = lib[name]                     # a function object of its own
-            f.argtypes, f.restype = [kinds[k] for k in sig], C.c_int32
-            setattr(fns, name, f)
-        _native_fns = fns
-    return _native_fns
+    """The calls of the path as C functions that take tensors and numbers as they are (csrc/mw_py.c)."""
+    global _calls
+    if _calls is None:
+        load()
+        if not os.path.exists(CALLS_PATH):
+            raise RuntimeError("HIP library's Python entry %s is not built (run __graft_entry__.build())" % CALLS_PATH)
+        from . import _mwcall
+        _calls = _mwcall
+    return _calls
 
 
 def status_string(status: int) -> str:
@@ -310,85 +279,73 @@ class Context:
     def mw_plan(self, topk_ids: torch.Tensor, mask: torch.Tensor, perm: torch.Tensor,
                 desc: torch.Tensor, stats: torch.Tensor):
         n_tokens = topk_ids.shape[0]
-        _check(_native().mw_plan(self._h, _addr(topk_ids), C.c_int32(n_tokens), _addr(mask), _addr(perm), _addr(desc),
-                                 _addr(stats), _stream_handle()), "mw_plan")
+        _check(_native().mw_plan(self._h, topk_ids, n_tokens, mask, perm, desc, stats, _stream_handle()), "mw_plan")
 
     def mw_pack(self, x: torch.Tensor, scales: Optional[torch.Tensor], topk_ids: torch.Tensor,
                 perm: torch.Tensor, stats: torch.Tensor, packed: torch.Tensor,
                 row_src_token: torch.Tensor, row_topk: torch.Tensor):
         n_tokens = topk_ids.shape[0]
-        _check(_native().mw_pack(self._h, _addr(x), _addr(scales), _addr(topk_ids), _addr(perm), _addr(stats),
-                                 C.c_int32(n_tokens), _addr(packed), _addr(row_src_token), _addr(row_topk),
+        _check(_native().mw_pack(self._h, x, scales, topk_ids, perm, stats, n_tokens, packed, row_src_token, row_topk,
                                  _stream_handle()), "mw_pack")
 
     def mw_pack_quantize(self, x_bf16: torch.Tensor, topk_ids: torch.Tensor, perm: torch.Tensor,
                          stats: torch.Tensor, packed: torch.Tensor, row_src_token: torch.Tensor,
                          row_topk: torch.Tensor):
         n_tokens = topk_ids.shape[0]
-        _check(_native().mw_pack_quantize(self._h, _addr(x_bf16), _addr(topk_ids), _addr(perm), _addr(stats),
-                                          C.c_int32(n_tokens), _addr(packed), _addr(row_src_token), _addr(row_topk),
-                                          _stream_handle()), "mw_pack_quantize")
+        _check(_native().mw_pack_quantize(self._h, x_bf16, topk_ids, perm, stats, n_tokens, packed, row_src_token,
+                                          row_topk, _stream_handle()), "mw_pack_quantize")
 
     def mw_plan_pack(self, topk_ids: torch.Tensor, x: torch.Tensor, scales: Optional[torch.Tensor],
                      mask: torch.Tensor, perm: torch.Tensor, desc: torch.Tensor, stats: torch.Tensor,
                      packed: torch.Tensor, row_src_token: torch.Tensor, row_topk: torch.Tensor):
         n_tokens = topk_ids.shape[0]
-        _check(_native().mw_plan_pack(self._h, _addr(topk_ids), _addr(x), _addr(scales), C.c_int32(n_tokens),
-                                      _addr(mask), _addr(perm), _addr(desc), _addr(stats), _addr(packed),
-                                      _addr(row_src_token), _addr(row_topk), _stream_handle()), "mw_plan_pack")
+        _check(_native().mw_plan_pack(self._h, topk_ids, x, scales, n_tokens, mask, perm, desc, stats, packed,
+                                      row_src_token, row_topk, _stream_handle()), "mw_plan_pack")
 
     def mw_pack_packets(self, x: torch.Tensor, scales: Optional[torch.Tensor], topk_ids: torch.Tensor,
                         mask: torch.Tensor, perm: torch.Tensor, stats: torch.Tensor, packets: torch.Tensor):
         n_tokens = topk_ids.shape[0]
-        _check(_native().mw_pack_packets(self._h, _addr(x), _addr(scales), _addr(topk_ids), _addr(mask), _addr(perm),
-                                         _addr(stats), C.c_int32(n_tokens), _addr(packets), _stream_handle()),
-               "mw_pack_packets")
+        _check(_native().mw_pack_packets(self._h, x, scales, topk_ids, mask, perm, stats, n_tokens, packets,
+                                         _stream_handle()), "mw_pack_packets")
 
     def mw_unpack_packets(self, peers: torch.Tensor, n_peers: int, out_rows: torch.Tensor,
                           out_scales: Optional[torch.Tensor], out_capacity_rows: int, out_src_peer: torch.Tensor,
                           out_src_token: torch.Tensor, expert_offsets: torch.Tensor, recv_stats: torch.Tensor):
-        _check(_native().mw_unpack_packets(self._h, _addr(peers), C.c_int32(n_peers), _addr(out_rows),
-                                           _addr(out_scales), C.c_int64(out_capacity_rows), _addr(out_src_peer),
-                                           _addr(out_src_token), _addr(expert_offsets), _addr(recv_stats),
-                                           _stream_handle()), "mw_unpack_packets")
+        _check(_native().mw_unpack_packets(self._h, peers, n_peers, out_rows, out_scales, out_capacity_rows, out_src_peer,
+                                           out_src_token, expert_offsets, recv_stats, _stream_handle()),
+               "mw_unpack_packets")
 
     def mw_plan_allgather(self, shard_bytes: int, desc: torch.Tensor, stats: torch.Tensor):
-        _check(_native().mw_plan_allgather(self._h, C.c_int64(shard_bytes), _addr(desc), _addr(stats),
-                                           _stream_handle()), "mw_plan_allgather")
+        _check(_native().mw_plan_allgather(self._h, shard_bytes, desc, stats, _stream_handle()), "mw_plan_allgather")
 
     def mw_pack_allgather(self, shard: torch.Tensor, shard_bytes: int, send_buf: torch.Tensor):
-        _check(_native().mw_pack_allgather(self._h, _addr(shard), C.c_int64(shard_bytes), _addr(send_buf),
-                                           _stream_handle()), "mw_pack_allgather")
+        _check(_native().mw_pack_allgather(self._h, shard, shard_bytes, send_buf, _stream_handle()), "mw_pack_allgather")
 
     def mw_plan_allgather_split(self, shard_bytes: int, direct_bytes: int, desc: torch.Tensor, stats: torch.Tensor):
-        _check(_native().mw_plan_allgather_split(self._h, C.c_int64(shard_bytes), C.c_int64(direct_bytes),
-                                                 _addr(desc), _addr(stats), _stream_handle()),
+        _check(_native().mw_plan_allgather_split(self._h, shard_bytes, direct_bytes, desc, stats, _stream_handle()),
                "mw_plan_allgather_split")
 
     def mw_unpack_allgather_split(self, direct: torch.Tensor, relayed: torch.Tensor, shard_bytes: int,
                                   direct_bytes: int, out: torch.Tensor):
-        _check(_native().mw_unpack_allgather_split(self._h, _addr(direct), _addr(relayed), C.c_int64(shard_bytes),
-                                                   C.c_int64(direct_bytes), _addr(out), _stream_handle()),
-               "mw_unpack_allgather_split")
+        _check(_native().mw_unpack_allgather_split(self._h, direct, relayed, shard_bytes, direct_bytes, out,
+                                                   _stream_handle()), "mw_unpack_allgather_split")
 
     # ---- receive side --------------------------------------------------------------------
     def mw_unpack(self, peers: torch.Tensor, n_peers: int, out_rows: torch.Tensor,
                   out_scales: Optional[torch.Tensor], out_capacity_rows: int, out_src_peer: torch.Tensor,
                   out_src_token: torch.Tensor, expert_offsets: torch.Tensor, recv_stats: torch.Tensor):
-        _check(_native().mw_unpack(self._h, _addr(peers), C.c_int32(n_peers), _addr(out_rows), _addr(out_scales),
-                                   C.c_int64(out_capacity_rows), _addr(out_src_peer), _addr(out_src_token),
-                                   _addr(expert_offsets), _addr(recv_stats), _stream_handle()), "mw_unpack")
+        _check(_native().mw_unpack(self._h, peers, n_peers, out_rows, out_scales, out_capacity_rows, out_src_peer,
+                                   out_src_token, expert_offsets, recv_stats, _stream_handle()), "mw_unpack")
 
     def mw_unpack_index(self, peers: torch.Tensor, n_peers: int, out_capacity_rows: int,
                         expert_offsets: torch.Tensor, recv_stats: torch.Tensor):
-        _check(_native().mw_unpack_index(self._h, _addr(peers), C.c_int32(n_peers), C.c_int64(out_capacity_rows),
-                                         _addr(expert_offsets), _addr(recv_stats), _stream_handle()), "mw_unpack_index")
+        _check(_native().mw_unpack_index(self._h, peers, n_peers, out_capacity_rows, expert_offsets, recv_stats,
+                                         _stream_handle()), "mw_unpack_index")
 
     def mw_unpack_expand(self, n_peers: int, out_rows: torch.Tensor, out_scales: Optional[torch.Tensor],
                          out_capacity_rows: int, out_src_peer: torch.Tensor, out_src_token: torch.Tensor):
-        _check(_native().mw_unpack_expand(self._h, C.c_int32(n_peers), _addr(out_rows), _addr(out_scales),
-                                          C.c_int64(out_capacity_rows), _addr(out_src_peer), _addr(out_src_token),
-                                          _stream_handle()), "mw_unpack_expand")
+        _check(_native().mw_unpack_expand(self._h, n_peers, out_rows, out_scales, out_capacity_rows, out_src_peer,
+                                          out_src_token, _stream_handle()), "mw_unpack_expand")
 
     def mw_unpack_expand_index_next(self, n_peers: int, out_rows: torch.Tensor, out_scales: Optional[torch.Tensor],
                                     out_capacity_rows: int, out_src_peer: torch.Tensor, out_src_token: torch.Tensor,
@@ -427,7 +384,7 @@ class Context:
         recv = recv_batch(n_peers, out_rows, out_scales, out_capacity_rows, out_src_peer, out_src_token)
         nxt = next_batch(next_ctx, next_peers, next_n_peers, next_out_capacity_rows, next_expert_offsets,
                          next_recv_stats, next_topk_ids, next_mask, next_perm, next_desc, next_send_stats)
-        _check(_native().mw_stream_step(self._h, C.byref(send), C.byref(recv), C.byref(nxt), _stream_handle()),
+        _check(_native().mw_stream_step(self._h, C.addressof(send), C.addressof(recv), C.addressof(nxt), _stream_handle()),
                "mw_stream_step")
 
     def mw_stream_step_records(self, send: MwSendBatch, recv: MwRecvBatch, nxt: MwNextBatch,
@@ -435,8 +392,9 @@ class Context:
         """mw_stream_step on records the caller built once (send_batch, recv_batch, next_batch) and keeps,
         together with the tensors they point to: a loop over the same buffers then marshals nothing.
         stream_handle: a stream's raw handle (torch.cuda.Stream.cuda_stream); default: the current stream."""
-        st = _stream_handle() if stream_handle is None else C.c_void_p(stream_handle)
-        _check(_native().mw_stream_step(self._h, C.byref(send), C.byref(recv), C.byref(nxt), st), "mw_stream_step")
+        st = _stream_handle() if stream_handle is None else stream_handle
+        _check(_native().mw_stream_step(self._h, C.addressof(send), C.addressof(recv), C.addressof(nxt), st),
+               "mw_stream_step")
 
     def mw_ctx_set_options(self, options: int):
         _check(load().mw_ctx_set_options(self._h, C.c_uint32(options)), "mw_ctx_set_options")
@@ -446,18 +404,16 @@ class Context:
 
     def mw_combine_gather(self, n_peers: int, y: torch.Tensor, out_capacity_rows: int, ret_rows: torch.Tensor,
                           ret_capacity_rows: int):
-        _check(_native().mw_combine_gather(self._h, C.c_int32(n_peers), _addr(y), C.c_int64(out_capacity_rows),
-                                           _addr(ret_rows), C.c_int64(ret_capacity_rows), _stream_handle()),
-               "mw_combine_gather")
+        _check(_native().mw_combine_gather(self._h, n_peers, y, out_capacity_rows, ret_rows, ret_capacity_rows,
+                                           _stream_handle()), "mw_combine_gather")
 
     def mw_unpack_allgather(self, peer_shards: torch.Tensor, shard_bytes: int, out: torch.Tensor):
-        _check(_native().mw_unpack_allgather(self._h, _addr(peer_shards), C.c_int64(shard_bytes), _addr(out),
-                                             _stream_handle()), "mw_unpack_allgather")
+        _check(_native().mw_unpack_allgather(self._h, peer_shards, shard_bytes, out, _stream_handle()),
+               "mw_unpack_allgather")
 
     def mw_allgather_step(self, shard: torch.Tensor, shard_bytes: int, send_buf: torch.Tensor, desc: torch.Tensor,
                           stats: torch.Tensor, peer_shards: torch.Tensor, out: torch.Tensor):
-        _check(_native().mw_allgather_step(self._h, _addr(shard), C.c_int64(shard_bytes), _addr(send_buf),
-                                           _addr(desc), _addr(stats), _addr(peer_shards), _addr(out),
+        _check(_native().mw_allgather_step(self._h, shard, shard_bytes, send_buf, desc, stats, peer_shards, out,
                                            _stream_handle()), "mw_allgather_step")
 
     # ---- relay ---------------------------------------------------------------------------
@@ -467,46 +423,42 @@ class Context:
 
     def mw_relay(self, in_record: torch.Tensor, children: torch.Tensor, child_capacity_rows: int,
                  stats: torch.Tensor):
-        _check(_native().mw_relay(self._h, _addr(in_record), _addr(children), C.c_int64(child_capacity_rows),
-                                  _addr(stats), _stream_handle()), "mw_relay")
+        _check(_native().mw_relay(self._h, in_record, children, child_capacity_rows, stats, _stream_handle()), "mw_relay")
 
     def mw_relay_index(self, in_record: torch.Tensor, children: torch.Tensor, child_capacity_rows: int,
                        stats: torch.Tensor):
-        _check(_native().mw_relay_index(self._h, _addr(in_record), _addr(children), C.c_int64(child_capacity_rows),
-                                        _addr(stats), _stream_handle()), "mw_relay_index")
+        _check(_native().mw_relay_index(self._h, in_record, children, child_capacity_rows, stats, _stream_handle()),
+               "mw_relay_index")
 
     def mw_relay_copy(self, in_record: torch.Tensor, children: torch.Tensor, stats: torch.Tensor):
-        _check(_native().mw_relay_copy(self._h, _addr(in_record), _addr(children), _addr(stats), _stream_handle()),
-               "mw_relay_copy")
+        _check(_native().mw_relay_copy(self._h, in_record, children, stats, _stream_handle()), "mw_relay_copy")
 
     def mw_relay_copy_index_next(self, in_record: torch.Tensor, children: torch.Tensor, stats: torch.Tensor,
                                  next_ctx: "Context", next_in_record: torch.Tensor, next_children: torch.Tensor,
                                  next_child_capacity_rows: int, next_stats: torch.Tensor):
-        _check(_native().mw_relay_copy_index_next(self._h, _addr(in_record), _addr(children), _addr(stats),
-                                                  next_ctx._h, _addr(next_in_record), _addr(next_children),
-                                                  C.c_int64(next_child_capacity_rows), _addr(next_stats),
-                                                  _stream_handle()), "mw_relay_copy_index_next")
+        _check(_native().mw_relay_copy_index_next(self._h, in_record, children, stats, next_ctx._h, next_in_record,
+                                                  next_children, next_child_capacity_rows, next_stats, _stream_handle()),
+               "mw_relay_copy_index_next")
 
     def mw_relay_packets(self, in_record: torch.Tensor, children: torch.Tensor, child_capacity_rows: int,
                          stats: torch.Tensor):
-        _check(_native().mw_relay_packets(self._h, _addr(in_record), _addr(children), C.c_int64(child_capacity_rows),
-                                          _addr(stats), _stream_handle()), "mw_relay_packets")
+        _check(_native().mw_relay_packets(self._h, in_record, children, child_capacity_rows, stats, _stream_handle()),
+               "mw_relay_packets")
 
     def mw_relay_packets_index(self, in_record: torch.Tensor, child_capacity_rows: int, stats: torch.Tensor):
-        _check(_native().mw_relay_packets_index(self._h, _addr(in_record), C.c_int64(child_capacity_rows),
-                                                _addr(stats), _stream_handle()), "mw_relay_packets_index")
+        _check(_native().mw_relay_packets_index(self._h, in_record, child_capacity_rows, stats, _stream_handle()),
+               "mw_relay_packets_index")
 
     def mw_relay_packets_copy(self, in_record: torch.Tensor, children: torch.Tensor, stats: torch.Tensor):
-        _check(_native().mw_relay_packets_copy(self._h, _addr(in_record), _addr(children), _addr(stats),
-                                               _stream_handle()), "mw_relay_packets_copy")
+        _check(_native().mw_relay_packets_copy(self._h, in_record, children, stats, _stream_handle()),
+               "mw_relay_packets_copy")
 
     def mw_relay_packets_copy_index_next(self, in_record: torch.Tensor, children: torch.Tensor, stats: torch.Tensor,
                                          next_ctx: "Context", next_in_record: torch.Tensor,
                                          next_child_capacity_rows: int, next_stats: torch.Tensor):
-        _check(_native().mw_relay_packets_copy_index_next(self._h, _addr(in_record), _addr(children), _addr(stats),
-                                                          next_ctx._h, _addr(next_in_record),
-                                                          C.c_int64(next_child_capacity_rows), _addr(next_stats),
-                                                          _stream_handle()), "mw_relay_packets_copy_index_next")
+        _check(_native().mw_relay_packets_copy_index_next(self._h, in_record, children, stats, next_ctx._h, next_in_record,
+                                                          next_child_capacity_rows, next_stats, _stream_handle()),
+               "mw_relay_packets_copy_index_next")
 
     def mw_get_relay_stats(self, stats: torch.Tensor) -> np.ndarray:
         host = np.zeros(1, dtype=RELAY_STATS_DTYPE)

@@ -1,14 +1,16 @@
-"""Compile the HIP sources under csrc/ into paper_2605_22428_amd/libmw.so for gfx950."""
+"""Compile the HIP sources under csrc/ into paper_2605_22428_amd/libmw.so for gfx950, and the calls' Python entry beside it."""
 from __future__ import annotations
 
 import glob
 import os
 import subprocess
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmw.so")
+CALLS = os.path.join(HERE, "_mwcall.so")
 
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -20,6 +22,16 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-fvi
 
 def sources():
     return sorted(glob.glob(os.path.join(CSRC, "*.hip")))
+
+
+def build_calls() -> str:
+    """The extension module through which the binding makes the path's calls; needs the library."""
+    tmp = CALLS + ".tmp%d" % os.getpid()
+    subprocess.run([os.environ.get("CC", "gcc"), "-std=gnu11", "-O2", "-Wall", "-shared", "-fPIC", "-I", os.path.join(ROOT, "include"),
+                    "-I", sysconfig.get_paths()["include"], os.path.join(CSRC, "mw_py.c"), "-L", HERE, "-l:" + os.path.basename(LIB),
+                    "-Wl,-rpath,$ORIGIN", "-o", tmp], check=True)
+    os.replace(tmp, CALLS)
+    return CALLS
 
 
 def build(verbose: bool = False) -> str:
@@ -38,6 +50,7 @@ def build(verbose: bool = False) -> str:
     if proc.returncode != 0:
         raise RuntimeError("hipcc failed with status %d" % proc.returncode)
     os.replace(tmp, LIB)
+    build_calls()
     return LIB
 
 

@@ -1,0 +1,53 @@
+"""The calls of the path as the binding makes them (csrc/mw_py.c), without a GPU: what they take, what they refuse, and that the
+library's own answer comes back.  A context of None is refused by every call before anything touches a device."""
+import ctypes as C
+import inspect
+import re
+
+import pytest
+import torch
+
+from paper_2605_22428_amd import binding as B
+
+
+def _calls():
+    return sorted(set(re.findall(r"_native\(\)\.(mw_\w+)", inspect.getsource(B))))
+
+
+def _kinds(name):
+    """The kinds of a call's arguments, from the source that defines it."""
+    source = open(B.os.path.join(B.HERE, "csrc", "mw_py.c")).read()
+    return re.search(r'CALL\(%s, "(\w+)"' % name, source).group(1)
+
+
+@pytest.mark.parametrize("name", _calls())
+def test_arguments_reach_the_library(name):
+    call, kinds = getattr(B._native(), name), _kinds(name)
+    t = torch.zeros(8, dtype=torch.int32)
+    good = [{"h": None, "t": t, "p": 0, "i": 1, "l": 16}[k] for k in kinds]
+    assert call(*good) == B.MW_ERR_INVALID_ARG                       # no context
+    assert call(*[C.c_void_p(0) if k == "h" else a for k, a in zip(kinds, good)]) == B.MW_ERR_INVALID_ARG
+    assert call(*[None if k == "t" else a for k, a in zip(kinds, good)]) == B.MW_ERR_INVALID_ARG
+    with pytest.raises(TypeError):
+        call(*good[:-1])
+    for at, kind in enumerate(kinds):
+        for bad, error in {"h": [(7, AttributeError)], "t": [(7, AttributeError), ("x", AttributeError)], "p": [(None, TypeError), (t, TypeError)],
+                           "i": [(1.5, TypeError), (None, TypeError)], "l": [(1.5, TypeError), ("3", TypeError)]}[kind]:
+            if kind == "p" and bad is t:
+                bad = torch.zeros(2)                                 # (a tensor of one whole number is an index)
+            with pytest.raises(error):
+                call(*(good[:at] + [bad] + good[at + 1:]))
+
+
+def test_every_method_of_a_context_that_is_closed_is_refused():
+    ctx = B.Context.__new__(B.Context)
+    ctx._h = None
+    t = torch.zeros(8, dtype=torch.int32)
+    B_stream, B._stream_handle = B._stream_handle, lambda: 0
+    try:
+        for call, args in ((ctx.mw_plan, (t, t, t, t, t)), (ctx.mw_unpack, (t, 1, t, None, 4, t, t, t, t)), (ctx.mw_relay, (t, t, 4, t))):
+            with pytest.raises(B.MwError) as e:
+                call(*args)
+            assert e.value.status == B.MW_ERR_INVALID_ARG
+    finally:
+        B._stream_handle = B_stream
