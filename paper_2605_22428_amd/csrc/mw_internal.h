@@ -167,6 +167,17 @@ __device__ __forceinline__ void mw_st16(u32x4 *p, u32x4 v)
 {
     asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1 nt" ::"v"(p), "v"(v) : "memory");
 }
+// The store of a row's chunk where rows lie `ns` chunks apart.  Written through, a line of which a wave has only a part goes to memory
+// by itself, and the other part again later; rows that are no whole number of lines have two such in every wave's
+// kilobyte.  They are stored streaming only, and the L2 puts the pieces of one CU together.  us for rows of 7392 bytes, written through /
+// not: relay over 15 hops 44.5 / 42.0, a stream of relays 76.9 / 72.2 for two, of packets of 7520 bytes 47.4 / 43.4; a step of 4096
+// such rows 92.4 / 89.6, mw_plan, mw_pack and mw_unpack 108.9 / 108.0; of 5280 bytes, relay 35.4 / 32.0.  Whole lines: relay of
+// 7424 bytes 38.3 / 38.9.  (`ns` is wave-uniform.)
+__device__ __forceinline__ void mw_st16_row(u32x4 *p, u32x4 v, int ns)
+{
+    if (ns & 7) __builtin_nontemporal_store(v, p);
+    else mw_st16(p, v);
+}
 // The same load through a pointer that was read from memory: saying that it is a global
 // address keeps it off the flat path, whose loads also count as LDS traffic and would make
 // every later wait for a scalar load wait for the payload too.

@@ -52,7 +52,7 @@ __global__ __launch_bounds__(1024) void k_pack_packets(const u32x4 *__restrict__
         u32x4 *pk = packets + (size_t)i * (hc + n);
         if (c < n) {
             const u32x4 v = (c < xc) ? mw_ld16(x + (size_t)t * xc + c) : mw_ld16(scales + (size_t)t * sc + (c - xc));
-            mw_st16(pk + hc + c, v);
+            mw_st16_row(pk + hc + c, v, hc + n);
         }
         if (blockIdx.x == 0) {
             uint32_t *hw = (uint32_t *)pk;

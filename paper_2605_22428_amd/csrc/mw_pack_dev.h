@@ -45,8 +45,8 @@ __device__ __forceinline__ void mw_pack_body(const u32x4 *__restrict__ x, const 
             u32x4 v2;
             if (kFold && c2 < n) v2 = (c2 < xc) ? mw_ld16(x + (size_t)t * xc + c2) : mw_ld16(scales + (size_t)t * sc + (c2 - xc));
             const u32x4 v = (c < xc) ? mw_ld16(x + (size_t)t * xc + c) : mw_ld16(scales + (size_t)t * sc + (c - xc));
-            mw_st16(packed + (size_t)i * ns + c, v);
-            if (kFold && c2 < n) mw_st16(packed + (size_t)i * ns + c2, v2);
+            mw_st16_row(packed + (size_t)i * ns + c, v, ns);
+            if (kFold && c2 < n) mw_st16_row(packed + (size_t)i * ns + c2, v2, ns);
         }
         if (seg == 0) {
             if (threadIdx.x == 0) row_src_token[i] = t;

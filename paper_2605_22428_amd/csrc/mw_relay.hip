@@ -307,7 +307,7 @@ __device__ __forceinline__ void relay_copy_body(
             hops &= hops - 1;
             const uint32_t dst = (uint32_t)__shfl((int)p, h, 64) + off;
             const mw_relay_child ch = children[h];
-            if (c < n_chunks) mw_st16((u32x4 *)ch.rows + (size_t)dst * ns + c, v);
+            if (c < n_chunks) mw_st16_row((u32x4 *)ch.rows + (size_t)dst * ns + c, v, ns);
             if (blockIdx.x == 0) {
                 if (threadIdx.x == 0) ch.row_src_token[dst] = st;
                 if ((int)threadIdx.x < K) ch.row_topk[(size_t)dst * K + threadIdx.x] = tk;
@@ -541,7 +541,7 @@ __device__ __forceinline__ void relay_packets_copy_body(
                 const uint64_t b1 = hop_bits[(size_t)h * MW_MASK_WORDS + 2 * c + 1];
                 o.x &= (uint32_t)b0; o.y &= (uint32_t)(b0 >> 32); o.z &= (uint32_t)b1; o.w &= (uint32_t)(b1 >> 32);
             }
-            if (c < n_chunks) mw_st16((u32x4 *)children[h] + (size_t)dst * n_chunks + c, o);
+            if (c < n_chunks) mw_st16_row((u32x4 *)children[h] + (size_t)dst * n_chunks + c, o, n_chunks);
         }
     }
     if (blockIdx.x == 0 && i_first == 0 && threadIdx.x == 0) {
