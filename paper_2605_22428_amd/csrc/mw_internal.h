@@ -175,7 +175,7 @@ __device__ __forceinline__ void mw_st16(u32x4 *p, u32x4 v)
 // 7424 bytes 38.3 / 38.9.  (`ns` is wave-uniform.)
 __device__ __forceinline__ void mw_st16_row(u32x4 *p, u32x4 v, int ns)
 {
-    if (ns & 7) __builtin_nontemporal_store(v, p);
+    if (ns & 7) __builtin_nontemporal_store(v, (__attribute__((address_space(1))) u32x4 *)p);     // (global also where `p` was read from memory)
     else mw_st16(p, v);
 }
 // The same load through a pointer that was read from memory: saying that it is a global
