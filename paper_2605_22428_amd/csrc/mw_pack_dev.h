@@ -19,7 +19,9 @@ struct mw_pack_args {
 };
 
 // kFold: a row is one workgroup, and its lane c takes chunk c + blockDim.x as well where there is one (mw_row_shape_folded).
-template <bool kFold>
+// kRowStore: mw_st16_row for the row's chunks; it has to repay the choice between two stores.  Folded rows do not (k_pack of 8000 rows
+// of 4224 bytes 15.6 us, written through always 13.8), nor the few rows of a small step (two of 64 tokens of 14336 bytes 15.12 / 15.03).
+template <bool kFold, bool kRowStore = !kFold>
 __device__ __forceinline__ void mw_pack_body(const u32x4 *__restrict__ x, const u32x4 *__restrict__ scales,
                                              int xc, int sc, int ns, const int32_t *__restrict__ topk, int K,
                                              const int32_t *__restrict__ perm,
@@ -37,6 +39,7 @@ __device__ __forceinline__ void mw_pack_body(const u32x4 *__restrict__ x, const 
     MW_PIN_PTR(x); MW_PIN_PTR(scales); MW_PIN_PTR(topk); MW_PIN_PTR(packed); MW_PIN_PTR(row_src_token);
     MW_PIN_PTR(row_topk);
     MW_PIN_S(t); MW_PIN_S(n_rows);
+    static_assert(!kRowStore || !kFold, "folded rows are written through");
     const int n = xc + sc;
     const int c = seg * bdim + threadIdx.x;
     const int c2 = c + (int)bdim;
@@ -45,8 +48,8 @@ __device__ __forceinline__ void mw_pack_body(const u32x4 *__restrict__ x, const 
             u32x4 v2;
             if (kFold && c2 < n) v2 = (c2 < xc) ? mw_ld16(x + (size_t)t * xc + c2) : mw_ld16(scales + (size_t)t * sc + (c2 - xc));
             const u32x4 v = (c < xc) ? mw_ld16(x + (size_t)t * xc + c) : mw_ld16(scales + (size_t)t * sc + (c - xc));
-            mw_st16_row(packed + (size_t)i * ns + c, v, ns);
-            if (kFold && c2 < n) mw_st16_row(packed + (size_t)i * ns + c2, v2, ns);
+            if constexpr (kRowStore) mw_st16_row(packed + (size_t)i * ns + c, v, ns); else mw_st16(packed + (size_t)i * ns + c, v);
+            if (kFold && c2 < n) mw_st16(packed + (size_t)i * ns + c2, v2);
         }
         if (seg == 0) {
             if (threadIdx.x == 0) row_src_token[i] = t;

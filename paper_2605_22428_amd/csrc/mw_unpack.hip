@@ -1272,7 +1272,7 @@ __global__ __launch_bounds__(kSmallLanes) void k_small_step(
         return;
     }
     if (blockIdx.y >= first_pack_row) {
-        mw_pack_body<false>(pack.x, pack.scales, pack.xc, pack.sc, pack.ns, pack.topk, pack.K, pack_perm, pack_stats, pack.packed,
+        mw_pack_body<false, false>(pack.x, pack.scales, pack.xc, pack.sc, pack.ns, pack.topk, pack.K, pack_perm, pack_stats, pack.packed,
                             pack.row_src_token, pack.row_topk, blockIdx.x, blockIdx.y - first_pack_row,
                             first_expand_row - first_pack_row);
         return;
