@@ -1070,13 +1070,15 @@ __global__ __launch_bounds__(1024) void k_expand(
 // with -- the counts acknowledged, a report of every workgroup (256 peers to one address: 8 ns each), the last one's reads of all
 // counts -- is a chain of three round trips in front of this launch.  Here a wave of grid row 0 makes bases, expert offsets
 // and statistics, and the movers do not wait for it: a wave requests the counts in front of the payload (one
-// kilobyte that its CU's cache holds) and adds up what is in front of its place while that is on its way, a dozen vector instructions.  kCounts: counts a lane holds, 1 (at most
-// 64 in all) or 4 (at most 256).  us for mw_plan, mw_pack and mw_unpack, before / after: 1000 fp8 tokens of 16 ranks 30.6 / 28.4, 4096 of 64
+// kilobyte that its CU's cache holds) and adds up what is in front of its place while that is on its way, a dozen vector instructions.
+// kCounts: counts a lane holds, 1 (at most 64 in all), 4 (at most 256) or 8 (at most 512: four of the first 256 and four
+// of the others, so that each request is a kilobyte in one piece).  us for mw_plan, mw_pack and mw_unpack, before / after: 1000 fp8 tokens of 16 ranks 30.6 / 28.4, 4096 of 64
 // ranks 107.3 / 106.5, 8192 bf16 tokens of 256 ranks 154.4 / 151.4; 2048 packets of 16 ranks 68.5 / 67.1.
 // Otherwise this is expand_body.  (The hits behind the first requested with the record and their rows stored without a wait
 // in between: 1000 tokens 28.2, but 8192 of 256 ranks 152.0; in the stream's launch 16000 rows of 1.5 hits 80 -> 82.)
 template <int kCounts> struct mw_counts_of { typedef uint32_t type; };
 template <> struct mw_counts_of<4> { typedef u32x4 type; };
+template <> struct mw_counts_of<8> { struct type { u32x4 lo, hi; }; };
 template <bool kFold, int kCounts>
 __device__ __forceinline__ void expand_counts_body(
     const mw_row_rec *__restrict__ recs, const mw_hit *__restrict__ hits, const uint32_t *__restrict__ cnt,
@@ -1094,19 +1096,27 @@ __device__ __forceinline__ void expand_counts_body(
     MW_PIN_PTR(hits); MW_PIN_PTR(out_rows); MW_PIN_PTR(out_scales); MW_PIN_PTR(out_src_peer);
     MW_PIN_PTR(out_src_token);
     // (a lane without counts reads the last ones again: nobody looks at what it adds up)
-    mw_counts own = ((const mw_counts *)cnt)[min(threadIdx.x & 63u, (n_counts - 1u) / (uint32_t)kCounts)];
+    mw_counts own;
+    if constexpr (kCounts == 8) {                          // (n_counts is more than 256: all lanes' first four are counts)
+        own.lo = ((const u32x4 *)cnt)[threadIdx.x & 63u];
+        own.hi = ((const u32x4 *)cnt)[64u + min(threadIdx.x & 63u, (n_counts - 257u) / 4u)];
+    } else own = ((const mw_counts *)cnt)[min(threadIdx.x & 63u, (n_counts - 1u) / (uint32_t)kCounts)];
     MW_PIN_S4(r0); MW_PIN_S4(r1); MW_PIN_S(m_total);
     gdim -= 1u;
     const int n = xc + sc;
     const int c = blockIdx.x * bdim + threadIdx.x;
     const int c2 = c + (int)bdim;
-    uint32_t in_front = 0;                                 // counts of the lanes before
+    uint32_t in_front = 0, in_front_hi = 0;                // counts of the lanes before
     bool summed = false;
     // first output row of (expert, peer) f
     auto base_of = [&](uint32_t f) __attribute__((always_inline)) -> uint32_t {
         uint32_t v = in_front;
         if constexpr (kCounts == 4) v += ((f & 3u) > 0 ? own.x : 0u) + ((f & 3u) > 1 ? own.y : 0u) + ((f & 3u) > 2 ? own.z : 0u);
-        return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)(f / kCounts));
+        if constexpr (kCounts == 8) {
+            const u32x4 w = f < 256u ? own.lo : own.hi;
+            v = (f < 256u ? in_front : in_front_hi) + ((f & 3u) > 0 ? w.x : 0u) + ((f & 3u) > 1 ? w.y : 0u) + ((f & 3u) > 2 ? w.z : 0u);
+        }
+        return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)(kCounts == 1 ? f : f / 4u & 63u));
     };
     while (g < m_total) {
         const int n_hits = (int)r1.x;
@@ -1117,10 +1127,19 @@ __device__ __forceinline__ void expand_counts_body(
             u32x4 v = mw_ld16_global(src, min(c, n - 1)), v2 = {0u, 0u, 0u, 0u};
             if (kFold) v2 = mw_ld16_global(src, min(c2, n - 1));
             if (!summed) {
-                asm volatile("" : "+v"(own));              // (here, not in front of the payload's request)
                 uint32_t sum;
-                if constexpr (kCounts == 4) sum = own.x + own.y + own.z + own.w; else sum = own;
-                in_front = mw_wave_incl_scan(sum) - sum;
+                if constexpr (kCounts == 8) {
+                    asm volatile("" : "+v"(own.lo), "+v"(own.hi));
+                    sum = own.hi.x + own.hi.y + own.hi.z + own.hi.w;
+                    in_front_hi = mw_wave_incl_scan(sum) - sum;
+                    sum = own.lo.x + own.lo.y + own.lo.z + own.lo.w;
+                } else {
+                    asm volatile("" : "+v"(own));          // (here, not in front of the payload's request)
+                    if constexpr (kCounts == 4) sum = own.x + own.y + own.z + own.w; else sum = own;
+                }
+                const uint32_t upto = mw_wave_incl_scan(sum);
+                in_front = upto - sum;
+                if constexpr (kCounts == 8) in_front_hi += (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
                 summed = true;
             }
             uint32_t dst = base_of(r1.y * (uint32_t)P + (uint32_t)peer) + r1.z;      // below 2^30: 2^24 rows, 64 experts each
@@ -1752,27 +1771,33 @@ int32_t mw_launch_unpack_expand(mw_ctx *ctx, int32_t P, void *out_rows, float *o
     return MW_OK;
 }
 
-// Counts that a wave of the expander adds up for itself: four a lane, one 16-byte request.  More are a second request of a kilobyte
-// in front of every kilobyte of payload; the index's last workgroup adds them up once for all.
-constexpr int64_t kCountsMax = 256;
+// Counts that a wave of the expander adds up for itself: four a lane, one request of a kilobyte, or eight, two.  What the second costs
+// grows with the payload, what the index saves does not: more than 256 counts are left to the expander up to kManyCountsBytes of
+// expected rows.  384 counts, us for mw_plan, mw_pack and mw_unpack, added up by the index's last workgroup / by every wave: rows of
+// 7424 bytes, 55 MB 40.1 / 38.5, 111 MB 64.3 / 63.4, 167 MB 86.8 / 87.1, 222 MB 108.3 / 109.7; of 4224 bytes, 54 MB
+// 46.9 / 44.7, 109 MB 72.9 / 71.6; of 2048 bytes, 123 MB 81.3 / 79.6.  512 counts of 128 ranks 32.5 / 30.0.
+constexpr int64_t kCountsMax = 512, kManyCountsBytes = 128ll << 20;
 
 // Index and expander of one batch in two launches.
 int32_t mw_launch_unpack_two(mw_ctx *ctx, const void *peers, bool packets, int32_t P, void *out_rows, float *out_scales, int64_t cap,
                              int32_t *out_src_peer, int32_t *out_src_token, int64_t *expert_offsets, mw_recv_stats *stats, hipStream_t s)
 {
     const uint32_t n_counts = (uint32_t)ctx->n_local * (uint32_t)P;
-    const bool defer = (int64_t)ctx->n_local * P <= kCountsMax && ctx->cfg.max_recv_rows > 0;
+    const bool defer = ctx->cfg.max_recv_rows > 0 &&
+                       (int64_t)ctx->n_local * P <= (expected_rows(ctx, P) * ctx->row_bytes <= kManyCountsBytes ? kCountsMax : 256);
     bool deferred;
     const int32_t rc = launch_unpack_index(ctx, peers, packets, P, cap, expert_offsets, stats, defer, &deferred, s);
     if (rc != MW_OK) return rc;
     if (!deferred) return mw_launch_unpack_expand(ctx, P, out_rows, out_scales, cap, out_src_peer, out_src_token, s);
     const int xc = (int)(ctx->x_row_bytes / 16), sc = (int)(ctx->s_row_bytes / 16);
     const mw_row_shape shape = mw_row_shape_folded(xc + sc);
-    const bool fold = mw_is_folded(shape, xc + sc), one = n_counts <= 64;
+    const bool fold = mw_is_folded(shape, xc + sc);
     const uint32_t gy = expand_grid_rows(ctx, P) + 1;
     {
         mw_timed tm(ctx, MW_KERNEL_EXPAND, s);
-        hipLaunchKernelGGL((one ? fold ? k_expand_counts<true, 1> : k_expand_counts<false, 1> : fold ? k_expand_counts<true, 4> : k_expand_counts<false, 4>),
+        hipLaunchKernelGGL((n_counts <= 64    ? fold ? k_expand_counts<true, 1> : k_expand_counts<false, 1>
+                            : n_counts <= 256 ? fold ? k_expand_counts<true, 4> : k_expand_counts<false, 4>
+                                              : fold ? k_expand_counts<true, 8> : k_expand_counts<false, 8>),
                            dim3(shape.nseg, gy), dim3(shape.bs), 0, s, ctx->d_recs, ctx->d_row_base, ctx->d_cnt, ctx->d_hits, P,
                            ctx->hit_slots, xc, sc, n_counts, (u32x4 *)out_rows, (u32x4 *)out_scales,
                            (uint32_t)(cap < 0x7fffffffLL ? cap : 0x7fffffffLL), out_src_peer, out_src_token, (uint32_t)ctx->n_local, cap,

@@ -23,7 +23,8 @@ def _filled(gu, ctx, n_peers, cap, want, what):
 
 #                         local experts, ranks, tokens, chunks
 @pytest.mark.parametrize("L,R,T,chunks", [(1, 1, 700, 1), (7, 9, 300, 1), (8, 8, 300, 65), (5, 13, 200, 1), (15, 17, 100, 264),
-                                          (1, 256, 40, 1), (4, 64, 40, 648), (32, 8, 300, 3), (257, 1, 700, 1), (6, 43, 50, 1)])
+                                          (1, 256, 40, 1), (4, 64, 40, 648), (32, 8, 300, 3), (257, 1, 700, 1), (6, 43, 50, 1),
+                                          (48, 8, 300, 65), (2, 250, 40, 264), (8, 64, 40, 648), (513, 1, 700, 1), (27, 19, 60, 1)])
 def test_counts(L, R, T, chunks):
     print("counts", L, R, T, chunks, flush=True)
     rng = np.random.default_rng(L * 1000 + R)
