@@ -128,13 +128,14 @@ _calls = None
 
 
 def _native():
-    """The calls of the path as C functions that take tensors and numbers as they are (csrc/mw_py.c)."""
+    """The calls of the path as C functions that take tensors and numbers as they are (csrc/mw_py.c), bound to load()'s library."""
     global _calls
     if _calls is None:
-        load()
+        lib = load()
         if not os.path.exists(CALLS_PATH):
             raise RuntimeError("HIP library's Python entry %s is not built (run __graft_entry__.build())" % CALLS_PATH)
         from . import _mwcall
+        _mwcall.bind({name: C.cast(lib[name], C.c_void_p).value for name in EXPORTS})
         _calls = _mwcall
     return _calls
 

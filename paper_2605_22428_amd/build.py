@@ -25,11 +25,11 @@ def sources():
 
 
 def build_calls() -> str:
-    """The extension module through which the binding makes the path's calls; needs the library."""
+    """The extension module through which the binding makes the path's calls; the binding gives it the library's addresses."""
     tmp = CALLS + ".tmp%d" % os.getpid()
     subprocess.run([os.environ.get("CC", "gcc"), "-std=gnu11", "-O2", "-Wall", "-shared", "-fPIC", "-I", os.path.join(ROOT, "include"),
-                    "-I", sysconfig.get_paths()["include"], os.path.join(CSRC, "mw_py.c"), "-L", HERE, "-l:" + os.path.basename(LIB),
-                    "-Wl,-rpath,$ORIGIN", "-o", tmp], check=True)
+                    "-I", sysconfig.get_paths()["include"], os.path.join(CSRC, "mw_py.c"), "-o", tmp],
+                   check=True)
     os.replace(tmp, CALLS)
     return CALLS
 

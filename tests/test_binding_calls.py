@@ -2,7 +2,11 @@
 library's own answer comes back.  A context of None is refused by every call before anything touches a device."""
 import ctypes as C
 import inspect
+import os
 import re
+import shutil
+import subprocess
+import sys
 
 import pytest
 import torch
@@ -51,3 +55,22 @@ def test_every_method_of_a_context_that_is_closed_is_refused():
             assert e.value.status == B.MW_ERR_INVALID_ARG
     finally:
         B._stream_handle = B_stream
+
+
+TWO_TREES = """
+import sys
+sys.path[:0] = sys.argv[1:]
+from paper_2605_22428_amd import binding as first
+first._native()
+from other import binding as second
+assert second._native().mw_allgather_step(None, None, 0, None, None, None, None, None, 0) == -77
+assert first._native().mw_allgather_step(None, None, 0, None, None, None, None, None, 0) == first.MW_ERR_INVALID_ARG
+"""
+
+
+def test_calls_reach_the_library_of_their_own_tree(tmp_path):
+    """A second tree in the process, whose library answers everything with -77."""
+    shutil.copytree(B.HERE, tmp_path / "other", ignore=shutil.ignore_patterns("libmw.so*", "csrc", "__pycache__"))
+    (tmp_path / "stub.c").write_text("".join("int %s(void) { return -77; }\n" % name for name in B.EXPORTS))
+    subprocess.run(["gcc", "-shared", "-fPIC", str(tmp_path / "stub.c"), "-o", str(tmp_path / "other" / "libmw.so")], check=True)
+    subprocess.run([sys.executable, "-c", TWO_TREES, os.path.dirname(B.HERE), str(tmp_path)], check=True)
