@@ -3,6 +3,8 @@ from __future__ import annotations
 
 import glob
 import os
+import shlex
+import shutil
 import subprocess
 import sysconfig
 
@@ -24,21 +26,39 @@ def sources():
     return sorted(glob.glob(os.path.join(CSRC, "*.hip")))
 
 
-def build_calls() -> str:
+def _hipcc() -> str:
+    return os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+
+
+def _c_compiler() -> list:
+    """$CC, of any number of words; else the system's compiler; else the one that comes with hipcc."""
+    given = shlex.split(os.environ.get("CC", ""))
+    return given or [shutil.which("gcc") or shutil.which("cc") or os.path.join(os.path.dirname(_hipcc()), "amdclang")]
+
+
+def _compile_calls(out: str) -> None:
     """The extension module through which the binding makes the path's calls; the binding gives it the library's addresses."""
-    tmp = CALLS + ".tmp%d" % os.getpid()
-    subprocess.run([os.environ.get("CC", "gcc"), "-std=gnu11", "-O2", "-Wall", "-shared", "-fPIC", "-I", os.path.join(ROOT, "include"),
-                    "-I", sysconfig.get_paths()["include"], os.path.join(CSRC, "mw_py.c"), "-o", tmp],
-                   check=True)
-    os.replace(tmp, CALLS)
-    return CALLS
+    subprocess.run(_c_compiler() + ["-std=gnu11", "-O2", "-Wall", "-shared", "-fPIC", "-I", os.path.join(ROOT, "include"),
+                                    "-I", sysconfig.get_paths()["include"], os.path.join(CSRC, "mw_py.c"), "-o", out], check=True)
 
 
 def build(verbose: bool = False) -> str:
-    """Always compiles; returns the path of the shared library."""
-    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    tmp = LIB + ".tmp%d" % os.getpid()
-    cmd = [hipcc] + FLAGS + ["-I", os.path.join(ROOT, "include"), "-I", CSRC] + sources() + ["-o", tmp]
+    """Always compiles; returns the path of the shared library.  Both files are replaced once both are compiled."""
+    tmp, tmp_calls = (f + ".tmp%d" % os.getpid() for f in (LIB, CALLS))
+    try:
+        _compile_library(tmp, verbose)
+        _compile_calls(tmp_calls)
+        os.replace(tmp, LIB)
+        os.replace(tmp_calls, CALLS)
+    finally:
+        for f in (tmp, tmp_calls):
+            if os.path.exists(f):
+                os.remove(f)
+    return LIB
+
+
+def _compile_library(out_path: str, verbose: bool) -> None:
+    cmd = [_hipcc()] + FLAGS + ["-I", os.path.join(ROOT, "include"), "-I", CSRC] + sources() + ["-o", out_path]
     if verbose:
         print(" ".join(cmd))
     proc = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
@@ -49,9 +69,6 @@ def build(verbose: bool = False) -> str:
         print(out)
     if proc.returncode != 0:
         raise RuntimeError("hipcc failed with status %d" % proc.returncode)
-    os.replace(tmp, LIB)
-    build_calls()
-    return LIB
 
 
 if __name__ == "__main__":
