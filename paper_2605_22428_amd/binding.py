@@ -7,7 +7,9 @@ else.  There is no CPU fallback: if the library is missing, loading fails.
 from __future__ import annotations
 
 import ctypes as C
+import operator
 import os
+import sysconfig
 from typing import List, Optional, Sequence
 
 import numpy as np
@@ -15,7 +17,7 @@ import torch
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libmw.so")
-CALLS_PATH = os.path.join(HERE, "_mwcall.so")
+CALLS_PATH = os.path.join(HERE, "_mwcall" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 MW_OK = 0
 MW_ERR_INVALID_ARG, MW_ERR_CAPACITY, MW_ERR_UNSUPPORTED, MW_ERR_HIP, MW_ERR_WORKSPACE = -1, -2, -3, -4, -5
@@ -124,19 +126,47 @@ def load():
     return _lib
 
 
+# Arguments of the calls of the path: h context, t tensor or None, p address, i int32, l int64 (csrc/mw_py.c has the same).
+_KINDS = {"mw_plan": "htittttp", "mw_pack": "htttttitttp", "mw_pack_quantize": "httttitttp", "mw_plan_pack": "htttitttttttp",
+          "mw_pack_packets": "httttttitp", "mw_unpack": "htittlttttp", "mw_unpack_packets": "htittlttttp",
+          "mw_unpack_index": "htilttp", "mw_unpack_expand": "hittlttp", "mw_combine_gather": "hitltlp",
+          "mw_stream_step": "hpppp", "mw_plan_allgather": "hlttp", "mw_pack_allgather": "htltp",
+          "mw_unpack_allgather": "htltp", "mw_plan_allgather_split": "hllttp", "mw_unpack_allgather_split": "httlltp",
+          "mw_allgather_step": "htltttttp", "mw_relay": "httltp", "mw_relay_index": "httltp", "mw_relay_copy": "htttp",
+          "mw_relay_copy_index_next": "httthttltp", "mw_relay_packets": "httltp", "mw_relay_packets_index": "htltp",
+          "mw_relay_packets_copy": "htttp", "mw_relay_packets_copy_index_next": "httthtltp"}
 _calls = None
 
 
+class _CtypesCalls:
+    """The same calls through ctypes, for an interpreter that the extension module was not built for: same arguments, same refusals,
+    1 us more a call (mw_plan_pack with no context, refused at once: 2.1 us, through the module 0.9 to 1.0)."""
+
+    _types = {"h": C.c_void_p, "t": C.c_void_p, "p": C.c_void_p, "i": C.c_int32, "l": C.c_int64}
+    _convert = {"h": "a%d and a%d.value", "t": "0 if a%d is None else a%d.data_ptr()", "p": "index(a%d)", "i": "int32(a%d)", "l": "int64(a%d)"}
+
+    def __init__(self, lib):
+        for name, kinds in _KINDS.items():
+            f = lib[name]                     # a function object of its own
+            f.argtypes, f.restype = [self._types[k] for k in kinds], C.c_int32
+            # one expression a call: a loop over its arguments took a microsecond more
+            source = "lambda %s: f(%s)" % (", ".join("a%d" % i for i in range(len(kinds))),
+                                           ", ".join(self._convert[k].replace("%d", str(i)) for i, k in enumerate(kinds)))
+            setattr(self, name, eval(source, {"f": f, "index": operator.index, "int32": C.c_int32, "int64": C.c_int64}))
+
+
 def _native():
-    """The calls of the path as C functions that take tensors and numbers as they are (csrc/mw_py.c), bound to load()'s library."""
+    """The calls of the path as functions that take tensors and numbers as they are, of load()'s library: C functions
+    (csrc/mw_py.c) where the build has made them for this interpreter, which takes Python's headers."""
     global _calls
     if _calls is None:
         lib = load()
-        if not os.path.exists(CALLS_PATH):
-            raise RuntimeError("HIP library's Python entry %s is not built (run __graft_entry__.build())" % CALLS_PATH)
-        from . import _mwcall
-        _mwcall.bind({name: C.cast(lib[name], C.c_void_p).value for name in EXPORTS})
-        _calls = _mwcall
+        if os.path.exists(CALLS_PATH):
+            from . import _mwcall
+            _mwcall.bind({name: C.cast(lib[name], C.c_void_p).value for name in _KINDS})
+            _calls = _mwcall
+        else:
+            _calls = _CtypesCalls(lib)
     return _calls
 
 

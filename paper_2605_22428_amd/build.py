@@ -12,7 +12,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmw.so")
-CALLS = os.path.join(HERE, "_mwcall.so")
+CALLS = os.path.join(HERE, "_mwcall" + sysconfig.get_config_var("EXT_SUFFIX"))      # (other interpreters do not see it)
 
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -36,20 +36,30 @@ def _c_compiler() -> list:
     return given or [shutil.which("gcc") or shutil.which("cc") or os.path.join(os.path.dirname(_hipcc()), "amdclang")]
 
 
-def _compile_calls(out: str) -> None:
-    """The extension module through which the binding makes the path's calls; the binding gives it the library's addresses."""
+def _compile_calls(out: str) -> bool:
+    """The extension module through which the binding makes the path's calls; the binding gives it the library's addresses.  Without
+    Python's headers there is none, and the binding makes them through ctypes."""
+    headers = sysconfig.get_paths()["include"]
+    if not os.path.exists(os.path.join(headers, "Python.h")):
+        print("no Python.h in %s: the calls go through ctypes" % headers)
+        return False
     subprocess.run(_c_compiler() + ["-std=gnu11", "-O2", "-Wall", "-shared", "-fPIC", "-I", os.path.join(ROOT, "include"),
-                                    "-I", sysconfig.get_paths()["include"], os.path.join(CSRC, "mw_py.c"), "-o", out], check=True)
+                                    "-I", headers, os.path.join(CSRC, "mw_py.c"), "-o", out], check=True)
+    return True
 
 
 def build(verbose: bool = False) -> str:
-    """Always compiles; returns the path of the shared library.  Both files are replaced once both are compiled."""
+    """Always compiles; returns the path of the shared library.  Both files are replaced once both are compiled; a module of an
+    earlier build does not outlive a library that has none."""
     tmp, tmp_calls = (f + ".tmp%d" % os.getpid() for f in (LIB, CALLS))
     try:
         _compile_library(tmp, verbose)
-        _compile_calls(tmp_calls)
+        calls = _compile_calls(tmp_calls)
         os.replace(tmp, LIB)
-        os.replace(tmp_calls, CALLS)
+        if calls:
+            os.replace(tmp_calls, CALLS)
+        elif os.path.exists(CALLS):
+            os.remove(CALLS)
     finally:
         for f in (tmp, tmp_calls):
             if os.path.exists(f):

@@ -18,15 +18,17 @@ def _calls():
     return sorted(set(re.findall(r"_native\(\)\.(mw_\w+)", inspect.getsource(B))))
 
 
-def _kinds(name):
-    """The kinds of a call's arguments, from the source that defines it."""
-    source = open(B.os.path.join(B.HERE, "csrc", "mw_py.c")).read()
-    return re.search(r'CALL\(%s, "(\w+)"' % name, source).group(1)
+def test_every_call_has_the_same_arguments_in_both_forms():
+    source = open(os.path.join(B.HERE, "csrc", "mw_py.c")).read()
+    assert dict(re.findall(r'CALL\((mw_\w+), "(\w+)"', source)) == B._KINDS and sorted(B._KINDS) == _calls()
 
 
+@pytest.mark.parametrize("form", ["module", "ctypes"])
 @pytest.mark.parametrize("name", _calls())
-def test_arguments_reach_the_library(name):
-    call, kinds = getattr(B._native(), name), _kinds(name)
+def test_arguments_reach_the_library(name, form):
+    calls = B._native() if form == "module" else B._CtypesCalls(B.load())
+    assert (form == "module") == (getattr(calls, "__name__", "").endswith("_mwcall"))
+    call, kinds = getattr(calls, name), B._KINDS[name]
     t = torch.zeros(8, dtype=torch.int32)
     good = [{"h": None, "t": t, "p": 0, "i": 1, "l": 16}[k] for k in kinds]
     assert call(*good) == B.MW_ERR_INVALID_ARG                       # no context
@@ -55,6 +57,22 @@ def test_every_method_of_a_context_that_is_closed_is_refused():
             assert e.value.status == B.MW_ERR_INVALID_ARG
     finally:
         B._stream_handle = B_stream
+
+
+OTHER_INTERPRETER = """
+import sys, sysconfig, ctypes
+sysconfig.get_config_vars()["EXT_SUFFIX"] = ".cpython-999-x86_64-linux-gnu.so"
+sys.path.insert(0, sys.argv[1])
+from paper_2605_22428_amd import binding as B
+calls = B._native()
+assert isinstance(calls, B._CtypesCalls), calls
+assert calls.mw_plan_allgather(None, 16, None, None, 0) == B.MW_ERR_INVALID_ARG
+"""
+
+
+def test_an_interpreter_without_the_module_calls_through_ctypes():
+    assert os.path.basename(B.CALLS_PATH) != "_mwcall.so"            # (which any interpreter would import)
+    subprocess.run([sys.executable, "-c", OTHER_INTERPRETER, os.path.dirname(B.HERE)], check=True)
 
 
 TWO_TREES = """

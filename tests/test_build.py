@@ -1,5 +1,5 @@
 """What a build leaves behind, without compiling the kernels: the C compiler is given in any number of words, and the library and the
-module of its calls are replaced together or not at all.  No GPU needed."""
+module of its calls are replaced together or not at all; without Python's headers there is no such module.  No GPU needed."""
 import subprocess
 
 import pytest
@@ -39,3 +39,9 @@ def test_a_failure_leaves_both_files_as_they_were(tree, monkeypatch):
     with pytest.raises(subprocess.CalledProcessError):
         build.build()
     assert sorted((f.name, f.read_text()) for f in tree.iterdir()) == [("CALLS", "old"), ("LIB", "old")]
+
+
+def test_without_pythons_headers_there_is_no_module(tree, monkeypatch):
+    monkeypatch.setattr(build.sysconfig, "get_paths", lambda: {"include": str(tree)})
+    build.build()
+    assert sorted(f.name for f in tree.iterdir()) == ["LIB"]
