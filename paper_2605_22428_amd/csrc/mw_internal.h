@@ -71,6 +71,19 @@ static inline mw_row_shape mw_row_shape_folded(int chunks)
 }
 static inline bool mw_is_folded(const mw_row_shape &s, int chunks) { return (int64_t)s.bs * s.nseg < chunks; }
 
+// Whether the expander of mw_unpack and mw_unpack_packets makes its places of the index's counts (k_expand_counts) or the index does.
+// What adding them up costs in every wave grows with the payload, what the index saves does not.  Up to 256 counts are four a
+// lane, one request of a kilobyte, up to 512 eight, two: those are left to the expander up to kManyCountsBytes of expected rows.
+// 384 counts, us for mw_plan, mw_pack and mw_unpack, added up by the index's last workgroup / by every wave: rows of
+// 7424 bytes, 55 MB 40.1 / 38.5, 111 MB 64.3 / 63.4, 167 MB 86.8 / 87.1, 222 MB 108.3 / 109.7; of 4224 bytes, 54 MB
+// 46.9 / 44.7, 109 MB 72.9 / 71.6; of 2048 bytes, 123 MB 81.3 / 79.6.  512 counts of 128 ranks 32.5 / 30.0.
+// A rank without experts has no counts that a lane could request.
+constexpr int64_t kCountsMax = 512, kManyCountsBytes = 128ll << 20;
+static inline bool mw_counts_by_expander(int64_t n_counts, int64_t expected_bytes)
+{
+    return n_counts >= 1 && n_counts <= (expected_bytes <= kManyCountsBytes ? kCountsMax : 256);
+}
+
 // Hash of a plan key (a bitmap of up to 64 ranks, or up to eight ranks a byte each) from its halves; its upper bits name a slot, bits
 // 12 to 16 a bit.  Each half is multiplied before they meet: a rotated upper half xor'ed in folds three of 64 ranks onto 5000 values,
 // so that most of 8192 tokens shared theirs with another key (mw_plan 71.9 us, with this 19.2; four ranks 23.2 / 16.7).

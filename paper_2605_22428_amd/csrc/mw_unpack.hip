@@ -1771,20 +1771,13 @@ int32_t mw_launch_unpack_expand(mw_ctx *ctx, int32_t P, void *out_rows, float *o
     return MW_OK;
 }
 
-// Counts that a wave of the expander adds up for itself: four a lane, one request of a kilobyte, or eight, two.  What the second costs
-// grows with the payload, what the index saves does not: more than 256 counts are left to the expander up to kManyCountsBytes of
-// expected rows.  384 counts, us for mw_plan, mw_pack and mw_unpack, added up by the index's last workgroup / by every wave: rows of
-// 7424 bytes, 55 MB 40.1 / 38.5, 111 MB 64.3 / 63.4, 167 MB 86.8 / 87.1, 222 MB 108.3 / 109.7; of 4224 bytes, 54 MB
-// 46.9 / 44.7, 109 MB 72.9 / 71.6; of 2048 bytes, 123 MB 81.3 / 79.6.  512 counts of 128 ranks 32.5 / 30.0.
-constexpr int64_t kCountsMax = 512, kManyCountsBytes = 128ll << 20;
-
 // Index and expander of one batch in two launches.
 int32_t mw_launch_unpack_two(mw_ctx *ctx, const void *peers, bool packets, int32_t P, void *out_rows, float *out_scales, int64_t cap,
                              int32_t *out_src_peer, int32_t *out_src_token, int64_t *expert_offsets, mw_recv_stats *stats, hipStream_t s)
 {
     const uint32_t n_counts = (uint32_t)ctx->n_local * (uint32_t)P;
     const bool defer = ctx->cfg.max_recv_rows > 0 &&
-                       (int64_t)ctx->n_local * P <= (expected_rows(ctx, P) * ctx->row_bytes <= kManyCountsBytes ? kCountsMax : 256);
+                       mw_counts_by_expander((int64_t)ctx->n_local * P, expected_rows(ctx, P) * ctx->row_bytes);
     bool deferred;
     const int32_t rc = launch_unpack_index(ctx, peers, packets, P, cap, expert_offsets, stats, defer, &deferred, s);
     if (rc != MW_OK) return rc;

@@ -58,6 +58,34 @@ def test_counts(L, R, T, chunks):
     ctx.close()
 
 
+@pytest.mark.parametrize("chunks", [3, 264])
+def test_a_rank_without_experts(chunks):
+    """No counts at all: whole senders' buffers and packets, of which no row is for this rank."""
+    print("no experts", chunks, flush=True)
+    rng = np.random.default_rng(chunks)
+    R, E, T, K, me, hidden = 5, 8, 400, 3, 2, 8 * chunks
+    e2r = np.array([0, 0, 1, 1, 3, 3, 4, 4], dtype=np.int32)
+    ctx = B.Context(R, E, K, me, hidden, B.MW_ROW_BF16, T, R * T, e2r, device=H.DEV)
+    recs, packets = [], []
+    for p in range(R):
+        tk = rng.integers(0, E, size=(T, K)).astype(np.int32)
+        x = rng.integers(0, 1 << 16, size=(T, hidden), dtype=np.uint16)
+        recs.append(H.GpuSend(ctx, tk, x, None).full_record())
+        mask, perm, _, _ = ref.plan(tk, e2r, R, 2 * hidden)
+        packets.append(H.dev(ref.pack_packets(x, None, tk, mask, perm)))
+    table = B.packets_table(packets, [int(t.shape[0]) for t in packets], H.DEV)
+    for _ in range(2):                               # (the second time the context knows how many rows there are)
+        buf = B.RecvBuffers(ctx, 64)
+        for call, tab in ((ctx.mw_unpack, B.peers_table(recs, H.DEV)), (ctx.mw_unpack_packets, table)):
+            buf.out_rows.fill_(0x5a), buf.expert_offsets.fill_(-1), buf.stats.fill_(0xff)
+            call(tab, R, buf.out_rows, None, 64, buf.out_src_peer, buf.out_src_token, buf.expert_offsets, buf.stats)
+            st = ctx.mw_get_recv_stats(buf.stats)
+            assert (int(st["n_recv_rows"]), int(st["n_out_rows"]), int(st["error_flags"])) == (0, 0, 0)
+            assert int(st["n_rows_seen"]) == R * T and buf.expert_offsets.tolist()[:1] == [0]
+            assert bool((buf.out_rows == 0x5a).all())
+    ctx.close()
+
+
 def test_counts_capacity_and_flags():
     """Fewer output rows than arrive, and an id outside the range: what is in front is written, the flags say so, once."""
     rng = np.random.default_rng(5)
