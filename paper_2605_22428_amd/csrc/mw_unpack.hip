@@ -49,6 +49,8 @@ __device__ __forceinline__ void st_agent(uint32_t *p, uint32_t v)
 }
 
 constexpr uint32_t kWaveCounts = 8;       // counts a lane of mw_finish_counts_wave
+// k_expand_counts has the same wave write the bases, unconditionally, and its own lanes hold at most eight counts
+static_assert(kCountsMax <= 64 * kWaveCounts && kCountsMax <= 64 * 8, "more counts than the expander can add up");
 
 // One workgroup: exclusive scan of the (expert, peer) counts in output order, expert
 // offsets, totals and flags.  `scratch` is LDS scan scratch of 17 words.  Every device-scope
