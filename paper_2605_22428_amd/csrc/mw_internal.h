@@ -72,16 +72,31 @@ static inline mw_row_shape mw_row_shape_folded(int chunks)
 static inline bool mw_is_folded(const mw_row_shape &s, int chunks) { return (int64_t)s.bs * s.nseg < chunks; }
 
 // Whether the expander of mw_unpack and mw_unpack_packets makes its places of the index's counts (k_expand_counts) or the index does.
-// What adding them up costs in every wave grows with the payload, what the index saves does not.  Up to 256 counts are four a
-// lane, one request of a kilobyte, up to 512 eight, two: those are left to the expander up to kManyCountsBytes of expected rows.
-// 384 counts, us for mw_plan, mw_pack and mw_unpack, added up by the index's last workgroup / by every wave: rows of
-// 7424 bytes, 55 MB 40.1 / 38.5, 111 MB 64.3 / 63.4, 167 MB 86.8 / 87.1, 222 MB 108.3 / 109.7; of 4224 bytes, 54 MB
-// 46.9 / 44.7, 109 MB 72.9 / 71.6; of 2048 bytes, 123 MB 81.3 / 79.6.  512 counts of 128 ranks 32.5 / 30.0.
+// What adding them up costs in every wave grows with the payload, what the index saves does not (it grows with the peers: a report
+// each), so there is a most of expected bytes.  Up to 256 counts are one a lane or four, one request of at most a kilobyte; up to 512
+// eight, two requests.  A wave of a folded row has two payload chunks a lane that wait for the counts.  us for mw_plan, mw_pack and
+// mw_unpack, added up by the index's last workgroup / by every wave:
+//   384 counts, rows of 7424 bytes, 55 MB 40.1 / 38.5, 111 MB 64.3 / 63.4, 167 MB 86.8 / 87.1, 222 MB 108.3 / 109.7; of 4224 bytes (folded),
+//     54 MB 46.9 / 44.7, 109 MB 72.9 / 71.6; of 2048 bytes, 123 MB 81.3 / 79.6.  512 counts of 128 ranks 32.5 / 30.0.
+//   Folded rows of 4224 bytes, 256 ranks, 169 MB 86.7 / 84.0, 237 MB 111.3 / 110.0, 277 MB 125.0 / 125.2, 473 MB 227.4 / 231.1; 128 ranks, 203 MB
+//     97.4 / 96.4, 250 MB 115.6 / 115.7, 277 MB 125.5 / 126.7; 64 ranks, 169 MB 84.8 / 83.8, 203 MB 97.0 / 96.9, 237 MB 111.2 / 111.6, 277 MB
+//     126.6 / 127.5.  Of 8448 bytes, 256 ranks, 237 MB 107.7 / 105.6, 338 MB 144.2 / 144.8, 541 MB 215.2 / 225.4; 64 ranks, 203 MB 93.9 / 94.3.
+//     Packets of 4352 bytes, 256 ranks, 203 MB 100.2 / 100.0, 237 MB 113.9 / 114.3, 250 MB 117.3 / 118.9; 64 ranks, 132 MB 74.4 / 73.9, 169 MB
+//     86.4 / 86.5, 203 MB 99.5 / 100.2; 128 ranks, 169 MB 87.6 / 86.8, 203 MB 99.4 / 99.5.
+//   The same of a rank with many experts, 1.2 hits a row and more, whose waves wait for their stores: 16 experts of 16 ranks, 226 MB 135.7 /
+//     134.2, 441 MB 286.9 / 284.7; 20 of 12, 360 MB 249.5 / 248.1; 32 of 8, 313 MB 249.0 / 247.2; of 8448 bytes, 220 MB 119.8 / 120.0.
+//   Other rows, 256 counts, 8192 bytes, 513 MB 228.5 / 227.8, 1002 MB 474.2 / 477.0; 14336 bytes, 705 MB 266.5 / 263.2, 897 MB 371.7 /
+//     372.2; 128 counts, 8192 bytes, 522 MB 221.4 / 220.8, 764 MB 352.1 / 353.0, 1019 MB 472.5 / 474.9.
 // A rank without experts has no counts that a lane could request.
-constexpr int64_t kCountsMax = 512, kManyCountsBytes = 128ll << 20;
-static inline bool mw_counts_by_expander(int64_t n_counts, int64_t expected_bytes)
+constexpr int64_t kCountsMax = 512;
+static inline bool mw_counts_by_expander(int64_t n_local, int64_t n_peers, bool packets, bool folded, double hits_a_row, int64_t expected_bytes)
 {
-    return n_counts >= 1 && n_counts <= (expected_bytes <= kManyCountsBytes ? kCountsMax : 256);
+    const int64_t n_counts = n_local * n_peers;
+    const int64_t most_mib = n_counts > 256      ? 128
+                             : !folded           ? 720
+                             : hits_a_row >= 1.2 ? 448
+                                                 : 160 + n_peers / 2 - (packets ? 56 : 0);
+    return n_counts >= 1 && n_counts <= kCountsMax && expected_bytes <= most_mib << 20;
 }
 
 // Hash of a plan key (a bitmap of up to 64 ranks, or up to eight ranks a byte each) from its halves; its upper bits name a slot, bits

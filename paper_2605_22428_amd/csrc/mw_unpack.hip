@@ -1778,15 +1778,17 @@ int32_t mw_launch_unpack_two(mw_ctx *ctx, const void *peers, bool packets, int32
                              int32_t *out_src_peer, int32_t *out_src_token, int64_t *expert_offsets, mw_recv_stats *stats, hipStream_t s)
 {
     const uint32_t n_counts = (uint32_t)ctx->n_local * (uint32_t)P;
+    const int xc = (int)(ctx->x_row_bytes / 16), sc = (int)(ctx->s_row_bytes / 16);
+    const mw_row_shape shape = mw_row_shape_folded(xc + sc);
+    const bool fold = mw_is_folded(shape, xc + sc);
+    double hits;
+    addressed_share(ctx, &hits);
     const bool defer = ctx->cfg.max_recv_rows > 0 &&
-                       mw_counts_by_expander((int64_t)ctx->n_local * P, expected_rows(ctx, P) * ctx->row_bytes);
+                       mw_counts_by_expander(ctx->n_local, P, packets, fold, hits, expected_rows(ctx, P) * ctx->row_bytes);
     bool deferred;
     const int32_t rc = launch_unpack_index(ctx, peers, packets, P, cap, expert_offsets, stats, defer, &deferred, s);
     if (rc != MW_OK) return rc;
     if (!deferred) return mw_launch_unpack_expand(ctx, P, out_rows, out_scales, cap, out_src_peer, out_src_token, s);
-    const int xc = (int)(ctx->x_row_bytes / 16), sc = (int)(ctx->s_row_bytes / 16);
-    const mw_row_shape shape = mw_row_shape_folded(xc + sc);
-    const bool fold = mw_is_folded(shape, xc + sc);
     const uint32_t gy = expand_grid_rows(ctx, P) + 1;
     {
         mw_timed tm(ctx, MW_KERNEL_EXPAND, s);
