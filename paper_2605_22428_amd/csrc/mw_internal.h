@@ -71,6 +71,9 @@ static inline mw_row_shape mw_row_shape_folded(int chunks)
 }
 static inline bool mw_is_folded(const mw_row_shape &s, int chunks) { return (int64_t)s.bs * s.nseg < chunks; }
 
+// Rows that are no whole number of cache lines apart are stored streaming only (mw_st16_part), others written through (mw_st16), by launch.
+static inline bool mw_rows_part(int64_t stride_bytes) { return stride_bytes % 128 != 0; }
+
 // Whether the expander of mw_unpack and mw_unpack_packets makes its places of the index's counts (k_expand_counts) or the index does.
 // What adding them up costs in every wave grows with the payload, what the index saves does not (it grows with the peers: a report
 // each), so there is a most of expected bytes.  Up to 256 counts are one a lane or four, one request of at most a kilobyte; up to 512
@@ -195,15 +198,20 @@ __device__ __forceinline__ void mw_st16(u32x4 *p, u32x4 v)
 {
     asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1 nt" ::"v"(p), "v"(v) : "memory");
 }
-// The store of a row's chunk where rows lie `ns` chunks apart.  Written through, a line of which a wave has only a part goes to memory
-// by itself, and the other part again later; rows that are no whole number of lines have two such in every wave's
-// kilobyte.  They are stored streaming only, and the L2 puts the pieces of one CU together.  us for rows of 7392 bytes, written through /
+// The store of a row's chunk where rows are no whole number of cache lines apart.  Written through, a line of which a wave has only a
+// part goes to memory by itself, and the other part again later; such rows have two of them in every wave's kilobyte.  They
+// are stored streaming only, and the L2 puts the pieces of one CU together.  us for rows of 7392 bytes, written through /
 // not: relay over 15 hops 44.5 / 42.0, a stream of relays 76.9 / 72.2 for two, of packets of 7520 bytes 47.4 / 43.4; a step of 4096
 // such rows 92.4 / 89.6, mw_plan, mw_pack and mw_unpack 108.9 / 108.0; of 5280 bytes, relay 35.4 / 32.0.  Whole lines: relay of
-// 7424 bytes 38.3 / 38.9.  (`ns` is wave-uniform.)
-__device__ __forceinline__ void mw_st16_row(u32x4 *p, u32x4 v, int ns)
+// 7424 bytes 38.3 / 38.9.
+__device__ __forceinline__ void mw_st16_part(u32x4 *p, u32x4 v)
 {
-    if (ns & 7) __builtin_nontemporal_store(v, (__attribute__((address_space(1))) u32x4 *)p);     // (global also where `p` was read from memory)
+    __builtin_nontemporal_store(v, (__attribute__((address_space(1))) u32x4 *)p);     // (global also where `p` was read from memory)
+}
+template <bool kPart>
+__device__ __forceinline__ void mw_st16_as(u32x4 *p, u32x4 v)
+{
+    if constexpr (kPart) mw_st16_part(p, v);
     else mw_st16(p, v);
 }
 // The same load through a pointer that was read from memory: saying that it is a global

@@ -17,14 +17,14 @@
 namespace {
 
 // blockIdx.x = segment of blockDim.x chunks, blockIdx.y walks packed rows.
-template <bool kFold>
+template <bool kFold, bool kPart>
 __global__ __launch_bounds__(1024) void k_pack(const int32_t *__restrict__ perm, const mw_send_stats *__restrict__ stats,
                                                const u32x4 *__restrict__ x, const u32x4 *__restrict__ scales,
                                                int xc, int sc, int ns, int K,      // (in registers when a wave starts)
                                                const int32_t *__restrict__ topk, u32x4 *__restrict__ packed,
                                                int32_t *__restrict__ row_src_token, int32_t *__restrict__ row_topk)
 {
-    mw_pack_body<kFold>(x, scales, xc, sc, ns, topk, K, perm, stats, packed, row_src_token, row_topk, blockIdx.x, blockIdx.y,
+    mw_pack_body<kFold, kPart>(x, scales, xc, sc, ns, topk, K, perm, stats, packed, row_src_token, row_topk, blockIdx.x, blockIdx.y,
                         gridDim.y);
 }
 
@@ -32,6 +32,7 @@ __global__ __launch_bounds__(1024) void k_pack(const int32_t *__restrict__ perm,
 // header | row of token perm[i], `hc` header chunks then the row's chunks.  Same launch shape
 // as k_pack; the workgroup of the row's first segment also writes the header, one 32-bit word
 // per lane: words 0..7 the bitmap, 8 the token index, 9 the id count, then the ids, then zeros.
+template <bool kPart>
 __global__ __launch_bounds__(1024) void k_pack_packets(const u32x4 *__restrict__ x, const u32x4 *__restrict__ scales,
                                                        int xc, int sc, int hc, const int32_t *__restrict__ topk, int K,
                                                        const uint64_t *__restrict__ mask,
@@ -52,7 +53,7 @@ __global__ __launch_bounds__(1024) void k_pack_packets(const u32x4 *__restrict__
         u32x4 *pk = packets + (size_t)i * (hc + n);
         if (c < n) {
             const u32x4 v = (c < xc) ? mw_ld16(x + (size_t)t * xc + c) : mw_ld16(scales + (size_t)t * sc + (c - xc));
-            mw_st16_row(pk + hc + c, v, hc + n);
+            mw_st16_as<kPart>(pk + hc + c, v);
         }
         if (blockIdx.x == 0) {
             uint32_t *hw = (uint32_t *)pk;
@@ -248,7 +249,8 @@ int32_t mw_launch_pack(mw_ctx *ctx, const void *x, const float *scales, const in
     const uint32_t gy = (uint32_t)T < kRowGridMax ? (uint32_t)T : kRowGridMax;
     {
         mw_timed tm(ctx, MW_KERNEL_PACK, s);
-        hipLaunchKernelGGL(mw_is_folded(shape, xc + sc) ? k_pack<true> : k_pack<false>, dim3(shape.nseg, gy), dim3(shape.bs), 0, s,
+        hipLaunchKernelGGL((mw_is_folded(shape, xc + sc) ? k_pack<true, false> : mw_rows_part(ctx->row_stride) ? k_pack<false, true> : k_pack<false, false>),
+                           dim3(shape.nseg, gy), dim3(shape.bs), 0, s,
                            perm, stats, (const u32x4 *)x, (const u32x4 *)scales, xc, sc, (int)(ctx->row_stride / 16), ctx->cfg.top_k, topk,
                            (u32x4 *)packed, row_src_token, row_topk);
     }
@@ -267,7 +269,7 @@ int32_t mw_launch_pack_packets(mw_ctx *ctx, const void *x, const float *scales, 
     const uint32_t gy = (uint32_t)T < kRowGridMax ? (uint32_t)T : kRowGridMax;
     {
         mw_timed tm(ctx, MW_KERNEL_PACK, s);
-        hipLaunchKernelGGL(k_pack_packets, dim3(shape.nseg, gy), dim3(shape.bs), 0, s, (const u32x4 *)x,
+        hipLaunchKernelGGL(mw_rows_part(16 * (int64_t)(hc + xc + sc)) ? k_pack_packets<true> : k_pack_packets<false>, dim3(shape.nseg, gy), dim3(shape.bs), 0, s, (const u32x4 *)x,
                            (const u32x4 *)scales, xc, sc, hc, topk, ctx->cfg.top_k, mask, perm, stats, (u32x4 *)packets);
     }
     MW_HIP_CHECK(hipGetLastError());

@@ -19,9 +19,10 @@ struct mw_pack_args {
 };
 
 // kFold: a row is one workgroup, and its lane c takes chunk c + blockDim.x as well where there is one (mw_row_shape_folded).
-// kRowStore: mw_st16_row for the row's chunks; it has to repay the choice between two stores.  Folded rows do not (k_pack of 8000 rows
-// of 4224 bytes 15.6 us, written through always 13.8), nor the few rows of a small step (two of 64 tokens of 14336 bytes 15.12 / 15.03).
-template <bool kFold, bool kRowStore = !kFold>
+// kPart: the rows' chunks by mw_st16_part.  The launch chooses (mw_rows_part): a choice for every chunk cost rows of whole
+// lines more than the store, us without / with: two steps of 8192 tokens of 10240 bytes 205.2 / 207.7, of 1024 bytes 79.2 / 80.4; k_pack
+// of 4096 rows of 14336 bytes 21.0 / 21.2, k_pack_packets 21.5 / 21.9.  Folded rows are written through, and the few of a small step.
+template <bool kFold, bool kPart>
 __device__ __forceinline__ void mw_pack_body(const u32x4 *__restrict__ x, const u32x4 *__restrict__ scales,
                                              int xc, int sc, int ns, const int32_t *__restrict__ topk, int K,
                                              const int32_t *__restrict__ perm,
@@ -39,7 +40,7 @@ __device__ __forceinline__ void mw_pack_body(const u32x4 *__restrict__ x, const 
     MW_PIN_PTR(x); MW_PIN_PTR(scales); MW_PIN_PTR(topk); MW_PIN_PTR(packed); MW_PIN_PTR(row_src_token);
     MW_PIN_PTR(row_topk);
     MW_PIN_S(t); MW_PIN_S(n_rows);
-    static_assert(!kRowStore || !kFold, "folded rows are written through");
+    static_assert(!kPart || !kFold, "folded rows are written through");
     const int n = xc + sc;
     const int c = seg * bdim + threadIdx.x;
     const int c2 = c + (int)bdim;
@@ -48,7 +49,7 @@ __device__ __forceinline__ void mw_pack_body(const u32x4 *__restrict__ x, const 
             u32x4 v2;
             if (kFold && c2 < n) v2 = (c2 < xc) ? mw_ld16(x + (size_t)t * xc + c2) : mw_ld16(scales + (size_t)t * sc + (c2 - xc));
             const u32x4 v = (c < xc) ? mw_ld16(x + (size_t)t * xc + c) : mw_ld16(scales + (size_t)t * sc + (c - xc));
-            if constexpr (kRowStore) mw_st16_row(packed + (size_t)i * ns + c, v, ns); else mw_st16(packed + (size_t)i * ns + c, v);
+            mw_st16_as<kPart>(packed + (size_t)i * ns + c, v);
             if (kFold && c2 < n) mw_st16(packed + (size_t)i * ns + c2, v2);
         }
         if (seg == 0) {

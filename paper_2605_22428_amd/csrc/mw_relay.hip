@@ -277,7 +277,9 @@ __global__ __launch_bounds__(kBlock) void k_relay_index(const mw_relay_index_arg
     relay_index_body(a, blockIdx.x);
 }
 
-// blockIdx.x selects a segment of blockDim.x chunks of a row; rows i_first, i_first + i_stride, ...
+// blockIdx.x selects a segment of blockDim.x chunks of a row; rows i_first, i_first + i_stride, ...  kPart: the rows by mw_st16_part
+// (mw_rows_part).
+template <bool kPart>
 __device__ __forceinline__ void relay_copy_body(
     const mw_recv_peer *__restrict__ in, const mw_relay_child *__restrict__ children, int n_hops, int K, int n_chunks,
     int ns, uint32_t max_tokens, uint64_t row_bytes, const int32_t *__restrict__ group_of_row,
@@ -307,7 +309,7 @@ __device__ __forceinline__ void relay_copy_body(
             hops &= hops - 1;
             const uint32_t dst = (uint32_t)__shfl((int)p, h, 64) + off;
             const mw_relay_child ch = children[h];
-            if (c < n_chunks) mw_st16_row((u32x4 *)ch.rows + (size_t)dst * ns + c, v, ns);
+            if (c < n_chunks) mw_st16_as<kPart>((u32x4 *)ch.rows + (size_t)dst * ns + c, v);
             if (blockIdx.x == 0) {
                 if (threadIdx.x == 0) ch.row_src_token[dst] = st;
                 if ((int)threadIdx.x < K) ch.row_topk[(size_t)dst * K + threadIdx.x] = tk;
@@ -323,12 +325,13 @@ __device__ __forceinline__ void relay_copy_body(
     }
 }
 
+template <bool kPart>
 __global__ __launch_bounds__(1024) void k_relay_copy(
     const mw_recv_peer *__restrict__ in, const mw_relay_child *__restrict__ children, int n_hops, int K, int n_chunks,
     int ns, uint32_t max_tokens, uint64_t row_bytes, const int32_t *__restrict__ group_of_row,
     const uint32_t *__restrict__ child_pos, uint32_t *relay_flags, mw_relay_stats *__restrict__ stats)
 {
-    relay_copy_body(in, children, n_hops, K, n_chunks, ns, max_tokens, row_bytes, group_of_row, child_pos, relay_flags,
+    relay_copy_body<kPart>(in, children, n_hops, K, n_chunks, ns, max_tokens, row_bytes, group_of_row, child_pos, relay_flags,
                     stats, blockIdx.y, gridDim.y);
 }
 
@@ -338,6 +341,7 @@ __global__ __launch_bounds__(1024) void k_relay_copy(
 // workspace.  The index is a chain of memory round trips that moves almost nothing; as a launch
 // of its own it costs about 15 us in front of every copy.  Held to 64 registers so that the copy
 // keeps every wave slot.
+template <bool kPart>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_relay_copy_index_next(
     const uint32_t first_copy_row, const uint32_t unused0,     // (the copy's arguments first: in registers when a wave starts)
     const mw_recv_peer *__restrict__ in, const mw_relay_child *__restrict__ children, int n_hops, int K, int n_chunks,
@@ -346,7 +350,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
     const mw_relay_index_args next)
 {
     if (blockIdx.y >= first_copy_row) {          // the copy's branch first: nothing to fetch in front of it
-        relay_copy_body(in, children, n_hops, K, n_chunks, ns, max_tokens, row_bytes, group_of_row, child_pos,
+        relay_copy_body<kPart>(in, children, n_hops, K, n_chunks, ns, max_tokens, row_bytes, group_of_row, child_pos,
                         relay_flags, stats, blockIdx.y - first_copy_row, gridDim.y - first_copy_row);
         return;
     }
@@ -367,6 +371,7 @@ struct mw_relay_batch_args {
     uint32_t index_first_row[MW_RELAY_BATCH_MAX + 1];      // grid rows [first[k], first[k + 1]) index buffer k
 };
 
+template <bool kPart>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_relay_batch(
     const uint32_t first_copy_row, const uint32_t rows_per_copy, int K, int n_chunks, int ns, uint32_t max_tokens,
     uint64_t row_bytes, const mw_relay_batch_args b)
@@ -374,7 +379,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
     if (blockIdx.y >= first_copy_row) {
         const uint32_t y = blockIdx.y - first_copy_row, j = y / rows_per_copy;
         const mw_relay_copy_args &c = b.copy[j];
-        relay_copy_body(c.in, c.children, c.n_hops, K, n_chunks, ns, max_tokens, row_bytes, c.group_of_row, c.child_pos,
+        relay_copy_body<kPart>(c.in, c.children, c.n_hops, K, n_chunks, ns, max_tokens, row_bytes, c.group_of_row, c.child_pos,
                         c.relay_flags, c.stats, y - j * rows_per_copy, rows_per_copy);
         return;
     }
@@ -516,6 +521,7 @@ __global__ __launch_bounds__(kBlock) void k_relay_packets_index(const mw_relay_p
 }
 
 // blockIdx.x selects a segment of blockDim.x chunks of a packet; packets i_first, i_first + i_stride, ...
+template <bool kPart>
 __device__ __forceinline__ void relay_packets_copy_body(
     const mw_recv_packets *__restrict__ in, void *const *__restrict__ children, int n_hops, int n_chunks,
     uint32_t max_tokens, uint64_t packet_bytes, const uint64_t *__restrict__ hop_bits,
@@ -541,7 +547,7 @@ __device__ __forceinline__ void relay_packets_copy_body(
                 const uint64_t b1 = hop_bits[(size_t)h * MW_MASK_WORDS + 2 * c + 1];
                 o.x &= (uint32_t)b0; o.y &= (uint32_t)(b0 >> 32); o.z &= (uint32_t)b1; o.w &= (uint32_t)(b1 >> 32);
             }
-            if (c < n_chunks) mw_st16_row((u32x4 *)children[h] + (size_t)dst * n_chunks + c, o, n_chunks);
+            if (c < n_chunks) mw_st16_as<kPart>((u32x4 *)children[h] + (size_t)dst * n_chunks + c, o);
         }
     }
     if (blockIdx.x == 0 && i_first == 0 && threadIdx.x == 0) {
@@ -553,13 +559,14 @@ __device__ __forceinline__ void relay_packets_copy_body(
     }
 }
 
+template <bool kPart>
 __global__ __launch_bounds__(1024) void k_relay_packets_copy(
     const mw_recv_packets *__restrict__ in, void *const *__restrict__ children, int n_hops, int n_chunks,
     uint32_t max_tokens, uint64_t packet_bytes, const uint64_t *__restrict__ hop_bits,
     const uint32_t *__restrict__ child_pos, uint32_t *relay_flags, mw_relay_stats *__restrict__ stats,
     const uint32_t keep_metadata)
 {
-    relay_packets_copy_body(in, children, n_hops, n_chunks, max_tokens, packet_bytes, hop_bits, child_pos, relay_flags,
+    relay_packets_copy_body<kPart>(in, children, n_hops, n_chunks, max_tokens, packet_bytes, hop_bits, child_pos, relay_flags,
                             stats, keep_metadata, blockIdx.y, gridDim.y);
 }
 
@@ -568,6 +575,7 @@ __global__ __launch_bounds__(1024) void k_relay_packets_copy(
 // registers as well: with the 69 the index's branch would take, the copy's step is 6 % longer
 // (56.9 -> 60.4 us; forcing the count up with nothing else changed shows the same), the four
 // values over the limit live in lanes of a vector register instead.
+template <bool kPart>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8), amdgpu_num_sgpr(64))) void k_relay_packets_copy_index_next(
     const uint32_t first_copy_row, const uint32_t unused0,
     const mw_recv_packets *__restrict__ in, void *const *__restrict__ children, int n_hops, int n_chunks,
@@ -576,7 +584,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8), amd
     const uint32_t keep_metadata, const mw_relay_packets_index_args next)
 {
     if (blockIdx.y >= first_copy_row) {
-        relay_packets_copy_body(in, children, n_hops, n_chunks, max_tokens, packet_bytes, hop_bits, child_pos,
+        relay_packets_copy_body<kPart>(in, children, n_hops, n_chunks, max_tokens, packet_bytes, hop_bits, child_pos,
                                 relay_flags, stats, keep_metadata, blockIdx.y - first_copy_row,
                                 gridDim.y - first_copy_row);
         return;
@@ -684,18 +692,19 @@ int32_t mw_launch_relay_copy(mw_ctx *ctx, const mw_recv_peer *in, const mw_relay
     }
     uint32_t gy = (uint32_t)c.max_tokens < kRowGridMax ? (uint32_t)c.max_tokens : kRowGridMax;
     if (gy < 1) gy = 1;
+    const bool part = mw_rows_part(ctx->row_stride);
     {
         mw_timed tm(ctx, MW_KERNEL_RELAY_COPY, s);
         if (!next) {
-            hipLaunchKernelGGL(k_relay_copy, dim3(shape.nseg, gy), dim3(shape.bs), 0, s, in, children, ctx->n_hops,
+            hipLaunchKernelGGL(part ? k_relay_copy<true> : k_relay_copy<false>, dim3(shape.nseg, gy), dim3(shape.bs), 0, s, in, children, ctx->n_hops,
                                c.top_k, n_chunks, (int)(ctx->row_stride / 16), (uint32_t)c.max_tokens,
                                (uint64_t)ctx->row_bytes, ctx->d_group_of_row, ctx->d_child_pos, ctx->d_relay_flags, stats);
         } else {
             mw_relay_index_args a = relay_index_args(next, next_in, next_children, next_cap, next_stats, shape.bs);
             a.chunks = relay_riding_chunks(next, shape.bs, relay_copy_us(ctx, ctx->row_bytes));
             const uint32_t riders = relay_index_rows(next, a.chunks, shape.nseg);
-            hipLaunchKernelGGL(k_relay_copy_index_next, dim3(shape.nseg, gy + riders), dim3(shape.bs), 0, s, riders, 0u, in, children, ctx->n_hops, c.top_k, n_chunks,
-                               (int)(ctx->row_stride / 16), (uint32_t)c.max_tokens, (uint64_t)ctx->row_bytes,
+            hipLaunchKernelGGL(part ? k_relay_copy_index_next<true> : k_relay_copy_index_next<false>, dim3(shape.nseg, gy + riders), dim3(shape.bs), 0, s,
+                               riders, 0u, in, children, ctx->n_hops, c.top_k, n_chunks, (int)(ctx->row_stride / 16), (uint32_t)c.max_tokens, (uint64_t)ctx->row_bytes,
                                ctx->d_group_of_row, ctx->d_child_pos, ctx->d_relay_flags, stats, a);
         }
     }
@@ -731,9 +740,10 @@ int32_t mw_launch_relay_batch(const mw_relay_job *copy, int32_t n_copy, const mw
         }
     }
     b.index_first_row[MW_RELAY_BATCH_MAX] = first;
+    const bool part = mw_rows_part(ctx->row_stride);
     {
         mw_timed tm(ctx, MW_KERNEL_RELAY_COPY, s);
-        hipLaunchKernelGGL(k_relay_batch, dim3(shape.nseg, first + gy * (uint32_t)n_copy), dim3(shape.bs), 0, s, first, gy,
+        hipLaunchKernelGGL(part ? k_relay_batch<true> : k_relay_batch<false>, dim3(shape.nseg, first + gy * (uint32_t)n_copy), dim3(shape.bs), 0, s, first, gy,
                            c.top_k, n_chunks, (int)(ctx->row_stride / 16), (uint32_t)c.max_tokens,
                            (uint64_t)ctx->row_bytes, b);
     }
@@ -800,10 +810,11 @@ int32_t mw_launch_relay_packets_copy(mw_ctx *ctx, const mw_recv_packets *in, voi
     }
     uint32_t gy = (uint32_t)c.max_tokens < kRowGridMax ? (uint32_t)c.max_tokens : kRowGridMax;
     if (gy < 1) gy = 1;
+    const bool part = mw_rows_part((int64_t)pb);
     {
         mw_timed tm(ctx, MW_KERNEL_RELAY_COPY, s);
         if (!next) {
-            hipLaunchKernelGGL(k_relay_packets_copy, dim3(shape.nseg, gy), dim3(shape.bs), 0, s, in, children, ctx->n_hops,
+            hipLaunchKernelGGL(part ? k_relay_packets_copy<true> : k_relay_packets_copy<false>, dim3(shape.nseg, gy), dim3(shape.bs), 0, s, in, children, ctx->n_hops,
                                n_chunks, (uint32_t)c.max_tokens, pb, ctx->d_hop_bits, ctx->d_child_pos,
                                ctx->d_relay_flags, stats, keep);
         } else {
@@ -816,7 +827,8 @@ int32_t mw_launch_relay_packets_copy(mw_ctx *ctx, const mw_recv_packets *in, voi
             for (uint32_t n = 1; n < a.chunks; ++n)
                 if (relay_rider_us(next, shape.bs, n) < copy_us + 10.0) a.chunks = n;
             const uint32_t riders = relay_index_rows(next, a.chunks, shape.nseg);
-            hipLaunchKernelGGL(k_relay_packets_copy_index_next, dim3(shape.nseg, gy + riders), dim3(shape.bs), 0, s, riders, 0u, in, children, ctx->n_hops, n_chunks, (uint32_t)c.max_tokens, pb,
+            hipLaunchKernelGGL(part ? k_relay_packets_copy_index_next<true> : k_relay_packets_copy_index_next<false>, dim3(shape.nseg, gy + riders),
+                               dim3(shape.bs), 0, s, riders, 0u, in, children, ctx->n_hops, n_chunks, (uint32_t)c.max_tokens, pb,
                                ctx->d_hop_bits, ctx->d_child_pos, ctx->d_relay_flags, stats, keep, a);
         }
     }

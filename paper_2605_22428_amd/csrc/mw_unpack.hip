@@ -1227,7 +1227,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
 // on a second stream and one event wait per batch (171 us); fp8 rows of half the size 101
 // against 105 us.  The riding plan is not free: its device-scope atomics and loads take
 // about 4 us of memory-channel time from the expander.
-template <int W, bool kKeyed, int kForm, bool kFold>
+template <int W, bool kKeyed, int kForm, bool kFold, bool kPart>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_expand_index_plan_next(
     const uint32_t first_pack_row, const uint32_t first_expand_row, const mw_row_rec *__restrict__ recs,
     const uint32_t *__restrict__ row_base, int P, int xc, const int32_t *__restrict__ pack_perm,
@@ -1252,7 +1252,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
         return;
     }
     if (blockIdx.y >= y_pack) {         // (mw_stream_step: the packer of a batch planned by an earlier launch)
-        mw_pack_body<kFold>(pack.x, pack.scales, pack.xc, pack.sc, pack.ns, pack.topk, pack.K, pack_perm, pack_stats, pack.packed,
+        mw_pack_body<kFold, kPart>(pack.x, pack.scales, pack.xc, pack.sc, pack.ns, pack.topk, pack.K, pack_perm, pack_stats, pack.packed,
                             pack.row_src_token, pack.row_topk, blockIdx.x, blockIdx.y - y_pack, y_expand - y_pack);
         return;
     }
@@ -2063,14 +2063,16 @@ int32_t mw_launch_unpack_expand_index_plan_next(mw_ctx *ctx, int32_t P, void *ou
         const uint32_t gy_fit = gy < 65535u - riders ? gy : 65535u - riders;
         const dim3 grid(shape.nseg, gy_fit + riders), block(shape.bs);
         const uint32_t cap32 = (uint32_t)(cap < 0x7fffffffLL ? cap : 0x7fffffffLL);
-        const bool fold = mw_is_folded(shape, xc + sc);
+        const bool fold = mw_is_folded(shape, xc + sc), part = n_pack_rows > 0 && mw_rows_part(ctx->row_stride);
         auto launch = [&](auto kernel) {
             hipLaunchKernelGGL(kernel, grid, block, lds, s, rider_rows, rider_rows + n_pack_rows, ctx->d_recs,
                                ctx->d_row_base, P, xc, pa.perm, pa.stats, sc, ctx->hit_slots, ctx->d_base, ctx->d_hits,
                                (u32x4 *)out_rows, (u32x4 *)out_scales, cap32, out_src_peer, out_src_token, a, pl, pa);
         };
 #define MW_RIDE_(W_, KEYED_, FORM_)                                                                                  \
-    launch(fold ? k_expand_index_plan_next<W_, KEYED_, FORM_, true> : k_expand_index_plan_next<W_, KEYED_, FORM_, false>)
+    launch(fold   ? k_expand_index_plan_next<W_, KEYED_, FORM_, true, false>                                         \
+           : part ? k_expand_index_plan_next<W_, KEYED_, FORM_, false, true>                                         \
+                  : k_expand_index_plan_next<W_, KEYED_, FORM_, false, false>)
 #define MW_RIDE(W_, KEYED_)                                                                                          \
     do {                                                                                                             \
         if (index_form(a) == kFormMany) MW_RIDE_(W_, false, kFormMany);                            /* (not keyed) */ \
