@@ -71,8 +71,31 @@ static inline mw_row_shape mw_row_shape_folded(int chunks)
 }
 static inline bool mw_is_folded(const mw_row_shape &s, int chunks) { return (int64_t)s.bs * s.nseg < chunks; }
 
-// Rows that are no whole number of cache lines apart are stored streaming only (mw_st16_part), others written through (mw_st16), by launch.
-static inline bool mw_rows_part(int64_t stride_bytes) { return stride_bytes % 128 != 0; }
+// Rows that are no whole number of cache lines apart are stored streaming only (mw_st16_part) or written through (mw_st16), by launch.
+// Whether a packer's launch of up to n_rows rows stores them streaming only.  Short rows of a batch of 2 to 18 MiB are written through: what the L2 has
+// put together is written at the launch's end, and with rows under 2560 bytes there is little to put together.  us of k_pack, written
+// through / not: 8192 rows of 272 bytes 6.0 / 6.2; 4096 of 656 4.4 / 4.3, 1056 4.5 / 4.9, 1584 4.8 / 5.1, 2112 4.8 / 5.1, 2448 5.6 / 5.9, 3168 6.6 / 6.6; 8192 of
+// 1056 6.1 / 6.9, 2112 7.9 / 8.2, 2448 9.5 / 9.3; 16384 of 656 9.6 / 10.7, 1200 12.6 / 12.2, 2112 15.4 / 14.5, 5280 39.1 / 31.3; 1024 of 1200
+// 3.2 / 2.8, 5280 4.1 / 4.0; 50000 of 656 20.3 / 19.3, 1584 37.3 / 34.1, 7392 152.6 / 129.0.
+static inline bool mw_rows_part(int64_t stride_bytes, int64_t n_rows)
+{
+    const int64_t bytes = stride_bytes * n_rows;
+    return stride_bytes % 128 != 0 && (stride_bytes >= 2560 || bytes < 2 << 20 || bytes > 18 << 20);
+}
+// The same beside the expander's rows in a step's launch.  us, two steps of 8192 tokens over 8 ranks: rows of 272 bytes 76.3 / 77.6, 656 77.2 /
+// 78.1, 1040 83.8 / 83.2, 2448 87.3 / 85.1, 7392 152.3 / 140.9.
+static inline bool mw_step_rows_part(int64_t stride_bytes) { return stride_bytes % 128 != 0 && stride_bytes >= 1024; }
+// The same for a relay's copies of up to n_rows rows or packets; `rides`: beside the index of the next buffer.  A copy scatters over
+// several buffers.  Pieces that begin on 64 bytes are written through as well as whole lines: 15 hops, us, written through / not,
+// relays of 8000 rows of 5824 bytes 67.5 / 70.4, of 14400 158.1 / 169.5, two of a stream 112.5 / 119.0 and 291.0 / 317.6, packets of 6464
+// bytes 73.0 / 80.3; only short ones of packets (3136 bytes 43.4 / 41.4) and beside an index (3008 bytes 80.9 / 79.0) are not.  Other
+// rows: relays of 4096 rows of 1056 bytes 15.8 / 15.1, of 272 bytes 12.2 / 12.4, of 1024 rows of 1584 bytes 9.6 / 10.0; packets of 400 bytes 15.4 /
+// 12.7.
+static inline bool mw_relay_rows_part(int64_t stride_bytes, int64_t n_rows, bool packets, bool rides)
+{
+    if (stride_bytes % 64 == 0) return stride_bytes % 128 != 0 && (packets || rides) && stride_bytes < 4096;
+    return packets || stride_bytes * n_rows >= 2 << 20;
+}
 
 // Whether the expander of mw_unpack and mw_unpack_packets makes its places of the index's counts (k_expand_counts) or the index does.
 // What adding them up costs in every wave grows with the payload, what the index saves does not (it grows with the peers: a report

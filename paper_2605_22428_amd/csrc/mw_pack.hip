@@ -249,7 +249,7 @@ int32_t mw_launch_pack(mw_ctx *ctx, const void *x, const float *scales, const in
     const uint32_t gy = (uint32_t)T < kRowGridMax ? (uint32_t)T : kRowGridMax;
     {
         mw_timed tm(ctx, MW_KERNEL_PACK, s);
-        hipLaunchKernelGGL((mw_is_folded(shape, xc + sc) ? k_pack<true, false> : mw_rows_part(ctx->row_stride) ? k_pack<false, true> : k_pack<false, false>),
+        hipLaunchKernelGGL((mw_is_folded(shape, xc + sc) ? k_pack<true, false> : mw_rows_part(ctx->row_stride, T) ? k_pack<false, true> : k_pack<false, false>),
                            dim3(shape.nseg, gy), dim3(shape.bs), 0, s,
                            perm, stats, (const u32x4 *)x, (const u32x4 *)scales, xc, sc, (int)(ctx->row_stride / 16), ctx->cfg.top_k, topk,
                            (u32x4 *)packed, row_src_token, row_topk);
@@ -269,7 +269,7 @@ int32_t mw_launch_pack_packets(mw_ctx *ctx, const void *x, const float *scales, 
     const uint32_t gy = (uint32_t)T < kRowGridMax ? (uint32_t)T : kRowGridMax;
     {
         mw_timed tm(ctx, MW_KERNEL_PACK, s);
-        hipLaunchKernelGGL(mw_rows_part(16 * (int64_t)(hc + xc + sc)) ? k_pack_packets<true> : k_pack_packets<false>, dim3(shape.nseg, gy), dim3(shape.bs), 0, s, (const u32x4 *)x,
+        hipLaunchKernelGGL(mw_rows_part(16 * (int64_t)(hc + xc + sc), T) ? k_pack_packets<true> : k_pack_packets<false>, dim3(shape.nseg, gy), dim3(shape.bs), 0, s, (const u32x4 *)x,
                            (const u32x4 *)scales, xc, sc, hc, topk, ctx->cfg.top_k, mask, perm, stats, (u32x4 *)packets);
     }
     MW_HIP_CHECK(hipGetLastError());

@@ -19,7 +19,7 @@ struct mw_pack_args {
 };
 
 // kFold: a row is one workgroup, and its lane c takes chunk c + blockDim.x as well where there is one (mw_row_shape_folded).
-// kPart: the rows' chunks by mw_st16_part.  The launch chooses (mw_rows_part): a choice for every chunk cost rows of whole
+// kPart: the rows' chunks by mw_st16_part.  The launch chooses (mw_rows_part, mw_step_rows_part): a choice for every chunk cost rows of whole
 // lines more than the store, us without / with: two steps of 8192 tokens of 10240 bytes 205.2 / 207.7, of 1024 bytes 79.2 / 80.4; k_pack
 // of 4096 rows of 14336 bytes 21.0 / 21.2, k_pack_packets 21.5 / 21.9.  Folded rows are written through, and the few of a small step.
 template <bool kFold, bool kPart>

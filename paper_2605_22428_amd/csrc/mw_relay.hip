@@ -278,7 +278,7 @@ __global__ __launch_bounds__(kBlock) void k_relay_index(const mw_relay_index_arg
 }
 
 // blockIdx.x selects a segment of blockDim.x chunks of a row; rows i_first, i_first + i_stride, ...  kPart: the rows by mw_st16_part
-// (mw_rows_part).
+// (mw_relay_rows_part).
 template <bool kPart>
 __device__ __forceinline__ void relay_copy_body(
     const mw_recv_peer *__restrict__ in, const mw_relay_child *__restrict__ children, int n_hops, int K, int n_chunks,
@@ -692,7 +692,7 @@ int32_t mw_launch_relay_copy(mw_ctx *ctx, const mw_recv_peer *in, const mw_relay
     }
     uint32_t gy = (uint32_t)c.max_tokens < kRowGridMax ? (uint32_t)c.max_tokens : kRowGridMax;
     if (gy < 1) gy = 1;
-    const bool part = mw_rows_part(ctx->row_stride);
+    const bool part = mw_relay_rows_part(ctx->row_stride, c.max_tokens, false, next != nullptr);
     {
         mw_timed tm(ctx, MW_KERNEL_RELAY_COPY, s);
         if (!next) {
@@ -740,7 +740,7 @@ int32_t mw_launch_relay_batch(const mw_relay_job *copy, int32_t n_copy, const mw
         }
     }
     b.index_first_row[MW_RELAY_BATCH_MAX] = first;
-    const bool part = mw_rows_part(ctx->row_stride);
+    const bool part = mw_relay_rows_part(ctx->row_stride, c.max_tokens, false, n_index > 0);
     {
         mw_timed tm(ctx, MW_KERNEL_RELAY_COPY, s);
         hipLaunchKernelGGL(part ? k_relay_batch<true> : k_relay_batch<false>, dim3(shape.nseg, first + gy * (uint32_t)n_copy), dim3(shape.bs), 0, s, first, gy,
@@ -810,7 +810,7 @@ int32_t mw_launch_relay_packets_copy(mw_ctx *ctx, const mw_recv_packets *in, voi
     }
     uint32_t gy = (uint32_t)c.max_tokens < kRowGridMax ? (uint32_t)c.max_tokens : kRowGridMax;
     if (gy < 1) gy = 1;
-    const bool part = mw_rows_part((int64_t)pb);
+    const bool part = mw_relay_rows_part((int64_t)pb, c.max_tokens, true, next != nullptr);
     {
         mw_timed tm(ctx, MW_KERNEL_RELAY_COPY, s);
         if (!next) {

@@ -2063,7 +2063,7 @@ int32_t mw_launch_unpack_expand_index_plan_next(mw_ctx *ctx, int32_t P, void *ou
         const uint32_t gy_fit = gy < 65535u - riders ? gy : 65535u - riders;
         const dim3 grid(shape.nseg, gy_fit + riders), block(shape.bs);
         const uint32_t cap32 = (uint32_t)(cap < 0x7fffffffLL ? cap : 0x7fffffffLL);
-        const bool fold = mw_is_folded(shape, xc + sc), part = n_pack_rows > 0 && mw_rows_part(ctx->row_stride);
+        const bool fold = mw_is_folded(shape, xc + sc), part = n_pack_rows > 0 && mw_step_rows_part(ctx->row_stride);
         auto launch = [&](auto kernel) {
             hipLaunchKernelGGL(kernel, grid, block, lds, s, rider_rows, rider_rows + n_pack_rows, ctx->d_recs,
                                ctx->d_row_base, P, xc, pa.perm, pa.stats, sc, ctx->hit_slots, ctx->d_base, ctx->d_hits,
