@@ -149,6 +149,17 @@ def traffic_from_profile(kernel: str, workload: str):
     return None
 
 
+def unpack_expander(n_local: int, n_peers: int, n_experts: int, top_k: int, rows: int, row_bytes: int) -> str:
+    """The kernel that moves the rows of an mw_unpack of `rows` received rows in two launches: the library's rule
+    (mw_counts_by_expander in csrc/mw_internal.h), for the roofline record's name and its counter profile."""
+    chunks, counts = row_bytes // 16, n_local * n_peers
+    folded = not (chunks % 8 == 0 and chunks > 640) and chunks // 64 in (4, 8, 16) and 1 <= chunks % 64 <= 16
+    share = n_local / n_experts
+    hits = top_k * share / (1.0 - (1.0 - share) ** top_k) if share > 0 else 1.0
+    most_mib = 128 if counts > 256 else 720 if not folded else 448 if hits >= 1.2 else 160 + n_peers // 2
+    return "k_expand_counts" if 1 <= counts <= 512 and rows * row_bytes <= most_mib << 20 else "k_expand"
+
+
 # ------------------------------------------------------------------------------------------ dispatch
 def bench_dispatch(args, name: str, brief: bool = False) -> dict:
     """brief: the step, its launch brackets and the per-kernel breakdown only (the per-configuration
@@ -433,7 +444,7 @@ def bench_dispatch(args, name: str, brief: bool = False) -> dict:
     st = ctx.mw_get_send_stats(sets[0]["send"].stats)
     rs0 = ctx.mw_get_recv_stats(sets[0]["recv"].stats)
     ctx_b.mw_get_recv_stats(sets[0]["recv"].stats)      # (both contexts size their launches from the rows seen)
-    N, Q = int(st["n_rows"]), int(rs0["n_out_rows"])
+    N, Q, rows_seen = int(st["n_rows"]), int(rs0["n_out_rows"]), int(rs0["n_rows_seen"])
     assert int(st["error_flags"]) == 0 and int(rs0["error_flags"]) == 0 and int(rs0["n_recv_rows"]) == M
 
     # An event pair costs a few microseconds of bubble on this platform, so the expander is
@@ -483,7 +494,8 @@ def bench_dispatch(args, name: str, brief: bool = False) -> dict:
         other[sched] = round((time.perf_counter() - t0) * 1e3 / args.steps, 4)
 
     # ---------------------------------------------------------------- per-kernel breakdown (one stream, untimed)
-    # (with events set for the index, mw_unpack of a small batch is two launches; without, as timed above, it is one)
+    # (with events set for the index, mw_unpack of a small batch is two launches; without, as timed above, it is one.  Where the
+    # expander adds up the index's counts, k_expand_counts, "expand" has the bases, offsets and statistics that "recv_index" has else.)
     names = {"plan_rank": B.MW_KERNEL_PLAN_RANK,
              "plan_groups": B.MW_KERNEL_PLAN_GROUPS, "pack": B.MW_KERNEL_PACK,
              "recv_index": B.MW_KERNEL_RECV_INDEX, "expand": B.MW_KERNEL_EXPAND}
@@ -902,7 +914,7 @@ def bench_dispatch(args, name: str, brief: bool = False) -> dict:
     # the next batch's index riding along (same bytes; the index's few MB are not counted)
     dominant = {"pipelined": "k_expand_index_next", "one_stream": "k_expand_index_plan_next",
                 "one_launch": "k_expand_index_plan_next",
-                "launch_and_plan": "k_expand_index_plan_next"}.get(sched0, "k_expand")
+                "launch_and_plan": "k_expand_index_plan_next"}.get(sched0) or unpack_expander(L, R, w.n_experts, K, rows_seen, rb)
     payload = "fp8 e4m3 codes + fp32 scales, moved as bytes" if fp8 else "bf16 payload, moved as bytes"
     traffic_key = "mw_stream_step" if sched0 in ("one_launch", "launch_and_plan") else dominant
     traffic = traffic_from_profile(traffic_key, name.upper())

@@ -778,6 +778,8 @@ MW_API int32_t mw_get_relay_stats(mw_ctx *ctx, const mw_relay_stats *stats_dev, 
  * mw_unpack of a few hundred rows is one launch of index and expander, recorded as
  * MW_KERNEL_EXPAND; while a pair is set for MW_KERNEL_RECV_INDEX it is two launches, like any
  * other mw_unpack, so that either pair brackets its own kernel.
+ * In mw_unpack and mw_unpack_packets of two launches the (expert, peer) counts may be finished -- bases, expert
+ * offsets, statistics -- in the MW_KERNEL_EXPAND launch; in mw_unpack_index they always are in MW_KERNEL_RECV_INDEX.
  */
 #define MW_KERNEL_PLAN_RANK    0
 #define MW_KERNEL_PLAN_GROUPS  1

@@ -4,6 +4,7 @@ import subprocess
 
 import pytest
 
+import bench
 from paper_2605_22428_amd import build
 
 PROGRAM = """
@@ -54,3 +55,15 @@ def test_most_bytes(rule, L, P, packets, folded, hits, most):
 def test_most_counts(rule):
     for folded in (0, 1):
         assert rule(2, 256, 0, folded, 1.0, MB) and not rule(513, 1, 0, folded, 1.0, MB) and not rule(1 << 14, 256, 0, folded, 2.0, 0)
+
+
+def test_the_bench_names_the_kernel_that_is_launched(rule):
+    """Row shapes and hits a row as the library derives them, for the configurations of the bench line and around the rule's sides."""
+    for L, P, E, K, chunks, folded in ((4, 64, 256, 8, 896, 0), (4, 64, 256, 8, 462, 0), (1, 256, 256, 8, 896, 0), (2, 8, 16, 2, 32, 0), (1, 256, 256, 8, 264, 1),
+                                       (16, 16, 256, 8, 264, 1), (6, 64, 384, 8, 462, 0), (8, 128, 1024, 8, 64, 0), (1, 64, 64, 8, 528, 1), (0, 8, 16, 2, 32, 0)):
+        share = L / E
+        hits = K * share / (1 - (1 - share) ** K) if L else 1.0
+        for mib in (1, 127, 129, 191, 193, 287, 289, 447, 449, 719, 721, 4000):
+            rows = (mib << 20) // (16 * chunks)
+            want = "k_expand_counts" if rule(L, P, 0, folded, hits, rows * 16 * chunks) else "k_expand"
+            assert bench.unpack_expander(L, P, E, K, rows, 16 * chunks) == want, (L, P, chunks, mib)
