@@ -1,6 +1,7 @@
 """GPU parity of mw_unpack and mw_unpack_packets where the expander makes its places of the index's counts: one count, a wave of them
 and one more or less, the most a wave takes and one more, rows of one and of several workgroups, folded rows; more rows than the launch
-was made for, the first ones of every workgroup not addressed; and what is left behind for a second expander.  Bit-exact."""
+was made for, the first ones of every workgroup not addressed; fp8 rows and their scales; a rank without experts; statistics that move
+a context to the index that finishes its counts and back; and what is left behind for a second expander.  Bit-exact."""
 import numpy as np
 import pytest
 
@@ -55,6 +56,78 @@ def test_counts(L, R, T, chunks):
         gu.ctx, gu.buf, gu.stats = ctx, buf, ctx.mw_get_recv_stats(buf.stats)
         gu.Q = int(gu.stats["n_out_rows"])
         _filled(gu, ctx, R, cap, want, "packets %d" % batch)
+    ctx.close()
+
+
+def _fp8_batch(rng, ctx, R, E, K, n, hidden, e2r, me):
+    toks, recs, packets = [], [], []
+    for _ in range(R):
+        tk = rng.integers(0, E, size=(n, K)).astype(np.int32)
+        x, sc = rng.integers(0, 256, size=(n, hidden), dtype=np.uint8), rng.random((n, hidden // 128), dtype=np.float32)
+        toks.append((tk, x, sc))
+        recs.append(H.shrink(H.GpuSend(ctx, tk, x, sc).deliver(me)))
+        mask, perm, _, _ = ref.plan(tk, e2r, R, hidden + hidden // 32)
+        packets.append(H.dev(ref.deliver_packets(ref.pack_packets(x, sc, tk, mask, perm), me)))
+    return toks, recs, packets
+
+
+def _same(ctx, buf, want, what):
+    gu = H.GpuUnpack.__new__(H.GpuUnpack)
+    gu.ctx, gu.buf, gu.stats = ctx, buf, ctx.mw_get_recv_stats(buf.stats)
+    gu.Q = int(gu.stats["n_out_rows"])
+    H.check_unpack(gu, want, what)
+    return gu
+
+
+#                         local experts, ranks, tokens, hidden: 64 counts, 65 to 256, 257 to 512, 513; rows folded (4096, 8192) and not
+@pytest.mark.parametrize("L,R,T,hidden", [(4, 16, 300, 4096), (5, 13, 300, 4096), (8, 12, 300, 7168), (1, 256, 40, 4096), (4, 64, 40, 8192), (4, 64, 40, 512),
+                                          (43, 6, 200, 4096), (48, 8, 200, 7168), (64, 8, 150, 8192), (27, 19, 60, 4096)])
+def test_fp8_rows_and_their_scales(L, R, T, hidden):
+    """Codes and scales of mw_unpack and mw_unpack_packets, of a second expander behind each, and of the two halves by themselves."""
+    print("fp8 counts", L, R, T, hidden, flush=True)
+    rng = np.random.default_rng(L * 1000 + R + hidden)
+    E, K, me = L * R, min(4, L * R), R // 2
+    e2r = (np.arange(E) // L).astype(np.int32)
+    ctx = B.Context(R, E, K, me, hidden, B.MW_ROW_FP8_E4M3_BLOCK128, T, R * T, e2r, device=H.DEV)
+    toks, recs, packets = _fp8_batch(rng, ctx, R, E, K, T, hidden, e2r, me)
+    cap = R * T * min(K, L)
+    want = ref.dispatch_plain(toks, e2r, me, cap)
+    table, ptable = B.peers_table(recs, H.DEV), B.packets_table(packets, [int(t.shape[0]) for t in packets], H.DEV)
+    for turn in ("", " again"):
+        for call, tab in ((ctx.mw_unpack, table), (ctx.mw_unpack_packets, ptable)):
+            buf, second = B.RecvBuffers(ctx, cap), B.RecvBuffers(ctx, cap)
+            call(tab, R, buf.out_rows, buf.out_scales, cap, buf.out_src_peer, buf.out_src_token, buf.expert_offsets, buf.stats)
+            ctx.mw_unpack_expand(R, second.out_rows, second.out_scales, cap, second.out_src_peer, second.out_src_token)
+            second.expert_offsets.copy_(buf.expert_offsets), second.stats.copy_(buf.stats)
+            _same(ctx, buf, want, "unpack" + turn)
+            _same(ctx, second, want, "second expander" + turn)
+    halves = B.RecvBuffers(ctx, cap)
+    ctx.mw_unpack_index(table, R, cap, halves.expert_offsets, halves.stats)
+    ctx.mw_unpack_expand(R, halves.out_rows, halves.out_scales, cap, halves.out_src_peer, halves.out_src_token)
+    _same(ctx, halves, want, "halves")
+    ctx.close()
+
+
+@pytest.mark.parametrize("L,R,T,hidden", [(4, 64, 40, 7168), (1, 256, 40, 4096), (16, 16, 60, 4096), (48, 8, 100, 4096), (48, 8, 100, 7168)])
+def test_statistics_take_a_context_across_the_most_bytes(L, R, T, hidden):
+    """The choice follows the rows that the last batch's statistics showed: from few to more than the expander adds up for, and back."""
+    print("counts across the bound", L, R, T, hidden, flush=True)
+    rng = np.random.default_rng(L + R)
+    E, K, me = L * R, min(4, L * R), R - 1
+    e2r = (np.arange(E) // L).astype(np.int32)
+    ctx = B.Context(R, E, K, me, hidden, B.MW_ROW_FP8_E4M3_BLOCK128, T, R * T, e2r, device=H.DEV)
+    toks, recs, packets = _fp8_batch(rng, ctx, R, E, K, T, hidden, e2r, me)
+    cap = R * T * min(K, L)
+    want = ref.dispatch_plain(toks, e2r, me, cap)
+    table, ptable = B.peers_table(recs, H.DEV), B.packets_table(packets, [int(t.shape[0]) for t in packets], H.DEV)
+    for seen in (600, 16000, 1 << 20, 700, 40000, 900):
+        host = np.zeros(1, dtype=B.RECV_STATS_DTYPE)
+        host["n_rows_seen"] = seen
+        for call, tab in ((ctx.mw_unpack, table), (ctx.mw_unpack_packets, ptable)):
+            ctx.mw_get_recv_stats(H.dev(host.view(np.uint8)))            # (a caller's statistics of some batch)
+            buf = B.RecvBuffers(ctx, cap)
+            call(tab, R, buf.out_rows, buf.out_scales, cap, buf.out_src_peer, buf.out_src_token, buf.expert_offsets, buf.stats)
+            _same(ctx, buf, want, "%d rows seen" % seen)
     ctx.close()
 
 
