@@ -81,7 +81,7 @@ __global__ __launch_bounds__(1024) void k_pack_packets(const u32x4 *__restrict__
 //   ties to the even mantissa, sign kept.  Inputs must be finite.
 // One workgroup per packed row, one 16-byte chunk (8 elements) per lane: a block of 128 elements
 // is 16 neighbouring lanes, whose maxima meet by four rotations in their row of 16, operand modifiers of the maximum itself
-// (exchanges through the LDS crossbar: mw_plan and this for 4096 x 7168 28.1 us, now 27.9).  The
+// (exchanges through the LDS crossbar: 4096 x 7168 17.9 us, rotations 17.2; 2048 x 4096 6.2 / 6.0; 16000 x 4096 35.3 / 35.0).  The
 // conversion is the hardware's (round to nearest even); the limit to +-448 in front of it means
 // it never sees a value it would have to saturate.
 __device__ __forceinline__ float mw_bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
@@ -283,7 +283,7 @@ int32_t mw_launch_pack_quantize(mw_ctx *ctx, const void *x_bf16, const int32_t *
     if (T == 0) return MW_OK;
     const int H = ctx->cfg.hidden, ic = H / 8;                  // H % 512 == 0 for fp8 rows
     // Two chunks per lane, both requested before either is processed: unlike the plain row
-    // movers this kernel has a long chain behind every load (exchanges, two divisions, the
+    // movers this kernel has a long chain behind every load (four maxima that depend on one another, two divisions, the
     // conversions), and a second load in flight hides it (23 -> 17 us at 4096 x 7168; four are
     // no better).
     constexpr int U = 2;

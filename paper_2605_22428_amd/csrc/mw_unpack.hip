@@ -15,10 +15,14 @@
 //                 whatever order the rows were packed in -- no sort, no order-dependent
 //                 atomics (LDS atomic ORs only set bits).  Emits per-(expert, peer)
 //                 counts and one record per received row: source address, source token,
-//                 peer and (expert slot, rank) pairs.  The workgroup that reports its counts last
-//                 (device-scope counter) scans them into output bases, so no
-//                 third launch and no grid-wide barrier is needed.
-//   k_expand      small workgroups (a single wave for long cache-line-sized rows, one
+//                 peer and (expert slot, rank) pairs.
+//                 Who turns the counts into output bases: up to 512 of them in mw_unpack and mw_unpack_packets,
+//                 where the payload is not too long for it (mw_counts_by_expander), the expander behind, k_expand_counts.  Its
+//                 waves add up what is in front of their places, and one wave of the launch writes bases, offsets and statistics.
+//                 Else -- more counts, long payloads, mw_unpack_index, an index that rides -- the workgroup that
+//                 reports its counts last (device-scope counter) scans them.  No third launch, no grid-wide barrier either way.
+//   k_expand, k_expand_counts
+//                 small workgroups (a single wave for long cache-line-sized rows, one
 //                 workgroup per row up to 10 KiB), each moving consecutive 16-byte chunks of
 //                 one received row (rows beyond 32768 by striding): a chunk is read once with
 //                 a streaming load and stored to each of the row's experts' slots.  Measured
@@ -1074,8 +1078,9 @@ __global__ __launch_bounds__(1024) void k_expand(
 // and statistics, and the movers do not wait for it: a wave requests the counts in front of the payload (one
 // kilobyte that its CU's cache holds) and adds up what is in front of its place while that is on its way, a dozen vector instructions.
 // kCounts: counts a lane holds, 1 (at most 64 in all), 4 (at most 256) or 8 (at most 512: four of the first 256 and four
-// of the others, so that each request is a kilobyte in one piece).  us for mw_plan, mw_pack and mw_unpack, before / after: 1000 fp8 tokens of 16 ranks 30.6 / 28.4, 4096 of 64
-// ranks 107.3 / 106.5, 8192 bf16 tokens of 256 ranks 154.4 / 151.4; 2048 packets of 16 ranks 68.5 / 67.1.
+// of the others, so that each request is a kilobyte in one piece).  us for mw_plan, mw_pack and mw_unpack, added up by the index's last
+// workgroup / here: 1000 fp8 tokens of 16 ranks 30.7 / 28.5, 2048 of 64 ranks 65.2 / 62.7, 4096 107.9 / 107.9, 8192 bf16 tokens of 256
+// ranks 154.4 / 152.0; 2048 packets of 16 ranks 69.0 / 67.8.
 // Otherwise this is expand_body.  (The hits behind the first requested with the record and their rows stored without a wait
 // in between: 1000 tokens 28.2, but 8192 of 256 ranks 152.0; in the stream's launch 16000 rows of 1.5 hits 80 -> 82.)
 template <int kCounts> struct mw_counts_of { typedef uint32_t type; };
